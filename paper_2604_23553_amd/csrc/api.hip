@@ -836,15 +836,17 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         P.rows = rows; P.n_layers = L;
         P.x_in = static_cast<const __half *>(x) + (size_t)t0 * h;
         P.out = static_cast<__half *>(out) + (size_t)t0 * h;
-        P.y1h = reinterpret_cast<__half *>(sc + pl.y1h); P.y1l = reinterpret_cast<__half *>(sc + pl.y1l);
-        P.y2h = reinterpret_cast<__half *>(sc + pl.y2h); P.y2l = reinterpret_cast<__half *>(sc + pl.y2l);
+        P.y1 = reinterpret_cast<__half *>(sc + pl.y1);
+        P.y2 = reinterpret_cast<__half *>(sc + pl.y2);
         P.stats = reinterpret_cast<float2 *>(sc + pl.stats);
         P.q = reinterpret_cast<float *>(sc + pl.q);
-        P.oh = reinterpret_cast<__half *>(sc + pl.oh); P.ol = reinterpret_cast<__half *>(sc + pl.ol);
-        P.mh = reinterpret_cast<__half *>(sc + pl.mh); P.ml = reinterpret_cast<__half *>(sc + pl.ml);
-        P.part = reinterpret_cast<float *>(sc + pl.part);
+        P.o = reinterpret_cast<__half *>(sc + pl.o);
+        P.m = reinterpret_cast<__half *>(sc + pl.m);
+        P.part = reinterpret_cast<float *>(sc + pl.part); P.part_bytes = pl.total - pl.part;
+        P.part_out = reinterpret_cast<float *>(sc + pl.y1); P.part_out_bytes = pl.total - pl.y1;
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
         P.sync = reinterpret_cast<unsigned *>(ctx->ws + ctx->wl.sync);
+        pf_plan_pass(P);
         float *xa = reinterpret_cast<float *>(sc + pl.xres), *xb2 = reinterpret_cast<float *>(sc + pl.xnext);
         for (int l = 0; l < L; ++l) {
             P.layer = l;

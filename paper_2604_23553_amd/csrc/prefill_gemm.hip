@@ -1,0 +1,500 @@
+// Projections of the prompt-sized path (paper Sec. 2.2 applied to hundreds of tokens): C[tokens][n] =
+// A[tokens][K] . W[n][K]^T as LDS-tiled GEMMs on the matrix cores (v_mfma_f32_32x32x16_f16).
+// Activations are two fp16 planes, head and remainder (y = hi + lo to ~2^-22), each fed to the
+// instruction in turn: the product of the fp32 values to rounding, fp32 accumulation.
+//
+//   k_pf_gemm<kPfIn>  : QKV rows and MLP-up rows of a layer, one launch (their output columns side by
+//                       side); the epilogue completes the LayerNorm, rotates, appends, applies GELU
+//   k_pf_gemm<kPfOut> : output projection and MLP-down as ONE product over the concatenated K
+//                       ([attention | GELU(up)] . [W_dense | W_down]^T) + biases + residual
+//   k_pf_reduce<>     : the parts of a product whose K is split over workgroups, added in order,
+//                       then the same epilogue
+//
+// Every sum has a fixed order: one bit pattern per build and pass size.
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+#include "prefill_device.h"
+
+namespace cfpp {
+
+typedef _Float16 pf_f16x8 __attribute__((ext_vector_type(8)));
+typedef float pf_f32x16 __attribute__((ext_vector_type(16)));
+typedef int pf_i32x4 __attribute__((ext_vector_type(4)));
+
+enum { kPfIn = 0, kPfOut = 1 };
+enum { kPfQkv = 0, kPfUp = 1, kPfRes = 2 };       // what follows a product
+
+// the LayerNorm, completed: inv (W (gamma x) - mu s) + c, with c = W beta + b from the packing
+template <int EPI>
+__device__ __forceinline__ float pf_complete(const PfParams &P, int row, int col, float val)
+{
+    if (EPI == kPfQkv || EPI == kPfUp) {
+        const float2 rc = reinterpret_cast<const float2 *>(P.w + (EPI == kPfQkv ? P.lay.rc_qkv : P.lay.rc_up))[col];
+        const float2 st = P.stats[row];
+        val = (val - st.x * rc.x) * st.y + rc.y;
+    }
+    return val;
+}
+
+// The element (row = token, col = output feature) with the completed value `val`;
+// other: the completed value of the neighbouring column (col ^ 1) of the same row (QKV only:
+// a rotation pair of the packed order sits in two adjacent columns, the first one even)
+template <int EPI>
+__device__ __forceinline__ void pf_store(const PfParams &P, int row, int col, float val, float other)
+{
+    const Dims &dm = P.dm;
+    const int h = dm.h;
+    if (EPI == kPfQkv) {
+        const int pd = col / dm.d, i = col - pd * dm.d, nh = pd / 3, c = pd - 3 * nh;
+        int dim = i;
+        if (c < 2 && i < dm.r) {
+            const float2 cs = P.rope[(size_t)(P.pos0 + row) * (dm.r >> 1) + (i >> 1)];
+            if (i & 1) { val = val * cs.x + other * cs.y; dim = (i >> 1) + (dm.r >> 1); }
+            else { val = val * cs.x - other * cs.y; dim = i >> 1; }
+        }
+        if (c == 0) P.q[(size_t)row * h + nh * dm.d + dim] = val;
+        else P.kv[kv_offset(dm, c - 1, P.b, nh, dim, P.pos0 + row)] = __float2half_rn(val);
+    } else if (EPI == kPfUp) {
+        __half hi, lo;
+        pf_split(pf_gelu(val, dm.flags), hi, lo);
+        const size_t at = pf_at(row, col, dm.f);
+        P.m[at] = hi; P.m[at + kPfLo] = lo;
+    } else {
+        const float branches = (val + __half2float(P.w[P.lay.b_dense + col])) + __half2float(P.w[P.lay.b_down + col]);
+        const float res = P.xres[(size_t)row * h + col] + branches;
+        if (P.layer == P.n_layers - 1) P.out[(size_t)row * h + col] = __float2half_rn(res);
+        else P.xnext[(size_t)row * h + col] = res;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// 64 lanes x 16 bytes from memory straight into LDS: lane l's piece lands at lds_addr + 16 l.
+// (M0: the compiler sets it right before each use of its own.  Counted in vmcnt like any load; the callers wait by count.  Out of range of the resource: zeros.)
+__device__ __forceinline__ void pf_dma16(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ pf_i32x4 pf_rsrc(const __half *p, unsigned bytes)
+{
+    const unsigned long long a = reinterpret_cast<unsigned long long>(p);
+    return pf_i32x4{(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)bytes, 0x00020000};
+}
+template <int N>
+__device__ __forceinline__ void pf_wait_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
+template <int BM, int BN, int BK, int ST>
+constexpr int pf_gemm_lds_bytes()
+{
+    return ST * (2 * BM + BN) * BK * 2;
+}
+constexpr int pf_per_cu(int lds) { return 160 * 1024 / lds > 3 ? 3 : 160 * 1024 / lds; }   // workgroups of a CU
+
+// GEMM.  Workgroup: WM x WN wavefronts, tile BM tokens x BN output features, K in steps of BK through a ring of ST
+// stages in LDS that is filled by DMA (memory -> LDS, no registers) up to ST - 1 steps ahead.  What bounds it, measured
+// at 4096 tokens of the 2560-wide shape with parts switched off: matrix instructions alone 430 - 460 us of the second
+// product's 541, the DMA alone 400 - 480; a CU's DMA rate is what is in flight (96 - 110 KB) over the latency of the
+// slowest line of a step (about 2 us under load), not a bandwidth: 128-byte segments instead of 64, prefetching the
+// weights' lines into the L2 (+ 5 % time) or K steps of 64 changed little.  Hence:
+//   - tiles with few bytes per operation and a ring that fills the LDS (one or two workgroups to a CU), or three
+//     workgroups of small tiles; which one: see pf_plan;
+//   - a step's DMA instructions, its fragment reads and its matrix instructions are interleaved; the next K values'
+//     fragments are read behind the first matrix instructions of the current ones, across the step's one barrier too;
+//   - a wavefront owns BM / WM x BN / WN of the tile (32 x 160 ... 64 x 160): wide in the features, because an activation
+//     fragment is two planes and a weight fragment one;
+//   - rows of the activation buffers sit 256 bytes further apart than their values (a step reads one K offset of every
+//     row: with strides of a multiple of 4 KiB those lines share memory channels: 594 -> 545 us, same product).
+// Tiles are dealt so that consecutive numbers run on the same XCD (workgroup i runs on XCD i % 8), in groups of gm token
+// tiles: an XCD works on a block of about gm x (its workgroups / gm) tiles and its L2 holds both operands' rows.
+// splits > 1: workgroup z of a tile takes the z-th part of K and leaves its sums in part[z][row][col] (rows of whole
+// token tiles); k_pf_reduce adds the parts in order and finishes.
+template <int FL, int BM, int BN, int BK, int ST, int WM, int WN>
+__global__ void __launch_bounds__(64 * WM * WN, pf_per_cu(pf_gemm_lds_bytes<BM, BN, BK, ST>()) * WM * WN / 4)
+k_pf_gemm(PfParams P, int splits, int gm)
+{
+    constexpr int NT = 64 * WM * WN, NWV = WM * WN;
+    constexpr int RB = BK * 2, PR = RB / 16, RU = 64 / PR;         // weights: bytes and 16-byte pieces of a row in LDS, rows of a DMA instruction
+    constexpr int SUB = BK / 32, RBA = 128, RUA = 8;               // activations: 128-byte rows of 32 values (heads, remainders), SUB blocks of them
+    constexpr int MT = BM / WM / 32, NTL = BN / WN / 32, KS = BK / 16;
+    constexpr int NA1 = BM / RUA / NWV, NA = SUB * NA1, NW = (BN / RU + NWV - 1) / NWV, NLD = NA + NW;   // DMA instructions of a wavefront and step
+    static_assert(BM % (RUA * NWV) == 0 && NWV % 2 == 0 && BN % RU == 0 && (BK == 32 || BN % (RU * NWV) == 0), "whole DMA instructions");
+    constexpr int STAGE = 2 * BM * RB + BN * RB;
+    constexpr int TS = 2 * kPfLo + 8, kScratch = NWV * 32 * TS * 2;   // epilogue: halves between rows of a wavefront's scratch, bytes of all
+    static_assert(kScratch + BM * 8 <= ST * STAGE, "the epilogue's memory");
+    extern __shared__ __align__(16) char pf_lds[];
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char *)pf_lds;
+    const Dims &dm = P.dm;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int h = dm.h, f = dm.f;
+    const int ntn0 = FL == kPfIn ? (3 * h + BN - 1) / BN : (h + BN - 1) / BN;
+    const int ntn = FL == kPfIn ? ntn0 + (f + BN - 1) / BN : ntn0;
+    const int mt = (P.n_rows + BM - 1) / BM, tiles = ntn * mt, total = tiles * splits;
+    const int per_xcd = (total + 7) >> 3;
+    const int v = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (v >= total) return;                               // (whole workgroup)
+    const int z = v / tiles, tile = v - z * tiles;
+    // groups of gm token tiles by all feature tiles, token tiles fastest: what an XCD works on at a time is a block
+    // of about gm x (its workgroups / gm) tiles
+    const int grp = tile / (gm * ntn), in_grp = tile - grp * gm * ntn, gh = min(gm, mt - grp * gm);
+    const int m0 = (grp * gm + in_grp % gh) * BM, tn = in_grp / gh;
+    const bool up = FL == kPfIn && tn >= ntn0;
+    const int n0 = (up ? tn - ntn0 : tn) * BN, N = FL == kPfIn ? (up ? f : 3 * h) : h;
+    const int n_steps = (FL == kPfIn ? h : h + f) / BK, j_dense = h / BK;
+    const int js = (int)((long long)n_steps * z / splits), je = (int)((long long)n_steps * (z + 1) / splits);
+
+    const __half *a_0 = FL == kPfIn ? (up ? P.y2 : P.y1) : P.o;
+    const __half *w_0 = P.w + (FL == kPfIn ? (up ? P.lay.w_up : P.lay.w_qkv) : P.lay.w_dense);
+    const unsigned as0 = (unsigned)pf_row_halves(h) * 2u, as1 = (unsigned)pf_row_halves(f) * 2u;       // bytes between activation rows
+    const unsigned abytes0 = (unsigned)P.rows * as0, wbytes0 = (unsigned)N * (unsigned)h * 2u;
+    const unsigned abytes1 = (unsigned)P.rows * as1, wbytes1 = (unsigned)h * (unsigned)f * 2u;
+    // A DMA instruction covers 8 rows x 128 bytes of the activations, or RU rows x RB bytes of the weights: lane l
+    // brings a 16-byte piece of one row into place l, which is where the row's piece (place ^ swizzle(row)) belongs:
+    // the fragment reads of 16 consecutive rows hit 64 different banks
+    const int r16 = (RU * wave + lane / PR) & 15, sw = BK == 32 ? (r16 >> 2) & 3 : (r16 >> 1) & 7;
+    const unsigned piece_w = (unsigned)(((lane % PR) ^ sw) * 16), piece_a = (unsigned)(((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) * 16);
+    const unsigned vw0 = (unsigned)(lane / PR) * (unsigned)h * 2u + piece_w, vw1 = (unsigned)(lane / PR) * (unsigned)f * 2u + piece_w;
+    const unsigned va0 = (unsigned)(lane >> 3) * as0 + piece_a, va1 = (unsigned)(lane >> 3) * as1 + piece_a;
+    // instructions [i0, i1) of those that bring step j in, so that they can be spread between matrix instructions
+    auto issue = [&](int j, int stage, int i0, int i1) {
+        const bool second = FL == kPfOut && j >= j_dense;
+        const unsigned jj = (unsigned)(second ? j - j_dense : j), width = (unsigned)(second ? f : h), as = second ? as1 : as0;
+        const unsigned va = second ? va1 : va0, vw = second ? vw1 : vw0;
+        const pf_i32x4 ra = pf_rsrc(second ? P.m : a_0, second ? abytes1 : abytes0);
+        const pf_i32x4 rw = pf_rsrc(second ? P.w + P.lay.w_down : w_0, second ? wbytes1 : wbytes0);
+        const unsigned dst = lds0 + (unsigned)stage * (unsigned)STAGE + 1024u * (unsigned)wave;
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            if (i < i0 || i >= i1) continue;
+            if (i < NA) {
+                const int sub = i / NA1, u = (i % NA1) * NWV;
+                pf_dma16(ra, dst + sub * BM * RBA + 1024u * u, va, (unsigned)(m0 + RUA * (wave + u)) * as + (jj * SUB + sub) * 128u);
+            } else {
+                // (where the wavefronts do not divide the rows, the last ones bring the last rows a second time)
+                const unsigned u = (i - NA + 1) * NWV <= BN / RU ? wave + (i - NA) * NWV : min(wave + (i - NA) * NWV, BN / RU - 1);
+                pf_dma16(rw, lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, vw, (n0 + RU * u) * width * 2u + jj * RB);
+            }
+        }
+    };
+    pf_f32x16 acc[MT][NTL];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NTL; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+    // fragment of this lane: row lane % 32 of an instruction tile, halves 8 * (lane / 32) .. + 7 of a step of 16
+    const int fr = lane & 31, hf = lane >> 5, fsw = BK == 32 ? (fr >> 2) & 3 : (fr >> 1) & 7;
+    const char *fa = pf_lds + wm * (BM / WM) * RBA, *fw = pf_lds + 2 * BM * RB + wn * (BN / WN) * RB;
+    int oa[2], ol[2], ow[KS];                              // heads, remainders (of a block of 32 values), weights
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        oa[k] = fr * RBA + (((2 * k + hf) ^ ((fr >> 1) & 7)) * 16);
+        ol[k] = fr * RBA + (((4 + 2 * k + hf) ^ ((fr >> 1) & 7)) * 16);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ow[ks] = fr * RB + (((2 * ks + hf) ^ fsw) * 16);
+    static_assert(KS % 2 == 0, "two fragment sets swap roles");
+    struct Frag { pf_f16x8 ah[MT], al[MT], w[NTL]; } F[2];
+    auto fetch = [&](Frag &g, int stage, int ks) {
+        const char *pa = fa + stage * STAGE + (ks >> 1) * BM * RBA, *pw = fw + stage * STAGE;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) g.ah[t] = *reinterpret_cast<const pf_f16x8 *>(pa + oa[ks & 1] + t * 32 * RBA);
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) g.w[t] = *reinterpret_cast<const pf_f16x8 *>(pw + ow[ks] + t * 32 * RB);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) g.al[t] = *reinterpret_cast<const pf_f16x8 *>(pa + ol[ks & 1] + t * 32 * RBA);
+    };
+#pragma unroll
+    for (int s = 0; s < ST; ++s)
+        if (js + s < je) issue(js + s, s, 0, NLD);
+    if (js + ST - 1 < je) pf_wait_barrier<(ST - 1) * NLD>();
+    else pf_wait_barrier<0>();
+    fetch(F[0], 0, 0);
+    int stage = 0, prev = ST - 1;                          // stage of step j; of step j - 1, free since the last barrier
+    for (int j = js; j < je; ++j) {
+        const int next = stage + 1 == ST ? 0 : stage + 1;
+        const bool more = j > js && j - 1 + ST < je;       // (the prologue requested the first ST steps)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const Frag &g = F[ks & 1];
+            constexpr int PER = (NLD + KS - 2) / (KS - 1);             // DMA instructions per instruction group (none in the last)
+#pragma unroll
+            for (int sl = 0; sl < 2 * MT; ++sl) {
+                const int a = sl % MT;
+#pragma unroll
+                for (int b = 0; b < NTL; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sl < MT ? g.ah[a] : g.al[a], g.w[b], acc[a][b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (sl == 0) {
+                    // the next group's fragments, behind this group's first instructions: the wait for this
+                    // group's own (all that is outstanding at its start) then never includes them
+                    if (ks + 1 < KS) {
+                        fetch(F[(ks + 1) & 1], stage, ks + 1);
+                    } else if (j + 1 < je) {
+        if (j + ST - 1 < je) pf_wait_barrier<(ST - 2) * NLD>();
+                        else pf_wait_barrier<0>();
+                        fetch(F[0], next, 0);
+                    }
+                }
+                if (ks + 1 < KS) {
+                    constexpr int SL = 2 * MT;
+                    const int d0 = ks * PER + PER * sl / SL, d1 = ks * PER + PER * (sl + 1) / SL;
+                    if (more && d0 < d1 && d0 < NLD) issue(j - 1 + ST, prev, d0, d1 < NLD ? d1 : NLD);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        prev = stage;
+        stage = next;
+    }
+    // this lane holds, per instruction tile, column lane % 32 and rows 8 (e / 4) + 4 (lane / 32) + e % 4
+    if (splits > 1) {
+        const int nall = FL == kPfIn ? 3 * h + f : h, c0 = up ? 3 * h : 0;
+        float *part = FL == kPfIn ? P.part : P.part_out;
+#pragma unroll
+        for (int b = 0; b < NTL; ++b) {
+            const int col = n0 + wn * (BN / WN) + b * 32 + (lane & 31);
+            if (col - (lane & 31) >= N) continue;          // (N: a multiple of 128)
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = m0 + wm * (BM / WM) + a * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                    part[((size_t)z * mt * BM + row) * nall + c0 + col] = acc[a][b][e];
+                }
+        }
+        return;
+    }
+    // What follows the product, from the instruction's layout: a lane has one column and 16 rows of an instruction
+    // tile.  Nothing is exchanged between the wavefronts, so nobody waits for the slowest.
+    const int r_lane = wm * (BM / WM) + (lane >> 5) * 4;    // row of element 0 of the first instruction tile
+    float2 *sst = reinterpret_cast<float2 *>(pf_lds + kScratch);
+    if (FL == kPfIn) {                                     // the rows' mean and 1/sigma
+        __syncthreads();                                   // the last step's fragments have been read: the memory is free
+        for (int r = tid; r < BM; r += NT) sst[r] = P.stats[min(m0 + r, P.n_rows - 1)];   // (rows past the pass's tokens are never stored)
+        __syncthreads();
+    }
+#pragma unroll
+    for (int b = 0; b < NTL; ++b) {
+        const int c0 = n0 + wn * (BN / WN) + b * 32, col = c0 + (lane & 31);
+        if (c0 >= N) break;                                // (uniform; N: a multiple of 128)
+        if (FL == kPfIn && up) {
+            // MLP-up: 32 tokens x 32 columns at a time through 4.5 KB of LDS that no other wavefront touches, so that
+            // whole 128-byte lines (32 heads, 32 remainders) are stored
+            __half *t = reinterpret_cast<__half *>(pf_lds) + wave * 32 * TS;
+            const float2 rc = reinterpret_cast<const float2 *>(P.w + P.lay.rc_up)[col];
+#pragma unroll
+            for (int a = 0; a < MT; ++a) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int rl = (e >> 2) * 8 + (e & 3);
+                    const float2 st = sst[r_lane + a * 32 + rl];
+                    __half hi, lo;
+                    pf_split(pf_gelu((acc[a][b][e] - st.x * rc.x) * st.y + rc.y, dm.flags), hi, lo);
+                    t[(rl + (lane >> 5) * 4) * TS + (lane & 31)] = hi;
+                    t[(rl + (lane >> 5) * 4) * TS + kPfLo + (lane & 31)] = lo;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int rl = i * 8 + (lane >> 3), row = m0 + wm * (BM / WM) + a * 32 + rl;
+                    const u32x4 v = *reinterpret_cast<const u32x4 *>(t + rl * TS + (lane & 7) * 8);
+                    if (row < P.n_rows) *reinterpret_cast<u32x4 *>(P.m + pf_at(row, c0, f) + (lane & 7) * 8) = v;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if (FL == kPfIn) {
+            // QKV: the column's head, part (q, k, v) and dimension; pairs of the rotated part sit in neighbouring columns
+            const float2 rc = reinterpret_cast<const float2 *>(P.w + P.lay.rc_qkv)[col];
+            const int pd = col / dm.d, i = col - pd * dm.d, nh = pd / 3, c = pd - 3 * nh;
+            const bool rot = c < 2 && i < dm.r;
+            const int dim = rot ? (i >> 1) + (i & 1) * (dm.r >> 1) : i;
+            const bool any_rot = __any(rot);
+            const unsigned qo = (unsigned)(nh * dm.d + dim);
+            __half *kp = P.kv + kv_offset(dm, c > 0 ? c - 1 : 0, P.b, nh, dim, P.pos0);
+            const unsigned co = (unsigned)P.pos0 * (unsigned)(dm.r >> 1) + (unsigned)(rot ? i >> 1 : 0);
+#pragma unroll
+            for (int a = 0; a < MT; ++a) {
+                const int ra = r_lane + a * 32;
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float2 st = sst[ra + (e >> 2) * 8 + (e & 3)];
+                    v[e] = (acc[a][b][e] - st.x * rc.x) * st.y + rc.y;
+                }
+                if (any_rot) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float other = dpp_mov<kDppXor1>(v[e]);     // (all lanes: the neighbouring lane holds col ^ 1)
+                        const int row = min(m0 + ra + (e >> 2) * 8 + (e & 3), P.n_rows - 1);
+                        if (rot) {
+                            const float2 cs = P.rope[co + (unsigned)row * (unsigned)(dm.r >> 1)];
+                            v[e] = i & 1 ? v[e] * cs.x + other * cs.y : v[e] * cs.x - other * cs.y;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = m0 + ra + (e >> 2) * 8 + (e & 3);
+                    if (row < P.n_rows) {
+                        if (c == 0) P.q[qo + (unsigned)row * (unsigned)h] = v[e];
+                        else kp[(size_t)row * 16] = __float2half_rn(v[e]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            const float bde = __half2float(P.w[P.lay.b_dense + col]), bdn = __half2float(P.w[P.lay.b_down + col]);
+            const bool last = P.layer == P.n_layers - 1;
+#pragma unroll
+            for (int a = 0; a < MT; ++a) {
+#pragma unroll
+                for (int e4 = 0; e4 < 4; ++e4) {
+                    float x[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int row = min(m0 + r_lane + a * 32 + e4 * 8 + e, P.n_rows - 1);
+                        x[e] = P.xres[(unsigned)row * (unsigned)h + (unsigned)col];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int row = m0 + r_lane + a * 32 + e4 * 8 + e;
+                        const unsigned at = (unsigned)row * (unsigned)h + (unsigned)col;
+                        const float o = x[e] + ((acc[a][b][4 * e4 + e] + bde) + bdn);
+                        if (row < P.n_rows) {
+                            if (last) P.out[at] = __float2half_rn(o);
+                            else P.xnext[at] = o;
+                        }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+}
+
+// the parts of a split-K product (part rows: prows per part), added in order, then what
+// follows the product; a thread takes four consecutive columns of a row (two rotation pairs)
+template <int FL>
+__global__ void __launch_bounds__(256) k_pf_reduce(PfParams P, int splits, int prows)
+{
+    const int nq = 3 * P.dm.h, N = FL == kPfIn ? nq + P.dm.f : P.dm.h, n4 = N >> 2;
+    const unsigned n_el = (unsigned)P.n_rows * (unsigned)n4;
+    const size_t zstride = (size_t)prows * N;
+    for (unsigned e = blockIdx.x * 256u + threadIdx.x; e < n_el; e += gridDim.x * 256u) {
+        const int row = (int)(e / (unsigned)n4), col = (int)(e - (unsigned)row * (unsigned)n4) * 4;
+        const float *p = (FL == kPfIn ? P.part : P.part_out) + (size_t)row * N + col;
+        f32x4 s = *as_global(reinterpret_cast<const f32x4 *>(p));
+        for (int z = 1; z < splits; ++z) s += *as_global(reinterpret_cast<const f32x4 *>(p + z * zstride));
+        float v[4];
+        if (FL == kPfOut) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pf_store<kPfRes>(P, row, col + j, s[j], 0.f);
+        } else if (col < nq) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = pf_complete<kPfQkv>(P, row, col + j, s[j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pf_store<kPfQkv>(P, row, col + j, v[j], v[j ^ 1]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pf_store<kPfUp>(P, row, col - nq + j, pf_complete<kPfUp>(P, row, col - nq + j, s[j]), 0.f);
+        }
+    }
+}
+
+template <int FL, int BM, int BN, int BK, int ST, int WM, int WN>
+static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
+{
+    const int h = P.dm.h, f = P.dm.f, splits = pl.splits;
+    const int ntn = FL == kPfIn ? (3 * h + BN - 1) / BN + (f + BN - 1) / BN : (h + BN - 1) / BN;
+    const int mt = (P.n_rows + BM - 1) / BM, nall = FL == kPfIn ? 3 * h + f : h;
+    // the parts of a split product, [splits][mt * BM][all columns] floats, must fit what the scratch holds for them
+    if (splits > 1 && (size_t)splits * mt * BM * nall * sizeof(float) > (FL == kPfIn ? P.part_bytes : P.part_out_bytes))
+        return hipErrorInvalidValue;
+    constexpr int lds = pf_gemm_lds_bytes<BM, BN, BK, ST>();
+    const hipError_t e = hipFuncSetAttribute((const void *)k_pf_gemm<FL, BM, BN, BK, ST, WM, WN>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_pf_gemm<FL, BM, BN, BK, ST, WM, WN>), dim3((ntn * mt * splits + 7) / 8 * 8), dim3(64 * WM * WN), lds, s, P,
+                       splits, BM == 256 ? 4 : 8);
+    if (splits > 1) {
+        const size_t n_el = (size_t)P.n_rows * (nall / 4);
+        hipLaunchKernelGGL(k_pf_reduce<FL>, dim3((unsigned)((n_el + 255) / 256)), dim3(256), 0, s, P, splits, mt * BM);
+    }
+    return hipSuccess;
+}
+
+// Tile and splits of K of a product.  No tile is best everywhere: what a CU does is whole tiles, so that the
+// best one is the one whose tiles (times splits) fill the 256 CUs evenly, and a big tile moves fewer bytes per
+// operation but finishes in one long epilogue.  The choice is the least estimate of
+//     most tiles of a CU x (K / 32 / splits x step + epilogue)  [where several tiles share a CU: at least
+//     rounds x K / 32 / splits x lone_step]
+//     + (split: the parts written and read again)
+// in us.  The constants are a least-squares fit to 1500 timings (hidden 512 .. 4096, 8 .. 4096 tokens, every tile,
+// splits 1 .. 16) and pick within 0.8 % of the fastest measured combination in the mean, 7.5 % at worst.
+// Measured per layer (attention and LayerNorm included), before this kernel -> now: hidden 2560: 37 tokens 107 -> 80,
+// 512: 303 -> 224, 4096: 2345 -> 1528; hidden 4096, 1531 tokens: 1810 -> 1203.
+struct PfTileCost { int bm, bn, per_cu; float step, lone_step, epi_in, epi_out; };
+static const PfTileCost kPfTiles[kPfTileKinds] = {
+    {64, 128, 1, 0.26f, 0.f, 3.74f, 2.19f},
+    {64, 128, 3, 0.25f, 0.37f, 0.01f, 1.13f},
+    {128, 128, 2, 0.36f, 0.46f, 3.17f, 2.15f},
+    {128, 320, 1, 0.88f, 0.f, 5.51f, 3.99f},
+    {256, 192, 1, 0.92f, 0.f, 9.92f, 4.42f},
+    {256, 256, 1, 1.10f, 0.f, 14.67f, 5.02f},
+    {256, 320, 1, 1.34f, 0.f, 27.44f, 6.68f},
+};
+constexpr int kPfCus = 256;
+
+static PfPlan pf_plan(const PfParams &P, bool in)
+{
+    const int h = P.dm.h, f = P.dm.f, nall = in ? 3 * h + f : h;
+    const float steps = (float)(in ? h : h + f) / 32.f;
+    const size_t part_bytes = in ? P.part_bytes : P.part_out_bytes;
+    PfPlan best = {0, 1};
+    float best_cost = 1e30f;
+    for (int k = 0; k < kPfTileKinds; ++k) {
+        const PfTileCost &t = kPfTiles[k];
+        if (in && t.bn == 320 && t.bm == 256) continue;    // (its QKV and MLP-up epilogues spill registers)
+        const int mt = (P.n_rows + t.bm - 1) / t.bm;
+        const int ntn = in ? (3 * h + t.bn - 1) / t.bn + (f + t.bn - 1) / t.bn : (h + t.bn - 1) / t.bn;
+        for (int sp = 1; sp <= 16; ++sp) {
+            if (sp > 1 && ((long long)mt * ntn * sp > 8 * kPfCus || (size_t)sp * mt * t.bm * nall * sizeof(float) > part_bytes)) break;
+            const int wgs = mt * ntn * sp, per = (wgs + kPfCus - 1) / kPfCus, rounds = (wgs + kPfCus * t.per_cu - 1) / (kPfCus * t.per_cu);
+            const float busy = per * (steps / sp) * t.step, lone = rounds * (steps / sp) * t.lone_step;
+            float cost = (busy > lone ? busy : lone) + per * (in && sp == 1 ? t.epi_in : t.epi_out);
+            if (sp > 1) cost += 0.89f + 1.12e-6f * sp * P.n_rows * (float)nall;
+            if (cost < best_cost) { best_cost = cost; best.tile = k; best.splits = sp; }
+        }
+    }
+    return best;
+}
+
+void pf_plan_pass(PfParams &P)
+{
+    P.plan_in = pf_plan(P, true);
+    P.plan_out = pf_plan(P, false);
+}
+
+template <int FL>
+static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
+{
+    switch (pl.tile) {
+    case 0: return pf_launch<FL, 64, 128, 64, 4, 2, 2>(P, pl, s);
+    case 1: return pf_launch<FL, 64, 128, 32, 3, 2, 2>(P, pl, s);
+    case 2: return pf_launch<FL, 128, 128, 32, 3, 2, 2>(P, pl, s);
+    case 3: return pf_launch<FL, 128, 320, 32, 4, 4, 2>(P, pl, s);
+    case 4: return pf_launch<FL, 256, 192, 32, 3, 4, 2>(P, pl, s);
+    case 5: return pf_launch<FL, 256, 256, 32, 3, 4, 2>(P, pl, s);
+    case 6: if (FL == kPfOut) return pf_launch<kPfOut, 256, 320, 32, 3, 4, 2>(P, pl, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s) { return pf_gemm<kPfIn>(P, P.plan_in, s); }
+hipError_t launch_pf_gemm_out(const PfParams &P, hipStream_t s) { return pf_gemm<kPfOut>(P, P.plan_out, s); }
+
+}  // namespace cfpp

@@ -8,21 +8,27 @@ namespace cfpp {
 
 constexpr int kPfTile = 128;           // rows (tokens) and columns (output features) of a GEMM workgroup tile
 constexpr int kPfMaxRows = 4096;       // most tokens a pass takes
-constexpr int kPfSplitTiles = 384;      // most 128 x 128 parts a split product leaves: K is halved only while the parts number
-                                       // at most half of this, and the scratch holds this many
+// bytes of the parts of a split product: what 384 tiles of 128 x 128 floats take, less the padding of the activation rows
+CFPP_HD size_t pf_part_bytes(int rows) { return (size_t)384 * kPfTile * kPfTile * 4 - (size_t)rows * 1024; }
+
+// Halves between the rows of an activation buffer of `width` values a row: 256 bytes more than the
+// values take, so that rows at one K offset - what a GEMM step reads - start in different memory channels.
+CFPP_HD size_t pf_row_halves(int width) { return 2 * (size_t)width + 128; }
 
 // Scratch of one pass over `rows` tokens (rows a multiple of kPfTile), byte
 // offsets; the caller owns the memory.  Activations that feed a GEMM are kept
-// as two fp16 planes, head and remainder (y = hi + lo to ~2^-22), row-major.
+// as two fp16 planes, head and remainder (y = hi + lo to ~2^-22), interleaved: a row is
+// groups of 64 halves, the heads of 32 consecutive values and then their remainders, so that
+// 32 values of K are one 128-byte line (see pf_at); rows sit pf_row_halves apart.
 struct PfLayout {
     size_t xres, xnext;            // float [rows][h]: residual stream entering / leaving the block
-    size_t y1h, y1l, y2h, y2l;     // half [rows][h]: gamma_1 * x and gamma_2 * x
+    size_t o;                      // half [rows][2 h + pad]: attention output
+    size_t m;                      // half [rows][2 f + pad]: GELU(up)
     size_t stats;                  // float2 [rows]: mean, 1 / sqrt(variance + eps)
+    size_t y1, y2;                 // half [rows][2 h + pad]: gamma_1 * x and gamma_2 * x
     size_t q;                      // float [rows][h]: rotated queries
-    size_t oh, ol;                 // half [rows][h]: attention output
-    size_t mh, ml;                 // half [rows][f]: GELU(up)
-    size_t part;                   // float [kPfSplitTiles][128][128]: the parts of a product whose K is split over workgroups
-    size_t total;
+    size_t part;                   // float [parts][rows][columns]: the parts of a product whose K is split over workgroups
+    size_t total;                  // (the second product's parts start at y1: what lies between is no longer needed then)
 };
 
 CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
@@ -30,17 +36,21 @@ CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
     PfLayout L;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    const size_t rh = (size_t)rows * m.h, rf = (size_t)rows * m.f;
+    const size_t rh = (size_t)rows * m.h, ah = (size_t)rows * pf_row_halves(m.h) * 2, af = (size_t)rows * pf_row_halves(m.f) * 2;
     L.xres = take(rh * 4); L.xnext = take(rh * 4);
-    L.y1h = take(rh * 2); L.y1l = take(rh * 2); L.y2h = take(rh * 2); L.y2l = take(rh * 2);
+    L.o = take(ah);
+    L.m = take(af);
     L.stats = take((size_t)rows * 8);
+    L.y1 = take(ah); L.y2 = take(ah);
     L.q = take(rh * 4);
-    L.oh = take(rh * 2); L.ol = take(rh * 2);
-    L.mh = take(rf * 2); L.ml = take(rf * 2);
-    L.part = take((size_t)kPfSplitTiles * kPfTile * kPfTile * 4);
+    L.part = take(pf_part_bytes(rows));
     L.total = o;
     return L;
 }
+
+// tile (index into the table of prefill_gemm.hip) and splits of K of a product
+constexpr int kPfTileKinds = 7;
+struct PfPlan { int tile, splits; };
 
 struct PfParams {
     Dims dm;
@@ -54,17 +64,25 @@ struct PfParams {
     const __half *x_in;     // [n_rows][h] fp16: input of layer 0
     __half *out;            // [n_rows][h] fp16: output of the last layer
     float *xres, *xnext;
-    __half *y1h, *y1l, *y2h, *y2l;
+    __half *y1, *y2;
     float2 *stats;
     float *q;
-    __half *oh, *ol, *mh, *ml;
-    float *part;
+    __half *o, *m;
+    float *part;            // parts of the first product (QKV, MLP-up), part_bytes
+    float *part_out;        // parts of the second one, part_out_bytes
+    size_t part_bytes, part_out_bytes;
+    PfPlan plan_in, plan_out;
     const float2 *rope;
     unsigned *sync;
 };
 
 bool pf_supported(const Dims &dm);
+// fills in the plans of a pass: everything else of P that does not depend on the layer is set
+void pf_plan_pass(PfParams &P);
 // one block for the tokens of a pass: LayerNorm inputs, QKV, attention, dense, up, down
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s);
+// its products (prefill_gemm.hip): QKV and MLP-up; output projection and MLP-down
+hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s);
+hipError_t launch_pf_gemm_out(const PfParams &P, hipStream_t s);
 
 }  // namespace cfpp

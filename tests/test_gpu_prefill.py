@@ -143,6 +143,55 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
     _check_prompt(orc, shape, 47, 0, 1030, 1, gemm_rows=1152, row_check_every=7)
 
 
+# Every tile of the GEMM's plan and its edges (token counts around multiples of 64, 128 and 256, split and unsplit
+# products): against the path through the batched projections, which the cases above hold to the oracle.  Both sides
+# round the same fp32 values to fp16 once, so an element differs by one step of its size at most, plus the drift of
+# the appended rows' own roundings (2e-3 of the row's root mean square covers it: a step of one V row in a mean of
+# two rows or more).
+@pytest.mark.parametrize("shape,pos0,T", [
+    (synth.ModelShape(2560, 32, 80, 20, 10240, name="pythia-2.8b-block"), 3, T) for T in (1, 37, 65, 129, 191, 257, 515, 701, 2049, 4095)
+] + [
+    (synth.ModelShape(640, 8, 80, 20, 2560, name="d80-h640"), 0, 333),          # features not a multiple of the wide tiles
+    (synth.ModelShape(128, 2, 64, 64, 128, name="d64-h128"), 1, 130),           # the smallest K: fewer steps than stages
+    (synth.ModelShape(1536, 24, 64, 16, 6144, name="d64-h1536"), 2, 1000),
+    (synth.ModelShape(4096, 32, 128, 32, 16384, name="pythia-6.9b-block"), 1, 1531),
+])
+def test_gemm_tiles_against_the_batched_projections(shape, pos0, T):
+    import torch
+    import synth.device as sdev
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] gemm tiles shape={shape.name} T={T}", flush=True)
+    cap = pos0 + T + 3
+    ds = DeviceStack(shape, cap, 8, 1)
+    try:
+        ds.load_layer_device(0, sdev.layer_tensors(shape, 5, 0, ds.dev))
+        sdev.fill_kv(ds.kv[0], 5, 0)
+        start = ds.kv[0].clone()
+        X = synth.x_input(shape, 6, batch=T)
+        want = ds.prefill(X, pos0).astype(np.float64)
+        kw, vw = ds.export_kv(0, 0, pos0, T)
+        ds.kv[0].copy_(start)
+        torch.cuda.synchronize()
+        got = ds.prefill_gemm(X, pos0, rows=(T + 127) // 128 * 128).astype(np.float64)
+        kg, vg = ds.export_kv(0, 0, pos0, T)
+        ds.check()
+        rms = np.sqrt((want ** 2).mean(axis=1, keepdims=True))
+        for g, w, scale in ((got, want, rms), (kg, kw, 0.0), (vg, vw, 0.0)):
+            g, w = g.astype(np.float64), w.astype(np.float64)
+            assert np.isfinite(g).all()
+            step = np.ldexp(1.0, np.frexp(np.maximum(np.abs(g), np.abs(w)).clip(2.0 ** -14))[1] - 11)
+            # K and V rows near zero: the fp32 sums behind them differ by their own rounding, 2e-6 of the terms
+            assert (np.abs(g - w) <= 1.001 * step + 2e-3 * scale + 2e-5).all(), float((np.abs(g - w) / (step + 2e-3 * scale + 2e-5)).max())
+            assert np.linalg.norm(g - w) <= 2.5e-4 * np.linalg.norm(w)
+        kv, st = ds.kv[0].view(torch.float16), start.view(torch.float16)
+        d, H = shape.head_dim, shape.n_heads
+        v, s = (t.view(2, 8, H, d // 16, cap, 16) for t in (kv, st))
+        assert torch.equal(v[:, :, :, :, :pos0], s[:, :, :, :, :pos0]) and torch.equal(v[:, :, :, :, pos0 + T:], s[:, :, :, :, pos0 + T:])
+        assert torch.equal(v[:, 1:], s[:, 1:])
+    finally:
+        ds.close()
+
+
 def test_gemm_prompt_refuses_the_sequential_form():
     import dataclasses
     from paper_2604_23553_amd import CfppError
