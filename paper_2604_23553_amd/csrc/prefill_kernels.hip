@@ -11,9 +11,9 @@
 //                 fp16 matrix instruction reproduces the fp32 product to rounding)
 //   the products: prefill_gemm.hip - QKV and MLP-up in one launch, output projection and
 //                 MLP-down as one product
-//   k_pf_attn<> : causal attention of a block of 16 queries of one head over the cache,
-//                 keys in LDS tiles of 64 positions, both products on the matrix
-//                 cores (v_mfma_f32_16x16x16_f16), online softmax in fp32
+//   k_pf_attn<> : causal attention of a block of 32, 64 or 128 queries of one head over the
+//                 cache, keys in LDS tiles, both products on the matrix cores
+//                 (v_mfma_f32_32x32x16_f16), online softmax in fp32
 //
 // Every sum has a fixed order: one bit pattern per build and pass size.
 #include <hip/hip_runtime.h>
@@ -95,322 +95,241 @@ __global__ void __launch_bounds__(256) k_pf_ln(PfParams P)
 }
 
 // ---------------------------------------------------------------------------
-// Causal attention of kPfQB = 16 consecutive queries of one head: grid (H, blocks of
-// queries), 4 wavefronts, on the matrix cores (v_mfma_f32_16x16x16_f16).  Keys and
-// values of 64 positions at a time in LDS; wavefront w takes the tile's keys
-// 16 w .. 16 w + 15:
-//   S^T = K Q^T  (keys x queries): the instruction's result layout - a lane holds 4
-//         consecutive keys of query lane % 16 - is at once the layout of the first
-//         operand of the next product, so the weights never leave the registers;
-//   O_w += P V   (queries x dimensions), P = exp(S - m) with the running maximum m of
-//         the online softmax exchanged between the wavefronts through LDS once per
-//         tile; V sits in LDS transposed ([dimension][key]) for that.
-// q and P are fp32 values and enter as fp16 head + remainder (two instructions each),
-// K and V are the cache's fp16; sums in fp32.  The wavefronts' partial outputs and
-// partial softmax sums are added in wavefront order at the end.
-constexpr int kPfQB = 16;
+// Causal attention of 32 QW consecutive queries of one head: grid (H, blocks of queries, the
+// last - longest - first), 4 wavefronts, both products on the matrix cores
+// (v_mfma_f32_32x32x16_f16).  Wavefront w takes 32 queries (w % QW) and, of every tile of TK keys
+// in LDS, 32 SUB keys (w / QW):
+//   S^T = K Q^T  (keys x queries): a lane holds query lane % 32 and keys 8 g + 4 (lane / 32) .. + 3,
+//         g < 4, so a query's softmax is lane arithmetic and one exchange with lane ^ 32, and
+//         registers 8 m .. 8 m + 7 are, as they stand, a lane's 8 K values of the next product
+//         if V's operand takes the same keys in the same order;
+//   O^T += V^T P^T (dimensions x queries): the running sums are rescaled lane by lane, and only
+//         when some query's maximum has moved; V sits in LDS transposed ([dimension][key]).
+// q (scaled by log2 e / sqrt(D)) and P are fp32 values and enter as fp16 head + remainder (two
+// instructions each), K and V are the cache's fp16; sums and softmax in fp32.  Keys behind a
+// query are masked in the tiles that the diagonal crosses only.  With QW < 4 the wavefronts of
+// the same queries keep a maximum and sums of their own and are added in wavefront order at the end.
+// What bounds it: vector instructions (about 12 per score for the exponential, the sum and the two
+// halves of P) beside 22 matrix instructions per 32 x 32 scores at D = 80, in equal parts.
 typedef _Float16 pf_f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 pf_f16x8 __attribute__((ext_vector_type(8)));
+typedef float pf_f32x16 __attribute__((ext_vector_type(16)));
 
-// maximum / sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the 16-lane rows of the wavefront)
-__device__ __forceinline__ float pf_rows_max(float v)
+// the value of lane ^ 32
+__device__ __forceinline__ float pf_other_half(float v)
 {
     const unsigned u = __float_as_uint(v);
-    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-    const unsigned u2 = __float_as_uint(v);
-    const auto q = __builtin_amdgcn_permlane32_swap(u2, u2, false, false);
-    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
-}
-__device__ __forceinline__ float pf_rows_sum(float v)
-{
-    const unsigned u = __float_as_uint(v);
-    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    const unsigned u2 = __float_as_uint(v);
-    const auto q = __builtin_amdgcn_permlane32_swap(u2, u2, false, false);
-    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float((threadIdx.x & 32) ? p[0] : p[1]);
 }
 
-// A tile of 64 cache positions x D dimensions of K and V on its way into LDS: pieces of 8 halves
-// (one 16-byte load, slab by slab) held in registers from the request, one tile ahead of the
-// arithmetic, to the store - K as rows [position][dimension], V transposed [dimension][position].
+// A tile of TK cache positions x D dimensions of K and V on its way into LDS: pieces of 8 halves
+// held in registers from the request, one tile ahead of the arithmetic, to the store - K as rows
+// [position][dimension], V transposed [dimension][position], two positions to a word.
 // Positions past `last_pos` repeat that row (the callers mask them).
-template <int D>
+template <int D, int TK>
 struct PfKvTile {
-    static constexpr int kPieces = 64 * (D / 8), kPer = (kPieces + 255) / 256;
-    u32x4 k[kPer], v[kPer];
+    static constexpr int kPieces = TK * (D / 8), kPer = (kPieces + 255) / 256, kPairs = kPieces / 2, kPerV = (kPairs + 255) / 256;
+    u32x4 k[kPer], v[kPerV][2];
     __device__ __forceinline__ void request(const __half *Kc, const __half *Vc, int t0, int last_pos, int max_seq, int tid)
     {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int e = min(tid + 256 * i, kPieces - 1);
-            const int pc = e / 64, t = e - pc * 64;        // piece pc = dims 8 pc .. 8 pc + 7 of position t0 + t
-            const int tp = min(t0 + t, last_pos);
-            const size_t off = ((size_t)(pc >> 1) * max_seq + tp) * 16 + (pc & 1) * 8;
-            k[i] = load16(Kc + off);
-            v[i] = load16(Vc + off);
+            const int pc = e / TK, t = min(t0 + e % TK, last_pos);         // piece pc = dims 8 pc .. 8 pc + 7
+            k[i] = load16(Kc + ((size_t)(pc >> 1) * max_seq + t) * 16 + (pc & 1) * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < kPerV; ++i) {
+            const int e = min(tid + 256 * i, kPairs - 1);
+            const int pc = e / (TK / 2), t = t0 + 2 * (e % (TK / 2));
+            const __half *p = Vc + (size_t)(pc >> 1) * max_seq * 16 + (pc & 1) * 8;
+            v[i][0] = load16(p + (size_t)min(t, last_pos) * 16);
+            v[i][1] = load16(p + (size_t)min(t + 1, last_pos) * 16);
         }
     }
-    __device__ __forceinline__ void store(__half *sK, __half *sVt, int QS, int VS, int tid) const
+    __device__ __forceinline__ void store(__half *sK, __half *sVt, int KS, int VS, int tid) const
     {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int e = tid + 256 * i;
-            if (e < kPieces) {
-                const int pc = e / 64, t = e - pc * 64;
-                unsigned *dk = reinterpret_cast<unsigned *>(&sK[t * QS + 8 * pc]);
-                dk[0] = k[i].x; dk[1] = k[i].y; dk[2] = k[i].z; dk[3] = k[i].w;
-                const __half *vh = reinterpret_cast<const __half *>(&v[i]);
+            if (kPieces % 256 == 0 || e < kPieces) *reinterpret_cast<u32x4 *>(&sK[(e % TK) * KS + 8 * (e / TK)]) = k[i];
+        }
 #pragma unroll
-                for (int j = 0; j < 8; ++j) sVt[(8 * pc + j) * VS + t] = vh[j];
+        for (int i = 0; i < kPerV; ++i) {
+            const int e = tid + 256 * i;
+            if (kPairs % 256 == 0 || e < kPairs) {
+                unsigned *d = reinterpret_cast<unsigned *>(&sVt[8 * (e / (TK / 2)) * VS + 2 * (e % (TK / 2))]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    d[(2 * j) * (VS / 2)] = __builtin_amdgcn_perm(v[i][1][j], v[i][0][j], 0x05040100u);
+                    d[(2 * j + 1) * (VS / 2)] = __builtin_amdgcn_perm(v[i][1][j], v[i][0][j], 0x07060302u);
+                }
             }
         }
     }
 };
 
-template <int D>
-__global__ void __launch_bounds__(256) k_pf_attn(PfParams P)
+template <int D, int QW>
+__global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
 {
-    constexpr int QS = D + 4;                              // halves per row of q and K in LDS (8-byte fragment reads, spread over the banks)
-    constexpr int VS = 64 + 4;                             // halves per row of V transposed
-    constexpr int NB = D / 16;                             // 16-dimension blocks
-    __shared__ __align__(16) __half sQh[kPfQB * QS], sQl[kPfQB * QS];
-    constexpr int KVH = 64 * QS + D * VS;                  // halves of a tile of K and V
-    static_assert(KVH * 2 >= 4 * kPfQB * D * 4 && (64 * QS) % 8 == 0, "the wavefronts' outputs reuse the tile's memory");
-    __shared__ __align__(16) __half sKV[KVH];
-    __shared__ float sMax[4][kPfQB], sCorr[4][kPfQB], sL[4][kPfQB];
-    __half *sK = sKV, *sVt = sKV + 64 * QS;
-    float (*sO)[kPfQB][D] = reinterpret_cast<float (*)[kPfQB][D]>(sKV);      // after the last tile
+    constexpr int KW = 4 / QW, SUB = QW == 4 ? 2 : 1, TK = 32 * KW * SUB;
+    constexpr int NK = D / 16, NB = (D + 31) / 32;         // K steps of S, 32-dimension tiles of O
+    constexpr int KS = D + 8, VS = TK + 4;                 // halves per row of K and of V transposed: fragment reads spread over all banks
+    constexpr int OS = D + 4;                              // floats per query of a wavefront's output in LDS
+    constexpr int kTileBytes = (TK * KS + 32 * NB * VS) * 2, kOutBytes = 4 * 32 * OS * 4;
+    __shared__ __align__(16) char mem[kTileBytes > kOutBytes ? kTileBytes : kOutBytes];
+    __shared__ float sM[4][32], sL[4][32];
+    __half *sK = reinterpret_cast<__half *>(mem), *sVt = sK + TK * KS;
+    static_assert((TK * KS * 2) % 16 == 0, "");
     const Dims &dm = P.dm;
-    const int head = blockIdx.x, q0 = blockIdx.y * kPfQB, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int head = blockIdx.x, q0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * 32 * QW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (q0 >= P.n_rows) return;
-    const int nq = min(kPfQB, P.n_rows - q0);
-    const float scale = 1.0f / sqrtf((float)D);
-    for (int e = tid; e < kPfQB * D; e += 256) {
-        const int qi = e / D, dmi = e - qi * D;
-        const float v = qi < nq ? P.q[(size_t)(q0 + qi) * dm.h + head * D + dmi] * scale : 0.f;
-        __half hi, lo;
-        pf_split(v, hi, lo);
-        sQh[qi * QS + dmi] = hi; sQl[qi * QS + dmi] = lo;
-    }
-    const int col = lane & 15, grp = lane >> 4;            // column of a result tile, group of 4 rows / 4 K values
-    const int qpos = P.pos0 + q0 + col;                    // position of the query this lane's S^T column belongs to
-    const bool qlive = col < nq;
-    float m_run = -INFINITY, l_part = 0.f;                 // running maximum (all wavefronts alike), this wavefront's sum
-    f32x4 O[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int last_pos = P.pos0 + q0 + nq - 1;             // the block's last query attends up to here
+    const int wq = wave % QW, wk = wave / QW, col = lane & 31, hf = lane >> 5;
+    const int qw0 = q0 + 32 * wq, qi = qw0 + col;          // this wavefront's first query, this lane's
+    const int qpos = P.pos0 + qi, first_pos = P.pos0 + qw0;
+    const int wave_last = qw0 < P.n_rows ? P.pos0 + min(qw0 + 31, P.n_rows - 1) : -1;
+    const int last_pos = P.pos0 + min(q0 + 32 * QW, P.n_rows) - 1;         // the block's last query attends up to here
     const __half *Kc = P.kv + kv_offset(dm, 0, P.b, head, 0, 0), *Vc = P.kv + kv_offset(dm, 1, P.b, head, 0, 0);
-    PfKvTile<D> tile;
+    PfKvTile<D, TK> tile;
     tile.request(Kc, Vc, 0, last_pos, dm.max_seq, tid);
-    for (int t0 = 0; t0 <= last_pos; t0 += 64) {
-        __syncthreads();                                   // the previous tile is no longer read (first: q is written)
-        tile.store(sK, sVt, QS, VS, tid);
-        tile.request(Kc, Vc, t0 + 64, last_pos, dm.max_seq, tid);   // the next tile travels while this one is worked on
-        __syncthreads();
-        // S^T of this wavefront's 16 keys: rows = keys 16 wave + 4 grp + v, column = query col
-        f32x4 st = {0.f, 0.f, 0.f, 0.f};
-        const __half *ka = &sK[(16 * wave + col) * QS + 4 * grp];
-        const __half *qh = &sQh[col * QS + 4 * grp], *ql = &sQl[col * QS + 4 * grp];
+    pf_f16x8 qh[NK], ql[NK];                               // Q^T: dimensions 16 ks + 8 hf .. + 7 of query col
+    const float scale = 1.44269504088896340736f / sqrtf((float)D);
 #pragma unroll
-        for (int ks = 0; ks < NB; ++ks) {
-            const pf_f16x4 kf = *reinterpret_cast<const pf_f16x4 *>(ka + 16 * ks);
-            st = __builtin_amdgcn_mfma_f32_16x16x16f16(kf, *reinterpret_cast<const pf_f16x4 *>(qh + 16 * ks), st, 0, 0, 0);
-            st = __builtin_amdgcn_mfma_f32_16x16x16f16(kf, *reinterpret_cast<const pf_f16x4 *>(ql + 16 * ks), st, 0, 0, 0);
-        }
-        const int key0 = t0 + 16 * wave + 4 * grp;
-        float mloc = -INFINITY;
+    for (int ks = 0; ks < NK; ++ks) {
+        // (a lane without a query takes the last one's: its results are not stored)
+        const f32x4 *qp = reinterpret_cast<const f32x4 *>(P.q + (size_t)min(qi, P.n_rows - 1) * dm.h + head * D + 16 * ks + 8 * hf);
+        const f32x4 a = qp[0], b = qp[1];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            st[v] = qlive && key0 + v <= qpos ? st[v] : -INFINITY;
-            mloc = fmaxf(mloc, st[v]);
-        }
-        mloc = pf_rows_max(mloc);                          // over this wavefront's 16 keys, for query col
-        if (lane < 16) sMax[wave][lane] = mloc;
-        __syncthreads();
-        const float mt = fmaxf(fmaxf(sMax[0][col], sMax[1][col]), fmaxf(sMax[2][col], sMax[3][col]));
-        const float mn = fmaxf(m_run, mt);
-        const float corr = m_run == -INFINITY ? 0.f : expf(m_run - mn);     // (mn finite whenever m_run is)
-        float p[4], psum = 0.f;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            p[v] = st[v] == -INFINITY ? 0.f : expf(st[v] - mn);
-            psum += p[v];
-        }
-        l_part = l_part * corr + pf_rows_sum(psum);
-        m_run = mn;
-        if (lane < 16) sCorr[wave][lane] = corr;           // (read below by this wavefront only: no barrier)
-        pf_f16x4 ph, pl;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const _Float16 h = (_Float16)p[v];
-            ph[v] = h;
-            pl[v] = (_Float16)(p[v] - (float)h);
-        }
-        // O rows = queries 4 grp + v, column = dimension 16 nb + col: rescale, then add P V of this wavefront's keys
-        float cr[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) cr[v] = sCorr[wave][4 * grp + v];
-        const __half *vb = &sVt[col * VS + 16 * wave + 4 * grp];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            f32x4 o = O[nb];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] *= cr[v];
-            const pf_f16x4 vf = *reinterpret_cast<const pf_f16x4 *>(vb + 16 * nb * VS);
-            o = __builtin_amdgcn_mfma_f32_16x16x16f16(ph, vf, o, 0, 0, 0);
-            o = __builtin_amdgcn_mfma_f32_16x16x16f16(pl, vf, o, 0, 0, 0);
-            O[nb] = o;
+        for (int j = 0; j < 8; ++j) {
+            const float v = (j < 4 ? a[j & 3] : b[j & 3]) * scale;
+            qh[ks][j] = (_Float16)v;
+            ql[ks][j] = (_Float16)(v - (float)qh[ks][j]);
         }
     }
-    // the wavefronts' parts, added in wavefront order
-    __syncthreads();                                       // (the last tile is no longer read)
+    float m_run = -INFINITY, l_run = 0.f;                  // l_run: of this lane's keys
+    pf_f32x16 O[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sO[wave][4 * grp + v][16 * nb + col] = O[nb][v];
-    if (lane < 16) sL[wave][lane] = l_part;
-    __syncthreads();
-    for (int e = tid; e < nq * D; e += 256) {
-        const int qi = e / D, dmi = e - qi * D;
-        const float l = ((sL[0][qi] + sL[1][qi]) + sL[2][qi]) + sL[3][qi];
-        const float o = ((sO[0][qi][dmi] + sO[1][qi][dmi]) + sO[2][qi][dmi]) + sO[3][qi][dmi];
-        __half hi, lo;
-        pf_split(o / l, hi, lo);
-        const size_t at = pf_at(q0 + qi, head * D + dmi, dm.h);
-        P.o[at] = hi; P.o[at + kPfLo] = lo;
-    }
-}
-
-// The same attention for long passes: 64 consecutive queries per workgroup, 16 per wavefront,
-// every wavefront over all 64 keys of a tile.  A tile of K and V is then fetched once per 64
-// queries instead of once per 16 (at 4096 tokens the narrow kernel pulls 10 GB per layer out of
-// the L2), a wavefront's softmax is its own (no exchange between wavefronts), its q stays in
-// registers as instruction operands, and a wavefront skips the tiles behind its last query.
-// Blocks of later queries (more tiles) are started first.
-constexpr int kPfQW = 64;
-#ifndef PF_WIDE_FROM
-#define PF_WIDE_FROM 1024
-#endif
-constexpr int kPfWideFrom = PF_WIDE_FROM;             // tokens in a pass from which the wide kernel runs
-
-template <int D>
-__global__ void __launch_bounds__(256) k_pf_attn_wide(PfParams P)
-{
-    constexpr int QS = D + 4, VS = 64 + 4, NB = D / 16;
-    __shared__ __align__(16) __half sK[64 * QS];
-    __shared__ __align__(16) __half sVt[D * VS];
-    __shared__ float sX[4][16];                            // a per-query value from the lanes of the score layout to those of the output layout
-    const Dims &dm = P.dm;
-    const int head = blockIdx.x, q0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * kPfQW;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (q0 >= P.n_rows) return;
-    const int nq = min(kPfQW, P.n_rows - q0);
-    const float scale = 1.0f / sqrtf((float)D);
-    const int col = lane & 15, grp = lane >> 4;
-    const int qw0 = q0 + 16 * wave, qi = qw0 + col;        // this wavefront's first query, this lane's query in the score layout
-    const bool qlive = qi < P.n_rows;
-    const int qpos = P.pos0 + qi;
-    const int wave_last = qw0 < P.n_rows ? P.pos0 + min(qw0 + 15, P.n_rows - 1) : -1;
-    pf_f16x4 qh[NB], ql[NB];                               // Q^T fragments: dimensions 16 ks + 4 grp .. + 3 of query col
+        for (int e = 0; e < 16; ++e) O[nb][e] = 0.f;
+    for (int t0 = 0; t0 <= last_pos; t0 += TK) {
+        __syncthreads();                                   // the previous tile is no longer read
+        tile.store(sK, sVt, KS, VS, tid);
+        tile.request(Kc, Vc, t0 + TK, last_pos, dm.max_seq, tid);      // the next tile travels while this one is worked on
+        __syncthreads();
+        const int kw0 = 32 * SUB * wk;                     // this wavefront's first key in the tile
+        if (t0 + kw0 > wave_last) continue;                // (whole wavefront; the barriers are above)
+        pf_f32x16 st[SUB];
 #pragma unroll
-    for (int ks = 0; ks < NB; ++ks)
+        for (int s = 0; s < SUB; ++s)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) st[s][e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            pf_f16x8 kf[SUB];
+#pragma unroll
+            for (int s = 0; s < SUB; ++s) kf[s] = *reinterpret_cast<const pf_f16x8 *>(&sK[(kw0 + 32 * s + col) * KS + 16 * ks + 8 * hf]);
+#pragma unroll
+            for (int s = 0; s < SUB; ++s) st[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s], qh[ks], st[s], 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < SUB; ++s) st[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s], ql[ks], st[s], 0, 0, 0);
+        }
+        if (t0 + kw0 + 32 * SUB - 1 > first_pos) {         // (uniform) the diagonal is not behind every key
+#pragma unroll
+            for (int s = 0; s < SUB; ++s)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (t0 + kw0 + 32 * s + 8 * (e >> 2) + 4 * hf + (e & 3) > qpos) st[s][e] = -INFINITY;
+        }
+        float mloc = st[0][0];
+#pragma unroll
+        for (int s = 0; s < SUB; ++s)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mloc = fmaxf(mloc, st[s][e]);
+        mloc = fmaxf(mloc, pf_other_half(mloc));
+        if (__any(mloc > m_run)) {                         // (uniform) some query's maximum moves
+            const float mn = fmaxf(m_run, mloc);
+            const float corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
+            m_run = mn;
+            l_run *= corr;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) O[nb][e] *= corr;
+        }
+        const float mref = m_run == -INFINITY ? 0.f : m_run;           // (a query none of whose keys this wavefront has seen)
+#pragma unroll
+        for (int s = 0; s < SUB; ++s) {
+            pf_f16x8 ph[2], pl[2];
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float p = __builtin_amdgcn_exp2f(st[s][e] - mref);
+                sum += p;
+                const _Float16 h = (_Float16)p;
+                ph[e >> 3][e & 7] = h;
+                pl[e >> 3][e & 7] = (_Float16)(p - (float)h);
+            }
+            l_run += sum;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const __half *vp = &sVt[(32 * nb + col) * VS + kw0 + 32 * s + 16 * m + 4 * hf];
+                    const pf_f16x4 v0 = *reinterpret_cast<const pf_f16x4 *>(vp), v1 = *reinterpret_cast<const pf_f16x4 *>(vp + 8);
+                    const pf_f16x8 vf = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+                    O[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, ph[m], O[nb], 0, 0, 0);
+                    O[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pl[m], O[nb], 0, 0, 0);
+                }
+        }
+    }
+    // the outputs through LDS (a query's dimensions side by side), where wavefronts of the same queries meet
+    l_run += pf_other_half(l_run);
+    float corr = 1.f;
+    if (KW > 1) {
+        if (hf == 0) { sM[wave][col] = m_run; }
+        __syncthreads();
+        float m = sM[wq][col];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) m = fmaxf(m, sM[wq + QW * w][col]);
+        corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
+    }
+    if (hf == 0) sL[wave][col] = l_run * corr;
+    __syncthreads();                                       // (the last tile is no longer read)
+    float *out = reinterpret_cast<float *>(mem) + (wave * 32 + col) * OS;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int dim = 32 * nb + 8 * g + 4 * hf;
+            if (32 * nb + 8 * g < D)
+                *reinterpret_cast<f32x4 *>(out + dim) = f32x4{O[nb][4 * g] * corr, O[nb][4 * g + 1] * corr, O[nb][4 * g + 2] * corr, O[nb][4 * g + 3] * corr};
+        }
+    __syncthreads();
+    const float *res = reinterpret_cast<const float *>(mem);
+    for (int e = tid; e < 32 * QW * (D / 8); e += 256) {
+        const int q = e / (D / 8), c8 = 8 * (e - q * (D / 8)), w0 = q >> 5, qc = q & 31;
+        if (q0 + q >= P.n_rows) continue;
+        float l = sL[w0][qc];
+        f32x4 a = *reinterpret_cast<const f32x4 *>(res + (w0 * 32 + qc) * OS + c8), b = *reinterpret_cast<const f32x4 *>(res + (w0 * 32 + qc) * OS + c8 + 4);
+#pragma unroll
+        for (int w = 1; w < KW; ++w) {
+            const int ww = w0 + QW * w;
+            l += sL[ww][qc];
+            a += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8);
+            b += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8 + 4);
+        }
+        __half hi[8], lo[8];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float v = qlive ? P.q[(size_t)qi * dm.h + head * D + 16 * ks + 4 * grp + j] * scale : 0.f;
-            const _Float16 hi = (_Float16)v;
-            qh[ks][j] = hi;
-            ql[ks][j] = (_Float16)(v - (float)hi);
+            pf_split(a[j] / l, hi[j], lo[j]);
+            pf_split(b[j] / l, hi[4 + j], lo[4 + j]);
         }
-    float m_run = -INFINITY, l_run = 0.f;
-    f32x4 O[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int last_pos = P.pos0 + q0 + nq - 1;
-    const __half *Kc = P.kv + kv_offset(dm, 0, P.b, head, 0, 0), *Vc = P.kv + kv_offset(dm, 1, P.b, head, 0, 0);
-    PfKvTile<D> tile;
-    tile.request(Kc, Vc, 0, last_pos, dm.max_seq, tid);
-    for (int t0 = 0; t0 <= last_pos; t0 += 64) {
-        __syncthreads();                                   // the previous tile is no longer read
-        tile.store(sK, sVt, QS, VS, tid);
-        tile.request(Kc, Vc, t0 + 64, last_pos, dm.max_seq, tid);   // the next tile travels while this one is worked on
-        __syncthreads();
-        if (t0 > wave_last) continue;                      // (whole wavefront; the barriers are above)
-        // S^T of the tile's four key blocks: rows = keys 16 kb + 4 grp + v, column = query col
-        f32x4 st[4];
-        float mloc = -INFINITY;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-            const __half *ka = &sK[(16 * kb + col) * QS + 4 * grp];
-#pragma unroll
-            for (int ks = 0; ks < NB; ++ks) {
-                const pf_f16x4 kf = *reinterpret_cast<const pf_f16x4 *>(ka + 16 * ks);
-                a = __builtin_amdgcn_mfma_f32_16x16x16f16(kf, qh[ks], a, 0, 0, 0);
-                a = __builtin_amdgcn_mfma_f32_16x16x16f16(kf, ql[ks], a, 0, 0, 0);
-            }
-            const int key0 = t0 + 16 * kb + 4 * grp;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                a[v] = qlive && key0 + v <= qpos ? a[v] : -INFINITY;
-                mloc = fmaxf(mloc, a[v]);
-            }
-            st[kb] = a;
-        }
-        mloc = pf_rows_max(mloc);                          // over the tile's 64 keys, for query col
-        const float mn = fmaxf(m_run, mloc);
-        const float corr = m_run == -INFINITY ? 0.f : expf(m_run - mn);
-        float psum = 0.f;
-        pf_f16x4 ph[4], pl[4];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float pv = st[kb][v] == -INFINITY ? 0.f : expf(st[kb][v] - mn);
-                psum += pv;
-                const _Float16 hi = (_Float16)pv;
-                ph[kb][v] = hi;
-                pl[kb][v] = (_Float16)(pv - (float)hi);
-            }
-        l_run = l_run * corr + pf_rows_sum(psum);
-        m_run = mn;
-        if (lane < 16) sX[wave][lane] = corr;              // (written and read by this wavefront only: no barrier)
-        float cr[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) cr[v] = sX[wave][4 * grp + v];
-        // O rows = queries 4 grp + v, column = dimension 16 nb + col
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            f32x4 o = O[nb];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] *= cr[v];
-            const __half *vb = &sVt[(16 * nb + col) * VS + 4 * grp];
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const pf_f16x4 vf = *reinterpret_cast<const pf_f16x4 *>(vb + 16 * kb);
-                o = __builtin_amdgcn_mfma_f32_16x16x16f16(ph[kb], vf, o, 0, 0, 0);
-                o = __builtin_amdgcn_mfma_f32_16x16x16f16(pl[kb], vf, o, 0, 0, 0);
-            }
-            O[nb] = o;
-        }
-    }
-    if (lane < 16) sX[wave][lane] = l_run;
-    float lr[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) lr[v] = sX[wave][4 * grp + v];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int qo = qw0 + 4 * grp + v;
-        if (qo < P.n_rows) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                __half hi, lo;
-                pf_split(O[nb][v] / lr[v], hi, lo);
-                const size_t at = pf_at(qo, head * D + 16 * nb + col, dm.h);
-                P.o[at] = hi; P.o[at + kPfLo] = lo;
-            }
-        }
+        const size_t at = pf_at(q0 + q, head * D + c8, dm.h);
+        *reinterpret_cast<u32x4 *>(P.o + at) = *reinterpret_cast<const u32x4 *>(hi);
+        *reinterpret_cast<u32x4 *>(P.o + at + kPfLo) = *reinterpret_cast<const u32x4 *>(lo);
     }
 }
 
@@ -421,6 +340,25 @@ bool pf_supported(const Dims &dm)
            !(dm.flags & kFlagSequentialResidual) && dm.r % 2 == 0;
 }
 
+// Queries per workgroup: a tile of K and V is fetched and transposed once per workgroup, so as many as leave the
+// chip filled; with fewer, the wavefronts split the keys instead.  By n = heads x blocks of 32 queries, us per layer
+// with 1 / 2 / 4 blocks of 32 (LayerNorm and products included): D = 80: n = 512 (3000 positions cached) 258 / 262 / 287,
+// 768: 288 / 287 / 291, 1024: 380 / 376 / 382, 2048: 689 / 681 / 678; D = 64: n = 128: 46 / 50 / 53, 1024: 145 / 148 / 172;
+// D = 128: n = 64 (3000 cached) 222 / 202 / 228, 1024: 785 / 762 / 768, 1536: 4 blocks 6 us faster than 2 (one block's
+// tile of 128 keys spills registers there and is not built).
+// Kernel times before (16 queries to a workgroup, 64 from 1024 tokens, 16x16x16 instructions) -> now: hidden 2560, 512
+// tokens 23 -> 16 us, 4096 tokens 370 -> 227; hidden 4096, 1531 tokens behind 700: 221 -> 126.
+template <int D>
+static void pf_attention(const PfParams &P, hipStream_t s)
+{
+    const int n = P.dm.H * ((P.n_rows + 31) / 32);
+    const int qw = n >= (D == 128 ? 1536 : 2048) ? 4 : D == 128 || n >= 768 ? 2 : 1;
+    const dim3 grid(P.dm.H, (P.n_rows + 32 * qw - 1) / (32 * qw));
+    if (qw == 4) hipLaunchKernelGGL((k_pf_attn<D, 4>), grid, dim3(256), 0, s, P);
+    else if (qw == 2) hipLaunchKernelGGL((k_pf_attn<D, 2>), grid, dim3(256), 0, s, P);
+    else if constexpr (D != 128) hipLaunchKernelGGL((k_pf_attn<D, 1>), grid, dim3(256), 0, s, P);
+}
+
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s)
 {
     const Dims &dm = P.dm;
@@ -428,22 +366,11 @@ hipError_t launch_pf_layer(const PfParams &P, hipStream_t s)
     hipLaunchKernelGGL(k_pf_ln, dim3(mt * kPfTile / 4), dim3(256), 0, s, P);
     hipError_t e = launch_pf_gemm_in(P, s);
     if (e != hipSuccess) return e;
-    if (P.n_rows >= kPfWideFrom) {
-        const dim3 ag(dm.H, (P.n_rows + kPfQW - 1) / kPfQW);
-        switch (dm.d) {
-        case 64: hipLaunchKernelGGL(k_pf_attn_wide<64>, ag, dim3(256), 0, s, P); break;
-        case 80: hipLaunchKernelGGL(k_pf_attn_wide<80>, ag, dim3(256), 0, s, P); break;
-        case 128: hipLaunchKernelGGL(k_pf_attn_wide<128>, ag, dim3(256), 0, s, P); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        const dim3 ag(dm.H, (P.n_rows + kPfQB - 1) / kPfQB);
-        switch (dm.d) {
-        case 64: hipLaunchKernelGGL(k_pf_attn<64>, ag, dim3(256), 0, s, P); break;
-        case 80: hipLaunchKernelGGL(k_pf_attn<80>, ag, dim3(256), 0, s, P); break;
-        case 128: hipLaunchKernelGGL(k_pf_attn<128>, ag, dim3(256), 0, s, P); break;
-        default: return hipErrorInvalidValue;
-        }
+    switch (dm.d) {
+    case 64: pf_attention<64>(P, s); break;
+    case 80: pf_attention<80>(P, s); break;
+    case 128: pf_attention<128>(P, s); break;
+    default: return hipErrorInvalidValue;
     }
     e = launch_pf_gemm_out(P, s);
     if (e != hipSuccess) return e;

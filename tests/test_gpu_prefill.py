@@ -144,7 +144,7 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
 
 
 # Every tile of the GEMM's plan and its edges (token counts around multiples of 64, 128 and 256, split and unsplit
-# products): against the path through the batched projections, which the cases above hold to the oracle.  Both sides
+# products) and of the attention: against the path through the batched projections, which the cases above hold to the oracle.  Both sides
 # round the same fp32 values to fp16 once, so an element differs by one step of its size at most, plus the drift of
 # the appended rows' own roundings (2e-3 of the row's root mean square covers it: a step of one V row in a mean of
 # two rows or more).
@@ -155,6 +155,11 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
     (synth.ModelShape(128, 2, 64, 64, 128, name="d64-h128"), 1, 130),           # the smallest K: fewer steps than stages
     (synth.ModelShape(1536, 24, 64, 16, 6144, name="d64-h1536"), 2, 1000),
     (synth.ModelShape(4096, 32, 128, 32, 16384, name="pythia-6.9b-block"), 1, 1531),
+    # the attention's three splits of a workgroup over queries and keys, at every head size, behind cached positions
+    (synth.ModelShape(512, 8, 64, 16, 2048, name="neox-h512"), 259, 95),
+    (synth.ModelShape(2048, 32, 64, 16, 2048, name="d64-h2048"), 31, 801),
+    (synth.ModelShape(2048, 32, 64, 16, 2048, name="d64-h2048"), 0, 2050),
+    (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 1000, 33),
 ])
 def test_gemm_tiles_against_the_batched_projections(shape, pos0, T):
     import torch
