@@ -843,7 +843,7 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         P.o = reinterpret_cast<__half *>(sc + pl.o);
         P.m = reinterpret_cast<__half *>(sc + pl.m);
         P.part = reinterpret_cast<float *>(sc + pl.part); P.part_bytes = pl.total - pl.part;
-        P.part_out = reinterpret_cast<float *>(sc + pl.y1); P.part_out_bytes = pl.total - pl.y1;
+        P.part_out_bytes = pl.total - pl.q;                // (where they start: pf_plan_pass)
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
         P.sync = reinterpret_cast<unsigned *>(ctx->ws + ctx->wl.sync);
         pf_plan_pass(P);
@@ -851,6 +851,7 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         for (int l = 0; l < L; ++l) {
             P.layer = l;
             P.w = static_cast<const __half *>(packed_layers[l]);
+            P.w_next = static_cast<const __half *>(packed_layers[l + 1 < L ? l + 1 : l]);
             P.kv = static_cast<__half *>(kv_layers[l]);
             P.xres = (l & 1) ? xb2 : xa;                   // the block's output is the next block's input
             P.xnext = (l & 1) ? xa : xb2;

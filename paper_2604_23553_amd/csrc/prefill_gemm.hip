@@ -7,8 +7,8 @@
 //                       side); the epilogue completes the LayerNorm, rotates, appends, applies GELU
 //   k_pf_gemm<kPfOut> : output projection and MLP-down as ONE product over the concatenated K
 //                       ([attention | GELU(up)] . [W_dense | W_down]^T) + biases + residual
-//   k_pf_reduce<>     : the parts of a product whose K is split over workgroups, added in order,
-//                       then the same epilogue
+//   k_pf_reduce       : the parts of the first product, where its K is split over workgroups, added in
+//                       order, then the same epilogue (the second one's: k_pf_row)
 //
 // Every sum has a fixed order: one bit pattern per build and pass size.
 #include <hip/hip_runtime.h>
@@ -22,18 +22,15 @@ typedef float pf_f32x16 __attribute__((ext_vector_type(16)));
 typedef int pf_i32x4 __attribute__((ext_vector_type(4)));
 
 enum { kPfIn = 0, kPfOut = 1 };
-enum { kPfQkv = 0, kPfUp = 1, kPfRes = 2 };       // what follows a product
+enum { kPfQkv = 0, kPfUp = 1 };                     // what follows the first product
 
 // the LayerNorm, completed: inv (W (gamma x) - mu s) + c, with c = W beta + b from the packing
 template <int EPI>
 __device__ __forceinline__ float pf_complete(const PfParams &P, int row, int col, float val)
 {
-    if (EPI == kPfQkv || EPI == kPfUp) {
-        const float2 rc = reinterpret_cast<const float2 *>(P.w + (EPI == kPfQkv ? P.lay.rc_qkv : P.lay.rc_up))[col];
-        const float2 st = P.stats[row];
-        val = (val - st.x * rc.x) * st.y + rc.y;
-    }
-    return val;
+    const float2 rc = reinterpret_cast<const float2 *>(P.w + (EPI == kPfQkv ? P.lay.rc_qkv : P.lay.rc_up))[col];
+    const float2 st = P.stats[row];
+    return (val - st.x * rc.x) * st.y + rc.y;
 }
 
 // The element (row = token, col = output feature) with the completed value `val`;
@@ -54,16 +51,11 @@ __device__ __forceinline__ void pf_store(const PfParams &P, int row, int col, fl
         }
         if (c == 0) P.q[(size_t)row * h + nh * dm.d + dim] = val;
         else P.kv[kv_offset(dm, c - 1, P.b, nh, dim, P.pos0 + row)] = __float2half_rn(val);
-    } else if (EPI == kPfUp) {
+    } else {
         __half hi, lo;
         pf_split(pf_gelu(val, dm.flags), hi, lo);
         const size_t at = pf_at(row, col, dm.f);
         P.m[at] = hi; P.m[at + kPfLo] = lo;
-    } else {
-        const float branches = (val + __half2float(P.w[P.lay.b_dense + col])) + __half2float(P.w[P.lay.b_down + col]);
-        const float res = P.xres[(size_t)row * h + col] + branches;
-        if (P.layer == P.n_layers - 1) P.out[(size_t)row * h + col] = __float2half_rn(res);
-        else P.xnext[(size_t)row * h + col] = res;
     }
 }
 
@@ -110,7 +102,7 @@ constexpr int pf_per_cu(int lds) { return 160 * 1024 / lds > 3 ? 3 : 160 * 1024 
 // Tiles are dealt so that consecutive numbers run on the same XCD (workgroup i runs on XCD i % 8), in groups of gm token
 // tiles: an XCD works on a block of about gm x (its workgroups / gm) tiles and its L2 holds both operands' rows.
 // splits > 1: workgroup z of a tile takes the z-th part of K and leaves its sums in part[z][row][col] (rows of whole
-// token tiles); k_pf_reduce adds the parts in order and finishes.
+// token tiles); k_pf_reduce and k_pf_row add the parts in order and finish.
 template <int FL, int BM, int BN, int BK, int ST, int WM, int WN>
 __global__ void __launch_bounds__(64 * WM * WN, pf_per_cu(pf_gemm_lds_bytes<BM, BN, BK, ST>()) * WM * WN / 4)
 k_pf_gemm(PfParams P, int splits, int gm)
@@ -376,24 +368,21 @@ k_pf_gemm(PfParams P, int splits, int gm)
     }
 }
 
-// the parts of a split-K product (part rows: prows per part), added in order, then what
-// follows the product; a thread takes four consecutive columns of a row (two rotation pairs)
-template <int FL>
+// the parts of the split first product (prows rows per part), added in order, then what follows it;
+// a thread takes four consecutive columns of a row (two rotation pairs).  (The second product's parts
+// are added by the kernel that prepares the next layer's input: k_pf_row.)
 __global__ void __launch_bounds__(256) k_pf_reduce(PfParams P, int splits, int prows)
 {
-    const int nq = 3 * P.dm.h, N = FL == kPfIn ? nq + P.dm.f : P.dm.h, n4 = N >> 2;
+    const int nq = 3 * P.dm.h, N = nq + P.dm.f, n4 = N >> 2;
     const unsigned n_el = (unsigned)P.n_rows * (unsigned)n4;
     const size_t zstride = (size_t)prows * N;
     for (unsigned e = blockIdx.x * 256u + threadIdx.x; e < n_el; e += gridDim.x * 256u) {
         const int row = (int)(e / (unsigned)n4), col = (int)(e - (unsigned)row * (unsigned)n4) * 4;
-        const float *p = (FL == kPfIn ? P.part : P.part_out) + (size_t)row * N + col;
+        const float *p = P.part + (size_t)row * N + col;
         f32x4 s = *as_global(reinterpret_cast<const f32x4 *>(p));
         for (int z = 1; z < splits; ++z) s += *as_global(reinterpret_cast<const f32x4 *>(p + z * zstride));
         float v[4];
-        if (FL == kPfOut) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pf_store<kPfRes>(P, row, col + j, s[j], 0.f);
-        } else if (col < nq) {
+        if (col < nq) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[j] = pf_complete<kPfQkv>(P, row, col + j, s[j]);
 #pragma unroll
@@ -420,9 +409,9 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_pf_gemm<FL, BM, BN, BK, ST, WM, WN>), dim3((ntn * mt * splits + 7) / 8 * 8), dim3(64 * WM * WN), lds, s, P,
                        splits, BM == 256 ? 4 : 8);
-    if (splits > 1) {
+    if (FL == kPfIn && splits > 1) {
         const size_t n_el = (size_t)P.n_rows * (nall / 4);
-        hipLaunchKernelGGL(k_pf_reduce<FL>, dim3((unsigned)((n_el + 255) / 256)), dim3(256), 0, s, P, splits, mt * BM);
+        hipLaunchKernelGGL(k_pf_reduce, dim3((unsigned)((n_el + 255) / 256)), dim3(256), 0, s, P, splits, mt * BM);
     }
     return hipSuccess;
 }
@@ -449,11 +438,10 @@ static const PfTileCost kPfTiles[kPfTileKinds] = {
 };
 constexpr int kPfCus = 256;
 
-static PfPlan pf_plan(const PfParams &P, bool in)
+static PfPlan pf_plan(const PfParams &P, bool in, size_t part_bytes, float *cost_out)
 {
     const int h = P.dm.h, f = P.dm.f, nall = in ? 3 * h + f : h;
     const float steps = (float)(in ? h : h + f) / 32.f;
-    const size_t part_bytes = in ? P.part_bytes : P.part_out_bytes;
     PfPlan best = {0, 1};
     float best_cost = 1e30f;
     for (int k = 0; k < kPfTileKinds; ++k) {
@@ -470,13 +458,31 @@ static PfPlan pf_plan(const PfParams &P, bool in)
             if (cost < best_cost) { best_cost = cost; best.tile = k; best.splits = sp; }
         }
     }
+    *cost_out = best_cost;
     return best;
 }
 
 void pf_plan_pass(PfParams &P)
 {
-    P.plan_in = pf_plan(P, true);
-    P.plan_out = pf_plan(P, false);
+    float cost, cost_y;
+    P.plan_in = pf_plan(P, true, P.part_bytes, &cost);
+    // The second product's parts lie behind y2, where the kernel that adds them can leave the next layer's y1 and
+    // y2; or, where that space is too small for the splits that pay, from y1 on, with the LayerNorm in a launch of
+    // its own again (10 us at 512 tokens and below, 24 at 4096).  An unsplit product has that launch as well.
+    const size_t ahead = (size_t)((char *)P.q - (char *)P.y1);
+    const float ln = 8.f + 1.6e-6f * P.n_rows * (float)P.dm.h;
+    P.part_out = reinterpret_cast<float *>(P.q);
+    P.plan_out = pf_plan(P, false, P.part_out_bytes, &cost);
+    if (P.plan_out.splits == 1) cost += ln;
+    const PfPlan wide = pf_plan(P, false, P.part_out_bytes + ahead, &cost_y);
+    if (cost_y + ln < cost) {
+        P.plan_out = wide;
+        P.part_out = reinterpret_cast<float *>(P.y1);
+        P.part_out_bytes += ahead;
+    }
+    P.row_fused = P.plan_out.splits > 1 && P.part_out == P.q;
+    const int bm = kPfTiles[P.plan_out.tile].bm;
+    P.part_out_stride = (size_t)((P.n_rows + bm - 1) / bm * bm) * P.dm.h;
 }
 
 template <int FL>

@@ -6,9 +6,10 @@
 // LDS-tiled GEMMs on the matrix cores (prefill_gemm.hip); the attention of
 // a pass reads the cache rows its own QKV launch appended.
 //
-//   k_pf_ln     : per token: mean, 1/sigma, and gamma_1 * x, gamma_2 * x as two fp16
-//                 planes each (head + remainder: y = hi + lo to ~2^-22, so that the
-//                 fp16 matrix instruction reproduces the fp32 product to rounding)
+//   k_pf_row<>  : per token: (the previous layer's output from the parts of its product,)
+//                 mean, 1/sigma, and gamma_1 * x, gamma_2 * x as two fp16 planes each (head +
+//                 remainder: y = hi + lo to ~2^-22, so that the fp16 matrix instruction
+//                 reproduces the fp32 product to rounding)
 //   the products: prefill_gemm.hip - QKV and MLP-up in one launch, output projection and
 //                 MLP-down as one product
 //   k_pf_attn<> : causal attention of a block of 32, 64 or 128 queries of one head over the
@@ -23,75 +24,110 @@
 namespace cfpp {
 
 // ---------------------------------------------------------------------------
-// One wavefront per scratch row, four rows per workgroup, no barrier: a lane holds the
-// row's elements 4 (lane + 64 j) .. + 3, j < h / 256 (hidden: a multiple of 128, at most
-// 4096; with an odd number of 128s the upper half of the lanes sits out the last j).
-// Rows past the pass's tokens get zero planes (their products are never stored).
-constexpr int kPfLnVec = 16;           // float4 per lane: hidden <= 4096
-__global__ void __launch_bounds__(256) k_pf_ln(PfParams P)
+// What a layer's first product reads, for one token: the layer input x, its mean and 1/sigma, and
+// gamma_1 * x, gamma_2 * x as head and remainder planes.  256 threads a token, a thread holds the
+// elements 4 (tid + 256 j) .. + 3, j < h / 1024 (hidden: a multiple of 128, at most 4096).  Rows
+// past the pass's tokens are left alone: what a product makes of them is never stored.
+// FROM_PARTS: x is the previous layer's output, still in the parts of its second product - the parts
+// are added in order, biases and residual follow, and the row goes to the residual stream (and, as
+// the last layer's output, to out) on the way: one launch where the sum and the LayerNorm were two
+// (512 tokens of the 2560-wide shape: 10.1 + 10.2 us).  Bound by the latency of a row's loads and
+// stores, hence four wavefronts to a row instead of one.
+constexpr int kPfRowVec = 4;           // float4 per thread: hidden <= 4096
+template <bool FROM_PARTS>
+__global__ void __launch_bounds__(256) k_pf_row(PfParams P)
 {
+    __shared__ float red[2][4];
     const Dims &dm = P.dm;
-    const int h = dm.h, lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int nv = h >> 2;                                 // groups of 4 elements in a row
-    if (row >= P.n_rows) {
-        const uint2 z = {0u, 0u};
-        for (int g = lane; g < nv; g += 64) {
-            const size_t at = pf_at(row, 4 * g, h);
-            *reinterpret_cast<uint2 *>(P.y1 + at) = z; *reinterpret_cast<uint2 *>(P.y1 + at + kPfLo) = z;
-            *reinterpret_cast<uint2 *>(P.y2 + at) = z; *reinterpret_cast<uint2 *>(P.y2 + at + kPfLo) = z;
+    const int h = dm.h, nv = h >> 2, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = blockIdx.x;
+    const bool last = FROM_PARTS && P.layer == P.n_layers - 1, bare = last || (FROM_PARTS && !P.row_fused);   // bare: no LayerNorm here
+    const __half *wn = FROM_PARTS ? P.w_next : P.w;        // the layer whose LayerNorms these are
+    f32x4 x[kPfRowVec];
+    uint2 g1[kPfRowVec], g2[kPfRowVec];
+#pragma unroll
+    for (int j = 0; j < kPfRowVec; ++j) {
+        const int g = tid + 256 * j;
+        x[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (g >= nv) continue;
+        const size_t at = (size_t)row * h + 4 * g;
+        if (!bare) {
+            g1[j] = *reinterpret_cast<const uint2 *>(wn + P.lay.ln1_g + 4 * g);
+            g2[j] = *reinterpret_cast<const uint2 *>(wn + P.lay.ln2_g + 4 * g);
         }
-        return;
+        if (FROM_PARTS) {
+            const size_t zstride = P.part_out_stride;
+            const float *p = P.part_out + at;
+            const f32x4 r = *as_global(reinterpret_cast<const f32x4 *>(P.xres + at));
+            const uint2 de = *reinterpret_cast<const uint2 *>(P.w + P.lay.b_dense + 4 * g), dn = *reinterpret_cast<const uint2 *>(P.w + P.lay.b_down + 4 * g);
+            f32x4 s = *as_global(reinterpret_cast<const f32x4 *>(p));
+            const int splits = P.plan_out.splits;
+            for (int z = 1; z < splits; z += 5) {          // five parts requested at a time (past the last: the last again)
+                f32x4 t[5];
+#pragma unroll
+                for (int u = 0; u < 5; ++u) t[u] = *as_global(reinterpret_cast<const f32x4 *>(p + min(z + u, splits - 1) * zstride));
+#pragma unroll
+                for (int u = 0; u < 5; ++u)
+                    if (z + u < splits) s += t[u];
+            }
+            const float2 de0 = unpack_h2(de.x), de1 = unpack_h2(de.y), dn0 = unpack_h2(dn.x), dn1 = unpack_h2(dn.y);
+            x[j][0] = r[0] + ((s[0] + de0.x) + dn0.x);
+            x[j][1] = r[1] + ((s[1] + de0.y) + dn0.y);
+            x[j][2] = r[2] + ((s[2] + de1.x) + dn1.x);
+            x[j][3] = r[3] + ((s[3] + de1.y) + dn1.y);
+            if (last) {
+                uint2 o;
+                o.x = pf_pack2(x[j][0], x[j][1]); o.y = pf_pack2(x[j][2], x[j][3]);
+                *reinterpret_cast<uint2 *>(P.out + at) = o;
+            } else {
+                *reinterpret_cast<f32x4 *>(P.xnext + at) = x[j];
+            }
+        } else if (P.layer == 0) {
+            const uint2 w = *reinterpret_cast<const uint2 *>(P.x_in + at);
+            const float2 a = unpack_h2(w.x), b = unpack_h2(w.y);
+            x[j] = f32x4{a.x, a.y, b.x, b.y};
+            *reinterpret_cast<f32x4 *>(P.xres + at) = x[j];
+        } else {
+            x[j] = *reinterpret_cast<const f32x4 *>(P.xres + at);
+        }
     }
-    f32x4 x[kPfLnVec];
+    if (bare) return;                                      // (uniform)
     float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < kPfLnVec; ++j) {
-        const int g = lane + 64 * j;
-        x[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (g < nv) {
-            if (P.layer == 0) {
-                const uint2 w = *reinterpret_cast<const uint2 *>(P.x_in + (size_t)row * h + 4 * g);
-                const float2 a = unpack_h2(w.x), b = unpack_h2(w.y);
-                x[j] = f32x4{a.x, a.y, b.x, b.y};
-                *reinterpret_cast<f32x4 *>(P.xres + (size_t)row * h + 4 * g) = x[j];
-            } else {
-                x[j] = *reinterpret_cast<const f32x4 *>(P.xres + (size_t)row * h + 4 * g);
-            }
-        }
-        s += (x[j][0] + x[j][1]) + (x[j][2] + x[j][3]);
-    }
-    const float mean = wave_sum(s) / (float)h;
+    for (int j = 0; j < kPfRowVec; ++j) s += (x[j][0] + x[j][1]) + (x[j][2] + x[j][3]);
+    s = wave_sum(s);
+    if (lane == 0) red[0][wave] = s;
+    __syncthreads();
+    const float mean = ((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])) / (float)h;
     float q = 0.f;
 #pragma unroll
-    for (int j = 0; j < kPfLnVec; ++j) {
-        if (lane + 64 * j < nv) {
+    for (int j = 0; j < kPfRowVec; ++j) {
+        if (tid + 256 * j < nv) {
             const f32x4 dl = x[j] - mean;
             q += (dl[0] * dl[0] + dl[1] * dl[1]) + (dl[2] * dl[2] + dl[3] * dl[3]);
         }
     }
-    const float inv = 1.0f / sqrtf(wave_sum(q) / (float)h + dm.ln_eps);
-    if (lane == 0) P.stats[row] = float2{mean, inv};
-    const __half *g1 = P.w + P.lay.ln1_g, *g2 = P.w + P.lay.ln2_g;
+    q = wave_sum(q);
+    if (lane == 0) red[1][wave] = q;
 #pragma unroll
-    for (int j = 0; j < kPfLnVec; ++j) {
-        const int g = lane + 64 * j;
-        if (g < nv) {
-            const uint2 w1 = *reinterpret_cast<const uint2 *>(g1 + 4 * g), w2 = *reinterpret_cast<const uint2 *>(g2 + 4 * g);
-            const float2 a1 = unpack_h2(w1.x), b1 = unpack_h2(w1.y), a2 = unpack_h2(w2.x), b2 = unpack_h2(w2.y);
-            const float ga[4] = {a1.x, a1.y, b1.x, b1.y}, gb[4] = {a2.x, a2.y, b2.x, b2.y};
-            __half h1[4], l1[4], h2[4], l2[4];
+    for (int j = 0; j < kPfRowVec; ++j) {
+        const int g = tid + 256 * j;
+        if (g >= nv) continue;
+        const float2 a1 = unpack_h2(g1[j].x), b1 = unpack_h2(g1[j].y), a2 = unpack_h2(g2[j].x), b2 = unpack_h2(g2[j].y);
+        const float ga[4] = {a1.x, a1.y, b1.x, b1.y}, gb[4] = {a2.x, a2.y, b2.x, b2.y};
+        __half h1[4], l1[4], h2[4], l2[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pf_split(x[j][e] * ga[e], h1[e], l1[e]);
-                pf_split(x[j][e] * gb[e], h2[e], l2[e]);
-            }
-            const size_t at = pf_at(row, 4 * g, h);
-            *reinterpret_cast<uint2 *>(P.y1 + at) = *reinterpret_cast<const uint2 *>(h1);
-            *reinterpret_cast<uint2 *>(P.y1 + at + kPfLo) = *reinterpret_cast<const uint2 *>(l1);
-            *reinterpret_cast<uint2 *>(P.y2 + at) = *reinterpret_cast<const uint2 *>(h2);
-            *reinterpret_cast<uint2 *>(P.y2 + at + kPfLo) = *reinterpret_cast<const uint2 *>(l2);
+        for (int e = 0; e < 4; ++e) {
+            pf_split(x[j][e] * ga[e], h1[e], l1[e]);
+            pf_split(x[j][e] * gb[e], h2[e], l2[e]);
         }
+        const size_t at = pf_at(row, 4 * g, h);
+        *reinterpret_cast<uint2 *>(P.y1 + at) = *reinterpret_cast<const uint2 *>(h1);
+        *reinterpret_cast<uint2 *>(P.y1 + at + kPfLo) = *reinterpret_cast<const uint2 *>(l1);
+        *reinterpret_cast<uint2 *>(P.y2 + at) = *reinterpret_cast<const uint2 *>(h2);
+        *reinterpret_cast<uint2 *>(P.y2 + at + kPfLo) = *reinterpret_cast<const uint2 *>(l2);
     }
+    __syncthreads();
+    if (tid == 0) P.stats[row] = float2{mean, 1.0f / sqrtf(((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])) / (float)h + dm.ln_eps)};
 }
 
 // ---------------------------------------------------------------------------
@@ -336,7 +372,7 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
 // ---------------------------------------------------------------------------
 bool pf_supported(const Dims &dm)
 {
-    return dm.h % kPfTile == 0 && dm.f % kPfTile == 0 && dm.h <= 256 * kPfLnVec && (dm.d == 64 || dm.d == 80 || dm.d == 128) &&
+    return dm.h % kPfTile == 0 && dm.f % kPfTile == 0 && dm.h <= 1024 * kPfRowVec && (dm.d == 64 || dm.d == 80 || dm.d == 128) &&
            !(dm.flags & kFlagSequentialResidual) && dm.r % 2 == 0;
 }
 
@@ -362,8 +398,8 @@ static void pf_attention(const PfParams &P, hipStream_t s)
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s)
 {
     const Dims &dm = P.dm;
-    const int mt = (P.n_rows + kPfTile - 1) / kPfTile;
-    hipLaunchKernelGGL(k_pf_ln, dim3(mt * kPfTile / 4), dim3(256), 0, s, P);
+    // (else the previous layer's last launch has left this one's input ready)
+    if (P.layer == 0 || !P.row_fused) hipLaunchKernelGGL(k_pf_row<false>, dim3(P.n_rows), dim3(256), 0, s, P);
     hipError_t e = launch_pf_gemm_in(P, s);
     if (e != hipSuccess) return e;
     switch (dm.d) {
@@ -374,6 +410,7 @@ hipError_t launch_pf_layer(const PfParams &P, hipStream_t s)
     }
     e = launch_pf_gemm_out(P, s);
     if (e != hipSuccess) return e;
+    if (P.plan_out.splits > 1) hipLaunchKernelGGL(k_pf_row<true>, dim3(P.n_rows), dim3(256), 0, s, P);
     return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ struct PfLayout {
     size_t y1, y2;                 // half [rows][2 h + pad]: gamma_1 * x and gamma_2 * x
     size_t q;                      // float [rows][h]: rotated queries
     size_t part;                   // float [parts][rows][columns]: the parts of a product whose K is split over workgroups
-    size_t total;                  // (the second product's parts start at y1: what lies between is no longer needed then)
+    size_t total;                  // (the second product's parts start at q or y1: what lies between is no longer needed then)
 };
 
 CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
@@ -56,6 +56,7 @@ struct PfParams {
     Dims dm;
     PackedLayout lay;
     const __half *w;        // packed layer
+    const __half *w_next;   // the layer behind it (last layer: unused)
     __half *kv;             // the layer's cache
     int b;                  // sequence inside the cache
     int pos0;               // position of the pass's first token
@@ -70,8 +71,9 @@ struct PfParams {
     __half *o, *m;
     float *part;            // parts of the first product (QKV, MLP-up), part_bytes
     float *part_out;        // parts of the second one, part_out_bytes
-    size_t part_bytes, part_out_bytes;
+    size_t part_bytes, part_out_bytes, part_out_stride;     // (stride: floats between the second product's parts)
     PfPlan plan_in, plan_out;
+    bool row_fused;         // the kernel that adds the second product's parts prepares the next layer's input too
     const float2 *rope;
     unsigned *sync;
 };
