@@ -444,8 +444,6 @@ static StepParams make_params(const cfpp_ctx *ctx, const Shape &sh, int b, const
     P.out = static_cast<__half *>(out) + (size_t)b * dm.h;
     P.n_layers = n_layers;
     P.parts = kPartAll;
-    P.attn_g0 = 0;
-    P.attn_G = 0;
     P.attn_bstep = 1;
     P.rows_qkv = sh.rows_qkv; P.rows_up = sh.rows_up; P.rows_h = sh.rows_h;
     P.f_a = sh.f_a; P.rows_up_a = sh.rows_up_a; P.rows_up_b = sh.rows_up_b;
@@ -518,17 +516,9 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
         B.rope = reinterpret_cast<const float2 *>(ctx->ws + wl.rope);
         B.sync = reinterpret_cast<unsigned *>(ctx->ws + wl.sync);
         HIP_OK(launch_bat_qkv_up(B, sh.grid, s));
-        if (sh.grid >= B.nb) {
-            StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
-            if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
-            HIP_OK(launch_attention_batched(P, B.nb, w, kv, sh.grid, sh.threads, s));
-        } else {
-            for (int b = b0; b < b0 + B.nb; ++b) {
-                StepParams P = make_params(ctx, sh, b, x, pos_dev, out, n_layers);
-                if (kv_seq >= 0) P.b = kv_seq;
-                HIP_OK(launch_attention_only(P, w, kv, sh.grid, sh.threads, s));
-            }
-        }
+        StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
+        if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
+        HIP_OK(launch_attention_batched(P, B.nb, kv, s));
         HIP_OK(launch_bat_out(B, sh.grid, s));
     }
     return CFPP_OK;

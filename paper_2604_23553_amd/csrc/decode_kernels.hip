@@ -367,23 +367,41 @@ k_phase_c(StepParams P, const __half *w, int layer)
     phase_c(P, w, layer, lds, sync);
 }
 
-// The attention of several sequences in one launch.  P holds the parameters of
-// the first sequence; sequence i follows at the workspace's usual strides.
-// Every workgroup works out the split from the positions in device memory:
-// workgroups are dealt in proportion to the cache rows of each sequence, at
-// least one each (grid >= nb).
-constexpr int kAttnBatchMax = 8;
-template <int D>
-__global__ void __launch_bounds__(kMaxThreads)
-k_attention_batched(StepParams P, int nb, const __half *w, const __half *kv)
+// The attention of several sequences in one launch.  P holds the parameters of the first
+// sequence; sequence i follows at the workspace's usual strides.  A workgroup (4 wavefronts,
+// several to a CU) takes one piece of ONE head of one sequence: every head of sequence i is cut
+// into 1 + spare * rows_i / rows_all pieces, worked out by every workgroup from the positions in
+// device memory (the grid is the most that can come out; what is over leaves at once).  So a
+// short sequence is as many workgroups as it has heads, and none does several heads one after
+// the other: dealing 256 workgroups of 512 threads to the sequences by length left the heads of
+// a short one to one or two of them, a staging, merge and hand-over (about 1.2 us) per head.
+// Wavefronts interleave the piece's rows (PPW positions each), two rows in flight; the running
+// softmax is per lane group and merged lane -> wavefront -> workgroup -> head, each in a fixed
+// order; the workgroup that delivers a head's last piece adds the pieces in order.  The new token's
+// K and V row is read from the cache like the others (the launch before this one wrote it).
+// STREAM: non-temporal loads (every row is read once); without: a group of prompt tokens, whose
+// queries read the same rows (attn_bstep = 0).
+constexpr int kAttnBatchMax = 8, kAttnBatchThreads = 256;
+// Workgroups dealt beyond one per head and sequence, and the fewest rows worth a piece.  us per step and layer, before
+// -> with pieces of 8 / 16 / 32 rows: five sequences of 37 .. 2048 positions (hidden 2560) 85.0 -> 65.9 / 65.7 / 63.6;
+// 8 prompt tokens behind 1000: 67.3 -> 70.5 / 66.4 / 64.2; two sequences of 8000: 80.0 -> 81.8 / 79.4 / 78.9.  512 spare
+// ones: eight sequences of 3000 .. 8000 132.3 -> 136.5 (1024: 132.2), one block of hidden 4096 with 8 sequences
+// 237.3 -> 238.7 (235.3).
+constexpr int kAttnSpareGroups = 1024, kAttnPieceRows = 32;
+
+template <int D, bool STREAM>
+__global__ void __launch_bounds__(kAttnBatchThreads, 3)
+k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
 {
-    extern __shared__ __align__(16) float lds[];
-    constexpr int PPW = AttnShape<D>::PPW;
+    using A = AttnShape<D>;
+    constexpr int LPP = A::LPP, PPW = A::PPW, NP = A::NP, NV = A::NV, NE = (D + 63) / 64, NW = kAttnBatchThreads / 64;
+    __shared__ __align__(16) float qs[D];
+    __shared__ float wp[NW * D], wm[NW], wl[NW];
     const Dims &dm = P.dm;
-    // (cache rows per head: every head of a sequence has the same number, so the shares are
-    // the same as by rows of all heads, and spare * sum stays below 2^32: max_seq <= 2^20)
-    unsigned rows[kAttnBatchMax];
-    unsigned total = 0;
+    const int H = dm.H, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // this workgroup's sequence, head and piece (rows: per head, every head of a sequence has the same number;
+    // spare * sum stays below 2^32: max_seq <= 2^20)
+    unsigned rows[kAttnBatchMax], total = 0;
     bool ok = true;
 #pragma unroll
     for (int i = 0; i < kAttnBatchMax; ++i) {
@@ -396,41 +414,174 @@ k_attention_batched(StepParams P, int nb, const __half *w, const __half *kv)
         }
     }
     if (!ok) {
-        if (threadIdx.x == 0 && blockIdx.x == 0)
+        if (tid == 0 && blockIdx.x == 0)
             __hip_atomic_store(&P.sync[kSyncErr], (unsigned)kErrBadPos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    const unsigned spare = gridDim.x - (unsigned)nb;
-    const int g = blockIdx.x;
-    unsigned before = 0;
-    int mine = -1, g0 = 0, g1 = 0;
-    int lo = 0;
+    int mine = -1, R = 0, pieces = 1, local = 0, base = 0;
 #pragma unroll
     for (int i = 0; i < kAttnBatchMax; ++i) {
         if (i < nb) {
-            before += rows[i];
-            const int hi = (int)(spare * before / total) + i + 1;
-            if (g >= lo && g < hi) { mine = i; g0 = lo; g1 = hi; }
-            lo = hi;
+            const int n = min(1 + (int)((unsigned)spare * rows[i] / total), ((int)rows[i] + kAttnPieceRows - 1) / kAttnPieceRows);
+            const int at = (int)blockIdx.x - base;
+            if (at >= 0 && at < n * H) { mine = i; R = (int)rows[i]; pieces = n; local = at; }
+            base += n * H;
         }
     }
-    if (mine < 0) return;
-    StepParams Q = P;
-    Q.b = P.b + mine * P.attn_bstep;
-    Q.pos = P.pos + mine;
-    Q.q = P.q + (size_t)mine * dm.h;
-    Q.o = P.o + (size_t)mine * dm.h;
-    Q.m = P.m + (size_t)mine * dm.f;
-    Q.part = P.part + (size_t)mine * dm.H * P.part_slots * (dm.d + 2);
-    Q.seg_cnt = P.seg_cnt + (size_t)mine * dm.H;
-    Q.attn_g0 = g0;
-    Q.attn_G = g1 - g0;
-    Q.parts = kPartAttention;
-    // the attention alone: nothing of the MLP-down stretch that shares phase B with it
-    // (no GELU(up) staged into LDS, no weights requested)
-    Tracer tr;
-    tr.init(Q, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), 16);
-    attn_share<D>(Q, kv, *Q.pos + 1, lds, opaque_thread_index(), [] {}, [] {}, [] {}, [] {}, tr);
+    if (mine < 0) return;                                  // (whole workgroup)
+    const int head = local % H, piece = local / H;
+    const int b = P.b + mine * P.attn_bstep, t_last = P.pos[mine];
+    const int lo = (int)((long long)R * piece / pieces), hi = (int)((long long)R * (piece + 1) / pieces);
+    const int sub = lane & (LPP - 1), tl = lane / LPP;
+    const __half *Kh = kv + kv_offset(dm, 0, b, head, 0, 0), *Vh = kv + kv_offset(dm, 1, b, head, 0, 0);
+    unsigned koff[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int pc = sub + LPP * k;
+        koff[k] = ((unsigned)(pc >> 1) * (unsigned)dm.max_seq * 16u + (unsigned)(pc & 1) * 8u) * 2u;
+    }
+    u32x4 k0[NP], v0[NP], k1[NP], v1[NP];
+    // always 2 NP loads, every lane active: the load counter tells rows in flight apart (rows past the piece's end
+    // and positions past the last re-read the last position; their weight is zero)
+    auto issue = [&](u32x4 (&kk)[NP], u32x4 (&vv)[NP], int row) {
+        const int t = row < hi ? row * PPW + tl : t_last;
+        const unsigned tb = (unsigned)min(t, t_last) * 32u;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (STREAM) kk[k] = load16_stream_at(Kh, koff[k] + tb);
+            else kk[k] = *as_global(reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(Kh) + (koff[k] + tb)));
+        }
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (STREAM) vv[k] = load16_stream_at(Vh, koff[k] + tb);
+            else vv[k] = *as_global(reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(Vh) + (koff[k] + tb)));
+        }
+        __builtin_amdgcn_sched_barrier(0);                 // the loads stay here, ahead of the arithmetic
+    };
+    const float q_r = tid < D ? P.q[(size_t)mine * dm.h + head * D + tid] : 0.f;
+    issue(k0, v0, lo + wave);
+    issue(k1, v1, lo + wave + NW);
+    if (tid < D) qs[tid] = q_r * (1.44269504088896340736f / sqrtf((float)D));
+    __syncthreads();
+    float acc[NV], m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) acc[i] = 0.f;
+    auto process = [&](const u32x4 (&kk)[NP], const u32x4 (&vv)[NP], int row) {
+        const bool valid = row * PPW + tl <= t_last;
+        int qoff = 8 * sub;
+        asm volatile("" : "+v"(qoff));                     // (q is re-read from LDS for every row, not kept in 8 NP registers)
+        float sp = 0.f;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const float4 qa = *reinterpret_cast<const float4 *>(qs + qoff + 8 * LPP * k);
+            const float4 qb = *reinterpret_cast<const float4 *>(qs + qoff + 8 * LPP * k + 4);
+            sp = dot8(kk[k], qa, qb, sp);
+        }
+        sp += lane_xor<1>(sp);                             // the lanes sharing this position
+        if constexpr (LPP == 4) sp += lane_xor<2>(sp);
+        const float sc = valid ? sp : -INFINITY;
+        const float mn = fmaxf(m_run, sc);
+        const float corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
+        const float p = valid ? __builtin_amdgcn_exp2f(sc - mn) : 0.f;
+        l_run = l_run * corr + p;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const float2 a = unpack_h2(vv[k].x), b2 = unpack_h2(vv[k].y), c = unpack_h2(vv[k].z), e = unpack_h2(vv[k].w);
+            float *ac = acc + 8 * k;
+            ac[0] = fmaf(p, a.x, ac[0] * corr); ac[1] = fmaf(p, a.y, ac[1] * corr);
+            ac[2] = fmaf(p, b2.x, ac[2] * corr); ac[3] = fmaf(p, b2.y, ac[3] * corr);
+            ac[4] = fmaf(p, c.x, ac[4] * corr); ac[5] = fmaf(p, c.y, ac[5] * corr);
+            ac[6] = fmaf(p, e.x, ac[6] * corr); ac[7] = fmaf(p, e.y, ac[7] * corr);
+        }
+        m_run = mn;
+    };
+    for (int r = lo + wave; r < hi; r += 2 * NW) {
+        process(k0, v0, r);
+        issue(k0, v0, r + 2 * NW);
+        if (r + NW < hi) process(k1, v1, r + NW);          // (uniform)
+        issue(k1, v1, r + 3 * NW);
+    }
+    // lanes -> wavefront (a wavefront without rows leaves (0, -inf, 0)) -> workgroup
+    {
+        const float mw = wave_max(m_run);
+        const float fl = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mw);
+        const float lw = wave_sum(sub == 0 ? l_run * fl : 0.f);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) acc[i] *= fl;
+        int off, cnt;
+        reduce_scatter<NV, LPP>(acc, lane, off, cnt);
+#pragma unroll
+        for (int i = 0; i < A::NLEFT; ++i) {
+            if (i < cnt) {
+                const int idx = off + i;                   // accumulator index: piece idx / 8, element idx % 8
+                wp[wave * D + 8 * (sub + LPP * (idx >> 3)) + (idx & 7)] = acc[i];
+            }
+        }
+        if (lane == 0) { wm[wave] = mw; wl[wave] = lw; }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    float M = wm[0], L = 0.f, O[NE];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, wm[w]);      // (the piece has rows: finite)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) O[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float ew = wm[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(wm[w] - M);
+        L += wl[w] * ew;
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (lane + 64 * e < D) O[e] += wp[w * D + lane + 64 * e] * ew;
+    }
+    float *out = P.o + (size_t)mine * dm.h + head * D;
+    if (pieces == 1) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (lane + 64 * e < D) out[lane + 64 * e] = O[e] / L;
+        return;
+    }
+    // publish the piece; the last one of the head adds them in order
+    const size_t hd = (size_t)mine * H + head;
+    float *first = P.part + hd * P.part_slots * (D + 2), *slot = first + (size_t)piece * (D + 2);
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        if (lane + 64 * e < D) xwg_store(slot + lane + 64 * e, O[e]);
+    if (lane == 0) { xwg_store(slot + D, M); xwg_store(slot + D + 1, L); }
+    xwg_wait_stores();
+    unsigned old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(&P.seg_cnt[hd], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane((int)old) != pieces - 1) return;
+    constexpr int CB = 8;                                  // pieces whose loads are in flight together
+    M = -INFINITY; L = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) O[e] = 0.f;
+    for (int j0 = 0; j0 < pieces; j0 += CB) {
+        float mj[CB], lj[CB], oj[CB][NE];
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const float *sj = first + (size_t)min(j0 + j, pieces - 1) * (D + 2);
+            mj[j] = xwg_load(sj + D);
+            lj[j] = xwg_load(sj + D + 1);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) oj[j][e] = xwg_load(sj + (lane + 64 * e < D ? lane + 64 * e : 0));
+        }
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            if (j0 + j < pieces) {
+                const float mn = fmaxf(M, mj[j]);
+                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = __builtin_amdgcn_exp2f(mj[j] - mn);
+                L = L * c0 + lj[j] * c1;
+#pragma unroll
+                for (int e = 0; e < NE; ++e) O[e] = O[e] * c0 + oj[j][e] * c1;
+                M = mn;
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        if (lane + 64 * e < D) out[lane + 64 * e] = O[e] / L;
+    if (lane == 0) __hip_atomic_store(&P.seg_cnt[hd], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int D>
@@ -478,29 +629,22 @@ hipError_t launch_phases(const StepParams &P, const __half *w, __half *kv, int l
     return hipErrorInvalidValue;
 }
 
-// the attention of one sequence alone (the batched path runs the projections for all sequences at once)
-hipError_t launch_attention_only(StepParams P, const __half *w, const __half *kv, int grid, int threads, hipStream_t s)
+hipError_t launch_attention_batched(const StepParams &P, int nb, const __half *kv, hipStream_t s)
 {
-    P.parts = kPartAttention;
-    const size_t lds = (size_t)P.lds_floats * 4;
+    const int H = P.dm.H, spare = kAttnSpareGroups / H;    // (part_slots = kMaxGrid / H + 2 pieces of a head fit the workspace)
+    if (nb < 1 || nb > kAttnBatchMax || 1 + spare > P.part_slots) return hipErrorInvalidValue;
+    const dim3 grid((nb + spare) * H), block(kAttnBatchThreads);
+    const bool stream = P.attn_bstep != 0;
     switch (P.dm.d) {
-    case 64: hipLaunchKernelGGL(k_phase_b<64>, dim3(grid), dim3(threads), lds, s, P, w, kv); break;
-    case 80: hipLaunchKernelGGL(k_phase_b<80>, dim3(grid), dim3(threads), lds, s, P, w, kv); break;
-    case 128: hipLaunchKernelGGL(k_phase_b<128>, dim3(grid), dim3(threads), lds, s, P, w, kv); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_attention_batched(StepParams P, int nb, const __half *w, const __half *kv, int grid, int threads,
-                                    hipStream_t s)
-{
-    if (nb < 1 || nb > kAttnBatchMax || grid < nb) return hipErrorInvalidValue;
-    const size_t lds = (size_t)P.lds_floats * 4;
-    switch (P.dm.d) {
-    case 64: hipLaunchKernelGGL(k_attention_batched<64>, dim3(grid), dim3(threads), lds, s, P, nb, w, kv); break;
-    case 80: hipLaunchKernelGGL(k_attention_batched<80>, dim3(grid), dim3(threads), lds, s, P, nb, w, kv); break;
-    case 128: hipLaunchKernelGGL(k_attention_batched<128>, dim3(grid), dim3(threads), lds, s, P, nb, w, kv); break;
+#define CFPP_ATTN(D) \
+    case D: \
+        if (stream) hipLaunchKernelGGL((k_attention_batched<D, true>), grid, block, 0, s, P, nb, spare, kv); \
+        else hipLaunchKernelGGL((k_attention_batched<D, false>), grid, block, 0, s, P, nb, spare, kv); \
+        break;
+    CFPP_ATTN(64)
+    CFPP_ATTN(80)
+    CFPP_ATTN(128)
+#undef CFPP_ATTN
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -553,9 +697,6 @@ hipError_t prepare_kernels(size_t lds_bytes)
     CFPP_TRY(hipFuncSetAttribute((const void *)k_phase_b<64>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
     CFPP_TRY(hipFuncSetAttribute((const void *)k_phase_b<80>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
     CFPP_TRY(hipFuncSetAttribute((const void *)k_phase_b<128>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
-    CFPP_TRY(hipFuncSetAttribute((const void *)k_attention_batched<64>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
-    CFPP_TRY(hipFuncSetAttribute((const void *)k_attention_batched<80>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
-    CFPP_TRY(hipFuncSetAttribute((const void *)k_attention_batched<128>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
     CFPP_TRY(hipFuncSetAttribute((const void *)k_block_persistent<64>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
     CFPP_TRY(hipFuncSetAttribute((const void *)k_block_persistent<80>, hipFuncAttributeMaxDynamicSharedMemorySize, v));
     CFPP_TRY(hipFuncSetAttribute((const void *)k_block_persistent<128>, hipFuncAttributeMaxDynamicSharedMemorySize, v));

@@ -638,6 +638,17 @@ def test_batched_attention_split_with_extreme_lengths(orc):
     _batched_case(orc, TINY_STACK, 6, 2, np.array([0, 1, 3000, 17, 0, 1500], dtype=np.int32))
 
 
+# Lengths on both sides of a lane group's row (32 positions; 16 at head size 128) and of a piece of
+# 32 rows, at every head size: heads in one piece, in a few, and a last piece of one row.
+@pytest.mark.parametrize("shape,lens", [
+    (synth.ModelShape(512, 8, 64, 16, 2048, n_layers=1, name="neox-h512"), [0, 30, 31, 32, 1023, 1024, 2111]),
+    (synth.ModelShape(640, 8, 80, 20, 2560, n_layers=1, name="d80-h640"), [31, 1022, 1023, 1024, 2048, 2500]),
+    (synth.ModelShape(1024, 8, 128, 32, 4096, n_layers=1, name="d128-h1024"), [14, 15, 16, 510, 511, 512, 1100, 1600]),
+])
+def test_batched_attention_pieces(orc, shape, lens):
+    _batched_case(orc, shape, len(lens), 1, np.array(lens, dtype=np.int32))
+
+
 def _batched_case(orc, shape, B, layers, lens):
     """Launch mode 0 with several sequences: the projections run once per group
     of up to 8 sequences (MFMA, activations split into fp16 head + remainder),
