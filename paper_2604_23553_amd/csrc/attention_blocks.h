@@ -168,6 +168,36 @@ struct AttnCore {
         if (lane == 0) { wm[slot] = mw; wl[slot] = lw; }
     }
 
+    // Deals whole heads instead of equal shares of the line: workgroup g takes head g (grid >= H).
+    __device__ __forceinline__ void take_whole_heads()
+    {
+        G = dm->H;
+        r0 = g < G ? R * g : 0;
+        r1 = g < G ? R * (g + 1) : 0;
+    }
+
+    // One wavefront: the nslots wavefront states in LDS -> the head's output (a head that is
+    // this workgroup's alone)
+    __device__ __forceinline__ void finish(const StepParams &P, int s, const float *wp, const float *wm,
+                                           const float *wl, int nslots) const
+    {
+        float M = -INFINITY;
+        for (int wv = 0; wv < nslots; ++wv) M = fmaxf(M, wm[wv]);
+        float L = 0.f, O[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) O[e] = 0.f;
+        for (int wv = 0; wv < nslots; ++wv) {
+            const float ew = wm[wv] == -INFINITY ? 0.f : expf(wm[wv] - M);
+            L += wl[wv] * ew;
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+                if (lane + 64 * e < D) O[e] += wp[wv * D + lane + 64 * e] * ew;
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (lane + 64 * e < D) xwg_store(P.o + s * D + lane + 64 * e, O[e] / L);
+    }
+
     // workgroups covering head s: first one and how many
     __device__ __forceinline__ void cover(int s, int &g_lo, int &ncover) const
     {

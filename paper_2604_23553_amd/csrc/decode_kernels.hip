@@ -129,6 +129,17 @@ __device__ __forceinline__ void phase_a(const StepParams &P, const __half *__res
 }
 
 // ---------------------------------------------------------------------------
+// A head of few rows is one workgroup's: its output needs no partial, acknowledgement, counter and
+// second reading (three dependent trips to memory).  Few: what 8 wavefronts take in four rows each,
+// less where the workgroup's own MLP-down rows are long beside it.  us per block, equal shares ->
+// whole heads: hidden 512: 128 positions 22.6 -> 21.1, 500: 24.3 -> 23.0, 1000 (32 rows): 28.0 -> 25.3,
+// 2000: 28.1 -> 29.6; hidden 1024, 500 (32 rows): 30.8 -> 28.1; hidden 1280, 128: 35.0 -> 33.9, 1000:
+// 38.4 -> 38.7; hidden 2560, 300: 43.6 -> 44.3, 1000: 44.6 -> 49.4.
+__device__ __forceinline__ bool whole_heads(const Dims &dm, int rows, int grid)
+{
+    return grid >= dm.H && dm.h < 2048 && rows <= 32 && rows * dm.h <= 32768;
+}
+
 // Split-KV decode attention over this workgroup's share of the cache, all
 // wavefronts taking rows round-robin.
 // scr: nw*(D+2) + 4 + 2*D floats of LDS.
@@ -153,6 +164,8 @@ __device__ __forceinline__ void attn_share(const StepParams &P, const __half *__
     __half *vn = kn + D;
     AC ac;
     ac.init(P, kv, n_tok, lane);
+    const bool whole = whole_heads(P.dm, ac.R, (int)gridDim.x);         // (uniform over the grid)
+    if (whole) ac.take_whole_heads();
 
     if (ac.r0 >= ac.r1 || !(P.parts & kPartAttention)) {   // no rows for this workgroup, or no attention in this launch
         pre();
@@ -217,7 +230,10 @@ __device__ __forceinline__ void attn_share(const StepParams &P, const __half *__
         ac.wave_merge(wp, wm, wl, wave);
         tr.mark(14);
         __syncthreads();
-        if (wave == 0) {
+        if (wave == 0 && whole) {
+            ac.finish(P, s, wp, wm, wl, nw);
+            if (last_seg) tail();
+        } else if (wave == 0) {
             ac.publish(P, s, wp, wm, wl, nw);
             if (!CFPP_SKIPPED(P, 8)) {
                 xwg_wait_stores();

@@ -112,6 +112,16 @@ def test_odd_shapes(orc, shape):
     check_block(orc, shape, 5, 70, 71, mode=1, grid=40, threads=256)
 
 
+# The longest contexts whose heads are one workgroup's each, and the first that are shared out.
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("shape,S", [(synth.SMALL_BLOCK, 1023), (synth.SMALL_BLOCK, 1024),
+                                     (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 511),
+                                     (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 512),
+                                     (synth.ModelShape(1280, 16, 80, 20, 5120, name="d80-h1280"), 799)])
+def test_whole_heads_and_shares(orc, shape, S, mode):
+    check_block(orc, shape, 13, S, S + 2, mode=mode, taps=True, repeats=2)
+
+
 def test_last_slot_of_the_cache(orc):
     check_block(orc, synth.SMALL_BLOCK, 3, 95, 96, mode=0)
 
