@@ -546,7 +546,6 @@ __host__ __device__ __forceinline__ int bat_rc(int rows) { return (rows + 3) & ~
 __global__ void __launch_bounds__(512) k_bat_qkv_up(BatParams P)
 {
     extern __shared__ __align__(16) float lds[];
-    if (!bat_positions_ok(P)) return;
     const Dims &dm = P.dm;
     const int h = dm.h, tid = threadIdx.x, Ks = h + kBatPad;
     __half *yh = reinterpret_cast<__half *>(lds), *yl = yh + kBatMax * Ks;
@@ -568,6 +567,7 @@ __global__ void __launch_bounds__(512) k_bat_qkv_up(BatParams P)
     const BatSeg su{(unsigned)P.lay.w_up * 2u, (unsigned)h * 2u, u_begin, u_n, redu, rcu};
     BatStream bs;
     bs.begin(w, sq, su, 1, 0u, 2, h, yh, yl, Ks, tid);
+    if (!bat_positions_ok(P)) return;
     ln.unpack(P);
     ln.write_scaled(P, 0, yh, yl, Ks, tid);
     ln.sums(P, stat, tid);
@@ -603,7 +603,6 @@ __global__ void __launch_bounds__(512) k_bat_qkv_up(BatParams P)
 __global__ void __launch_bounds__(512) k_bat_out(BatParams P)
 {
     extern __shared__ __align__(16) float lds[];
-    if (!bat_positions_ok(P)) return;
     const Dims &dm = P.dm;
     const int h = dm.h, f = dm.f, tid = threadIdx.x, Ks = h + kBatPad;
     __half *yh = reinterpret_cast<__half *>(lds), *yl = yh + kBatMax * Ks;
@@ -617,7 +616,13 @@ __global__ void __launch_bounds__(512) k_bat_out(BatParams P)
     BatStage st;
     BatStream bs;
     st.load(P.o, (size_t)h, h, P.nb, tid);
+    // what the epilogue needs of memory, ahead of the weights; the positions are looked at behind their first requests
+    const __half *bde = w + P.lay.b_dense, *bdn = w + P.lay.b_down;
+    const int b = tid & (kBatMax - 1), i0 = min(r_begin + (tid >> 3), h - 1);
+    const __half de0 = bde[i0], dn0 = bdn[i0];
+    const float x0 = bat_x(P, min(b, P.nb - 1), i0);
     bs.begin(w, sd, sm, nslices, (unsigned)h * 2u, 1, h, yh, yl, Ks, tid);
+    if (!bat_positions_ok(P)) return;
     st.commit(h, yh, yl, Ks, P.nb, tid);                   // this wavefront's columns: no meeting, here or between the segments
     bs.run([&](int seg) {                                  // seg = 1..nslices: slice seg - 1 of GELU(up), into registers
         st.load(P.m + (size_t)(seg - 1) * h, (size_t)f, h, P.nb, tid);
@@ -625,14 +630,13 @@ __global__ void __launch_bounds__(512) k_bat_out(BatParams P)
         st.commit(h, yh, yl, Ks, P.nb, tid);
     });
     __syncthreads();
-    const int b = tid & (kBatMax - 1);
     if (b >= P.nb) return;
-    const __half *bde = w + P.lay.b_dense, *bdn = w + P.lay.b_down;
     const bool last = P.layer == P.n_layers - 1;
     for (int row = tid >> 3; row < r_n; row += 64) {
         const int i = r_begin + row;
-        const float branches = (bat_total(red, rc, row, b) + __half2float(bde[i])) + __half2float(bdn[i]);
-        const float res = bat_x(P, b, i) + branches;
+        const bool pre = row == tid >> 3;
+        const float branches = (bat_total(red, rc, row, b) + __half2float(pre ? de0 : bde[i])) + __half2float(pre ? dn0 : bdn[i]);
+        const float res = (pre ? x0 : bat_x(P, b, i)) + branches;
         if (last) P.out[(size_t)b * h + i] = __float2half_rn(res);
         else P.xres[((size_t)b * 2 + (P.layer & 1)) * h + i] = res;
     }

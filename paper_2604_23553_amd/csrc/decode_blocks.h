@@ -357,10 +357,8 @@ __device__ __forceinline__ float load_x(const LayerIO &io, int i)
 __device__ __forceinline__ int round_up_chunk(int k) { return (k + kChunk - 1) / kChunk * kChunk; }
 
 // position of the new token; out of range raises the error flag (no work is done)
-__device__ __forceinline__ bool read_pos(const StepParams &P, int *pos)
+__device__ __forceinline__ bool pos_ok(const StepParams &P, int p)
 {
-    const int p = *P.pos;
-    *pos = p;
     if (p < 0 || p >= P.dm.max_seq) {
         if (threadIdx.x == 0 && blockIdx.x == 0)
             __hip_atomic_store(&P.sync[kSyncErr], (unsigned)kErrBadPos, __ATOMIC_RELAXED,
@@ -368,6 +366,11 @@ __device__ __forceinline__ bool read_pos(const StepParams &P, int *pos)
         return false;
     }
     return true;
+}
+__device__ __forceinline__ bool read_pos(const StepParams &P, int *pos)
+{
+    *pos = *P.pos;
+    return pos_ok(P, *pos);
 }
 
 // Both LayerNorms of a block (they read the same input): load() requests the

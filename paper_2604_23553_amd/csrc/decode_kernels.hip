@@ -59,11 +59,13 @@ __device__ __forceinline__ void phase_a(const StepParams &P, const __half *__res
     const int item0 = (tid & 63) * hw + ((tid >> 6) - (up_half ? hw : 0));
     float bq0 = 0.f, bq1 = 0.f, bu0 = 0.f;
     float2 cs0 = {1.f, 0.f};
+    int rot0 = -1;                                         // pair index of this thread's first item in the rotated part, else -1
     if (!up_half && item0 < q_n / 2) {
         const int p = q_begin + 2 * item0;
         const int i = p % d, c = (p / d) % 3;
         bq0 = __half2float(bq[p]); bq1 = __half2float(bq[p + 1]);
-        if (c < 2 && i < r) cs0 = P.rope[(size_t)pos * (r >> 1) + (i >> 1)];
+        rot0 = c < 2 && i < r ? i >> 1 : -1;
+        if (!Sync::kInputsReady && rot0 >= 0) cs0 = P.rope[(size_t)pos * (r >> 1) + rot0];
     }
     if (up_half && item0 < u_n) bu0 = __half2float(bu[u_begin + item0]);
 
@@ -78,6 +80,11 @@ __device__ __forceinline__ void phase_a(const StepParams &P, const __half *__res
     ln.load(P, w, io, tid);
     if constexpr (Sync::kInputsReady) gs.issue_first();    // x is already on its way: it returns first
     gs.issue_second();
+    if constexpr (Sync::kInputsReady) {
+        // a launch of its own looks at the position behind its first requests, not before them
+        if (!pos_ok(P, pos)) return;
+        if (rot0 >= 0) cs0 = P.rope[(size_t)pos * (r >> 1) + rot0];
+    }
     ln.finish(P, y1, y2, red, tid);
     __syncthreads();
     tr.mark(3);
@@ -322,6 +329,10 @@ __device__ __forceinline__ void phase_c(const StepParams &P, const __half *__res
     if constexpr (Sync::kInputsReady) so.issue(P.o, h, tid);
     gs.issue_first();
     gs.issue_second();
+    if constexpr (Sync::kInputsReady) {
+        int pos;
+        if (!read_pos(P, &pos)) return;
+    }
     sync.wait();
     tr.mark(21);
     if constexpr (!Sync::kInputsReady) so.issue(P.o, h, tid);
@@ -356,10 +367,8 @@ __global__ void __launch_bounds__(kMaxThreads)
 k_phase_a(StepParams P, const __half *w, __half *kv, int layer)
 {
     extern __shared__ __align__(16) float lds[];
-    int pos;
-    if (!read_pos(P, &pos)) return;
     NoSync sync;
-    phase_a(P, w, kv, layer, pos, lds, sync);
+    phase_a(P, w, kv, layer, *P.pos, lds, sync);           // (checks the position itself)
 }
 
 template <int D>
@@ -377,10 +386,8 @@ __global__ void __launch_bounds__(kMaxThreads)
 k_phase_c(StepParams P, const __half *w, int layer)
 {
     extern __shared__ __align__(16) float lds[];
-    int pos;
-    if (!read_pos(P, &pos)) return;
     NoSync sync;
-    phase_c(P, w, layer, lds, sync);
+    phase_c(P, w, layer, lds, sync);                       // (checks the position itself)
 }
 
 // The attention of several sequences in one launch.  P holds the parameters of the first
