@@ -67,6 +67,12 @@ __device__ __forceinline__ void pf_dma16(pf_i32x4 rsrc, unsigned lds_addr, unsig
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
+// The same for lines that are read once (non-temporal): whole 128-byte lines only.
+__device__ __forceinline__ void pf_dma16_once(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
 __device__ __forceinline__ pf_i32x4 pf_rsrc(const __half *p, unsigned bytes)
 {
     const unsigned long long a = reinterpret_cast<unsigned long long>(p);
@@ -167,7 +173,11 @@ k_pf_gemm(PfParams P, int splits, int gm)
             } else {
                 // (where the wavefronts do not divide the rows, the last ones bring the last rows a second time)
                 const unsigned u = (i - NA + 1) * NWV <= BN / RU ? wave + (i - NA) * NWV : min(wave + (i - NA) * NWV, BN / RU - 1);
-                pf_dma16(rw, lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, vw, (n0 + RU * u) * width * 2u + jj * RB);
+                const unsigned at = lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, from = (n0 + RU * u) * width * 2u + jj * RB;
+                // with one token tile the weights are read once; the hint pays where an instruction takes whole lines (BK 64:
+                // 37 tokens, hidden 4096: 130 -> 120 us per layer; on half lines, BK 32, it costs: 72 -> 77 at hidden 2560)
+                if (BK == 64 && mt == 1) pf_dma16_once(rw, at, vw, from);
+                else pf_dma16(rw, at, vw, from);
             }
         }
     };
