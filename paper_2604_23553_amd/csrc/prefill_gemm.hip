@@ -434,9 +434,11 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 //     + (split: the parts written and read again)
 // in us.  The constants are a least-squares fit to 1500 timings (hidden 512 .. 4096, 8 .. 4096 tokens, every tile,
 // splits 1 .. 16) and pick within 0.8 % of the fastest measured combination in the mean, 7.5 % at worst.
-// Measured per layer (attention and LayerNorm included), before this kernel -> now: hidden 2560: 37 tokens 107 -> 80,
-// 512: 303 -> 224, 4096: 2345 -> 1528; hidden 4096, 1531 tokens: 1810 -> 1203.
+// Measured per layer (attention and LayerNorm included), before this kernel -> now: hidden 2560: 100 tokens 144 -> 103,
+// 512: 303 -> 224, 4096: 2345 -> 1528; hidden 4096, 1531 tokens: 1810 -> 1203.  (Up to 64 tokens: pf_plan_short.)
+constexpr int kPfCus = 256;
 struct PfTileCost { int bm, bn, per_cu; float step, lone_step, epi_in, epi_out; };
+constexpr int kPfTile32x256 = 7, kPfTile32x128 = 8, kPfTile64x256 = 9;    // (up to 64 tokens: pf_plan_short)
 static const PfTileCost kPfTiles[kPfTileKinds] = {
     {64, 128, 1, 0.26f, 0.f, 3.74f, 2.19f},
     {64, 128, 3, 0.25f, 0.37f, 0.01f, 1.13f},
@@ -445,16 +447,47 @@ static const PfTileCost kPfTiles[kPfTileKinds] = {
     {256, 192, 1, 0.92f, 0.f, 9.92f, 4.42f},
     {256, 256, 1, 1.10f, 0.f, 14.67f, 5.02f},
     {256, 320, 1, 1.34f, 0.f, 27.44f, 6.68f},
+    {32, 256}, {32, 128}, {64, 256},
 };
-constexpr int kPfCus = 256;
+
+// Up to 64 tokens a product is its weights' way from memory, once.  One token tile of 32 or 64 rows (the activations
+// of a tile are as many bytes as twice its rows of weights); K steps of 64, whole lines; and the 256 CUs filled once, by
+// the wider tile or by splitting K: the first product at most three ways (its parts cost a launch that adds them), the
+// second up to sixteen (they are added where the next layer's input is made).  us per layer, least estimate above -> this:
+// hidden 2560: 20 tokens 69.0 -> 55, 37 tokens 73.3 -> 66.0, 64 tokens 76.0 -> 71; hidden 4096, 20 tokens 129 -> 107.
+// False where that leaves half the CUs without a tile of 64 (hidden 512, 40 tokens: 31 us, 27 by the estimate).
+static bool pf_plan_short(const PfParams &P, bool in, size_t part_bytes, PfPlan *plan)
+{
+    const int h = P.dm.h, f = P.dm.f, nall = in ? 3 * h + f : h;
+    const bool low = P.n_rows <= 32;
+    const int kinds[2] = {low ? kPfTile32x128 : 0, low ? kPfTile32x256 : kPfTile64x256};
+    PfPlan best = {kinds[0], 1};
+    int most = 0;
+    for (int i = 0; i < (in ? 2 : 1); ++i) {
+        const PfTileCost &t = kPfTiles[kinds[i]];
+        const int tiles = in ? (3 * h + t.bn - 1) / t.bn + (f + t.bn - 1) / t.bn : (h + t.bn - 1) / t.bn;
+        for (int sp = 1; sp <= (in ? 3 : 16); ++sp) {
+            if (sp > 1 && (tiles * sp > kPfCus || (size_t)sp * t.bm * nall * sizeof(float) > part_bytes)) break;
+            const int wgs = tiles < kPfCus ? tiles * sp : kPfCus;
+            if (wgs > most || (wgs == most && sp < best.splits)) { most = wgs; best.tile = kinds[i]; best.splits = sp; }
+        }
+    }
+    *plan = best;
+    return low || most >= kPfCus / 2;
+}
 
 static PfPlan pf_plan(const PfParams &P, bool in, size_t part_bytes, float *cost_out)
 {
+    PfPlan few;
+    if (P.n_rows <= 64 && pf_plan_short(P, in, part_bytes, &few)) {
+        *cost_out = 0.f;
+        return few;
+    }
     const int h = P.dm.h, f = P.dm.f, nall = in ? 3 * h + f : h;
     const float steps = (float)(in ? h : h + f) / 32.f;
     PfPlan best = {0, 1};
     float best_cost = 1e30f;
-    for (int k = 0; k < kPfTileKinds; ++k) {
+    for (int k = 0; k < kPfTile32x256; ++k) {
         const PfTileCost &t = kPfTiles[k];
         if (in && t.bn == 320 && t.bm == 256) continue;    // (its QKV and MLP-up epilogues spill registers)
         const int mt = (P.n_rows + t.bm - 1) / t.bm;
@@ -505,7 +538,10 @@ static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
     case 3: return pf_launch<FL, 128, 320, 32, 4, 4, 2>(P, pl, s);
     case 4: return pf_launch<FL, 256, 192, 32, 3, 4, 2>(P, pl, s);
     case 5: return pf_launch<FL, 256, 256, 32, 3, 4, 2>(P, pl, s);
-    case 6: if (FL == kPfOut) return pf_launch<kPfOut, 256, 320, 32, 3, 4, 2>(P, pl, s);
+    case 6: if (FL == kPfOut) return pf_launch<kPfOut, 256, 320, 32, 3, 4, 2>(P, pl, s); break;
+    case kPfTile32x256: if (FL == kPfIn) return pf_launch<kPfIn, 32, 256, 64, 3, 1, 4>(P, pl, s); break;
+    case kPfTile32x128: return pf_launch<FL, 32, 128, 64, 3, 1, 4>(P, pl, s);
+    case kPfTile64x256: if (FL == kPfIn) return pf_launch<kPfIn, 64, 256, 64, 3, 1, 4>(P, pl, s); break;
     }
     return hipErrorInvalidValue;
 }

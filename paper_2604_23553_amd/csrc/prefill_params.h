@@ -49,7 +49,7 @@ CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
 }
 
 // tile (index into the table of prefill_gemm.hip) and splits of K of a product
-constexpr int kPfTileKinds = 7;
+constexpr int kPfTileKinds = 10;
 struct PfPlan { int tile, splits; };
 
 struct PfParams {

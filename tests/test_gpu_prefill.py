@@ -149,9 +149,11 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
 # the appended rows' own roundings (2e-3 of the row's root mean square covers it: a step of one V row in a mean of
 # two rows or more).
 @pytest.mark.parametrize("shape,pos0,T", [
-    (synth.ModelShape(2560, 32, 80, 20, 10240, name="pythia-2.8b-block"), 3, T) for T in (1, 37, 65, 129, 191, 257, 515, 701, 2049, 4095)
+    (synth.ModelShape(2560, 32, 80, 20, 10240, name="pythia-2.8b-block"), 3, T) for T in (1, 31, 32, 33, 64, 65, 129, 191, 257, 515, 701, 2049, 4095)
 ] + [
     (synth.ModelShape(640, 8, 80, 20, 2560, name="d80-h640"), 0, 333),          # features not a multiple of the wide tiles
+    (synth.ModelShape(128, 2, 64, 64, 128, name="d64-h128"), 5, 20),
+    (synth.ModelShape(4096, 32, 128, 32, 16384, name="pythia-6.9b-block"), 0, 24),
     (synth.ModelShape(128, 2, 64, 64, 128, name="d64-h128"), 1, 130),           # the smallest K: fewer steps than stages
     (synth.ModelShape(1536, 24, 64, 16, 6144, name="d64-h1536"), 2, 1000),
     (synth.ModelShape(4096, 32, 128, 32, 16384, name="pythia-6.9b-block"), 1, 1531),
