@@ -271,11 +271,11 @@ cfpp_status cfpp_stack_prefill(cfpp_ctx *ctx, const void *const *packed_layers,
                                int32_t n_tokens, int32_t b, void *out, cfpp_stream stream);
 
 /* The same computation for long prompts, with each layer's weights read once
- * per pass of up to `rows` tokens instead of once per 8: per layer a LayerNorm
- * launch, the four projections as LDS-tiled GEMMs on the matrix cores
- * (tokens x K activations times K x rows weights: here the paper's memory-bound
- * GEMVs, Sec. 2.2, are dense contractions), and one causal-attention launch over
- * the cache rows the pass has just appended.  Activations enter the fp16 matrix
+ * per pass of up to `rows` tokens instead of once per 8: per layer the projections
+ * as two LDS-tiled products on the matrix cores (QKV and MLP-up; output projection
+ * and MLP-down: tokens x K activations times K x rows weights, here the paper's
+ * memory-bound GEMVs, Sec. 2.2, are dense contractions), one causal-attention launch
+ * over the cache rows the pass has just appended, and a LayerNorm launch.  Activations enter the fp16 matrix
  * instruction as head + remainder, so the products match the fp32 path to
  * rounding.  Arguments as for cfpp_stack_prefill, plus
  *   scratch      : DEVICE, 256-byte aligned, at least

@@ -6,7 +6,7 @@
 
 namespace cfpp {
 
-constexpr int kPfTile = 128;           // rows (tokens) and columns (output features) of a GEMM workgroup tile
+constexpr int kPfTile = 128;           // hidden, ffn and the scratch's rows are whole multiples of this
 constexpr int kPfMaxRows = 4096;       // most tokens a pass takes
 // bytes of the parts of a split product: what 384 tiles of 128 x 128 floats take, less the padding of the activation rows
 CFPP_HD size_t pf_part_bytes(int rows) { return (size_t)384 * kPfTile * kPfTile * 4 - (size_t)rows * 1024; }

@@ -112,12 +112,10 @@ def test_gemm_prompt_with_head_dim_128_and_tanh_gelu(orc):
     _check_prompt(orc, shape, 31, 7, 90, 1, gemm_rows=128)
 
 
-# The cases above are small enough that every product splits K (few tiles) and the parts meet in
-# k_pf_reduce.  These two are long enough for the other ways through the GEMM: products that are
-# not split and finish out of LDS, with 64-token tiles (600 tokens: QKV and up) and with 128-token
-# tiles (2200 tokens: QKV and up; dense and down unsplit with 64-token tiles), at a head size that
-# does not divide the 128-column tile (heads cut by tile edges) and a rotated part that is not a
-# multiple of 8 dimensions.  Layer-0 rows are held to the rounding bound for every 7th token.
+# The cases above are small enough that products split K (few tiles) and the parts meet in k_pf_reduce
+# and k_pf_row.  These two are long enough for products that are not split, at a head size that does not
+# divide the tiles (heads cut by tile edges) and a rotated part that is not a multiple of 8 dimensions.
+# Layer-0 rows are held to the rounding bound for every 7th token.
 
 
 def test_gemm_prompt_long_enough_for_unsplit_products(orc):
@@ -130,9 +128,7 @@ def test_gemm_prompt_long_enough_for_128_token_tiles(orc):
     _check_prompt(orc, shape, 41, 0, 2200, 1, gemm_rows=2304, row_check_every=7)
 
 
-# From 1024 tokens in a pass the attention launch is the 64-query kernel (16 queries per wavefront,
-# every wavefront over all keys of a tile); the 2200-token case above runs it at head size 80,
-# these two at 64 and 128, with a pass that ends inside a query block and inside a key tile.
+# Long passes at head sizes 64 and 128 that end inside a query block and inside a key tile.
 def test_gemm_prompt_wide_attention_head_dim_64(orc):
     shape = synth.ModelShape(512, 8, 64, 16, 2048, n_layers=2, name="neox-h512-x2")
     _check_prompt(orc, shape, 43, 3, 1100, 1, gemm_rows=1152, row_check_every=7)
