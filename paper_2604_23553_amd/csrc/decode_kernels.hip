@@ -407,10 +407,13 @@ k_phase_c(StepParams P, const __half *w, int layer)
 constexpr int kAttnBatchMax = 8, kAttnBatchThreads = 256;
 // Workgroups dealt beyond one per head and sequence, and the fewest rows worth a piece.  us per step and layer, before
 // -> with pieces of 8 / 16 / 32 rows: five sequences of 37 .. 2048 positions (hidden 2560) 85.0 -> 65.9 / 65.7 / 63.6;
-// 8 prompt tokens behind 1000: 67.3 -> 70.5 / 66.4 / 64.2; two sequences of 8000: 80.0 -> 81.8 / 79.4 / 78.9.  512 spare
-// ones: eight sequences of 3000 .. 8000 132.3 -> 136.5 (1024: 132.2), one block of hidden 4096 with 8 sequences
-// 237.3 -> 238.7 (235.3).
-constexpr int kAttnSpareGroups = 1024, kAttnPieceRows = 32;
+// 8 prompt tokens behind 1000: 67.3 -> 70.5 / 66.4 / 64.2; two sequences of 8000: 80.0 -> 81.8 / 79.4 / 78.9. 
+// Spare ones of sequences with K/V rows of their own: 640, so that eight long sequences make about 768 workgroups, what is
+// resident at 3 a CU, in pieces of about one size.  One block of hidden 4096 with 8 sequences of 3219 .. 7696 positions,
+// 256 / 512 / 640 / 1024 / 2048 spare ones: 224.4 / 219.4 / 218.2 / 222.7 / 223.7 us (218.2 with the 256 workgroups of
+// before); of 1024 .. 8192 positions 640 / 1024 / 2048: 231.8 / 232.0 / 230.4 (234 .. 236 before).  A prompt group's queries share their
+// rows and don't stream: 1024, as measured above.  Pieces of a head never exceed the workspace's part_slots.
+constexpr int kAttnSpareGroups = 640, kAttnSpareShared = 1024, kAttnPieceRows = 32;
 
 template <int D, bool STREAM>
 __global__ void __launch_bounds__(kAttnBatchThreads, 3)
@@ -445,7 +448,7 @@ k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
 #pragma unroll
     for (int i = 0; i < kAttnBatchMax; ++i) {
         if (i < nb) {
-            const int n = min(1 + (int)((unsigned)spare * rows[i] / total), ((int)rows[i] + kAttnPieceRows - 1) / kAttnPieceRows);
+            const int n = min(min(1 + (int)((unsigned)spare * rows[i] / total), ((int)rows[i] + kAttnPieceRows - 1) / kAttnPieceRows), P.part_slots);
             const int at = (int)blockIdx.x - base;
             if (at >= 0 && at < n * H) { mine = i; R = (int)rows[i]; pieces = n; local = at; }
             base += n * H;
@@ -654,10 +657,12 @@ hipError_t launch_phases(const StepParams &P, const __half *w, __half *kv, int l
 
 hipError_t launch_attention_batched(const StepParams &P, int nb, const __half *kv, hipStream_t s)
 {
-    const int H = P.dm.H, spare = kAttnSpareGroups / H;    // (part_slots = kMaxGrid / H + 2 pieces of a head fit the workspace)
-    if (nb < 1 || nb > kAttnBatchMax || 1 + spare > P.part_slots) return hipErrorInvalidValue;
-    const dim3 grid((nb + spare) * H), block(kAttnBatchThreads);
+    if (nb < 1 || nb > kAttnBatchMax) return hipErrorInvalidValue;
     const bool stream = P.attn_bstep != 0;
+    const int H = P.dm.H, spare = (stream ? kAttnSpareGroups : kAttnSpareShared) / H;
+    // no sequence has more pieces than its longest context allows (64 / LPP positions a row, as in AttnShape)
+    const int row = P.dm.d >= 128 ? 16 : 32, most = (P.dm.max_seq + row * kAttnPieceRows - 1) / (row * kAttnPieceRows);
+    const dim3 grid(min(nb + spare, nb * most) * H), block(kAttnBatchThreads);
     switch (P.dm.d) {
 #define CFPP_ATTN(D) \
     case D: \
