@@ -42,6 +42,15 @@ extern "C" {
 cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_t count,
                             cfpp_stream stream);
 
+/* The plan of one pass of cfpp_stack_prefill_gemm over n_tokens <= rows tokens (host
+ * arithmetic, no GPU).  plan[0..3]: the first product (QKV, MLP-up), plan[4..7]: the
+ * second (output projection, MLP-down); of each the tokens, output features and K
+ * values of a tile's step and the parts K is split into.  past[0..3]: by how many rows
+ * the tiles' loads reach past the activations and the weights of the first product,
+ * then of the second: 0 unless something is wrong. */
+cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
+                                    int32_t plan[8], int32_t past[4]);
+
 /* Plain streaming kernels whose HBM traffic is known exactly, used to find the
  * streaming bandwidth this GPU sustains and to scale hardware traffic counters.
  * cfpp_stream_read loads every 16-byte word of src (DEVICE, `bytes` a multiple of

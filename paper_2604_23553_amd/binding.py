@@ -271,6 +271,14 @@ def cfpp_debug_read(ctx: int, which: int, count: int, stream=None):
     return out
 
 
+def cfpp_debug_prefill_plan(cfg: Config, rows: int, n_tokens: int):
+    """((tokens, features, K step, parts) of each product, (rows past activations, past weights) of each)."""
+    plan, past = (C.c_int32 * 8)(), (C.c_int32 * 4)()
+    _check(lib().cfpp_debug_prefill_plan(C.byref(cfg), C.c_int32(rows), C.c_int32(n_tokens), plan, past),
+           "cfpp_debug_prefill_plan")
+    return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
+
+
 def cfpp_stream_read(src, nbytes: int, sink, grid: int, threads: int, unroll: int, stream=None):
     _check(lib().cfpp_stream_read(_ptr(src), C.c_size_t(nbytes), _ptr(sink), C.c_int32(grid),
                                   C.c_int32(threads), C.c_int32(unroll), _ptr(stream)), "cfpp_stream_read")

@@ -826,14 +826,7 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         P.rows = rows; P.n_layers = L;
         P.x_in = static_cast<const __half *>(x) + (size_t)t0 * h;
         P.out = static_cast<__half *>(out) + (size_t)t0 * h;
-        P.y1 = reinterpret_cast<__half *>(sc + pl.y1);
-        P.y2 = reinterpret_cast<__half *>(sc + pl.y2);
-        P.stats = reinterpret_cast<float2 *>(sc + pl.stats);
-        P.q = reinterpret_cast<float *>(sc + pl.q);
-        P.o = reinterpret_cast<__half *>(sc + pl.o);
-        P.m = reinterpret_cast<__half *>(sc + pl.m);
-        P.part = reinterpret_cast<float *>(sc + pl.part); P.part_bytes = pl.total - pl.part;
-        P.part_out_bytes = pl.total - pl.q;                // (where they start: pf_plan_pass)
+        pf_place(P, pl, sc);
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
         P.sync = reinterpret_cast<unsigned *>(ctx->ws + ctx->wl.sync);
         pf_plan_pass(P);
@@ -1143,6 +1136,25 @@ extern "C" cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_
     if (count > n) return fail(CFPP_EINVAL, "count %zu exceeds the buffer (%zu floats)", count, n);
     HIP_OK(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
     HIP_OK(hipMemcpy(dst_host, ctx->ws + off, count * sizeof(float), hipMemcpyDeviceToHost));
+    return CFPP_OK;
+}
+
+extern "C" cfpp_status cfpp_debug_prefill_plan(const cfpp_config *c, int32_t rows, int32_t n_tokens, int32_t plan[8],
+                                               int32_t past[4])
+{
+    cfpp_status st = cfpp_validate_config(c);
+    if (st != CFPP_OK) return st;
+    if (!plan || !past) return fail(CFPP_EINVAL, "NULL argument");
+    if (rows <= 0 || rows > kPfMaxRows || rows % kPfTile != 0 || n_tokens <= 0 || n_tokens > rows)
+        return fail(CFPP_EINVAL, "rows %d, n_tokens %d", rows, n_tokens);
+    PfParams P;
+    std::memset(&P, 0, sizeof P);
+    P.dm = dims_of(*c); P.lay = packed_layout(P.dm.h, P.dm.f);
+    if (!pf_supported(P.dm)) return fail(CFPP_EUNSUPPORTED, "a shape without prompt-sized kernels");
+    P.n_rows = n_tokens; P.rows = rows; P.n_layers = c->n_layers;
+    pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));    // (a stand-in: only distances are used)
+    pf_plan_pass(P);
+    pf_describe_plan(P, plan, past);
     return CFPP_OK;
 }
 

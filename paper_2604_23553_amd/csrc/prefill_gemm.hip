@@ -61,7 +61,8 @@ __device__ __forceinline__ void pf_store(const PfParams &P, int row, int col, fl
 
 // ---------------------------------------------------------------------------
 // 64 lanes x 16 bytes from memory straight into LDS: lane l's piece lands at lds_addr + 16 l.
-// (M0: the compiler sets it right before each use of its own.  Counted in vmcnt like any load; the callers wait by count.  Out of range of the resource: zeros.)
+// (M0: the compiler sets it right before each use of its own.  Counted in vmcnt like any load; the callers wait by count.
+// The row is in the scalar offset, which the resource's range check need not cover: the callers keep it inside, pf_dma_row.)
 __device__ __forceinline__ void pf_dma16(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
@@ -78,6 +79,10 @@ __device__ __forceinline__ pf_i32x4 pf_rsrc(const __half *p, unsigned bytes)
     const unsigned long long a = reinterpret_cast<unsigned long long>(p);
     return pf_i32x4{(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)bytes, 0x00020000};
 }
+// First row of a DMA instruction that takes `group` rows of an operand of `rows`: an instruction of a tile that overhangs
+// the operand brings its last rows instead (what is made of them is never stored), so that no address leaves it.
+// rows: a multiple of 128, group: at most 16
+CFPP_HD int pf_dma_row(int row, int rows, int group) { return row < rows - group ? row : rows - group; }
 template <int N>
 __device__ __forceinline__ void pf_wait_barrier()
 {
@@ -169,11 +174,11 @@ k_pf_gemm(PfParams P, int splits, int gm)
             if (i < i0 || i >= i1) continue;
             if (i < NA) {
                 const int sub = i / NA1, u = (i % NA1) * NWV;
-                pf_dma16(ra, dst + sub * BM * RBA + 1024u * u, va, (unsigned)(m0 + RUA * (wave + u)) * as + (jj * SUB + sub) * 128u);
+                pf_dma16(ra, dst + sub * BM * RBA + 1024u * u, va, (unsigned)pf_dma_row(m0 + RUA * (wave + u), P.rows, RUA) * as + (jj * SUB + sub) * 128u);
             } else {
                 // (where the wavefronts do not divide the rows, the last ones bring the last rows a second time)
                 const unsigned u = (i - NA + 1) * NWV <= BN / RU ? wave + (i - NA) * NWV : min(wave + (i - NA) * NWV, BN / RU - 1);
-                const unsigned at = lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, from = (n0 + RU * u) * width * 2u + jj * RB;
+                const unsigned at = lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, from = (unsigned)pf_dma_row(n0 + RU * u, N, RU) * width * 2u + jj * RB;
                 // with one token tile the weights are read once; the hint pays where an instruction takes whole lines (BK 64:
                 // 37 tokens, hidden 4096: 130 -> 120 us per layer; on half lines, BK 32, it costs: 72 -> 77 at hidden 2560)
                 if (BK == 64 && mt == 1) pf_dma16_once(rw, at, vw, from);
@@ -437,17 +442,17 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 // Measured per layer (attention and LayerNorm included), before this kernel -> now: hidden 2560: 100 tokens 144 -> 103,
 // 512: 303 -> 224, 4096: 2345 -> 1528; hidden 4096, 1531 tokens: 1810 -> 1203.  (Up to 64 tokens: pf_plan_short.)
 constexpr int kPfCus = 256;
-struct PfTileCost { int bm, bn, per_cu; float step, lone_step, epi_in, epi_out; };
+struct PfTileCost { int bm, bn, bk, per_cu; float step, lone_step, epi_in, epi_out; };
 constexpr int kPfTile32x256 = 7, kPfTile32x128 = 8, kPfTile64x256 = 9;    // (up to 64 tokens: pf_plan_short)
 static const PfTileCost kPfTiles[kPfTileKinds] = {
-    {64, 128, 1, 0.26f, 0.f, 3.74f, 2.19f},
-    {64, 128, 3, 0.25f, 0.37f, 0.01f, 1.13f},
-    {128, 128, 2, 0.36f, 0.46f, 3.17f, 2.15f},
-    {128, 320, 1, 0.88f, 0.f, 5.51f, 3.99f},
-    {256, 192, 1, 0.92f, 0.f, 9.92f, 4.42f},
-    {256, 256, 1, 1.10f, 0.f, 14.67f, 5.02f},
-    {256, 320, 1, 1.34f, 0.f, 27.44f, 6.68f},
-    {32, 256}, {32, 128}, {64, 256},
+    {64, 128, 64, 1, 0.26f, 0.f, 3.74f, 2.19f},
+    {64, 128, 32, 3, 0.25f, 0.37f, 0.01f, 1.13f},
+    {128, 128, 32, 2, 0.36f, 0.46f, 3.17f, 2.15f},
+    {128, 320, 32, 1, 0.88f, 0.f, 5.51f, 3.99f},
+    {256, 192, 32, 1, 0.92f, 0.f, 9.92f, 4.42f},
+    {256, 256, 32, 1, 1.10f, 0.f, 14.67f, 5.02f},
+    {256, 320, 32, 1, 1.34f, 0.f, 27.44f, 6.68f},
+    {32, 256, 64}, {32, 128, 64}, {64, 256, 64},
 };
 
 // Up to 64 tokens a product is its weights' way from memory, once.  One token tile of 32 or 64 rows (the activations
@@ -527,6 +532,25 @@ void pf_plan_pass(PfParams &P)
     const int bm = kPfTiles[P.plan_out.tile].bm;
     P.part_out_stride = (size_t)((P.n_rows + bm - 1) / bm * bm) * P.dm.h;
 }
+
+#ifdef CFPP_PROFILE
+void pf_describe_plan(const PfParams &P, int plan[8], int past[4])
+{
+    for (int k = 0; k < 2; ++k) {
+        const PfPlan &pl = k ? P.plan_out : P.plan_in;
+        const int bm = kPfTiles[pl.tile].bm, bn = kPfTiles[pl.tile].bn, ru = 1024 / (2 * kPfTiles[pl.tile].bk), h = P.dm.h, f = P.dm.f;
+        plan[4 * k] = bm; plan[4 * k + 1] = bn; plan[4 * k + 2] = kPfTiles[pl.tile].bk; plan[4 * k + 3] = pl.splits;
+        // rows past the operand that the last instruction of a tile reaches, as k_pf_gemm's issue() forms them: the
+        // first product's matrices have 3 h and f rows, the second's h
+        int a = 0, w = 0;
+        for (int u = 0; u < (P.n_rows + bm - 1) / bm * bm; u += 8) a = max(a, pf_dma_row(u, P.rows, 8) + 8 - P.rows);
+        const int n[2] = {k ? h : 3 * h, k ? h : f};
+        for (int i = 0; i < 2; ++i)
+            for (int u = 0; u < (n[i] + bn - 1) / bn * bn; u += ru) w = max(w, pf_dma_row(u, n[i], ru) + ru - n[i]);
+        past[2 * k] = a; past[2 * k + 1] = w;
+    }
+}
+#endif
 
 template <int FL>
 static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)

@@ -78,9 +78,24 @@ struct PfParams {
     unsigned *sync;
 };
 
+// where a pass's buffers lie in the scratch at `sc`
+inline void pf_place(PfParams &P, const PfLayout &pl, char *sc)
+{
+    P.y1 = reinterpret_cast<__half *>(sc + pl.y1);
+    P.y2 = reinterpret_cast<__half *>(sc + pl.y2);
+    P.stats = reinterpret_cast<float2 *>(sc + pl.stats);
+    P.q = reinterpret_cast<float *>(sc + pl.q);
+    P.o = reinterpret_cast<__half *>(sc + pl.o);
+    P.m = reinterpret_cast<__half *>(sc + pl.m);
+    P.part = reinterpret_cast<float *>(sc + pl.part); P.part_bytes = pl.total - pl.part;
+    P.part_out_bytes = pl.total - pl.q;                    // (where they start: pf_plan_pass)
+}
+
 bool pf_supported(const Dims &dm);
 // fills in the plans of a pass: everything else of P that does not depend on the layer is set
 void pf_plan_pass(PfParams &P);
+// that plan, and what the products' DMA would request past their operands (profiling library): see cfpp_debug_prefill_plan
+void pf_describe_plan(const PfParams &P, int plan[8], int past[4]);
 // one block for the tokens of a pass: LayerNorm inputs, QKV, attention, dense, up, down
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s);
 // its products (prefill_gemm.hip): QKV and MLP-up; output projection and MLP-down

@@ -1,0 +1,36 @@
+"""Host-only checks of how the prompt-sized products are cut into tiles (no GPU): the
+profiling library reports the plan that a pass of a given size gets and the rows that its
+tiles' loads reach."""
+import pytest
+
+import paper_2604_23553_amd as cf
+
+TOKENS = (1, 20, 32, 33, 64, 65, 100, 128, 129, 256, 300, 384, 500, 640, 900, 1100, 1153, 1408, 1531, 2048, 2600, 2688,
+          2700, 3100, 3200, 3400, 3840, 3968, 4096)
+
+
+def plan(h, d, f, tokens, rows=None):
+    cfg = cf.Config(h, h // d, d, 16, f, 2, 16, 1, 10000.0, 1e-5, 0)
+    with cf.profile_build():
+        return cf.cfpp_debug_prefill_plan(cfg, rows or -(-tokens // 128) * 128, tokens)
+
+
+@pytest.mark.parametrize("h,d", [(128, 64), (256, 64), (512, 64), (640, 80), (1024, 128), (1280, 80), (1536, 64), (2048, 64),
+                                 (2560, 80), (2688, 128), (3200, 80), (3968, 64), (4096, 128), (4096, 64)])
+def test_no_tile_loads_outside_its_operands(h, d):
+    """Tiles overhang the features (192, 256 and 320 columns) and the tokens (256 rows): their loads stay inside."""
+    for f in {128, h, 4 * h, 4 * h + 128, 32768} & set(range(128, 32769, 128)):
+        for t in TOKENS:
+            _, past = plan(h, d, f, t)
+            assert past == ((0, 0), (0, 0)), (h, f, t, past)
+
+
+def test_a_plan_is_refused_as_the_call_is():
+    cfg = cf.Config(512, 8, 64, 16, 2048, 2, 16, 1, 10000.0, 1e-5, 2)          # the sequential form
+    with cf.profile_build():
+        for rows, n in ((128, 129), (100, 20), (4224, 20), (128, 0)):
+            with pytest.raises(cf.CfppError):
+                cf.cfpp_debug_prefill_plan(cfg, rows, n)
+        with pytest.raises(cf.CfppError) as e:
+            cf.cfpp_debug_prefill_plan(cfg, 128, 20)
+        assert e.value.status == -2
