@@ -61,19 +61,23 @@ __device__ __forceinline__ void pf_store(const PfParams &P, int row, int col, fl
 
 // ---------------------------------------------------------------------------
 // 64 lanes x 16 bytes from memory straight into LDS: lane l's piece lands at lds_addr + 16 l.
-// (M0: the compiler sets it right before each use of its own.  Counted in vmcnt like any load; the callers wait by count.
+// (Counted in vmcnt like any load; the callers wait by count.
 // The row is in the scalar offset, which the resource's range check need not cover: the callers keep it inside, pf_dma_row.)
+// (Winline-asm: M0 is reserved, nothing of the compiler's is kept in it; the clobber orders its own settings of it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void pf_dma16(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 // The same for lines that are read once (non-temporal): whole 128-byte lines only.
 __device__ __forceinline__ void pf_dma16_once(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ pf_i32x4 pf_rsrc(const __half *p, unsigned bytes)
 {
     const unsigned long long a = reinterpret_cast<unsigned long long>(p);

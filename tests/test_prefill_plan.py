@@ -1,10 +1,14 @@
 """Host-only checks of how the prompt-sized products are cut into tiles (no GPU): the
 profiling library reports the plan that a pass of a given size gets and the rows that its
 tiles' loads reach."""
+import os
+import re
+
 import pytest
 
 import paper_2604_23553_amd as cf
 
+CSRC = os.path.join(os.path.dirname(os.path.abspath(cf.__file__)), "csrc")
 TOKENS = (1, 20, 32, 33, 64, 65, 100, 128, 129, 256, 300, 384, 500, 640, 900, 1100, 1153, 1408, 1531, 2048, 2600, 2688,
           2700, 3100, 3200, 3400, 3840, 3968, 4096)
 
@@ -34,3 +38,16 @@ def test_a_plan_is_refused_as_the_call_is():
         with pytest.raises(cf.CfppError) as e:
             cf.cfpp_debug_prefill_plan(cfg, 128, 20)
         assert e.value.status == -2
+
+
+def test_asm_that_sets_m0_says_so():
+    """M0 carries the LDS address of a memory-to-LDS load: the compiler has to know of it."""
+    found = 0
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".hip", ".h")):
+            text = open(os.path.join(CSRC, name)).read()
+            for stmt in re.findall(r"\basm\s+(?:volatile)?\s*\(.*?\)\s*;", text, flags=re.S):
+                if "m0," in stmt:
+                    found += 1
+                    assert '"m0"' in stmt.rsplit(":", 1)[1], f"{name}: {stmt}"
+    assert found >= 2
