@@ -492,8 +492,12 @@ k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
     float acc[NV], m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) acc[i] = 0.f;
-    auto process = [&](const u32x4 (&kk)[NP], const u32x4 (&vv)[NP], int row) {
+    auto process = [&](const u32x4 (&kk)[NP], u32x4 (&vv)[NP], int row) {
         const bool valid = row * PPW + tl <= t_last;
+        if (row * PPW + PPW - 1 > t_last) {                // (uniform) a head's last row: the re-read V weighs nothing, infinite or not
+#pragma unroll
+            for (int k = 0; k < NP; ++k) vv[k] = valid ? vv[k] : u32x4{0u, 0u, 0u, 0u};
+        }
         int qoff = 8 * sub;
         asm volatile("" : "+v"(qoff));                     // (q is re-read from LDS for every row, not kept in 8 NP registers)
         float sp = 0.f;
