@@ -206,6 +206,43 @@ struct PfKvTile {
     }
 };
 
+// One wavefront: the attention of one query (row of the pass) of one head, key by key in fp32, nothing behind the query read.
+template <int D>
+__device__ __forceinline__ void pf_attn_alone(const PfParams &P, const __half *Kc, const __half *Vc, int head, int row, int lane)
+{
+    constexpr int NE = (D + 63) / 64;                      // dimensions lane + 64 e
+    const Dims &dm = P.dm;
+    const float scale = 1.44269504088896340736f / sqrtf((float)D);
+    size_t at[NE];
+    float q[NE], o[NE], m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const int dim = min(lane + 64 * e, D - 1);
+        at[e] = (size_t)(dim >> 4) * dm.max_seq * 16 + (dim & 15);
+        q[e] = lane + 64 * e < D ? P.q[(size_t)row * dm.h + head * D + dim] * scale : 0.f;
+        o[e] = 0.f;
+    }
+    for (int t = 0; t <= P.pos0 + row; ++t) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) s = lane + 64 * e < D ? fmaf(q[e], __half2float(Kc[at[e] + (size_t)t * 16]), s) : s;
+        s = wave_sum(s);
+        const float mn = fmaxf(m, s), corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(s - mn);
+        m = mn;
+        l = l * corr + p;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) o[e] = fmaf(p, __half2float(Vc[at[e] + (size_t)t * 16]), o[e] * corr);
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        if (lane + 64 * e >= D) continue;
+        __half hi, lo;
+        pf_split(o[e] / l, hi, lo);
+        const size_t to = pf_at(row, head * D + lane + 64 * e, dm.h);
+        P.o[to] = hi; P.o[to + kPfLo] = lo;
+    }
+}
+
 template <int D, int QW>
 __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
 {
@@ -216,6 +253,7 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
     constexpr int kTileBytes = (TK * KS + 32 * NB * VS) * 2, kOutBytes = 4 * 32 * OS * 4;
     __shared__ __align__(16) char mem[kTileBytes > kOutBytes ? kTileBytes : kOutBytes];
     __shared__ float sM[4][32], sL[4][32];
+    __shared__ int sBad[32 * QW], sEnd[3];                 // queries whose output is not finite; any; the positions of pf_attn_alone's rule
     __half *sK = reinterpret_cast<__half *>(mem), *sVt = sK + TK * KS;
     static_assert((TK * KS * 2) % 16 == 0, "");
     const Dims &dm = P.dm;
@@ -230,6 +268,8 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
     const __half *Kc = P.kv + kv_offset(dm, 0, P.b, head, 0, 0), *Vc = P.kv + kv_offset(dm, 1, P.b, head, 0, 0);
     PfKvTile<D, TK> tile;
     tile.request(Kc, Vc, 0, last_pos, dm.max_seq, tid);
+    if (tid < 32 * QW) sBad[tid] = 0;
+    if (tid == 0) { sEnd[0] = 0; sEnd[1] = -1; sEnd[2] = 0x7fffffff; }
     pf_f16x8 qh[NK], ql[NK];                               // Q^T: dimensions 16 ks + 8 hf .. + 7 of query col
     const float scale = 1.44269504088896340736f / sqrtf((float)D);
 #pragma unroll
@@ -358,15 +398,39 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
             b += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8 + 4);
         }
         __half hi[8], lo[8];
+        bool finite = true;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            pf_split(a[j] / l, hi[j], lo[j]);
-            pf_split(b[j] / l, hi[4 + j], lo[4 + j]);
+            const float va = a[j] / l, vb = b[j] / l;
+            finite = finite && fabsf(va) < INFINITY && fabsf(vb) < INFINITY;
+            pf_split(va, hi[j], lo[j]);
+            pf_split(vb, hi[4 + j], lo[4 + j]);
         }
         const size_t at = pf_at(q0 + q, head * D + c8, dm.h);
         *reinterpret_cast<u32x4 *>(P.o + at) = *reinterpret_cast<const u32x4 *>(hi);
         *reinterpret_cast<u32x4 *>(P.o + at + kPfLo) = *reinterpret_cast<const u32x4 *>(lo);
+        if (!finite) { sBad[q] = 1; sEnd[0] = 1; }
     }
+    // A masked key's weight is zero, and zero times an infinite or NaN V row of a later token of this block is NaN: such
+    // queries are worked out once more, each alone.  Which: those ahead of the last position of the block whose V is not
+    // finite, unless they see a V row that is finite nowhere (nothing of their output is).
+    __syncthreads();
+    if (!sEnd[0]) return;                                  // (uniform)
+    const int first = P.pos0 + q0;
+    if (first + tid <= last_pos) {                         // (a thread per position: 32 QW are at most 128)
+        int bad = 0;
+        for (int pc = 0; pc < D / 8; ++pc) {
+            const u32x4 v = load16(Vc + ((size_t)(pc >> 1) * dm.max_seq + first + tid) * 16 + (pc & 1) * 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bad += ((v[j] & 0x7c00u) == 0x7c00u) + ((v[j] & 0x7c000000u) == 0x7c000000u);
+        }
+        if (bad) atomicMax(&sEnd[1], first + tid);
+        if (bad == D) atomicMin(&sEnd[2], first + tid);
+    }
+    __syncthreads();
+    const int end = min(sEnd[1], sEnd[2]);
+    for (int q = wave; q < 32 * QW && first + q < end; q += 4)         // (a query ahead of a position of the block is one of the pass)
+        if (sBad[q]) pf_attn_alone<D>(P, Kc, Vc, head, q0 + q, lane);
 }
 
 // ---------------------------------------------------------------------------

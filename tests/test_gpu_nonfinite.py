@@ -1,5 +1,5 @@
-"""Values that are not finite stay where they belong: a V element that overflows fp16 makes that dimension of what
-attends to it infinite and nothing else."""
+"""Values that are not finite stay where they belong: a V element that overflows fp16, or a token that is NaN,
+reaches the tokens that attend to it and no earlier one, whatever shares a tile with it."""
 import numpy as np
 import pytest
 
@@ -18,6 +18,46 @@ def _overflowing(shape, seed, layer, x):
     y = (x - x.mean()) / np.sqrt(x.var() + shape.ln_eps) * w["ln1_g"].astype(np.float64) + w["ln1_b"].astype(np.float64)
     w["w_qkv"][(3 * HEAD + 2) * shape.head_dim + DIM] = (y * (120000.0 / (y @ y))).astype(np.float16)
     return w
+
+
+# Every way the prompt attention splits a workgroup over queries and keys (32, 64 and 128 queries), at the three head
+# sizes: the token in a block's middle, at its first and its last query, behind cached positions and from an empty cache.
+@pytest.mark.parametrize("kind", ["overflow", "nan"])
+@pytest.mark.parametrize("shape,pos0,T,bad", [
+    (synth.ModelShape(512, 8, 64, 16, 2048, n_layers=2, name="neox-h512-x2"), 5, 95, 43),
+    (synth.ModelShape(640, 8, 80, 20, 2560, n_layers=2, name="d80-h640-x2"), 0, 64, 63),
+    (synth.ModelShape(640, 8, 80, 20, 2560, n_layers=2, name="d80-h640-x2"), 3, 70, 32),
+    (synth.ModelShape(1024, 8, 128, 32, 4096, n_layers=2, name="d128-h1024-x2"), 100, 140, 101),
+    (synth.ModelShape(2560, 32, 80, 20, 2560, n_layers=1, name="d80-h2560"), 0, 801, 700),
+    (synth.ModelShape(2048, 32, 64, 16, 2048, n_layers=1, name="d64-h2048"), 9, 2050, 1300),
+])
+def test_prompt_tokens_ahead_of_one_that_is_not_finite(shape, pos0, T, bad, kind):
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] nonfinite prompt {shape.name} T={T} bad={bad} {kind}", flush=True)
+    X = synth.x_input(shape, 71, batch=T)
+    cap = pos0 + T + 1
+    ds = DeviceStack(shape, cap, 8, shape.n_layers)
+    try:
+        for l in range(shape.n_layers):
+            ds.load_layer(l, _overflowing(shape, 70, l, X[bad]) if kind == "overflow" and l == 0 else synth.layer_weights(shape, 70, l))
+            ds.load_kv(l, *synth.kv_cache(shape, 70, l, pos0, cap, 8), pos0)
+        want = ds.prefill(X[:bad], pos0).astype(np.float64)
+        assert np.isfinite(want).all()
+        if kind == "nan":
+            X[bad] = np.nan
+        got = ds.prefill_gemm(X, pos0, rows=-(-T // 128) * 128).astype(np.float64)
+        ds.check()
+        assert not np.isfinite(got[bad:]).all(axis=1).any()
+        g = got[:bad]
+        assert np.isfinite(g).all(), f"tokens {sorted(set(np.where(~np.isfinite(g))[0]))} are not finite"
+        # the bound of the two paths' agreement: one fp16 step of the element, a step of the appended rows (2e-3 of the
+        # row's root mean square covers it), which the second layer's attention and products take up once more
+        rms = np.sqrt((want ** 2).mean(axis=1, keepdims=True))
+        step = np.ldexp(1.0, np.frexp(np.maximum(np.abs(g), np.abs(want)).clip(2.0 ** -14))[1] - 11)
+        assert (np.abs(g - want) <= step + 2e-3 * shape.n_layers * rms + 2e-5).all()
+        assert np.linalg.norm(g - want) <= 2.5e-4 * shape.n_layers * np.linalg.norm(want)
+    finally:
+        ds.close()
 
 
 # A new token whose V overflows in one dimension: that dimension of its own attention output is infinite, the others
