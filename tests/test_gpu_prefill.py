@@ -6,6 +6,7 @@ import pytest
 
 import synth
 from tests.parity import assert_appended_rows, assert_block_close, errors
+from tests.prefill_plans import PLANS
 
 pytestmark = pytest.mark.gpu
 
@@ -139,8 +140,8 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
     _check_prompt(orc, shape, 47, 0, 1030, 1, gemm_rows=1152, row_check_every=7)
 
 
-# Every tile of the GEMM's plan and its edges (token counts around multiples of 64, 128 and 256, split and unsplit
-# products) and of the attention: against the path through the batched projections, which the cases above hold to the oracle.  Both sides
+# Edges of the GEMM's tiles (token counts around multiples of 64, 128 and 256) and of the attention's: against the path
+# through the batched projections, which the cases above hold to the oracle.  Both sides
 # round the same fp32 values to fp16 once, so an element differs by one step of its size at most, plus the drift of
 # the appended rows' own roundings (2e-3 of the row's root mean square covers it: a step of one V row in a mean of
 # two rows or more).
@@ -191,6 +192,43 @@ def test_gemm_tiles_against_the_batched_projections(shape, pos0, T):
         v, s = (t.view(2, 8, H, d // 16, cap, 16) for t in (kv, st))
         assert torch.equal(v[:, :, :, :, :pos0], s[:, :, :, :, :pos0]) and torch.equal(v[:, :, :, :, pos0 + T:], s[:, :, :, :, pos0 + T:])
         assert torch.equal(v[:, 1:], s[:, 1:])
+    finally:
+        ds.close()
+
+
+# Every kind of tile, with K split and whole, that a plan takes for either product, each over two layers, so that what a
+# pass hands to the next layer (parts added on the way, or an unsplit result and a launch of its own) is used.  The bounds
+# are those above, per layer: the second layer's input carries the first's differences, and so do its K and V rows.
+@pytest.mark.parametrize("shape,T,first,second", PLANS)
+def test_gemm_plans_over_two_layers(shape, T, first, second):
+    import torch
+    import paper_2604_23553_amd as cf
+    import synth.device as sdev
+    from paper_2604_23553_amd.harness import DeviceStack
+    rows, pos0 = (T + 127) // 128 * 128, 3
+    with cf.profile_build():
+        assert cf.cfpp_debug_prefill_plan(cf.Config.from_shape(shape, pos0 + T), rows, T)[0] == (first, second)
+    print(f"[case] gemm plan shape={shape.name} T={T}", flush=True)
+    ds = DeviceStack(shape, pos0 + T, 8, 2)
+    try:
+        for l in range(2):
+            ds.load_layer_device(l, sdev.layer_tensors(shape, 5, l, ds.dev))
+            sdev.fill_kv(ds.kv[l], 5, l)
+        X = synth.x_input(shape, 6, batch=T)
+        want = [ds.prefill(X, pos0)] + [a for l in range(2) for a in ds.export_kv(l, 0, pos0, T)]
+        for l in range(2):
+            sdev.fill_kv(ds.kv[l], 5, l)
+        torch.cuda.synchronize()
+        got = [ds.prefill_gemm(X, pos0, rows=rows)] + [a for l in range(2) for a in ds.export_kv(l, 0, pos0, T)]
+        ds.check()
+        for g, w, layers in zip(got, want, (2, 0, 0, 1, 1)):       # layers in front of the values
+            g, w = g.astype(np.float64), w.astype(np.float64)
+            assert np.isfinite(g).all()
+            rms = np.sqrt((w ** 2).mean(axis=-1, keepdims=True))
+            step = np.ldexp(1.0, np.frexp(np.maximum(np.abs(g), np.abs(w)).clip(2.0 ** -14))[1] - 11)
+            bound = 1.001 * step + 2e-3 * layers * rms + 2e-5
+            assert (np.abs(g - w) <= bound).all(), float((np.abs(g - w) / bound).max())
+            assert np.linalg.norm(g - w) <= 2.5e-4 * max(layers, 1) * np.linalg.norm(w)
     finally:
         ds.close()
 

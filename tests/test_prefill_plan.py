@@ -7,6 +7,7 @@ import re
 import pytest
 
 import paper_2604_23553_amd as cf
+from tests.prefill_plans import PLANS
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(cf.__file__)), "csrc")
 TOKENS = (1, 20, 32, 33, 64, 65, 100, 128, 129, 256, 300, 384, 500, 640, 900, 1100, 1153, 1408, 1531, 2048, 2600, 2688,
@@ -27,6 +28,23 @@ def test_no_tile_loads_outside_its_operands(h, d):
         for t in TOKENS:
             _, past = plan(h, d, f, t)
             assert past == ((0, 0), (0, 0)), (h, f, t, past)
+
+
+@pytest.mark.parametrize("shape,tokens,first,second", PLANS)
+def test_what_a_size_selects(shape, tokens, first, second):
+    got, _ = plan(shape.hidden, shape.head_dim, shape.ffn, tokens)
+    assert got == (first, second)
+
+
+def test_the_passes_run_on_the_gpu_take_every_tile_that_plans_take():
+    def kinds(p):
+        return {(k, p[k][:3], p[k][3] > 1) for k in (0, 1)}
+    run = set().union(*(kinds(p[2:]) for p in PLANS))
+    for h, d in ((128, 64), (256, 64), (512, 64), (640, 80), (768, 64), (1024, 128), (1280, 80), (1536, 64), (1920, 80), (2048, 64),
+                 (2304, 64), (2560, 80), (2688, 64), (3072, 128), (3200, 80), (4096, 128)):
+        for t in (*range(1, 260, 3), *range(260, 4097, 19)):
+            new = kinds(plan(h, d, 4 * h, t)[0]) - run
+            assert not new, (h, t, new)
 
 
 def test_a_plan_is_refused_as_the_call_is():
