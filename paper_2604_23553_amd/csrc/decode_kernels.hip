@@ -141,10 +141,13 @@ __device__ __forceinline__ void phase_a(const StepParams &P, const __half *__res
 // less where the workgroup's own MLP-down rows are long beside it.  us per block, equal shares ->
 // whole heads: hidden 512: 128 positions 22.6 -> 21.1, 500: 24.3 -> 23.0, 1000 (32 rows): 28.0 -> 25.3,
 // 2000: 28.1 -> 29.6; hidden 1024, 500 (32 rows): 30.8 -> 28.1; hidden 1280, 128: 35.0 -> 33.9, 1000:
-// 38.4 -> 38.7; hidden 2560, 300: 43.6 -> 44.3, 1000: 44.6 -> 49.4.
-__device__ __forceinline__ bool whole_heads(const Dims &dm, int rows, int grid)
+// 38.4 -> 38.7; hidden 2560, 300: 43.6 -> 44.3, 1000: 44.6 -> 49.4.  Those rows are the longer the fewer
+// workgroups there are; with 64 of them: hidden 512, 450 (15 rows): 24.2 -> 22.4, 1000: 24.3 -> 24.5; hidden
+// 1024, 100 (7 rows): 30.9 -> 30.8, 450 (29): 31.8 -> 34.5; with 32: hidden 512, 450: 28.4 -> 28.7, 1000: 28.9 -> 31.4.
+// Four wavefronts to a workgroup: hidden 1024, 450: 29.6 -> 27.0, hidden 1280, 780 (25 rows): 41.6 -> 42.5.
+__device__ __forceinline__ bool whole_heads(const Dims &dm, int rows, int grid, int nw)
 {
-    return grid >= dm.H && dm.h < 2048 && rows <= 32 && rows * dm.h <= 32768;
+    return grid >= dm.H && dm.h < 2048 && rows <= 32 && rows * dm.h <= (nw >= 8 ? 128 : 120) * min(grid, 256);
 }
 
 // Split-KV decode attention over this workgroup's share of the cache, all
@@ -171,7 +174,7 @@ __device__ __forceinline__ void attn_share(const StepParams &P, const __half *__
     __half *vn = kn + D;
     AC ac;
     ac.init(P, kv, n_tok, lane);
-    const bool whole = whole_heads(P.dm, ac.R, (int)gridDim.x);         // (uniform over the grid)
+    const bool whole = whole_heads(P.dm, ac.R, (int)gridDim.x, nw);     // (uniform over the grid)
     if (whole) ac.take_whole_heads();
 
     if (ac.r0 >= ac.r1 || !(P.parts & kPartAttention)) {   // no rows for this workgroup, or no attention in this launch

@@ -122,6 +122,14 @@ def test_whole_heads_and_shares(orc, shape, S, mode):
     check_block(orc, shape, 13, S, S + 2, mode=mode, taps=True, repeats=2)
 
 
+# The same edge where an explicit launch shape moves it: 16 rows with 64 workgroups, 30 with four wavefronts each.
+@pytest.mark.parametrize("shape,S,grid,threads", [(synth.SMALL_BLOCK, 511, 64, 512), (synth.SMALL_BLOCK, 512, 64, 512),
+                                                  (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 479, 256, 256),
+                                                  (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 480, 256, 256)])
+def test_whole_heads_and_shares_at_other_launch_shapes(orc, shape, S, grid, threads):
+    check_block(orc, shape, 13, S, S + 2, mode=0, grid=grid, threads=threads, taps=True, repeats=2)
+
+
 def test_last_slot_of_the_cache(orc):
     check_block(orc, synth.SMALL_BLOCK, 3, 95, 96, mode=0)
 
