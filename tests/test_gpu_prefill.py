@@ -88,8 +88,8 @@ def test_prompt_at_the_2_8b_shape(orc):
     _check_prompt(orc, shape, 23, 100, 11, 8)
 
 
-# The same prompts through the prompt-sized kernels (cfpp_stack_prefill_gemm): LayerNorm launch,
-# four GEMMs on the matrix cores and one causal-attention launch per layer and pass.
+# The same prompts through the prompt-sized kernels (cfpp_stack_prefill_gemm): two products on the
+# matrix cores, one causal-attention launch and the LayerNorm's per layer and pass.
 @pytest.mark.parametrize("pos0,T,max_batch,b,rows", [
     (5, 19, 8, 0, 128),       # one pass, most of its tile padding
     (0, 7, 3, 0, 128),        # from an empty cache
@@ -114,7 +114,8 @@ def test_gemm_prompt_with_head_dim_128_and_tanh_gelu(orc):
 
 
 # The cases above are small enough that products split K (few tiles) and the parts meet in k_pf_reduce
-# and k_pf_row.  These two are long enough for products that are not split, at a head size that does not
+# and k_pf_row.  These two are long enough for a first product that is not split (in tiles of 64 x 128 and of
+# 128 x 320; the second one's parts are 5 and 4), at a head size that does not
 # divide the tiles (heads cut by tile edges) and a rotated part that is not a multiple of 8 dimensions.
 # Layer-0 rows are held to the rounding bound for every 7th token.
 
@@ -159,6 +160,8 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
     (synth.ModelShape(2048, 32, 64, 16, 2048, name="d64-h2048"), 31, 801),
     (synth.ModelShape(2048, 32, 64, 16, 2048, name="d64-h2048"), 0, 2050),
     (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 1000, 33),
+    # a group of 8 whose heads are 16 pieces each in the batched attention
+    (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 8000, 8),
 ])
 def test_gemm_tiles_against_the_batched_projections(shape, pos0, T):
     import torch

@@ -260,8 +260,8 @@ def test_full_pythia_2_8b_stack_graph_and_argmax(orc):
             ma, rl = assert_block_close(outs[0], ref16, f"32-layer output at {S2} cached positions")
             print(f"[result] S {S2}: max-abs {ma:.4e} rel-L2 {rl:.4e}", flush=True)
         # The prompt-sized kernels on the same resident stack, in the configuration the benchmark
-        # times: 512 tokens from position 0 in one pass (64-token tiles, QKV and up unsplit, dense
-        # and down split over K).  The oracle takes one decode step per token, so the whole prompt is
+        # times: 512 tokens from position 0 in one pass (QKV and up unsplit, dense and down split
+        # over K).  The oracle takes one decode step per token, so the whole prompt is
         # out of its reach at this depth; what it can compute one by one is checked against it -
         # token 0 through all 32 layers (it attends to itself only) and the layer-0 cache rows of
         # sampled tokens (they depend on the token's own input only) - and the last token's output
@@ -627,9 +627,9 @@ def test_batched_projections_on_the_matrix_cores(orc, shape, B, layers):
 
 
 def test_batched_attention_split_with_extreme_lengths(orc):
-    """Sequences from an empty cache to thousands of positions in one group: the
-    attention launch gives every sequence at least one workgroup and the long
-    ones nearly all."""
+    """Sequences from an empty cache to thousands of positions in one group: every
+    head of every sequence is at least one workgroup's, those of the long ones are
+    cut into pieces."""
     # (with an empty cache the attention output IS the new token's fp16 V row: where the two
     # sides round that row to neighbouring fp16 values - both correct roundings - the step
     # enters the output projection with weight 1, and the second layer's rows of such a
@@ -639,11 +639,15 @@ def test_batched_attention_split_with_extreme_lengths(orc):
 
 
 # Lengths on both sides of a lane group's row (32 positions; 16 at head size 128) and of a piece of
-# 32 rows, at every head size: heads in one piece, in a few, and a last piece of one row.
+# 32 rows, at every head size: heads in one piece, in a few, and a last piece of one row; and in more
+# pieces than the eight whose sums are read at a time, the last eight not full.
 @pytest.mark.parametrize("shape,lens", [
     (synth.ModelShape(512, 8, 64, 16, 2048, n_layers=1, name="neox-h512"), [0, 30, 31, 32, 1023, 1024, 2111]),
     (synth.ModelShape(640, 8, 80, 20, 2560, n_layers=1, name="d80-h640"), [31, 1022, 1023, 1024, 2048, 2500]),
     (synth.ModelShape(1024, 8, 128, 32, 4096, n_layers=1, name="d128-h1024"), [14, 15, 16, 510, 511, 512, 1100, 1600]),
+    (synth.ModelShape(512, 8, 64, 16, 2048, n_layers=1, name="neox-h512"), [8300, 40]),
+    (synth.ModelShape(640, 8, 80, 20, 2560, n_layers=1, name="d80-h640"), [12000, 0, 9000]),
+    (synth.ModelShape(1024, 8, 128, 32, 4096, n_layers=1, name="d128-h1024"), [17, 8100]),
 ])
 def test_batched_attention_pieces(orc, shape, lens):
     _batched_case(orc, shape, len(lens), 1, np.array(lens, dtype=np.int32))
