@@ -781,7 +781,7 @@ extern "C" cfpp_status cfpp_stack_prefill(cfpp_ctx *ctx, const void *const *pack
 }
 
 // Prompt processing with the weights read once per pass of up to `rows` tokens: every pass
-// goes through all layers (LayerNorm inputs, four GEMMs and the causal attention per layer)
+// goes through all layers (LayerNorm inputs, two products and the causal attention per layer)
 // before the next pass starts, which attends over this pass's rows in every layer's cache.
 extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const *packed_layers, void *const *kv_layers,
                                                const void *x, int32_t pos0, int32_t n_tokens, int32_t b, void *out,
@@ -828,7 +828,6 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         P.out = static_cast<__half *>(out) + (size_t)t0 * h;
         pf_place(P, pl, sc);
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
-        P.sync = reinterpret_cast<unsigned *>(ctx->ws + ctx->wl.sync);
         pf_plan_pass(P);
         float *xa = reinterpret_cast<float *>(sc + pl.xres), *xb2 = reinterpret_cast<float *>(sc + pl.xnext);
         for (int l = 0; l < L; ++l) {

@@ -411,10 +411,13 @@ constexpr int kAttnBatchMax = 8, kAttnBatchThreads = 256;
 // Workgroups dealt beyond one per head and sequence, and the fewest rows worth a piece.  us per step and layer, before
 // -> with pieces of 8 / 16 / 32 rows: five sequences of 37 .. 2048 positions (hidden 2560) 85.0 -> 65.9 / 65.7 / 63.6;
 // 8 prompt tokens behind 1000: 67.3 -> 70.5 / 66.4 / 64.2; two sequences of 8000: 80.0 -> 81.8 / 79.4 / 78.9. 
-// Spare ones of sequences with K/V rows of their own: 640, so that eight long sequences make about 768 workgroups, what is
-// resident at 3 a CU, in pieces of about one size.  One block of hidden 4096 with 8 sequences of 3219 .. 7696 positions,
-// 256 / 512 / 640 / 1024 / 2048 spare ones: 224.4 / 219.4 / 218.2 / 222.7 / 223.7 us (218.2 with the 256 workgroups of
-// before); of 1024 .. 8192 positions 640 / 1024 / 2048: 231.8 / 232.0 / 230.4 (234 .. 236 before).  A prompt group's queries share their
+// Spare ones of sequences with K/V rows of their own: 640, shared out by rows and rounded down per sequence, so that with one
+// per head it comes to 650 .. 900 workgroups of about one size for up to 32 heads, about what is resident at 3 a CU.  Chosen at 32 heads and 8
+// sequences: one block of hidden 4096, 3219 .. 7696 positions, 256 / 512 / 640 / 1024 / 2048 spare ones: 224.4 / 219.4 /
+// 218.2 / 222.7 / 223.7 us (218.2 with the 256 workgroups of before); of 1024 .. 8192 positions 640 / 1024 / 2048: 231.8 /
+// 232.0 / 230.4 (234 .. 236 before).  Elsewhere 640 was held against the kernels of before only, us per whole step: 8 heads, 4 layers,
+// 2 sequences of 6000 .. 8000 183 -> 157, 8 of 2000 190 -> 169; 24 heads, 4 layers 245 -> 232, 266 -> 257; 32 heads of 80,
+// 2 layers 168 -> 156, 182 -> 178.  A prompt group's queries share their
 // rows and don't stream: 1024, as measured above.  Pieces of a head never exceed the workspace's part_slots.
 constexpr int kAttnSpareGroups = 640, kAttnSpareShared = 1024, kAttnPieceRows = 32;
 

@@ -246,7 +246,7 @@ k_pf_gemm(PfParams P, int splits, int gm)
                     if (ks + 1 < KS) {
                         fetch(F[(ks + 1) & 1], stage, ks + 1);
                     } else if (j + 1 < je) {
-        if (j + ST - 1 < je) pf_wait_barrier<(ST - 2) * NLD>();
+                        if (j + ST - 1 < je) pf_wait_barrier<(ST - 2) * NLD>();
                         else pf_wait_barrier<0>();
                         fetch(F[0], next, 0);
                     }
@@ -441,8 +441,9 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 //     most tiles of a CU x (K / 32 / splits x step + epilogue)  [where several tiles share a CU: at least
 //     rounds x K / 32 / splits x lone_step]
 //     + (split: the parts written and read again)
-// in us.  The constants are a least-squares fit to 1500 timings (hidden 512 .. 4096, 8 .. 4096 tokens, every tile,
-// splits 1 .. 16) and pick within 0.8 % of the fastest measured combination in the mean, 7.5 % at worst.
+// The constants are a least-squares fit in us to 1500 timings of one product alone (hidden 512 .. 4096, 8 .. 4096 tokens,
+// every tile, splits 1 .. 16): they order the choices, and pick within 0.8 % of the fastest measured combination in the mean,
+// 7.5 % at worst; inside a layer a product takes longer than its estimate (512 tokens: 106 us, estimate 76).
 // Measured per layer (attention and LayerNorm included), before this kernel -> now: hidden 2560: 100 tokens 144 -> 103,
 // 512: 303 -> 224, 4096: 2345 -> 1528; hidden 4096, 1531 tokens: 1810 -> 1203.  (Up to 64 tokens: pf_plan_short.)
 constexpr int kPfCus = 256;
@@ -464,6 +465,7 @@ static const PfTileCost kPfTiles[kPfTileKinds] = {
 // the wider tile or by splitting K: the first product at most three ways (its parts cost a launch that adds them), the
 // second up to sixteen (they are added where the next layer's input is made).  us per layer, least estimate above -> this:
 // hidden 2560: 20 tokens 69.0 -> 55, 37 tokens 73.3 -> 66.0, 64 tokens 76.0 -> 71; hidden 4096, 20 tokens 129 -> 107.
+// (With a feed-forward of four times hidden the 256-wide tiles fill more CUs at hidden 2432 .. 3200 and at some sizes above.)
 // False where that leaves half the CUs without a tile of 64 (hidden 512, 40 tokens: 31 us, 27 by the estimate).
 static bool pf_plan_short(const PfParams &P, bool in, size_t part_bytes, PfPlan *plan)
 {

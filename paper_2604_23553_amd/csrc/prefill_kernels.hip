@@ -1,7 +1,7 @@
 // Prompt processing with the weights read once per pass over up to kPfMaxRows
 // tokens (the paper names a prefill phase beside its fused decode kernel, Sec. 4.2;
 // what is computed is the block of Sec. 2.2 applied to every prompt token with
-// causal attention).  With hundreds of tokens the four projections are dense
+// causal attention).  With hundreds of tokens the projections are dense
 // contractions - tokens x K activations times K x rows weights - and run as
 // LDS-tiled GEMMs on the matrix cores (prefill_gemm.hip); the attention of
 // a pass reads the cache rows its own QKV launch appended.

@@ -75,7 +75,6 @@ struct PfParams {
     PfPlan plan_in, plan_out;
     bool row_fused;         // the kernel that adds the second product's parts prepares the next layer's input too
     const float2 *rope;
-    unsigned *sync;
 };
 
 // where a pass's buffers lie in the scratch at `sc`
@@ -96,7 +95,7 @@ bool pf_supported(const Dims &dm);
 void pf_plan_pass(PfParams &P);
 // that plan, and what the products' DMA would request past their operands (profiling library): see cfpp_debug_prefill_plan
 void pf_describe_plan(const PfParams &P, int plan[8], int past[4]);
-// one block for the tokens of a pass: LayerNorm inputs, QKV, attention, dense, up, down
+// one block for the tokens of a pass: LayerNorm inputs, QKV and up, attention, dense and down
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s);
 // its products (prefill_gemm.hip): QKV and MLP-up; output projection and MLP-down
 hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s);
