@@ -51,6 +51,12 @@ cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_
 cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                     int32_t plan[8], int32_t past[4]);
 
+/* GELU of n fp32 values z (DEVICE) as the prompt-sized kernels' epilogues work it out
+ * and as the other kernels do, with the device library's erff or tanhf (flags:
+ * CFPP_FLAG_TANH_GELU or 0), into two DEVICE arrays. */
+cfpp_status cfpp_debug_gelu(const float *z, float *epilogue, float *library, int32_t n, int32_t flags,
+                            cfpp_stream stream);
+
 /* Plain streaming kernels whose HBM traffic is known exactly, used to find the
  * streaming bandwidth this GPU sustains and to scale hardware traffic counters.
  * cfpp_stream_read loads every 16-byte word of src (DEVICE, `bytes` a multiple of

@@ -279,6 +279,11 @@ def cfpp_debug_prefill_plan(cfg: Config, rows: int, n_tokens: int):
     return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
 
 
+def cfpp_debug_gelu(z, epilogue, library, n: int, flags: int, stream=None):
+    _check(lib().cfpp_debug_gelu(_ptr(z), _ptr(epilogue), _ptr(library), C.c_int32(n), C.c_int32(flags), _ptr(stream)),
+           "cfpp_debug_gelu")
+
+
 def cfpp_stream_read(src, nbytes: int, sink, grid: int, threads: int, unroll: int, stream=None):
     _check(lib().cfpp_stream_read(_ptr(src), C.c_size_t(nbytes), _ptr(sink), C.c_int32(grid),
                                   C.c_int32(threads), C.c_int32(unroll), _ptr(stream)), "cfpp_stream_read")

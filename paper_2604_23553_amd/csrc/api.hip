@@ -1157,6 +1157,14 @@ extern "C" cfpp_status cfpp_debug_prefill_plan(const cfpp_config *c, int32_t row
     return CFPP_OK;
 }
 
+extern "C" cfpp_status cfpp_debug_gelu(const float *z, float *epilogue, float *library, int32_t n, int32_t flags,
+                                       cfpp_stream stream)
+{
+    if (!z || !epilogue || !library || n <= 0) return fail(CFPP_EINVAL, "NULL argument or n <= 0");
+    HIP_OK(launch_debug_gelu(z, epilogue, library, n, flags & CFPP_FLAG_TANH_GELU, static_cast<hipStream_t>(stream)));
+    return CFPP_OK;
+}
+
 // ---- bandwidth calibration -------------------------------------------------------------
 extern "C" cfpp_status cfpp_stream_read(const void *src, size_t bytes, void *sink, int32_t grid,
                                         int32_t threads, int32_t unroll, cfpp_stream stream)

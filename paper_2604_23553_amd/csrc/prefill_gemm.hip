@@ -540,6 +540,19 @@ void pf_plan_pass(PfParams &P)
 }
 
 #ifdef CFPP_PROFILE
+__global__ void __launch_bounds__(256) k_debug_gelu(const float *z, float *epilogue, float *library, int n, int flags)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    epilogue[i] = pf_gelu(z[i], flags);
+    library[i] = gelu_act(z[i], flags);
+}
+hipError_t launch_debug_gelu(const float *z, float *epilogue, float *library, int n, int flags, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_debug_gelu, dim3((n + 255) / 256), dim3(256), 0, s, z, epilogue, library, n, flags);
+    return hipGetLastError();
+}
+
 void pf_describe_plan(const PfParams &P, int plan[8], int past[4])
 {
     for (int k = 0; k < 2; ++k) {

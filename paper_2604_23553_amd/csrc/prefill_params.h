@@ -95,6 +95,8 @@ bool pf_supported(const Dims &dm);
 void pf_plan_pass(PfParams &P);
 // that plan, and what the products' DMA would request past their operands (profiling library): see cfpp_debug_prefill_plan
 void pf_describe_plan(const PfParams &P, int plan[8], int past[4]);
+// the epilogues' GELU and the library's on n values (profiling library)
+hipError_t launch_debug_gelu(const float *z, float *epilogue, float *library, int n, int flags, hipStream_t s);
 // one block for the tokens of a pass: LayerNorm inputs, QKV and up, attention, dense and down
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s);
 // its products (prefill_gemm.hip): QKV and MLP-up; output projection and MLP-down
