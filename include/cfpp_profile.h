@@ -51,6 +51,14 @@ cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_
 cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                     int32_t plan[8], int32_t past[4]);
 
+/* Where cfpp_stack_prefill_gemm keeps a layer's intermediates in the caller's scratch, byte
+ * offsets: at[0], at[1] gamma_1 x and gamma_2 x, at[3] the attention output, at[4] GELU(up),
+ * each as rows of groups of 32 fp16 heads and then their 32 fp16 remainders (value = head +
+ * remainder), halves[0] fp16 values from row to row (at[4]: halves[1]); at[2] the rotated
+ * queries, fp32 [rows][hidden].  After the call they are the last layer's, where the
+ * second product's K is in one part (cfpp_debug_prefill_plan); its parts overwrite the queries. */
+cfpp_status cfpp_debug_prefill_scratch(const cfpp_config *cfg, int32_t rows, size_t at[5], int32_t halves[2]);
+
 /* GELU of n fp32 values z (DEVICE) as the prompt-sized kernels' epilogues work it out
  * and as the other kernels do, with the device library's erff or tanhf (flags:
  * CFPP_FLAG_TANH_GELU or 0), into two DEVICE arrays. */

@@ -279,6 +279,13 @@ def cfpp_debug_prefill_plan(cfg: Config, rows: int, n_tokens: int):
     return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
 
 
+def cfpp_debug_prefill_scratch(cfg: Config, rows: int):
+    """((offsets of gamma_1 x, gamma_2 x, q, attention output, GELU(up)), (halves per row of hidden, of ffn))."""
+    at, halves = (C.c_size_t * 5)(), (C.c_int32 * 2)()
+    _check(lib().cfpp_debug_prefill_scratch(C.byref(cfg), C.c_int32(rows), at, halves), "cfpp_debug_prefill_scratch")
+    return tuple(at), tuple(halves)
+
+
 def cfpp_debug_gelu(z, epilogue, library, n: int, flags: int, stream=None):
     _check(lib().cfpp_debug_gelu(_ptr(z), _ptr(epilogue), _ptr(library), C.c_int32(n), C.c_int32(flags), _ptr(stream)),
            "cfpp_debug_gelu")

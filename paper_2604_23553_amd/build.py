@@ -18,7 +18,7 @@ LIB_PROFILE = os.path.join(PKG, "libcfpp_profile.so")
 SOURCES = ["api.hip", "decode_kernels.hip", "fused_kernel.hip", "lm_kernels.hip", "batched_kernels.hip",
            "prep_kernels.hip", "prefill_kernels.hip", "prefill_gemm.hip"]
 HEADERS = ["layout.h", "device_utils.h", "decode_params.h", "attention_common.h", "decode_blocks.h",
-           "attention_blocks.h", "lm_params.h", "batched_params.h", "prefill_params.h", "prefill_device.h"]
+           "attention_blocks.h", "lm_params.h", "batched_params.h", "prefill_params.h", "prefill_device.h", "half_split.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

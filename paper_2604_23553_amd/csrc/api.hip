@@ -1157,6 +1157,19 @@ extern "C" cfpp_status cfpp_debug_prefill_plan(const cfpp_config *c, int32_t row
     return CFPP_OK;
 }
 
+extern "C" cfpp_status cfpp_debug_prefill_scratch(const cfpp_config *c, int32_t rows, size_t at[5], int32_t halves[2])
+{
+    cfpp_status st = cfpp_validate_config(c);
+    if (st != CFPP_OK) return st;
+    if (!at || !halves) return fail(CFPP_EINVAL, "NULL argument");
+    if (rows <= 0 || rows > kPfMaxRows || rows % kPfTile != 0) return fail(CFPP_EINVAL, "rows %d", rows);
+    const Dims dm = dims_of(*c);
+    const PfLayout pl = pf_layout(dm, rows);
+    at[0] = pl.y1; at[1] = pl.y2; at[2] = pl.q; at[3] = pl.o; at[4] = pl.m;
+    halves[0] = (int32_t)pf_row_halves(dm.h); halves[1] = (int32_t)pf_row_halves(dm.f);
+    return CFPP_OK;
+}
+
 extern "C" cfpp_status cfpp_debug_gelu(const float *z, float *epilogue, float *library, int32_t n, int32_t flags,
                                        cfpp_stream stream)
 {

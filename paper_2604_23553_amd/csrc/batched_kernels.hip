@@ -42,6 +42,7 @@
 #include <hip/hip_fp16.h>
 #include "decode_blocks.h"
 #include "batched_params.h"
+#include "half_split.h"
 
 namespace cfpp {
 
@@ -333,8 +334,7 @@ __device__ __forceinline__ void bat_put8(__half *yh, __half *yl, int at, const f
     union { __half h[8]; u32x4 u; } hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        hi.h[e] = __float2half_rn(v[e]);
-        lo.h[e] = __float2half_rn(v[e] - __half2float(hi.h[e]));
+        split_half(v[e], hi.h[e], lo.h[e]);
     }
     *reinterpret_cast<u32x4 *>(yh + at) = hi.u;
     *reinterpret_cast<u32x4 *>(yl + at) = lo.u;

@@ -3,15 +3,10 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include "device_utils.h"
+#include "half_split.h"
 #include "prefill_params.h"
 
 namespace cfpp {
-
-__device__ __forceinline__ void pf_split(float v, __half &hi, __half &lo)
-{
-    hi = __float2half_rn(v);
-    lo = __float2half_rn(v - __half2float(hi));
-}
 
 __device__ __forceinline__ unsigned pf_pack2(float a, float b)
 {

@@ -53,7 +53,7 @@ __device__ __forceinline__ void pf_store(const PfParams &P, int row, int col, fl
         else P.kv[kv_offset(dm, c - 1, P.b, nh, dim, P.pos0 + row)] = __float2half_rn(val);
     } else {
         __half hi, lo;
-        pf_split(pf_gelu(val, dm.flags), hi, lo);
+        split_half(pf_gelu(val, dm.flags), hi, lo);
         const size_t at = pf_at(row, col, dm.f);
         P.m[at] = hi; P.m[at + kPfLo] = lo;
     }
@@ -305,7 +305,7 @@ k_pf_gemm(PfParams P, int splits, int gm)
                     const int rl = (e >> 2) * 8 + (e & 3);
                     const float2 st = sst[r_lane + a * 32 + rl];
                     __half hi, lo;
-                    pf_split(pf_gelu((acc[a][b][e] - st.x * rc.x) * st.y + rc.y, dm.flags), hi, lo);
+                    split_half(pf_gelu((acc[a][b][e] - st.x * rc.x) * st.y + rc.y, dm.flags), hi, lo);
                     t[(rl + (lane >> 5) * 4) * TS + (lane & 31)] = hi;
                     t[(rl + (lane >> 5) * 4) * TS + kPfLo + (lane & 31)] = lo;
                 }

@@ -117,8 +117,8 @@ __global__ void __launch_bounds__(256) k_pf_row(PfParams P)
         __half h1[4], l1[4], h2[4], l2[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            pf_split(x[j][e] * ga[e], h1[e], l1[e]);
-            pf_split(x[j][e] * gb[e], h2[e], l2[e]);
+            split_half(x[j][e] * ga[e], h1[e], l1[e]);
+            split_half(x[j][e] * gb[e], h2[e], l2[e]);
         }
         const size_t at = pf_at(row, 4 * g, h);
         *reinterpret_cast<uint2 *>(P.y1 + at) = *reinterpret_cast<const uint2 *>(h1);
@@ -237,7 +237,7 @@ __device__ __forceinline__ void pf_attn_alone(const PfParams &P, const __half *K
     for (int e = 0; e < NE; ++e) {
         if (lane + 64 * e >= D) continue;
         __half hi, lo;
-        pf_split(o[e] / l, hi, lo);
+        split_half(o[e] / l, hi, lo);
         const size_t to = pf_at(row, head * D + lane + 64 * e, dm.h);
         P.o[to] = hi; P.o[to + kPfLo] = lo;
     }
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
         const f32x4 a = qp[0], b = qp[1];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float v = (j < 4 ? a[j & 3] : b[j & 3]) * scale;
+            const float v = split_value((j < 4 ? a[j & 3] : b[j & 3]) * scale);
             qh[ks][j] = (_Float16)v;
             ql[ks][j] = (_Float16)(v - (float)qh[ks][j]);
         }
@@ -403,8 +403,8 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
         for (int j = 0; j < 4; ++j) {
             const float va = a[j] / l, vb = b[j] / l;
             finite = finite && fabsf(va) < INFINITY && fabsf(vb) < INFINITY;
-            pf_split(va, hi[j], lo[j]);
-            pf_split(vb, hi[4 + j], lo[4 + j]);
+            split_half(va, hi[j], lo[j]);
+            split_half(vb, hi[4 + j], lo[4 + j]);
         }
         const size_t at = pf_at(q0 + q, head * D + c8, dm.h);
         *reinterpret_cast<u32x4 *>(P.o + at) = *reinterpret_cast<const u32x4 *>(hi);

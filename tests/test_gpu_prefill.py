@@ -236,6 +236,79 @@ def test_gemm_plans_over_two_layers(shape, T, first, second):
         ds.close()
 
 
+# What passes between a layer's kernels as head + remainder, and the attention, against 64 bits: a value whose head and
+# remainder come from two roundings is off by up to 2^-11, which the fp16 output hides.  Sizes whose second product keeps
+# K whole (the queries stay in the scratch), with 32, 64 and 128 queries to a workgroup; the scores reach 10 and more.
+@pytest.mark.parametrize("shape,T", [
+    (synth.ModelShape(512, 8, 64, 16, 2048, n_layers=1, name="d64-h512"), 2700),
+    (synth.ModelShape(768, 12, 64, 16, 3072, n_layers=1, name="d64-h768"), 2300),
+    (synth.ModelShape(2560, 32, 80, 20, 10240, n_layers=1, name="d80-h2560"), 3100),
+    (synth.ModelShape(4096, 32, 128, 32, 16384, n_layers=1, name="d128-h4096"), 2600),
+])
+def test_intermediates_of_a_pass_against_64_bits(shape, T):
+    import math
+    import torch
+    import paper_2604_23553_amd as cf
+    import synth.device as sdev
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] intermediates shape={shape.name} T={T}", flush=True)
+    h, f, H, d = shape.hidden, shape.ffn, shape.n_heads, shape.head_dim
+    rows = (T + 127) // 128 * 128
+    with cf.profile_build():
+        cfg = cf.Config.from_shape(shape, T)
+        assert cf.cfpp_debug_prefill_plan(cfg, rows, T)[0][1][3] == 1
+        at, halves = cf.cfpp_debug_prefill_scratch(cfg, rows)
+    ds = DeviceStack(shape, T, 1, 1)
+    try:
+        w = sdev.layer_tensors(shape, 5, 0, ds.dev)
+        w["w_qkv"] *= 2
+        ds.load_layer_device(0, w)
+        x = torch.from_numpy(synth.x_input(shape, 6, batch=T)).to(ds.dev)
+        out = torch.zeros_like(x)
+        nbytes = cf.cfpp_prefill_scratch_bytes(ds.cfg, rows)
+        sc = torch.empty(nbytes, dtype=torch.uint8, device=ds.dev)
+        torch.cuda.synchronize()
+        cf.cfpp_stack_prefill_gemm(ds.ctx, ds.packed, ds.kv, x, 0, T, 0, out, sc, nbytes, rows, ds.s)
+        ds.check()
+        k, v = (torch.from_numpy(a).to(ds.dev).double() for a in ds.export_kv(0, 0, 0, T))
+
+        def planes(i, width, stride):
+            t = sc[at[i]:at[i] + rows * stride * 2].view(torch.float16).view(rows, stride)[:T, :2 * width]
+            return t.reshape(T, width // 32, 2, 32).double().sum(2).reshape(T, width)
+
+        xd = x.double()
+        for i, g in ((0, "ln1_g"), (1, "ln2_g")):          # one rounding to 2^-22, or to a step of the smallest fp16
+            want = xd * w[g].double()
+            assert ((planes(i, h, halves[0]) - want).abs() <= want.abs() * 2.0 ** -21 + 2.0 ** -24).all(), g
+        # GELU(up): an fp32 sum of h products (64 x its rounding), then as above
+        mu = xd.mean(1, keepdim=True)
+        y = (xd - mu) / torch.sqrt(((xd - mu) ** 2).mean(1, keepdim=True) + shape.ln_eps) * w["ln2_g"].double() + w["ln2_b"].double()
+        m = planes(4, f, halves[1])
+        for r in range(0, T, 512):
+            z = y[r:r + 512] @ w["w_up"].double().t().contiguous() + w["b_up"].double()
+            want = 0.5 * z * torch.special.erfc(-z / math.sqrt(2.0))
+            assert ((m[r:r + 512] - want).abs() <= 64 * 2.0 ** -24 * (1.0 + z.abs())).all(), "GELU(up)"
+        # attention from the queries and the cache as they stand: a score is an fp32 sum over d / 16 steps (4 x the rounding of
+        # its terms' absolute sum, and of the two planes'), a weight the exponential of it, the sums over keys 32 x a rounding;
+        # a weight's remainder is rounded to half a step of the smallest fp16 where the largest weight is 1
+        q, o = sc[at[2]:at[2] + rows * h * 4].view(torch.float32).view(rows, h)[:T].double(), planes(3, h, halves[0])
+        worst = 0.0
+        for n in range(0, H, max(1, H // 8)):
+            for r in range(0, T, 1024):
+                s = (q[r:r + 1024, n * d:(n + 1) * d] @ k[n].t().contiguous()) / math.sqrt(d)
+                s.masked_fill_(torch.arange(T, device=ds.dev)[None] > torch.arange(r, min(r + 1024, T), device=ds.dev)[:, None], -math.inf)
+                p = torch.softmax(s, 1)
+                A = (q[r:r + 1024, n * d:(n + 1) * d].abs() @ k[n].abs().t().contiguous()).masked_fill_(s == -math.inf, 0.0) / math.sqrt(d)
+                e = (o[r:r + 1024, n * d:(n + 1) * d] - p @ v[n]).abs()
+                bound = 2.0 ** -24 * (32.0 + 4.0 * A.max(1, keepdim=True).values) * (p @ v[n].abs())
+                bound += 2.0 ** -25 * p.max(1, keepdim=True).values * v[n].abs().cumsum(0)[r:r + 1024]
+                worst = max(worst, float((e / bound).max()))
+                assert (e <= bound).all(), f"head {n} rows {r} ..: {int((e > bound).any(1).sum())} queries, up to {float((e / bound).max()):.1f} x"
+        print(f"[result] attention {shape.name}: {worst:.2f} of the bound", flush=True)
+    finally:
+        ds.close()
+
+
 # The epilogues' GELU loses nothing against the forms with the device library's functions: over what the MLP-up
 # products of the supported sizes give (0.02 sqrt(hidden) or so: N(0, 0.2) .. N(0, 1.3)) and over the whole curve its distance
 # from 64 bits is no larger, and infinities and NaN come out the same.
