@@ -16,7 +16,7 @@
 #include "cfpp_profile.h"
 #endif
 #include "lm_params.h"
-#include "batched_params.h"
+#include "narrow_params.h"
 #include "prefill_params.h"
 #include "decode_params.h"
 
@@ -215,7 +215,7 @@ struct cfpp_ctx {
     unsigned long long graph_epochs;   // tagged-word epochs one replay of the captured graph uses up
     int fused_grid, fused_threads;     // launch shape the whole-stack kernel was last found to fit
     bool fused_ok;
-    int last_batch;
+    int planes;             // tokens whose GELU(up) and attention output the last step left as heads and remainders (ng_at); 0: fp32
 };
 
 extern "C" cfpp_status cfpp_create(const cfpp_config *c, void *workspace, size_t workspace_bytes,
@@ -257,7 +257,6 @@ extern "C" cfpp_status cfpp_create(const cfpp_config *c, void *workspace, size_t
     ctx->exec = nullptr;
     ctx->graph_epochs = 0;
     ctx->fused_grid = 0; ctx->fused_threads = 0; ctx->fused_ok = false;
-    ctx->last_batch = 1;
 
     // barrier words, error flag and per-head arrival counters start at zero
     hipError_t e = hipMemset(ctx->ws + wl.sync, 0, wl.layer_ptrs - wl.sync);
@@ -414,7 +413,7 @@ static cfpp_status prepare(cfpp_ctx *ctx)
     if (ctx->prepared) return CFPP_OK;
     HIP_OK(prepare_kernels(160 * 1024));
     HIP_OK(prepare_fused_kernels(160 * 1024));
-    HIP_OK(prepare_bat_kernels(160 * 1024));
+    HIP_OK(prepare_narrow_kernels());
     ctx->prepared = true;
     return CFPP_OK;
 }
@@ -499,27 +498,27 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
     const Dims &dm = ctx->dm;
     const WorkspaceLayout &wl = ctx->wl;
     for (int b0 = 0; b0 < batch; b0 += kBatMax) {
-        BatParams B;
+        NarrowParams B;
         std::memset(&B, 0, sizeof B);
         B.dm = dm; B.lay = ctx->lay; B.w = w; B.kv = kv;
         B.pos = pos_dev + b0;
-        B.nb = batch - b0 < kBatMax ? batch - b0 : kBatMax;
-        B.b0 = b0; B.layer = l; B.n_layers = n_layers;
+        B.n = B.nt = batch - b0 < kBatMax ? batch - b0 : kBatMax;
+        B.layer = l; B.n_layers = n_layers;
         B.kv_b0 = kv_seq < 0 ? b0 : kv_seq;
         B.kv_bstep = kv_seq < 0 ? 1 : 0;
         B.x_in = static_cast<const __half *>(x) + (size_t)b0 * dm.h;
         B.out = static_cast<__half *>(out) + (size_t)b0 * dm.h;
         B.xres = reinterpret_cast<float *>(ctx->ws + wl.xres) + (size_t)b0 * 2 * dm.h;
         B.q = reinterpret_cast<float *>(ctx->ws + wl.q) + (size_t)b0 * dm.h;
-        B.m = reinterpret_cast<float *>(ctx->ws + wl.m) + (size_t)b0 * dm.f;
-        B.o = reinterpret_cast<float *>(ctx->ws + wl.o) + (size_t)b0 * dm.h;
+        B.m = reinterpret_cast<__half *>(ctx->ws + wl.m + (size_t)b0 * dm.f * 4);
+        B.o = reinterpret_cast<__half *>(ctx->ws + wl.o + (size_t)b0 * dm.h * 4);
         B.rope = reinterpret_cast<const float2 *>(ctx->ws + wl.rope);
         B.sync = reinterpret_cast<unsigned *>(ctx->ws + wl.sync);
-        HIP_OK(launch_bat_qkv_up(B, sh.grid, s));
+        HIP_OK(launch_bat_in(B, ctx->n_cu, s));
         StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
         if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
-        HIP_OK(launch_attention_batched(P, B.nb, kv, s));
-        HIP_OK(launch_bat_out(B, sh.grid, s));
+        HIP_OK(launch_attention_batched(P, B.n, kv, s));
+        HIP_OK(launch_bat_out(B, ctx->n_cu, s));
     }
     return CFPP_OK;
 }
@@ -639,7 +638,7 @@ static cfpp_status block_decode(cfpp_ctx *ctx, const void *packed_layer, void *k
         return st;
     const __half *w = static_cast<const __half *>(packed_layer);
     __half *kv = static_cast<__half *>(kv_layer);
-    ctx->last_batch = batch;
+    ctx->planes = mode == 0 && batched_path(ctx, sh, batch) ? batch : 0;
     if (mode == 0 && batched_path(ctx, sh, batch)) return launch_batched_layer(ctx, sh, w, kv, 0, 1, x, pos_dev, batch, out, s);
     if (mode == 2 && !capturing(s) && (st = account_epochs(ctx, 2ull * batch)) != CFPP_OK) return st;
     for (int b = 0; b < batch; ++b) {
@@ -692,7 +691,7 @@ static cfpp_status enqueue_stack(cfpp_ctx *ctx, const void *const *packed_layers
     if (store_table && mode == 2) HIP_OK(launch_store_layer_ptrs(ptrs, dev_ptrs, L, s));
     if (epochs) *epochs = mode == 2 ? (unsigned long long)(L + 1) * batch : 0;
     if (!launch) return CFPP_OK;
-    ctx->last_batch = batch;
+    ctx->planes = mode == 0 && batched_path(ctx, sh, batch) ? batch : 0;
     if (mode == 0 && batched_path(ctx, sh, batch)) {
         for (int l = 0; l < L; ++l)
             if ((st = launch_batched_layer(ctx, sh, ptrs.w[l], ptrs.kv[l], l, L, x, pos_dev, batch, out, s)) != CFPP_OK)
@@ -776,7 +775,7 @@ extern "C" cfpp_status cfpp_stack_prefill(cfpp_ctx *ctx, const void *const *pack
                                            b)) != CFPP_OK)
                 return st;
     }
-    ctx->last_batch = 1;
+    ctx->planes = (n_tokens - 1) % group + 1;
     return CFPP_OK;
 }
 
@@ -840,7 +839,6 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
             HIP_OK(launch_pf_layer(P, s));
         }
     }
-    ctx->last_batch = 1;
     return CFPP_OK;
 }
 
@@ -1102,7 +1100,6 @@ extern "C" cfpp_status cfpp_block_decode_static(const cfpp_config *c, const void
         ctx.lds_limit = lds_limit > 0 ? (size_t)lds_limit : 65536;
         ctx.prepared = prepared;
         ctx.lm_prepared = lm_prepared;
-        ctx.last_batch = 1;
         // the array keeps whatever the last configuration left: this one's sync words and
         // arrival counters start at zero, its rotary table is written (on `stream`, ahead of the step)
         const int half = dm.r / 2;
@@ -1134,6 +1131,20 @@ extern "C" cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_
     }
     if (count > n) return fail(CFPP_EINVAL, "count %zu exceeds the buffer (%zu floats)", count, n);
     HIP_OK(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
+    if ((which == 1 || which == 3) && ctx->planes > 0) {   // heads and remainders, in groups of kBatMax tokens
+        const int width = which == 1 ? dm.f : dm.h;
+        std::vector<__half> planes(2 * n);
+        HIP_OK(hipMemcpy(planes.data(), ctx->ws + off, 2 * n * sizeof(__half), hipMemcpyDeviceToHost));
+        for (size_t e = 0; e < count; ++e) {
+            const int token = (int)(e / width), g0 = token / kBatMax * kBatMax, left = ctx->planes - g0, nt = left < kBatMax ? left : kBatMax;
+            const __half *p = planes.data() + (size_t)g0 * width * 2;
+            if (token >= ctx->planes) { dst_host[e] = 0.f; continue; }
+            const size_t at = ng_at(token - g0, (int)(e % width), width, nt);
+            const float hi = __half2float(p[at]);
+            dst_host[e] = std::isinf(hi) ? hi : hi + __half2float(p[at + 8 * nt]);
+        }
+        return CFPP_OK;
+    }
     HIP_OK(hipMemcpy(dst_host, ctx->ws + off, count * sizeof(float), hipMemcpyDeviceToHost));
     return CFPP_OK;
 }

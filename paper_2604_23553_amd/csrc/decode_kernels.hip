@@ -24,6 +24,8 @@
 #include <hip/hip_fp16.h>
 #include "decode_blocks.h"
 #include "attention_blocks.h"
+#include "half_split.h"
+#include "narrow_params.h"
 
 namespace cfpp {
 
@@ -570,11 +572,19 @@ k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
         for (int e = 0; e < NE; ++e)
             if (lane + 64 * e < D) O[e] += wp[w * D + lane + 64 * e] * ew;
     }
-    float *out = P.o + (size_t)mine * dm.h + head * D;
-    if (pieces == 1) {
+    auto deliver = [&]() {                                 // heads and remainders, as the output projection takes them
+        __half *out = reinterpret_cast<__half *>(P.o);
 #pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (lane + 64 * e < D) out[lane + 64 * e] = O[e] / L;
+        for (int e = 0; e < NE; ++e) {
+            if (lane + 64 * e >= D) continue;
+            __half hi, lo;
+            split_half(O[e] / L, hi, lo);
+            const size_t at = ng_at(mine, head * D + lane + 64 * e, dm.h, nb);
+            out[at] = hi; out[at + 8 * nb] = lo;
+        }
+    };
+    if (pieces == 1) {
+        deliver();
         return;
     }
     // publish the piece; the last one of the head adds them in order
@@ -614,9 +624,7 @@ k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
             }
         }
     }
-#pragma unroll
-    for (int e = 0; e < NE; ++e)
-        if (lane + 64 * e < D) out[lane + 64 * e] = O[e] / L;
+    deliver();
     if (lane == 0) __hip_atomic_store(&P.seg_cnt[hd], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

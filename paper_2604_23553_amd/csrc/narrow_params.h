@@ -1,0 +1,49 @@
+// Arguments of the narrow products (narrow_gemm.hip): a layer's projections for a few tokens - sequences of a
+// decode step, a group of prompt tokens, or a short prompt.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+#include "layout.h"
+
+namespace cfpp {
+
+constexpr int kNgSet = 8;              // tokens whose heads and remainders are the 16 columns of a matrix instruction
+constexpr int kBatMax = kNgSet;        // sequences per launch of the batched path
+
+// Activations that feed a narrow product: fp16 heads and remainders in the order in which the matrix instruction
+// takes them.  A set of (up to) 8 tokens is K / 32 blocks; a block holds, for each of its four groups of 8 columns, the
+// heads of the set's tokens and then their remainders, 8 halves each: one contiguous load of 128 bytes a token.
+// nt: tokens a block has room for (8, or those there are, where only one set exists).  The remainder of a value is 8 nt
+// halves behind its head.
+CFPP_HD size_t ng_at(int token, int k, int width, int nt)
+{
+    return (size_t)(token >> 3) * width * 16 + (size_t)(k >> 5) * (64 * nt) + ((k >> 3) & 3) * (16 * nt) + (token & 7) * 8 + (k & 7);
+}
+
+struct NarrowParams {
+    Dims dm;
+    PackedLayout lay;
+    const __half *w;        // packed layer
+    __half *kv;             // the layer's cache
+    const int *pos;         // positions of the tokens, device (checked)
+    int n, nt;              // tokens; ng_at's nt
+    // token i appends to the cache of sequence kv_b0 + i * kv_bstep: its own sequence (first of the group, 1), or -
+    // consecutive positions of one prompt - all the same one (b, 0)
+    int kv_b0, kv_bstep;
+    int layer, n_layers;    // position in the fp32 residual ping-pong
+    const __half *x_in;     // [n][h] fp16: input of layer 0
+    __half *out;            // [n][h] fp16: output of the last layer
+    float *xres;            // [n][2][h]
+    float *q;               // [n][h]
+    __half *m, *o;          // planes (ng_at): GELU(up), attention output
+    const float2 *rope;
+    unsigned *sync;
+    int rows, wgs_q;        // matrix rows per workgroup, workgroups of the QKV matrix (set by the launcher)
+};
+
+bool bat_supported(const Dims &dm, int grid, int threads);
+hipError_t launch_bat_in(NarrowParams P, int n_cu, hipStream_t s);
+hipError_t launch_bat_out(NarrowParams P, int n_cu, hipStream_t s);
+hipError_t prepare_narrow_kernels();
+
+}  // namespace cfpp

@@ -14,12 +14,12 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include "prefill_device.h"
+#include "lds_dma.h"
 
 namespace cfpp {
 
 typedef _Float16 pf_f16x8 __attribute__((ext_vector_type(8)));
 typedef float pf_f32x16 __attribute__((ext_vector_type(16)));
-typedef int pf_i32x4 __attribute__((ext_vector_type(4)));
 
 enum { kPfIn = 0, kPfOut = 1 };
 enum { kPfQkv = 0, kPfUp = 1 };                     // what follows the first product
@@ -60,29 +60,6 @@ __device__ __forceinline__ void pf_store(const PfParams &P, int row, int col, fl
 }
 
 // ---------------------------------------------------------------------------
-// 64 lanes x 16 bytes from memory straight into LDS: lane l's piece lands at lds_addr + 16 l.
-// (Counted in vmcnt like any load; the callers wait by count.
-// The row is in the scalar offset, which the resource's range check need not cover: the callers keep it inside, pf_dma_row.)
-// (Winline-asm: M0 is reserved, nothing of the compiler's is kept in it; the clobber orders its own settings of it.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void pf_dma16(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
-}
-// The same for lines that are read once (non-temporal): whole 128-byte lines only.
-__device__ __forceinline__ void pf_dma16_once(pf_i32x4 rsrc, unsigned lds_addr, unsigned voff, unsigned soff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-__device__ __forceinline__ pf_i32x4 pf_rsrc(const __half *p, unsigned bytes)
-{
-    const unsigned long long a = reinterpret_cast<unsigned long long>(p);
-    return pf_i32x4{(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)bytes, 0x00020000};
-}
 // First row of a DMA instruction that takes `group` rows of an operand of `rows`: an instruction of a tile that overhangs
 // the operand brings its last rows instead (what is made of them is never stored), so that no address leaves it.
 // rows: a multiple of 128, group: at most 16
@@ -170,23 +147,23 @@ k_pf_gemm(PfParams P, int splits, int gm)
         const bool second = FL == kPfOut && j >= j_dense;
         const unsigned jj = (unsigned)(second ? j - j_dense : j), width = (unsigned)(second ? f : h), as = second ? as1 : as0;
         const unsigned va = second ? va1 : va0, vw = second ? vw1 : vw0;
-        const pf_i32x4 ra = pf_rsrc(second ? P.m : a_0, second ? abytes1 : abytes0);
-        const pf_i32x4 rw = pf_rsrc(second ? P.w + P.lay.w_down : w_0, second ? wbytes1 : wbytes0);
+        const i32x4 ra = dma_rsrc(second ? P.m : a_0, second ? abytes1 : abytes0);
+        const i32x4 rw = dma_rsrc(second ? P.w + P.lay.w_down : w_0, second ? wbytes1 : wbytes0);
         const unsigned dst = lds0 + (unsigned)stage * (unsigned)STAGE + 1024u * (unsigned)wave;
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
             if (i < i0 || i >= i1) continue;
             if (i < NA) {
                 const int sub = i / NA1, u = (i % NA1) * NWV;
-                pf_dma16(ra, dst + sub * BM * RBA + 1024u * u, va, (unsigned)pf_dma_row(m0 + RUA * (wave + u), P.rows, RUA) * as + (jj * SUB + sub) * 128u);
+                lds_dma16(ra, dst + sub * BM * RBA + 1024u * u, va, (unsigned)pf_dma_row(m0 + RUA * (wave + u), P.rows, RUA) * as + (jj * SUB + sub) * 128u);
             } else {
                 // (where the wavefronts do not divide the rows, the last ones bring the last rows a second time)
                 const unsigned u = (i - NA + 1) * NWV <= BN / RU ? wave + (i - NA) * NWV : min(wave + (i - NA) * NWV, BN / RU - 1);
                 const unsigned at = lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, from = (unsigned)pf_dma_row(n0 + RU * u, N, RU) * width * 2u + jj * RB;
                 // with one token tile the weights are read once; the hint pays where an instruction takes whole lines (BK 64:
                 // 37 tokens, hidden 4096: 130 -> 120 us per layer; on half lines, BK 32, it costs: 72 -> 77 at hidden 2560)
-                if (BK == 64 && mt == 1) pf_dma16_once(rw, at, vw, from);
-                else pf_dma16(rw, at, vw, from);
+                if (BK == 64 && mt == 1) lds_dma16_once(rw, at, vw, from);
+                else lds_dma16(rw, at, vw, from);
             }
         }
     };

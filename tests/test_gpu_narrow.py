@@ -1,0 +1,57 @@
+"""GPU parity of the products for few tokens (csrc/narrow_gemm.hip) where their cut can go wrong: wavefronts with
+unequal shares of K or with none, tiles of 16 rows that are partly there, one row group or eight tiles to a workgroup."""
+import numpy as np
+import pytest
+
+import synth
+from tests.parity import assert_appended_rows, assert_block_close
+from tests.test_gpu_stack import _batched_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(h, d, f, r, layers=2):
+    return synth.ModelShape(h, h // d, d, r, f, n_layers=layers, name=f"d{d}-h{h}-f{f}")
+
+
+# hidden / 64 chunks over 8 wavefronts: 2 (six wavefronts without), 6, 10, 20, 22; rows of a workgroup by tiles of 16:
+# 2 .. 14 (one tile), 18 (two, the second a quarter), 36, 48 (three), 72 (five), 84 (eight)
+@pytest.mark.parametrize("shape,B", [
+    (_shape(128, 64, 128, 16), 1 + 1), (_shape(384, 128, 384, 0), 8), (_shape(640, 80, 2560, 20), 3), (_shape(1280, 80, 5120, 80), 7),
+    (_shape(1408, 128, 4224, 32), 9), (_shape(3072, 128, 3072, 32, 1), 4), (_shape(3072, 64, 12288, 16, 1), 2),
+])
+def test_shares_of_rows_and_columns(orc, shape, B):
+    _batched_case(orc, shape, B, shape.n_layers, synth.seq_lens(5, B, 0, 40))
+
+
+# The statistics come from 16 columns at a time: inputs far from zero mean and with single large values lose nothing
+# (the appended rows are held to the bound of fp32 sums, in which the mean's size enters).
+@pytest.mark.parametrize("shape", [_shape(640, 80, 2560, 20, 1), _shape(1024, 128, 4096, 32, 1)])
+@pytest.mark.parametrize("offset,spike", [(0.0, 0.0), (25.0, 0.0), (-3.0, 900.0)])
+def test_layer_inputs_far_from_zero_mean(orc, shape, offset, spike):
+    from paper_2604_23553_amd.harness import DeviceStack
+    B, S, cap = 5, 9, 10
+    print(f"[case] {shape.name} offset {offset} spike {spike}", flush=True)
+    lens = np.full(B, S, dtype=np.int32)
+    w, (K, V) = synth.layer_weights(shape, 7, 0), synth.kv_cache(shape, 7, 0, lens, cap, B)
+    x = (synth.x_input(shape, 7, B).astype(np.float32) + offset)
+    x[:, 3::517] += spike
+    x = x.astype(np.float16)
+    ds = DeviceStack(shape, cap, B, 1)
+    try:
+        ds.set_options(mode=0)
+        ds.load_layer(0, w)
+        ds.load_kv(0, K, V, lens)
+        ds.set_inputs(x, lens)
+        ds.block_decode(0)
+        ds.check()
+        got = ds.result().copy()
+        for b in range(B):
+            _, taps = orc.block_decode(shape, w, K[b].copy(), V[b].copy(), S, orc.half_to_real(x[b]), taps=True)
+            kg, vg = ds.export_kv(0, b, S, 1)
+            assert_appended_rows(kg[:, 0], vg[:, 0], shape, w, orc.half_to_real(x[b]), taps, f"sequence {b}")
+            if spike == 0.0:
+                ref = orc.block_decode_f16(shape, w, K[b].copy(), V[b].copy(), S, x[b])
+                assert_block_close(got[b], ref, f"sequence {b}")
+    finally:
+        ds.close()
