@@ -43,7 +43,8 @@ cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_
                             cfpp_stream stream);
 
 /* The plan of one pass of cfpp_stack_prefill_gemm over n_tokens <= rows tokens (host
- * arithmetic, no GPU).  plan[0..3]: the first product (QKV, MLP-up), plan[4..7]: the
+ * arithmetic, no GPU) in its tiled products; passes of up to 64 tokens take the narrow
+ * ones instead where they can (cfpp_debug_prefill_narrow).  plan[0..3]: the first product (QKV, MLP-up), plan[4..7]: the
  * second (output projection, MLP-down); of each the tokens, output features and K
  * values of a tile's step and the parts K is split into.  past[0..3]: by how many rows
  * the tiles' loads reach past the activations and the weights of the first product,
@@ -51,10 +52,16 @@ cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_
 cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                     int32_t plan[8], int32_t past[4]);
 
+/* The narrow products of a pass of n_tokens tokens on a device of n_cu CUs (host arithmetic, no
+ * GPU): plan[0] 1 if the pass takes them; plan[1], plan[2] rows and tiles of a workgroup of the
+ * first product, plan[3], plan[4] of the second, plan[5] the parts of the second one's K,
+ * plan[6] the sets of tokens. */
+cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *cfg, int32_t rows, int32_t n_tokens, int32_t n_cu, int32_t plan[7]);
+
 /* Where cfpp_stack_prefill_gemm keeps a layer's intermediates in the caller's scratch, byte
  * offsets: at[0], at[1] gamma_1 x and gamma_2 x, at[3] the attention output, at[4] GELU(up),
  * each as rows of groups of 32 fp16 heads and then their 32 fp16 remainders (value = head +
- * remainder), halves[0] fp16 values from row to row (at[4]: halves[1]); at[2] the rotated
+ * remainder; after a pass through the narrow products in another order), halves[0] fp16 values from row to row (at[4]: halves[1]); at[2] the rotated
  * queries, fp32 [rows][hidden].  After the call they are the last layer's, where the
  * second product's K is in one part (cfpp_debug_prefill_plan); its parts overwrite the queries. */
 cfpp_status cfpp_debug_prefill_scratch(const cfpp_config *cfg, int32_t rows, size_t at[5], int32_t halves[2]);

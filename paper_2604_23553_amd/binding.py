@@ -279,6 +279,14 @@ def cfpp_debug_prefill_plan(cfg: Config, rows: int, n_tokens: int):
     return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
 
 
+def cfpp_debug_prefill_narrow(cfg: Config, rows: int, n_tokens: int, n_cu: int = 256):
+    """None, or (rows, tiles of the first product, rows, tiles, parts of the second, sets of tokens)."""
+    plan = (C.c_int32 * 7)()
+    _check(lib().cfpp_debug_prefill_narrow(C.byref(cfg), C.c_int32(rows), C.c_int32(n_tokens), C.c_int32(n_cu), plan),
+           "cfpp_debug_prefill_narrow")
+    return tuple(plan[1:]) if plan[0] else None
+
+
 def cfpp_debug_prefill_scratch(cfg: Config, rows: int):
     """((offsets of gamma_1 x, gamma_2 x, q, attention output, GELU(up)), (halves per row of hidden, of ffn))."""
     at, halves = (C.c_size_t * 5)(), (C.c_int32 * 2)()

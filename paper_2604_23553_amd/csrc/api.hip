@@ -828,6 +828,7 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         pf_place(P, pl, sc);
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
         pf_plan_pass(P);
+        pf_plan_narrow(P, ctx->n_cu);
         float *xa = reinterpret_cast<float *>(sc + pl.xres), *xb2 = reinterpret_cast<float *>(sc + pl.xnext);
         for (int l = 0; l < L; ++l) {
             P.layer = l;
@@ -1165,6 +1166,25 @@ extern "C" cfpp_status cfpp_debug_prefill_plan(const cfpp_config *c, int32_t row
     pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));    // (a stand-in: only distances are used)
     pf_plan_pass(P);
     pf_describe_plan(P, plan, past);
+    return CFPP_OK;
+}
+
+extern "C" cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *c, int32_t rows, int32_t n_tokens, int32_t n_cu, int32_t plan[7])
+{
+    cfpp_status st = cfpp_validate_config(c);
+    if (st != CFPP_OK) return st;
+    if (!plan) return fail(CFPP_EINVAL, "NULL argument");
+    if (rows <= 0 || rows > kPfMaxRows || rows % kPfTile != 0 || n_tokens <= 0 || n_tokens > rows || n_cu <= 0)
+        return fail(CFPP_EINVAL, "rows %d, n_tokens %d, n_cu %d", rows, n_tokens, n_cu);
+    PfParams P;
+    std::memset(&P, 0, sizeof P);
+    P.dm = dims_of(*c); P.lay = packed_layout(P.dm.h, P.dm.f);
+    if (!pf_supported(P.dm)) return fail(CFPP_EUNSUPPORTED, "a shape without prompt-sized kernels");
+    P.n_rows = n_tokens; P.rows = rows; P.n_layers = c->n_layers;
+    pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));    // (a stand-in: only distances are used)
+    pf_plan_pass(P);
+    std::memset(plan, 0, 7 * sizeof plan[0]);
+    if (pf_plan_narrow(P, n_cu)) pf_describe_narrow(P, plan);
     return CFPP_OK;
 }
 

@@ -4,248 +4,19 @@
 //   k_ng_in  : both LayerNorms, QKV rows + bias, rotary, K/V append, q; MLP-up rows + bias + GELU
 //   k_ng_out : output projection and MLP-down as one product over the concatenated K, + biases + residual
 //
-// A workgroup (8 wavefronts, one to a CU) owns a contiguous range of rows of one matrix and its wavefronts split K: a
-// wavefront streams its columns of all rows, 64 columns (a chunk: whole 128-byte lines) at a time, through an LDS ring of its
-// own that is filled by memory-to-LDS loads.  No wavefront waits for another before the sums are added, no register
-// holds what is in flight, and a row counts for nothing but its own bytes, whatever their number.  Measured with loads alone
-// (one launch, launch included): 92 MB of 17920 x 2560: 15.7 us, 235 MB of 28672 x 4096: 36 us = 6.5 TB/s.
+// How the weights are streamed: narrow_stream.h.
 // Kernel times, 8 sequences, the kernels before (weights through registers, four rows to a load, activations of a
 // workgroup in LDS) -> these: hidden 2560: k_ng_in 28.7 -> 17.5 us, k_ng_out 23.5 -> 15.2 (5 sequences) and 24.7 -> 17.8 (8);
 // hidden 4096: 49.0 -> 39.6, 42.8 -> 32.8.  What is left of k_ng_out beyond its weights (13 us at 2560) is the activations:
 // every workgroup reads all of them from the L2, 8 tokens 410 KB beside 256 KB of weights.
-//
-// v_mfma_f32_16x16x32_f16: A = 16 rows x 32 columns of weights, from the ring; B = the same 32 columns of 8 tokens, the
-// fp16 heads of their fp32 activations in columns 0..7 and the remainders in 8..15 (y = hi + lo to ~2^-22): one
-// instruction per KiB of weights.  The two columns of a token and the 8 wavefronts' parts of K are added in a fixed
-// order at the end: one bit pattern per build.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
-#include "device_utils.h"
-#include "half_split.h"
-#include "lds_dma.h"
-#include "narrow_params.h"
+#include "narrow_stream.h"
 #include "prefill_device.h"
 
 namespace cfpp {
 
-typedef _Float16 ng_f16x8 __attribute__((ext_vector_type(8)));
-
-constexpr int kNgWaves = 8, kNgThreads = 64 * kNgWaves, kNgChunk = 64, kNgTileMax = 8;
-// what the activations are in memory: planes (ng_at), or the layer input itself (fp32 or fp16), which the
-// wavefronts multiply by gamma and split on the way
-enum { kNgPlanes, kNgRaw32, kNgRaw16 };
-
-// chunks [c0, c0 + n) of a workgroup's rows of one matrix, and where their activations are
-struct NgPiece {
-    const void *w, *b;      // first row; activations
-    unsigned row_bytes, b_bytes;
-    int c0, n;
-};
-
-template <int N>
-__device__ __forceinline__ void ng_wait() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-template <int MOST>
-__device__ __forceinline__ void ng_wait_for(int left)      // left <= MOST: a constant where this is expanded
-{
-    if (left == MOST) ng_wait<MOST>();
-    else if constexpr (MOST > 0) ng_wait_for<MOST - 1>(left);
-}
-__device__ __forceinline__ void ng_lds_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-// The stream of one wavefront.  A stage is CH chunks; of each, NB loads bring the activations and 2 T the weights of
-// T tiles of 16 rows (a load: 8 rows x 128 bytes).  Every load of a stage has its place in the ring, and is requested
-// again - for the next stage - as soon as what it brought has been read: NI - 2 or NI - NB loads are always in
-// flight behind the one that is waited for, by count.  Loads without a purpose (rows past the last, chunks past
-// the end) read one line over and over.
-template <int T, int SRC, int CH>
-struct NgStream {
-    static constexpr int NB = SRC == kNgRaw16 ? 1 : 2, PER = NB + 2 * T, NI = CH * PER, kStage = NI * 1024;
-    static_assert(NI <= 62, "the memory counter's range");
-    NgPiece p0, p1;
-    unsigned ring;          // LDS address of this wavefront's ring
-    const char *mem;        // the same as a pointer
-    const char *gamma;      // this wavefront's columns of gamma in LDS (layer input only)
-    int lane, octets, tail; // whole 8-row groups, rows beyond them
-    unsigned v_b, place, a_at;
-    f32x4 acc[T];
-    float mean, m2;         // of the layer input's columns this lane has seen
-
-    __device__ __forceinline__ void issue_b(int i, int ch) const
-    {
-        const bool second = i >= p0.n, live = i < p0.n + p1.n;
-        const int c = second ? p1.c0 + i - p0.n : p0.c0 + i;
-        const i32x4 rs = dma_rsrc(second ? p1.b : p0.b, second ? p1.b_bytes : p0.b_bytes);
-#pragma unroll
-        for (int k = 0; k < NB; ++k)
-            lds_dma16(rs, ring + (unsigned)(ch * PER + k) * 1024u, live ? v_b : 0u, live ? (unsigned)(NB * c + k) * b_step() : 0u);
-    }
-    unsigned b_block;       // planes: bytes of a block of 32 columns
-    __device__ __forceinline__ unsigned b_step() const { return SRC == kNgPlanes ? b_block : 128u; }
-
-    __device__ __forceinline__ void issue_w(int i, int ch, int t) const
-    {
-        const bool second = i >= p0.n, live = i < p0.n + p1.n;
-        const int c = second ? p1.c0 + i - p0.n : p0.c0 + i;
-        const unsigned row_bytes = second ? p1.row_bytes : p0.row_bytes;
-        const i32x4 rs = dma_rsrc(second ? p1.w : p0.w, row_bytes * (unsigned)(8 * octets + tail));
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int o = 2 * t + k;                       // row group; its last rows may not be there
-            const unsigned r = o < octets ? (unsigned)(lane >> 3) : (unsigned)min(lane >> 3, tail - 1);
-            const bool real = live && (o < octets || (o == octets && tail > 0));
-            const unsigned v = r * row_bytes + (place ^ (unsigned)(16 * k));
-            lds_dma16_once(rs, ring + (unsigned)(ch * PER + NB + o) * 1024u, real ? v : 0u, real ? (unsigned)(8 * o) * row_bytes + (unsigned)c * 128u : 0u);
-        }
-    }
-
-    // nt: tokens of a block of planes; n: tokens there are
-    __device__ __forceinline__ void begin(int rows, int n, int nt, unsigned x_stride, int tid)
-    {
-        lane = tid & 63;
-        octets = rows >> 3; tail = rows & 7;
-        // row r of a row group keeps its 16-byte pieces at (piece ^ r ^ (group & 1)): 16 rows' reads of one piece hit all banks
-        place = (unsigned)(((lane & 7) ^ (lane >> 3)) * 16);
-        const int row = lane & 15, kg = lane >> 4;
-        a_at = (unsigned)(NB * 1024 + (row >> 3) * 1024 + (row & 7) * 128 + ((kg ^ (row & 7) ^ (row >> 3)) & 7) * 16);
-        b_block = (unsigned)nt * 128u;
-        if (SRC == kNgPlanes) v_b = (unsigned)((2 * kg + ((lane >> 3) & 1)) * nt + min(lane & 7, nt - 1)) * 16u;
-        else v_b = (unsigned)min(lane >> 3, n - 1) * x_stride + place;     // 128 bytes of every token
-#pragma unroll
-        for (int t = 0; t < T; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        mean = m2 = 0.f;
-        if (p0.n + p1.n > 0) {
-#pragma unroll
-            for (int ch = 0; ch < CH; ++ch) {
-                issue_b(ch, ch);
-#pragma unroll
-                for (int t = 0; t < T; ++t) issue_w(ch, ch, t);
-            }
-        }
-    }
-
-    // this lane's operand: column lane % 16 (head or remainder of token lane % 8), 8 columns of K at 8 (lane / 16), of both
-    // halves of chunk i; of the layer input also its contribution to mean and variance
-    __device__ __forceinline__ void activations(int i, int ch, ng_f16x8 (&b)[2])
-    {
-        const char *at = mem + ch * PER * 1024;
-        if (SRC == kNgPlanes) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) b[k] = *reinterpret_cast<const ng_f16x8 *>(at + k * 1024 + lane * 16);
-            return;
-        }
-        const int token = lane & 7, kg = lane >> 4;
-        float x[16];
-        if (SRC == kNgRaw16) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const u32x4 v = *reinterpret_cast<const u32x4 *>(at + (token * 8 + ((4 * k + kg) ^ token)) * 16);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float2 f = unpack_h2(v[e]);
-                    x[8 * k + 2 * e] = f.x; x[8 * k + 2 * e + 1] = f.y;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(at + k * 1024 + (token * 8 + ((2 * kg + p) ^ token)) * 16);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) x[8 * k + 4 * p + e] = v[e];
-                }
-        }
-        u32x4 g[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) g[k] = *reinterpret_cast<const u32x4 *>(gamma + (8 * i + 4 * k + kg) * 16);
-        ng_lds_read();                                     // the place in the ring is free
-        const bool rest = lane & 8;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float2 gg = unpack_h2(g[j >> 3][(j & 7) >> 1]);
-            const float v = split_value(x[j] * (j & 1 ? gg.y : gg.x));
-            const _Float16 hi = (_Float16)v, lo = (_Float16)(v - (float)hi);
-            b[j >> 3][j & 7] = rest ? lo : hi;
-        }
-        // mean and sum of squared deviations of these 16, joined to those of the 16 i before
-        float s = 0.f, q = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) s += x[j];
-        const float mc = s * 0.0625f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) q = fmaf(x[j] - mc, x[j] - mc, q);
-        const float w = 1.f / (float)(i + 1), dl = mc - mean;
-        mean = fmaf(dl, w, mean);
-        m2 += fmaf(dl * dl, 16.f * (float)i * w, q);
-    }
-
-    template <bool LAST>
-    __device__ __forceinline__ void stage(int i)
-    {
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            const bool live = CH == 1 || i + ch < p0.n + p1.n;             // (uniform)
-            ng_f16x8 b[2];
-            if (LAST) ng_wait_for<NI>(NI - ch * PER - NB);
-            else ng_wait<NI - NB>();
-            if (live) activations(i + ch, ch, b);
-            ng_lds_read();
-            if (!LAST) issue_b(i + CH + ch, ch);
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                if (LAST) ng_wait_for<NI>(NI - ch * PER - NB - 2 * (t + 1));
-                else ng_wait<NI - 2>();
-                const char *at = mem + (ch * PER + 2 * t) * 1024;
-                const ng_f16x8 w0 = *reinterpret_cast<const ng_f16x8 *>(at + a_at), w1 = *reinterpret_cast<const ng_f16x8 *>(at + (a_at ^ 64u));
-                ng_lds_read();
-                if (!LAST) issue_w(i + CH + ch, ch, t);
-                if (live) {
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w0, b[0], acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1, b[1], acc[t], 0, 0, 0);
-                }
-            }
-        }
-    }
-    __device__ __forceinline__ void run()
-    {
-        const int n = p0.n + p1.n;
-        if (n == 0) return;
-        int i = 0;
-        for (; i + CH < n; i += CH) stage<false>(i);
-        stage<true>(i);
-    }
-
-    // the sums of the wavefront's tiles, rows side by side: kNgRedCol floats per column
-    __device__ __forceinline__ void leave(float *red, int wave) const
-    {
-        const int col = lane & 15, r4 = 4 * (lane >> 4);
-#pragma unroll
-        for (int t = 0; t < T; ++t) *reinterpret_cast<f32x4 *>(red + ((wave * T + t) * 16 + col) * 20 + r4) = acc[t];
-    }
-};
-
-// row `row` of the workgroup for token b (of a set): heads' and remainders' columns of the 8 wavefronts, in order
-template <int T>
-__device__ __forceinline__ float ng_total(const float *red, int row, int b)
-{
-    const float *p = red + ((row >> 4) * 16 + b) * 20 + (row & 15);
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < kNgWaves; ++w) s += p[w * T * 320] + p[w * T * 320 + 160];
-    return s;
-}
-template <int T>
-__device__ __forceinline__ float2 ng_total2(const float *red, int row, int b)         // rows row, row + 1 (row even)
-{
-    const float *p = red + ((row >> 4) * 16 + b) * 20 + (row & 15);
-    float2 s{0.f, 0.f};
-#pragma unroll
-    for (int w = 0; w < kNgWaves; ++w) {
-        const float2 h = *reinterpret_cast<const float2 *>(p + w * T * 320), l = *reinterpret_cast<const float2 *>(p + w * T * 320 + 160);
-        s.x += h.x + l.x; s.y += h.y + l.y;
-    }
-    return s;
-}
+constexpr int kNgWaves = 8, kNgThreads = 64 * kNgWaves;
 
 // All positions inside the cache?  (uniform over the grid.)  pos: that of token b.  Scalar loads: a vector load behind the
 // stream's first requests would have to wait for them.
@@ -268,7 +39,7 @@ __device__ __forceinline__ bool ng_positions_ok(const NarrowParams &P, int b, in
 }
 
 template <int T, int SRC>
-constexpr int ng_in_lds() { return kNgWaves * (NgStream<T, SRC, 1>::kStage + 1024 + kNgSet * 8); }
+constexpr int ng_in_lds() { return kNgWaves * (NgStream<T, 1, SRC, 1>::kStage + 1024 + kNgSet * 8); }
 
 // LayerNorms, QKV rows and MLP-up rows.  Workgroups 0 .. wgs_q - 1 have P.rows rows each of the QKV matrix (even: a rotary
 // pair stays in one), the others of the MLP-up matrix: a workgroup needs one LayerNorm's input.  The statistics are not waited
@@ -280,7 +51,7 @@ constexpr int ng_in_lds() { return kNgWaves * (NgStream<T, SRC, 1>::kStage + 102
 template <int T, int SRC>
 __global__ void __launch_bounds__(kNgThreads, 2) k_ng_in(NarrowParams P)
 {
-    using Stream = NgStream<T, SRC, 1>;
+    using Stream = NgStream<T, 1, SRC, 1>;
     extern __shared__ __align__(16) char ng_lds[];
     const Dims &dm = P.dm;
     const int h = dm.h, f = dm.f, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -330,7 +101,7 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_in(NarrowParams P)
     }
     __syncthreads();                                       // the rings have been read
     float *red = reinterpret_cast<float *>(ng_lds);
-    st.leave(red, wave);
+    st.template leave<1>(red, wave, 0);
     __syncthreads();
     if (!ok || b >= P.n) return;
     float mean = 0.f, m2 = 0.f;
@@ -351,7 +122,7 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_in(NarrowParams P)
             if (rr < rn) {
                 const float2 k = j ? k1 : k0;
                 __half hi, lo;
-                split_half(pf_gelu((ng_total<T>(red, rr, b) - mean * k.x) * inv + k.y, dm.flags), hi, lo);
+                split_half(pf_gelu((ng_total<kNgWaves>(red, Stream::kSetFloats, rr, b) - mean * k.x) * inv + k.y, dm.flags), hi, lo);
                 const size_t at = ng_at(b, r0 + rr, f, P.nt);
                 P.m[at] = hi; P.m[at + 8 * P.nt] = lo;
             }
@@ -359,7 +130,7 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_in(NarrowParams P)
         return;
     }
     if (2 * row >= rn) return;
-    const float2 s = ng_total2<T>(red, 2 * row, b);
+    const float2 s = ng_total2<kNgWaves>(red, Stream::kSetFloats, 2 * row, b);
     float v0 = (s.x - mean * k0.x) * inv + k0.y, v1 = (s.y - mean * k1.x) * inv + k1.y;
     int d0 = i, d1 = i + 1;
     if (rot) {
@@ -379,10 +150,10 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_in(NarrowParams P)
 // Output projection and MLP-down as one product over the concatenated K ([attention | GELU(up)] . [W_dense | W_down]^T),
 // + biases + residual.  A workgroup has at most 16 rows; a wavefront an eighth of the K values.
 constexpr int kNgOutChunks = 3;
-constexpr int ng_out_lds() { return kNgWaves * NgStream<1, kNgPlanes, kNgOutChunks>::kStage; }
+constexpr int ng_out_lds() { return kNgWaves * NgStream<1, 1, kNgPlanes, kNgOutChunks>::kStage; }
 __global__ void __launch_bounds__(kNgThreads, 2) k_ng_out(NarrowParams P)
 {
-    using Stream = NgStream<1, kNgPlanes, kNgOutChunks>;
+    using Stream = NgStream<1, 1, kNgPlanes, kNgOutChunks>;
     extern __shared__ __align__(16) char ng_lds[];
     const Dims &dm = P.dm;
     const int h = dm.h, f = dm.f, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -409,28 +180,16 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_out(NarrowParams P)
     st.run();
     __syncthreads();
     float *red = reinterpret_cast<float *>(ng_lds);
-    st.leave(red, wave);
+    st.leave<1>(red, wave, 0);
     __syncthreads();
     if (!ok || b >= P.n || (tid >> 3) >= rn) return;
     const float x = P.layer == 0 ? __half2float(x16) : x32;
-    const float res = x + ((ng_total<1>(red, row, b) + __half2float(de)) + __half2float(dn));
+    const float res = x + ((ng_total<kNgWaves>(red, Stream::kSetFloats, row, b) + __half2float(de)) + __half2float(dn));
     if (P.layer == P.n_layers - 1) P.out[(size_t)b * h + r0 + row] = __float2half_rn(res);
     else P.xres[((size_t)b * 2 + (P.layer & 1)) * h + r0 + row] = res;
 }
 
 // ---------------------------------------------------------------------------
-// Rows of a workgroup such that the workgroups of both matrices come to at most one (or, where that would be more
-// than kNgTileMax tiles of 16, a few) per CU; even.
-static int ng_in_rows(const Dims &dm, int n_cu, int *wgs_q, int *wgs)
-{
-    for (int per = 1;; ++per) {
-        for (int rows = 2; rows <= 16 * kNgTileMax; rows += 2) {
-            const int q = (3 * dm.h + rows - 1) / rows, u = (dm.f + rows - 1) / rows;
-            if (q + u <= per * n_cu) { *wgs_q = q; *wgs = q + u; return rows; }
-        }
-    }
-}
-
 // Shapes and launch options that run the batched path.  (The bounds on rows per workgroup and on LDS are those of the
 // grid that the option names; the kernels here choose their own.)
 bool bat_supported(const Dims &dm, int grid, int threads)

@@ -5,6 +5,7 @@
 #include "device_utils.h"
 #include "half_split.h"
 #include "prefill_params.h"
+#include "narrow_params.h"
 
 namespace cfpp {
 
@@ -61,5 +62,11 @@ __device__ __forceinline__ size_t pf_at(int row, int k, int width)
 {
     return (size_t)row * pf_row_halves(width) + (k >> 5) * 64 + (k & 31);
 }
+// The same in the order that the pass's products read, and the distance of the remainder.
+__device__ __forceinline__ size_t pf_out_at(const PfParams &P, int row, int k, int width)
+{
+    return P.nrw.on ? ng_at(row, k, width, kNgSet) : pf_at(row, k, width);
+}
+__device__ __forceinline__ int pf_out_lo(const PfParams &P) { return P.nrw.on ? 8 * kNgSet : kPfLo; }
 
 }  // namespace cfpp

@@ -32,21 +32,27 @@ namespace cfpp {
 // are added in order, biases and residual follow, and the row goes to the residual stream (and, as
 // the last layer's output, to out) on the way: one launch where the sum and the LayerNorm were two
 // (512 tokens of the 2560-wide shape: 10.1 + 10.2 us).  Bound by the latency of a row's loads and
-// stores, hence four wavefronts to a row instead of one.
-constexpr int kPfRowVec = 4;           // float4 per thread: hidden <= 4096
-template <bool FROM_PARTS>
-__global__ void __launch_bounds__(256) k_pf_row(PfParams P)
+// stores, hence four or sixteen wavefronts to a row.
+// With few tokens there is one row to a CU and what counts is how many trips to memory follow one another: 1024 threads
+// to a row, one float4 each, all its parts in flight together (37 tokens of hidden 2560, 8 parts: 7.8 us with 256
+// threads, 5.6; 128 tokens, whole layer: 106.1, 104.0).  Up to kPfRowWide tokens; from about 1000 on 256 threads are faster (hidden
+// 512, 1000 tokens, layer: 51.3 against 53.0), in between the two are within 1 % of a layer.
+constexpr int kPfRowVec = 4;           // float4 per thread of 256: hidden <= 4096
+constexpr int kPfRowWide = 256;
+template <bool FROM_PARTS, int NT>
+__global__ void __launch_bounds__(NT) k_pf_row(PfParams P)
 {
-    __shared__ float red[2][4];
+    constexpr int VEC = 1024 / NT, NW = NT / 64;
+    __shared__ float red[2][NW];
     const Dims &dm = P.dm;
     const int h = dm.h, nv = h >> 2, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = blockIdx.x;
     const bool last = FROM_PARTS && P.layer == P.n_layers - 1, bare = last || (FROM_PARTS && !P.row_fused);   // bare: no LayerNorm here
     const __half *wn = FROM_PARTS ? P.w_next : P.w;        // the layer whose LayerNorms these are
-    f32x4 x[kPfRowVec];
-    uint2 g1[kPfRowVec], g2[kPfRowVec];
+    f32x4 x[VEC];
+    uint2 g1[VEC], g2[VEC];
 #pragma unroll
-    for (int j = 0; j < kPfRowVec; ++j) {
-        const int g = tid + 256 * j;
+    for (int j = 0; j < VEC; ++j) {
+        const int g = tid + NT * j;
         x[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (g >= nv) continue;
         const size_t at = (size_t)row * h + 4 * g;
@@ -61,12 +67,13 @@ __global__ void __launch_bounds__(256) k_pf_row(PfParams P)
             const uint2 de = *reinterpret_cast<const uint2 *>(P.w + P.lay.b_dense + 4 * g), dn = *reinterpret_cast<const uint2 *>(P.w + P.lay.b_down + 4 * g);
             f32x4 s = *as_global(reinterpret_cast<const f32x4 *>(p));
             const int splits = P.plan_out.splits;
-            for (int z = 1; z < splits; z += 5) {          // five parts requested at a time (past the last: the last again)
-                f32x4 t[5];
+            constexpr int AT = NT == 1024 ? 9 : 5;         // parts requested at a time (past the last: the last again)
+            for (int z = 1; z < splits; z += AT) {
+                f32x4 t[AT];
 #pragma unroll
-                for (int u = 0; u < 5; ++u) t[u] = *as_global(reinterpret_cast<const f32x4 *>(p + min(z + u, splits - 1) * zstride));
+                for (int u = 0; u < AT; ++u) t[u] = *as_global(reinterpret_cast<const f32x4 *>(p + min(z + u, splits - 1) * zstride));
 #pragma unroll
-                for (int u = 0; u < 5; ++u)
+                for (int u = 0; u < AT; ++u)
                     if (z + u < splits) s += t[u];
             }
             const float2 de0 = unpack_h2(de.x), de1 = unpack_h2(de.y), dn0 = unpack_h2(dn.x), dn1 = unpack_h2(dn.y);
@@ -93,15 +100,18 @@ __global__ void __launch_bounds__(256) k_pf_row(PfParams P)
     if (bare) return;                                      // (uniform)
     float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < kPfRowVec; ++j) s += (x[j][0] + x[j][1]) + (x[j][2] + x[j][3]);
+    for (int j = 0; j < VEC; ++j) s += (x[j][0] + x[j][1]) + (x[j][2] + x[j][3]);
     s = wave_sum(s);
     if (lane == 0) red[0][wave] = s;
     __syncthreads();
-    const float mean = ((red[0][0] + red[0][1]) + (red[0][2] + red[0][3])) / (float)h;
+    float total = red[0][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) total += red[0][w];
+    const float mean = total / (float)h;
     float q = 0.f;
 #pragma unroll
-    for (int j = 0; j < kPfRowVec; ++j) {
-        if (tid + 256 * j < nv) {
+    for (int j = 0; j < VEC; ++j) {
+        if (tid + NT * j < nv) {
             const f32x4 dl = x[j] - mean;
             q += (dl[0] * dl[0] + dl[1] * dl[1]) + (dl[2] * dl[2] + dl[3] * dl[3]);
         }
@@ -109,8 +119,8 @@ __global__ void __launch_bounds__(256) k_pf_row(PfParams P)
     q = wave_sum(q);
     if (lane == 0) red[1][wave] = q;
 #pragma unroll
-    for (int j = 0; j < kPfRowVec; ++j) {
-        const int g = tid + 256 * j;
+    for (int j = 0; j < VEC; ++j) {
+        const int g = tid + NT * j;
         if (g >= nv) continue;
         const float2 a1 = unpack_h2(g1[j].x), b1 = unpack_h2(g1[j].y), a2 = unpack_h2(g2[j].x), b2 = unpack_h2(g2[j].y);
         const float ga[4] = {a1.x, a1.y, b1.x, b1.y}, gb[4] = {a2.x, a2.y, b2.x, b2.y};
@@ -120,14 +130,19 @@ __global__ void __launch_bounds__(256) k_pf_row(PfParams P)
             split_half(x[j][e] * ga[e], h1[e], l1[e]);
             split_half(x[j][e] * gb[e], h2[e], l2[e]);
         }
-        const size_t at = pf_at(row, 4 * g, h);
+        const size_t at = pf_out_at(P, row, 4 * g, h), al = at + pf_out_lo(P);
         *reinterpret_cast<uint2 *>(P.y1 + at) = *reinterpret_cast<const uint2 *>(h1);
-        *reinterpret_cast<uint2 *>(P.y1 + at + kPfLo) = *reinterpret_cast<const uint2 *>(l1);
+        *reinterpret_cast<uint2 *>(P.y1 + al) = *reinterpret_cast<const uint2 *>(l1);
         *reinterpret_cast<uint2 *>(P.y2 + at) = *reinterpret_cast<const uint2 *>(h2);
-        *reinterpret_cast<uint2 *>(P.y2 + at + kPfLo) = *reinterpret_cast<const uint2 *>(l2);
+        *reinterpret_cast<uint2 *>(P.y2 + al) = *reinterpret_cast<const uint2 *>(l2);
     }
     __syncthreads();
-    if (tid == 0) P.stats[row] = float2{mean, 1.0f / sqrtf(((red[1][0] + red[1][1]) + (red[1][2] + red[1][3])) / (float)h + dm.ln_eps)};
+    if (tid == 0) {
+        float sq = red[1][0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sq += red[1][w];
+        P.stats[row] = float2{mean, 1.0f / sqrtf(sq / (float)h + dm.ln_eps)};
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -238,8 +253,8 @@ __device__ __forceinline__ void pf_attn_alone(const PfParams &P, const __half *K
         if (lane + 64 * e >= D) continue;
         __half hi, lo;
         split_half(o[e] / l, hi, lo);
-        const size_t to = pf_at(row, head * D + lane + 64 * e, dm.h);
-        P.o[to] = hi; P.o[to + kPfLo] = lo;
+        const size_t to = pf_out_at(P, row, head * D + lane + 64 * e, dm.h);
+        P.o[to] = hi; P.o[to + pf_out_lo(P)] = lo;
     }
 }
 
@@ -406,9 +421,9 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
             split_half(va, hi[j], lo[j]);
             split_half(vb, hi[4 + j], lo[4 + j]);
         }
-        const size_t at = pf_at(q0 + q, head * D + c8, dm.h);
+        const size_t at = pf_out_at(P, q0 + q, head * D + c8, dm.h);
         *reinterpret_cast<u32x4 *>(P.o + at) = *reinterpret_cast<const u32x4 *>(hi);
-        *reinterpret_cast<u32x4 *>(P.o + at + kPfLo) = *reinterpret_cast<const u32x4 *>(lo);
+        *reinterpret_cast<u32x4 *>(P.o + at + pf_out_lo(P)) = *reinterpret_cast<const u32x4 *>(lo);
         if (!finite) { sBad[q] = 1; sEnd[0] = 1; }
     }
     // A masked key's weight is zero, and zero times an infinite or NaN V row of a later token of this block is NaN: such
@@ -459,12 +474,19 @@ static void pf_attention(const PfParams &P, hipStream_t s)
     else if constexpr (D != 128) hipLaunchKernelGGL((k_pf_attn<D, 1>), grid, dim3(256), 0, s, P);
 }
 
+template <bool FROM_PARTS>
+static void pf_rows(const PfParams &P, hipStream_t s)
+{
+    if (P.n_rows <= kPfRowWide) hipLaunchKernelGGL((k_pf_row<FROM_PARTS, 1024>), dim3(P.n_rows), dim3(1024), 0, s, P);
+    else hipLaunchKernelGGL((k_pf_row<FROM_PARTS, 256>), dim3(P.n_rows), dim3(256), 0, s, P);
+}
+
 hipError_t launch_pf_layer(const PfParams &P, hipStream_t s)
 {
     const Dims &dm = P.dm;
     // (else the previous layer's last launch has left this one's input ready)
-    if (P.layer == 0 || !P.row_fused) hipLaunchKernelGGL(k_pf_row<false>, dim3(P.n_rows), dim3(256), 0, s, P);
-    hipError_t e = launch_pf_gemm_in(P, s);
+    if (P.layer == 0 || !P.row_fused) pf_rows<false>(P, s);
+    hipError_t e = P.nrw.on ? launch_pf_narrow_in(P, s) : launch_pf_gemm_in(P, s);
     if (e != hipSuccess) return e;
     switch (dm.d) {
     case 64: pf_attention<64>(P, s); break;
@@ -472,9 +494,9 @@ hipError_t launch_pf_layer(const PfParams &P, hipStream_t s)
     case 128: pf_attention<128>(P, s); break;
     default: return hipErrorInvalidValue;
     }
-    e = launch_pf_gemm_out(P, s);
+    e = P.nrw.on ? launch_pf_narrow_out(P, s) : launch_pf_gemm_out(P, s);
     if (e != hipSuccess) return e;
-    if (P.plan_out.splits > 1) hipLaunchKernelGGL(k_pf_row<true>, dim3(P.n_rows), dim3(256), 0, s, P);
+    if (P.plan_out.splits > 1 || P.nrw.on) pf_rows<true>(P, s);
     return hipGetLastError();
 }
 

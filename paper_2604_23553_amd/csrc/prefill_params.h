@@ -52,6 +52,15 @@ CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
 constexpr int kPfTileKinds = 10;
 struct PfPlan { int tile, splits; };
 
+// Passes of up to this many tokens may take the narrow products (prefill_narrow.hip); the activations that feed a
+// product are then in their order (ng_at with room for 8 tokens a block) instead of pf_at's.
+constexpr int kPfNarrowMax = 64;
+struct PfNarrow {
+    bool on;
+    int rows_in, wgs_q, wgs_in;     // first product: rows of a workgroup, workgroups of the QKV matrix and in all
+    int rows_out;                   // second product: rows of a workgroup (parts of K: plan_out.splits)
+};
+
 struct PfParams {
     Dims dm;
     PackedLayout lay;
@@ -73,6 +82,7 @@ struct PfParams {
     float *part_out;        // parts of the second one, part_out_bytes
     size_t part_bytes, part_out_bytes, part_out_stride;     // (stride: floats between the second product's parts)
     PfPlan plan_in, plan_out;
+    PfNarrow nrw;
     bool row_fused;         // the kernel that adds the second product's parts prepares the next layer's input too
     const float2 *rope;
 };
@@ -102,5 +112,10 @@ hipError_t launch_pf_layer(const PfParams &P, hipStream_t s);
 // its products (prefill_gemm.hip): QKV and MLP-up; output projection and MLP-down
 hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s);
 hipError_t launch_pf_gemm_out(const PfParams &P, hipStream_t s);
+// The narrow products (prefill_narrow.hip).  pf_plan_narrow: behind pf_plan_pass; true, and P for them, if the pass takes them.
+bool pf_plan_narrow(PfParams &P, int n_cu);
+void pf_describe_narrow(const PfParams &P, int plan[7]);   // (profiling library: cfpp_debug_prefill_narrow)
+hipError_t launch_pf_narrow_in(const PfParams &P, hipStream_t s);
+hipError_t launch_pf_narrow_out(const PfParams &P, hipStream_t s);
 
 }  // namespace cfpp

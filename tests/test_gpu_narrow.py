@@ -55,3 +55,30 @@ def test_layer_inputs_far_from_zero_mean(orc, shape, offset, spike):
                 assert_block_close(got[b], ref, f"sequence {b}")
     finally:
         ds.close()
+
+
+# A short prompt's products: sets of 1 .. 6 and 8 tokens' eights (7 runs as 8), the last one partly there, with 1, 2, 3, 5 and 8
+# tiles; K of the second product in unequal parts; pairs of rows over the ends of items.  Over two layers, every token against the oracle.
+@pytest.mark.parametrize("shape,T", [
+    (_shape(128, 64, 128, 16), 9), (_shape(384, 128, 896, 0), 64), (_shape(512, 64, 2048, 16), 31), (_shape(512, 64, 2048, 64), 50),
+    (_shape(640, 80, 2560, 20), 1), (_shape(640, 80, 2560, 20), 48), (_shape(1280, 80, 5120, 20), 17), (_shape(1280, 80, 5120, 20), 64),
+    (_shape(1408, 128, 4224, 32), 40), (_shape(2560, 80, 10240, 20), 8), (_shape(2560, 80, 10240, 20), 37),
+    (_shape(2560, 80, 10240, 20), 57), (_shape(3072, 64, 12288, 16), 3), (_shape(3072, 128, 12288, 32), 26), (_shape(3072, 128, 12288, 32), 45),
+])
+def test_short_prompts(orc, shape, T):
+    import paper_2604_23553_amd as cf
+    from tests.test_gpu_prefill import _check_prompt
+    with cf.profile_build():
+        assert cf.cfpp_debug_prefill_narrow(cf.Config.from_shape(shape, 16), 128, T)
+    _check_prompt(orc, shape, 29, 5, T, 2, 1, then_decode=False, gemm_rows=128, row_check_every=7)
+
+
+# The tiled products of few tokens, where the narrow ones do not go: an MLP of more than 128 rows to a CU.
+@pytest.mark.parametrize("T", [20, 40, 64])
+def test_short_prompts_in_tiles(orc, T):
+    import paper_2604_23553_amd as cf
+    from tests.test_gpu_prefill import _check_prompt
+    shape = _shape(512, 64, 32768, 16)
+    with cf.profile_build():
+        assert cf.cfpp_debug_prefill_narrow(cf.Config.from_shape(shape, 16), 128, T) is None
+    _check_prompt(orc, shape, 31, 3, T, 1, 0, then_decode=False, gemm_rows=128, row_check_every=9)
