@@ -172,12 +172,13 @@ void cfpp_destroy(cfpp_ctx *ctx);
  * cfpp_device_error).  Calls of one context, and of contexts sharing a GPU,
  * belong on one stream. */
 #define CFPP_OPT_MODE     1  /* CFPP_MODE_AUTO (the default): the fastest mode
-                                that supports the call - the whole-stack kernel
-                                (2) for a stack step and for a block of hidden
-                                size >= 2048 when the shape and the device allow
-                                it, the batched projections (0) for several
-                                sequences, else the phase kernels (0); never
-                                refuses a call for the mode's sake;
+                                that supports the call - the batched path's
+                                three kernels (0) for several sequences, for a
+                                block on its own and for a stack step of hidden
+                                size < 2048, the whole-stack kernel (2) for a
+                                stack step of hidden size >= 2048, when the shape
+                                and the device allow it, else the phase kernels
+                                (0); never refuses a call for the mode's sake;
                                 0: one kernel per phase (3 per block);
                                 1: one persistent kernel per block;
                                 2: one fused persistent kernel for the whole
@@ -220,8 +221,8 @@ cfpp_status cfpp_block_decode(cfpp_ctx *ctx, const void *packed_layer, void *kv_
 /* cfpp_block_decode for callers that cannot allocate device memory or keep a
  * context: code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation.  It takes the configuration instead of a context and runs
- * the same step with the phase kernels (launch mode 0; several sequences: the
- * batched projections) on a workspace that is a fixed 16 MiB array in the
+ * the same step with the batched path's kernels (where the shape has none: the
+ * phase kernels) on a workspace that is a fixed 16 MiB array in the
  * library's device image - no hipMalloc/hipFree, no workspace argument, nothing
  * to create or destroy.  Inputs and outputs are the caller's, as above.
  *   - CFPP_ENOMEM when cfpp_workspace_bytes(cfg) exceeds the 16 MiB (it grows

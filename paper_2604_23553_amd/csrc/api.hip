@@ -481,9 +481,12 @@ static bool batched_path_shape(const cfpp_ctx *ctx, const Shape &sh)
 {
     return !(ctx->dm.flags & kFlagSequentialResidual) && bat_supported(ctx->dm, sh.grid, sh.threads);
 }
-static bool batched_path(const cfpp_ctx *ctx, const Shape &sh, int batch)
+// A single sequence takes it too where nothing asks for another mode or launch shape.  Measured, us a block, phase
+// kernels (whole-stack kernel from hidden 2048) -> narrow products, 20 .. 8000 positions: hidden 512 20.4 .. 29.9 -> 16.3 .. 20.0,
+// 1280 33.2 .. 43.4 -> 21.9 .. 30.0, 2560 42.0 .. 52.0 -> 36.2 .. 48.8, 4096 77.8 .. 95.0 -> 70.5 .. 91.8.
+static bool batched_path(const cfpp_ctx *ctx, const Shape &sh, int batch, bool single)
 {
-    return batch > 1 && batched_path_shape(ctx, sh);
+    return (batch > 1 || single) && batched_path_shape(ctx, sh);
 }
 
 // kv_seq < 0: row i of x / pos / out is sequence i with its own cache (a decode step of
@@ -571,24 +574,30 @@ static cfpp_status check_io(const cfpp_ctx *ctx, const void *x, const int32_t *p
 
 // The launch mode a call runs in.  An explicit mode is checked and refused when
 // the shape has no kernel in it; CFPP_MODE_AUTO takes the fastest mode that
-// supports the call and never refuses: several sequences -> the batched
-// projections (mode 0); the whole-stack kernel where its shape limits and the
-// residency check allow it (a step of several layers always, a block on its own - or
-// a one-layer stack - from hidden 2048 on: below that a block is a handful of
-// dependent hand-overs with nothing to stream behind them and the three phase
-// kernels are quicker); else the phase kernels.
+// supports the call and never refuses: the batched path (mode 0 with *narrow_out) for several
+// sequences, for a block on its own and for a step of several layers of hidden sizes below 2048; the
+// whole-stack kernel, where its shape limits and the residency check allow it, for a step of several
+// layers from hidden 2048 on (a layer, batched path against it, at 20 / 4000 positions: hidden 2048 29.8 / 36.8
+// against 28.9 / 33.1 us, 2560 36.4 / 45.0 against 32.7 / 37.0; below it hidden 1536 21.3 / 27.4 against 23.4 / 29.8,
+// 1024 17.7 / 24.1 against 22.1 / 27.5); else the phase kernels.  An explicit grid keeps a single
+// sequence with the kernels that follow it.
 static cfpp_status resolve_mode(cfpp_ctx *ctx, const Shape &sh, const StepParams &P, int batch, bool stack,
-                                int *mode_out)
+                                int *mode_out, bool *narrow_out)
 {
     int mode = ctx->mode;
+    *narrow_out = batch > 1;
     if (mode == CFPP_MODE_AUTO) {
         mode = 0;
-        const bool one_by_one = batch == 1 || !batched_path_shape(ctx, sh);
-        if (one_by_one && ((stack && ctx->cfg.n_layers > 1) || ctx->dm.h >= 2048)) {
-            g_err_hold hold;                               // a refusal here is not the caller's error
-            if (check_fused(ctx, sh, P) == CFPP_OK) mode = 2;
+        const bool shape_ok = batched_path_shape(ctx, sh), layers = stack && ctx->cfg.n_layers > 1;
+        const bool narrow = shape_ok && (batch > 1 || ctx->grid == 0);
+        if (batch == 1 || !shape_ok) {
+            if (narrow ? layers && ctx->dm.h >= 2048 : layers || ctx->dm.h >= 2048) {
+                g_err_hold hold;                           // a refusal here is not the caller's error
+                if (check_fused(ctx, sh, P) == CFPP_OK) mode = 2;
+            }
         }
         *mode_out = mode;
+        *narrow_out = mode == 0 && narrow;
         return CFPP_OK;
     }
     *mode_out = mode;
@@ -618,7 +627,7 @@ static bool capturing(hipStream_t s)
     return cs != hipStreamCaptureStatusNone;
 }
 
-// phases_only: run the phase kernels (launch mode 0) whatever the context's mode says
+// phases_only: the batched path, or the phase kernels (launch mode 0), whatever the context's mode says
 static cfpp_status block_decode(cfpp_ctx *ctx, const void *packed_layer, void *kv_layer, const void *x,
                                 const int32_t *pos_dev, int32_t batch, void *out, cfpp_stream stream,
                                 bool phases_only)
@@ -633,13 +642,14 @@ static cfpp_status block_decode(cfpp_ctx *ctx, const void *packed_layer, void *k
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool seq = ctx->dm.flags & kFlagSequentialResidual;
     int mode = 0;
+    bool narrow = true;
     if (!phases_only &&
-        (st = resolve_mode(ctx, sh, make_params(ctx, sh, 0, x, pos_dev, out, 1), batch, false, &mode)) != CFPP_OK)
+        (st = resolve_mode(ctx, sh, make_params(ctx, sh, 0, x, pos_dev, out, 1), batch, false, &mode, &narrow)) != CFPP_OK)
         return st;
     const __half *w = static_cast<const __half *>(packed_layer);
     __half *kv = static_cast<__half *>(kv_layer);
-    ctx->planes = mode == 0 && batched_path(ctx, sh, batch) ? batch : 0;
-    if (mode == 0 && batched_path(ctx, sh, batch)) return launch_batched_layer(ctx, sh, w, kv, 0, 1, x, pos_dev, batch, out, s);
+    ctx->planes = mode == 0 && batched_path(ctx, sh, batch, narrow) ? batch : 0;
+    if (ctx->planes > 0) return launch_batched_layer(ctx, sh, w, kv, 0, 1, x, pos_dev, batch, out, s);
     if (mode == 2 && !capturing(s) && (st = account_epochs(ctx, 2ull * batch)) != CFPP_OK) return st;
     for (int b = 0; b < batch; ++b) {
         StepParams P = make_params(ctx, sh, b, x, pos_dev, out, mode != 2 && seq ? 2 : 1);
@@ -679,7 +689,8 @@ static cfpp_status enqueue_stack(cfpp_ctx *ctx, const void *const *packed_layers
     Shape sh;
     if ((st = launch_shape(ctx, &sh)) != CFPP_OK) return st;
     int mode = 0;
-    if ((st = resolve_mode(ctx, sh, make_params(ctx, sh, 0, x, pos_dev, out, L), batch, true, &mode)) != CFPP_OK)
+    bool narrow = false;
+    if ((st = resolve_mode(ctx, sh, make_params(ctx, sh, 0, x, pos_dev, out, L), batch, true, &mode, &narrow)) != CFPP_OK)
         return st;
     LayerPtrs ptrs;
     std::memset(&ptrs, 0, sizeof ptrs);
@@ -691,8 +702,8 @@ static cfpp_status enqueue_stack(cfpp_ctx *ctx, const void *const *packed_layers
     if (store_table && mode == 2) HIP_OK(launch_store_layer_ptrs(ptrs, dev_ptrs, L, s));
     if (epochs) *epochs = mode == 2 ? (unsigned long long)(L + 1) * batch : 0;
     if (!launch) return CFPP_OK;
-    ctx->planes = mode == 0 && batched_path(ctx, sh, batch) ? batch : 0;
-    if (mode == 0 && batched_path(ctx, sh, batch)) {
+    ctx->planes = mode == 0 && batched_path(ctx, sh, batch, narrow) ? batch : 0;
+    if (ctx->planes > 0) {
         for (int l = 0; l < L; ++l)
             if ((st = launch_batched_layer(ctx, sh, ptrs.w[l], ptrs.kv[l], l, L, x, pos_dev, batch, out, s)) != CFPP_OK)
                 return st;

@@ -82,3 +82,40 @@ def test_short_prompts_in_tiles(orc, T):
     with cf.profile_build():
         assert cf.cfpp_debug_prefill_narrow(cf.Config.from_shape(shape, 16), 128, T) is None
     _check_prompt(orc, shape, 31, 3, T, 1, 0, then_decode=False, gemm_rows=128, row_check_every=9)
+
+
+# A sequence on its own takes the same products (a block at any size, a stack below hidden 2048): against the oracle, and the
+# same bits as beside a second one (short contexts: every head is one piece whatever the group).
+@pytest.mark.parametrize("shape,S", [
+    (_shape(128, 64, 128, 16), 0), (_shape(512, 64, 2048, 16), 128), (_shape(640, 80, 2560, 20), 33), (_shape(1536, 64, 6144, 16), 700),
+    (_shape(1792, 128, 7168, 32), 64), (_shape(2560, 80, 10240, 20, 1), 1000), (_shape(4096, 128, 16384, 32, 1), 17),
+])
+def test_a_single_sequence(orc, shape, S):
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] single sequence {shape.name} S={S}", flush=True)
+    L, outs = shape.n_layers, []
+    ws = [synth.layer_weights(shape, 9, l) for l in range(L)]
+    x = synth.x_input(shape, 9, 2)
+    for B in (1, 2):
+        lens = np.full(B, S, dtype=np.int32)
+        kvs = [synth.kv_cache(shape, 9, l, lens, S + 1, B) for l in range(L)]
+        ds = DeviceStack(shape, S + 1, B, L)
+        try:
+            for l in range(L):
+                ds.load_layer(l, ws[l])
+                ds.load_kv(l, kvs[l][0], kvs[l][1], lens)
+            ds.set_inputs(x[:B], lens)
+            if L == 1:
+                ds.block_decode(0)
+            else:
+                ds.stack_decode()
+            ds.check()
+            outs.append(ds.result().copy())
+            if B == 1:
+                Ks, Vs = [kv[0][0].copy() for kv in kvs], [kv[1][0].copy() for kv in kvs]
+                want, _ = orc.stack_decode(shape, ws, Ks, Vs, S, x[0])
+                assert_block_close(outs[0][0], want, shape.name)
+        finally:
+            ds.close()
+    if S <= 512:
+        assert np.array_equal(outs[0][0].view(np.uint16), outs[1][0].view(np.uint16))
