@@ -258,8 +258,63 @@ __device__ __forceinline__ void pf_attn_alone(const PfParams &P, const __half *K
     }
 }
 
-template <int D, int QW>
-__global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
+// The end of a block of 32 QW queries of a head (256 threads): `sums` gives a query's unnormalised sums of 8 dimensions and
+// its weight; the outputs go to the planes.
+template <int D, int QW, class Sums>
+__device__ __forceinline__ void pf_attn_finish(const PfParams &P, const __half *Kc, const __half *Vc, int head, int q0, int last_pos, int tid, Sums sums)
+{
+    __shared__ int sBad[32 * QW], sEnd[3];                 // queries whose output is not finite; any; the positions of pf_attn_alone's rule
+    const Dims &dm = P.dm;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 32 * QW) sBad[tid] = 0;
+    if (tid == 0) { sEnd[0] = 0; sEnd[1] = -1; sEnd[2] = 0x7fffffff; }
+    __syncthreads();
+    for (int e = tid; e < 32 * QW * (D / 8); e += 256) {
+        const int q = e / (D / 8), c8 = 8 * (e - q * (D / 8));
+        if (q0 + q >= P.n_rows) continue;
+        f32x4 v[2];
+        const float l = sums(q, c8, v);
+        __half hi[8], lo[8];
+        bool finite = true;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float va = v[0][j] / l, vb = v[1][j] / l;
+            finite = finite && fabsf(va) < INFINITY && fabsf(vb) < INFINITY;
+            split_half(va, hi[j], lo[j]);
+            split_half(vb, hi[4 + j], lo[4 + j]);
+        }
+        const size_t at = pf_out_at(P, q0 + q, head * D + c8, dm.h);
+        *reinterpret_cast<u32x4 *>(P.o + at) = *reinterpret_cast<const u32x4 *>(hi);
+        *reinterpret_cast<u32x4 *>(P.o + at + pf_out_lo(P)) = *reinterpret_cast<const u32x4 *>(lo);
+        if (!finite) { sBad[q] = 1; sEnd[0] = 1; }
+    }
+    // A masked key's weight is zero, and zero times an infinite or NaN V row of a later token of this block is NaN: such
+    // queries are worked out once more, each alone.  Which: those ahead of the last position of the block whose V is not
+    // finite, unless they see a V row that is finite nowhere (nothing of their output is).
+    __syncthreads();
+    if (!sEnd[0]) return;                                  // (uniform)
+    const int first = P.pos0 + q0;
+    if (first + tid <= last_pos) {                         // (a thread per position: 32 QW are at most 128)
+        int bad = 0;
+        for (int pc = 0; pc < D / 8; ++pc) {
+            const u32x4 v = load16(Vc + ((size_t)(pc >> 1) * dm.max_seq + first + tid) * 16 + (pc & 1) * 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bad += ((v[j] & 0x7c00u) == 0x7c00u) + ((v[j] & 0x7c000000u) == 0x7c000000u);
+        }
+        if (bad) atomicMax(&sEnd[1], first + tid);
+        if (bad == D) atomicMin(&sEnd[2], first + tid);
+    }
+    __syncthreads();
+    const int end = min(sEnd[1], sEnd[2]);
+    for (int q = wave; q < 32 * QW && first + q < end; q += 4)         // (a query ahead of a position of the block is one of the pass)
+        if (sBad[q]) pf_attn_alone<D>(P, Kc, Vc, head, q0 + q, lane);
+}
+
+// SPLIT: workgroup z of a head's block takes the z-th part of the block's tiles of keys and leaves its queries' sums,
+// maxima and weights in memory, where k_pf_attn_join adds them.  For few queries behind a long context: a workgroup takes a
+// tile of keys in about 1.4 us, and 37 queries of 32 heads are 64 workgroups.
+template <int D, int QW, bool SPLIT>
+__global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P, PfAttnParts A)
 {
     constexpr int KW = 4 / QW, SUB = QW == 4 ? 2 : 1, TK = 32 * KW * SUB;
     constexpr int NK = D / 16, NB = (D + 31) / 32;         // K steps of S, 32-dimension tiles of O
@@ -268,7 +323,6 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
     constexpr int kTileBytes = (TK * KS + 32 * NB * VS) * 2, kOutBytes = 4 * 32 * OS * 4;
     __shared__ __align__(16) char mem[kTileBytes > kOutBytes ? kTileBytes : kOutBytes];
     __shared__ float sM[4][32], sL[4][32];
-    __shared__ int sBad[32 * QW], sEnd[3];                 // queries whose output is not finite; any; the positions of pf_attn_alone's rule
     __half *sK = reinterpret_cast<__half *>(mem), *sVt = sK + TK * KS;
     static_assert((TK * KS * 2) % 16 == 0, "");
     const Dims &dm = P.dm;
@@ -281,10 +335,10 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
     const int wave_last = qw0 < P.n_rows ? P.pos0 + min(qw0 + 31, P.n_rows - 1) : -1;
     const int last_pos = P.pos0 + min(q0 + 32 * QW, P.n_rows) - 1;         // the block's last query attends up to here
     const __half *Kc = P.kv + kv_offset(dm, 0, P.b, head, 0, 0), *Vc = P.kv + kv_offset(dm, 1, P.b, head, 0, 0);
+    const int tiles = (last_pos + TK) / TK;                // (last_pos / TK + 1)
+    const int t_first = SPLIT ? tiles * (int)blockIdx.z / A.parts * TK : 0, t_end = SPLIT ? tiles * ((int)blockIdx.z + 1) / A.parts * TK : tiles * TK;
     PfKvTile<D, TK> tile;
-    tile.request(Kc, Vc, 0, last_pos, dm.max_seq, tid);
-    if (tid < 32 * QW) sBad[tid] = 0;
-    if (tid == 0) { sEnd[0] = 0; sEnd[1] = -1; sEnd[2] = 0x7fffffff; }
+    tile.request(Kc, Vc, t_first, last_pos, dm.max_seq, tid);
     pf_f16x8 qh[NK], ql[NK];                               // Q^T: dimensions 16 ks + 8 hf .. + 7 of query col
     const float scale = 1.44269504088896340736f / sqrtf((float)D);
 #pragma unroll
@@ -305,7 +359,7 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) O[nb][e] = 0.f;
-    for (int t0 = 0; t0 <= last_pos; t0 += TK) {
+    for (int t0 = t_first; t0 < t_end; t0 += TK) {
         __syncthreads();                                   // the previous tile is no longer read
         tile.store(sK, sVt, KS, VS, tid);
         tile.request(Kc, Vc, t0 + TK, last_pos, dm.max_seq, tid);      // the next tile travels while this one is worked on
@@ -379,9 +433,11 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
     // the outputs through LDS (a query's dimensions side by side), where wavefronts of the same queries meet
     l_run += pf_other_half(l_run);
     float corr = 1.f;
-    if (KW > 1) {
+    if (KW > 1 || SPLIT) {
         if (hf == 0) { sM[wave][col] = m_run; }
         __syncthreads();
+    }
+    if (KW > 1) {
         float m = sM[wq][col];
 #pragma unroll
         for (int w = 1; w < KW; ++w) m = fmaxf(m, sM[wq + QW * w][col]);
@@ -400,52 +456,79 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P)
         }
     __syncthreads();
     const float *res = reinterpret_cast<const float *>(mem);
-    for (int e = tid; e < 32 * QW * (D / 8); e += 256) {
-        const int q = e / (D / 8), c8 = 8 * (e - q * (D / 8)), w0 = q >> 5, qc = q & 31;
-        if (q0 + q >= P.n_rows) continue;
+    // what the block's wavefronts have of query q, dimensions c8 .. + 7: unnormalised sums and weight
+    auto sums = [&](int q, int c8, f32x4 (&v)[2]) {
+        const int w0 = q >> 5, qc = q & 31;
         float l = sL[w0][qc];
-        f32x4 a = *reinterpret_cast<const f32x4 *>(res + (w0 * 32 + qc) * OS + c8), b = *reinterpret_cast<const f32x4 *>(res + (w0 * 32 + qc) * OS + c8 + 4);
+        v[0] = *reinterpret_cast<const f32x4 *>(res + (w0 * 32 + qc) * OS + c8); v[1] = *reinterpret_cast<const f32x4 *>(res + (w0 * 32 + qc) * OS + c8 + 4);
 #pragma unroll
         for (int w = 1; w < KW; ++w) {
             const int ww = w0 + QW * w;
             l += sL[ww][qc];
-            a += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8);
-            b += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8 + 4);
+            v[0] += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8);
+            v[1] += *reinterpret_cast<const f32x4 *>(res + (ww * 32 + qc) * OS + c8 + 4);
         }
-        __half hi[8], lo[8];
-        bool finite = true;
+        return l;
+    };
+    if (SPLIT) {
+        for (int e = tid; e < 32 * QW * (D / 8); e += 256) {
+            const int q = e / (D / 8), c8 = 8 * (e - q * (D / 8));
+            if (q0 + q >= P.n_rows) continue;
+            f32x4 v[2];
+            const float l = sums(q, c8, v);
+            const size_t row = (size_t)blockIdx.z * P.n_rows + q0 + q;
+            f32x4 *o = reinterpret_cast<f32x4 *>(A.o + row * dm.h + head * D + c8);
+            o[0] = v[0]; o[1] = v[1];
+            if (c8 == 0) {
+                float m = sM[q >> 5][q & 31];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float va = a[j] / l, vb = b[j] / l;
-            finite = finite && fabsf(va) < INFINITY && fabsf(vb) < INFINITY;
-            split_half(va, hi[j], lo[j]);
-            split_half(vb, hi[4 + j], lo[4 + j]);
+                for (int w = 1; w < KW; ++w) m = fmaxf(m, sM[(q >> 5) + QW * w][q & 31]);
+                A.ml[row * dm.H + head] = float2{m, l};
+            }
         }
-        const size_t at = pf_out_at(P, q0 + q, head * D + c8, dm.h);
-        *reinterpret_cast<u32x4 *>(P.o + at) = *reinterpret_cast<const u32x4 *>(hi);
-        *reinterpret_cast<u32x4 *>(P.o + at + pf_out_lo(P)) = *reinterpret_cast<const u32x4 *>(lo);
-        if (!finite) { sBad[q] = 1; sEnd[0] = 1; }
+        return;
     }
-    // A masked key's weight is zero, and zero times an infinite or NaN V row of a later token of this block is NaN: such
-    // queries are worked out once more, each alone.  Which: those ahead of the last position of the block whose V is not
-    // finite, unless they see a V row that is finite nowhere (nothing of their output is).
-    __syncthreads();
-    if (!sEnd[0]) return;                                  // (uniform)
-    const int first = P.pos0 + q0;
-    if (first + tid <= last_pos) {                         // (a thread per position: 32 QW are at most 128)
-        int bad = 0;
-        for (int pc = 0; pc < D / 8; ++pc) {
-            const u32x4 v = load16(Vc + ((size_t)(pc >> 1) * dm.max_seq + first + tid) * 16 + (pc & 1) * 8);
+    pf_attn_finish<D, QW>(P, Kc, Vc, head, q0, last_pos, tid, sums);
+}
+
+// The parts of a split attention, added in order: a workgroup per head and block of 32 queries.  (A query's output may carry
+// a later token's V from up to 127 positions behind the block's first: those that k_pf_attn's largest block holds.)
+template <int D>
+__global__ void __launch_bounds__(256) k_pf_attn_join(PfParams P, PfAttnParts A)
+{
+    const Dims &dm = P.dm;
+    const int head = blockIdx.x, q0 = (int)blockIdx.y * 32;
+    const __half *Kc = P.kv + kv_offset(dm, 0, P.b, head, 0, 0), *Vc = P.kv + kv_offset(dm, 1, P.b, head, 0, 0);
+    pf_attn_finish<D, 1>(P, Kc, Vc, head, q0, P.pos0 + min(q0 + 128, P.n_rows) - 1, threadIdx.x, [&](int q, int c8, f32x4 (&v)[2]) {
+        constexpr int AT = 8;                              // parts requested at a time (past the last: the last again)
+        float m = -INFINITY, l = 0.f;
+        v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int z = 0; z < A.parts; z += AT) {
+            float2 ml[AT];
+            f32x4 a[AT], b[AT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bad += ((v[j] & 0x7c00u) == 0x7c00u) + ((v[j] & 0x7c000000u) == 0x7c000000u);
+            for (int u = 0; u < AT; ++u) {
+                const size_t row = (size_t)min(z + u, A.parts - 1) * P.n_rows + q0 + q;
+                ml[u] = A.ml[row * dm.H + head];
+                const f32x4 *o = reinterpret_cast<const f32x4 *>(A.o + row * dm.h + head * D + c8);
+                a[u] = o[0]; b[u] = o[1];
+            }
+            float mn = m;
+#pragma unroll
+            for (int u = 0; u < AT; ++u) mn = fmaxf(mn, ml[u].x);
+            const float c0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+            l *= c0; v[0] *= c0; v[1] *= c0;
+#pragma unroll
+            for (int u = 0; u < AT; ++u) {
+                if (z + u >= A.parts) continue;            // (uniform)
+                const float c = ml[u].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - mn);
+                l = fmaf(ml[u].y, c, l);
+                v[0] += a[u] * c; v[1] += b[u] * c;
+            }
+            m = mn;
         }
-        if (bad) atomicMax(&sEnd[1], first + tid);
-        if (bad == D) atomicMin(&sEnd[2], first + tid);
-    }
-    __syncthreads();
-    const int end = min(sEnd[1], sEnd[2]);
-    for (int q = wave; q < 32 * QW && first + q < end; q += 4)         // (a query ahead of a position of the block is one of the pass)
-        if (sBad[q]) pf_attn_alone<D>(P, Kc, Vc, head, q0 + q, lane);
+        return l;
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -463,15 +546,39 @@ bool pf_supported(const Dims &dm)
 // tile of 128 keys spills registers there and is not built).
 // Kernel times before (16 queries to a workgroup, 64 from 1024 tokens, 16x16x16 instructions) -> now: hidden 2560, 512
 // tokens 23 -> 16 us, 4096 tokens 370 -> 227; hidden 4096, 1531 tokens behind 700: 221 -> 126.
+// Parts of the keys: as many as leave every CU a workgroup and each part two tiles, if a workgroup saves at least five
+// tiles (1.3 us each) by it: the launch that adds the parts takes 4 - 5 us.  us per layer, whole -> in parts: hidden 2560: 1
+// token behind 1000 / 3000 51.6 -> 48.1 / 73.3 -> 49.9, 37 tokens 65.7 -> 63.4 / 86.4 -> 67.5, 128 tokens behind 3000 143 -> 131;
+// hidden 4096, 37 tokens 120 -> 109 / 160 -> 114; hidden 512, 37 tokens 29.4 -> 28.0 / 44.8 -> 26.7.  With more (16 parts, or
+// two workgroups to a CU) the parts' traffic and the join cost what the shorter walks save.
+constexpr int kPfAttnPartsMax = 8;
+template <int D, int QW>
+static void pf_attention_of(const PfParams &P, hipStream_t s)
+{
+    constexpr int TK = 128 / QW * (QW == 4 ? 2 : 1);
+    const int blocks = (P.n_rows + 32 * QW - 1) / (32 * QW), wgs = P.dm.H * blocks, tiles = (P.pos0 + P.n_rows + TK - 1) / TK;
+    PfAttnParts A{P.part, nullptr, 1};
+    if constexpr (QW == (D == 128 ? 2 : 1)) {              // (with more queries to a workgroup there are more workgroups than CUs)
+        const size_t row = (size_t)P.n_rows * (P.dm.h * sizeof(float) + P.dm.H * sizeof(float2));
+        const int parts = min(min(tiles / 2, (256 + wgs - 1) / wgs), min(kPfAttnPartsMax, (int)(P.part_bytes / row)));
+        if (parts >= 2 && tiles - (tiles + parts - 1) / parts >= 5) {
+            A.parts = parts;
+            A.ml = reinterpret_cast<float2 *>(P.part + (size_t)parts * P.n_rows * P.dm.h);
+            hipLaunchKernelGGL((k_pf_attn<D, QW, true>), dim3(P.dm.H, blocks, parts), dim3(256), 0, s, P, A);
+            hipLaunchKernelGGL(k_pf_attn_join<D>, dim3(P.dm.H, (P.n_rows + 31) / 32), dim3(256), 0, s, P, A);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_pf_attn<D, QW, false>), dim3(P.dm.H, blocks), dim3(256), 0, s, P, A);
+}
 template <int D>
 static void pf_attention(const PfParams &P, hipStream_t s)
 {
     const int n = P.dm.H * ((P.n_rows + 31) / 32);
     const int qw = n >= (D == 128 ? 1536 : 2048) ? 4 : D == 128 || n >= 768 ? 2 : 1;
-    const dim3 grid(P.dm.H, (P.n_rows + 32 * qw - 1) / (32 * qw));
-    if (qw == 4) hipLaunchKernelGGL((k_pf_attn<D, 4>), grid, dim3(256), 0, s, P);
-    else if (qw == 2) hipLaunchKernelGGL((k_pf_attn<D, 2>), grid, dim3(256), 0, s, P);
-    else if constexpr (D != 128) hipLaunchKernelGGL((k_pf_attn<D, 1>), grid, dim3(256), 0, s, P);
+    if (qw == 4) pf_attention_of<D, 4>(P, s);
+    else if (qw == 2) pf_attention_of<D, 2>(P, s);
+    else if constexpr (D != 128) pf_attention_of<D, 1>(P, s);
 }
 
 template <bool FROM_PARTS>

@@ -61,6 +61,13 @@ struct PfNarrow {
     int rows_out;                   // second product: rows of a workgroup (parts of K: plan_out.splits)
 };
 
+// the parts of a split attention (k_pf_attn): unnormalised sums [parts][tokens][h], maximum and weight [parts][tokens][H]
+struct PfAttnParts {
+    float *o;
+    float2 *ml;
+    int parts;
+};
+
 struct PfParams {
     Dims dm;
     PackedLayout lay;

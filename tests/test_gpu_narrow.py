@@ -119,3 +119,23 @@ def test_a_single_sequence(orc, shape, S):
             ds.close()
     if S <= 512:
         assert np.array_equal(outs[0][0].view(np.uint16), outs[1][0].view(np.uint16))
+
+
+# Few queries behind a long context: the keys in 2 .. 8 parts, parts of unequal tiles, blocks of queries with unequal tiles, at the
+# three head sizes, through narrow and tiled products.
+@pytest.mark.parametrize("shape,pos0,T", [
+    (_shape(512, 64, 2048, 16, 1), 1500, 1), (_shape(512, 64, 2048, 16, 1), 890, 70), (_shape(640, 80, 2560, 20, 1), 2100, 33),
+    (_shape(640, 80, 2560, 20, 1), 1000, 100), (_shape(1024, 128, 4096, 32, 1), 700, 65), (_shape(2560, 80, 2560, 20, 1), 1400, 5),
+])
+def test_prompt_attention_in_parts(orc, shape, pos0, T):
+    from tests.test_gpu_prefill import _check_prompt
+    _check_prompt(orc, shape, 37, pos0, T, 1, 0, then_decode=False, gemm_rows=128, row_check_every=11)
+
+
+@pytest.mark.parametrize("kind", ["overflow", "nan"])
+@pytest.mark.parametrize("shape,pos0,T,bad", [
+    (_shape(512, 64, 2048, 16), 1200, 64, 31), (_shape(640, 80, 2560, 20), 1210, 37, 36), (_shape(1024, 128, 4096, 32), 640, 100, 63),
+])
+def test_prompt_attention_in_parts_ahead_of_a_token_that_is_not_finite(shape, pos0, T, bad, kind):
+    from tests.test_gpu_nonfinite import test_prompt_tokens_ahead_of_one_that_is_not_finite as check
+    check(shape, pos0, T, bad, kind)
