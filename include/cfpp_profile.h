@@ -43,14 +43,19 @@ cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_
                             cfpp_stream stream);
 
 /* The plan of one pass of cfpp_stack_prefill_gemm over n_tokens <= rows tokens (host
- * arithmetic, no GPU) in its tiled products; passes of up to 64 tokens take the narrow
- * ones instead where they can (cfpp_debug_prefill_narrow).  plan[0..3]: the first product (QKV, MLP-up), plan[4..7]: the
+ * arithmetic, no GPU) in its tiled products, before passes of up to 64 tokens take the
+ * narrow ones (cfpp_debug_prefill_narrow) and passes of 65 .. 1024 tokens other tiles
+ * (cfpp_debug_prefill_tiles).  plan[0..3]: the first product (QKV, MLP-up), plan[4..7]: the
  * second (output projection, MLP-down); of each the tokens, output features and K
  * values of a tile's step and the parts K is split into.  past[0..3]: by how many rows
  * the tiles' loads reach past the activations and the weights of the first product,
  * then of the second: 0 unless something is wrong. */
 cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                     int32_t plan[8], int32_t past[4]);
+
+/* The same with the tiles that a pass of 65 .. 1024 tokens takes in the end. */
+cfpp_status cfpp_debug_prefill_tiles(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
+                                     int32_t plan[8], int32_t past[4]);
 
 /* The narrow products of a pass of n_tokens tokens on a device of n_cu CUs (host arithmetic, no
  * GPU): plan[0] 1 if the pass takes them; plan[1], plan[2] rows and tiles of a workgroup of the

@@ -279,6 +279,14 @@ def cfpp_debug_prefill_plan(cfg: Config, rows: int, n_tokens: int):
     return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
 
 
+def cfpp_debug_prefill_tiles(cfg: Config, rows: int, n_tokens: int):
+    """As cfpp_debug_prefill_plan, with the tiles that passes of 65 .. 1024 tokens take in the end."""
+    plan, past = (C.c_int32 * 8)(), (C.c_int32 * 4)()
+    _check(lib().cfpp_debug_prefill_tiles(C.byref(cfg), C.c_int32(rows), C.c_int32(n_tokens), plan, past),
+           "cfpp_debug_prefill_tiles")
+    return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
+
+
 def cfpp_debug_prefill_narrow(cfg: Config, rows: int, n_tokens: int, n_cu: int = 256):
     """None, or (rows, tiles of the first product, rows, tiles, parts of the second, sets of tokens)."""
     plan = (C.c_int32 * 7)()

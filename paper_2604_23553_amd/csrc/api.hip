@@ -839,7 +839,7 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         pf_place(P, pl, sc);
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
         pf_plan_pass(P);
-        pf_plan_narrow(P, ctx->n_cu);
+        if (!pf_plan_narrow(P, ctx->n_cu)) pf_plan_middle(P);
         float *xa = reinterpret_cast<float *>(sc + pl.xres), *xb2 = reinterpret_cast<float *>(sc + pl.xnext);
         for (int l = 0; l < L; ++l) {
             P.layer = l;
@@ -1176,6 +1176,22 @@ extern "C" cfpp_status cfpp_debug_prefill_plan(const cfpp_config *c, int32_t row
     P.n_rows = n_tokens; P.rows = rows; P.n_layers = c->n_layers;
     pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));    // (a stand-in: only distances are used)
     pf_plan_pass(P);
+    pf_describe_plan(P, plan, past);
+    return CFPP_OK;
+}
+
+extern "C" cfpp_status cfpp_debug_prefill_tiles(const cfpp_config *c, int32_t rows, int32_t n_tokens, int32_t plan[8],
+                                                int32_t past[4])
+{
+    cfpp_status st = cfpp_debug_prefill_plan(c, rows, n_tokens, plan, past);       // (refuses what it refuses)
+    if (st != CFPP_OK) return st;
+    PfParams P;
+    std::memset(&P, 0, sizeof P);
+    P.dm = dims_of(*c); P.lay = packed_layout(P.dm.h, P.dm.f);
+    P.n_rows = n_tokens; P.rows = rows; P.n_layers = c->n_layers;
+    pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));
+    pf_plan_pass(P);
+    pf_plan_middle(P);
     pf_describe_plan(P, plan, past);
     return CFPP_OK;
 }

@@ -159,7 +159,7 @@ k_pf_gemm(PfParams P, int splits, int gm)
             } else {
                 // (where the wavefronts do not divide the rows, the last ones bring the last rows a second time)
                 const unsigned u = (i - NA + 1) * NWV <= BN / RU ? wave + (i - NA) * NWV : min(wave + (i - NA) * NWV, BN / RU - 1);
-                const unsigned at = lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, from = (unsigned)pf_dma_row(n0 + RU * u, N, RU) * width * 2u + jj * RB;
+                const unsigned at = lds0 + (unsigned)stage * (unsigned)STAGE + 2 * BM * RB + 1024u * u, from = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)pf_dma_row(n0 + RU * (int)u, N, RU) * width * 2u + jj * RB));
                 // with one token tile the weights are read once; the hint pays where an instruction takes whole lines (BK 64:
                 // 37 tokens, hidden 4096: 130 -> 120 us per layer; on half lines, BK 32, it costs: 72 -> 77 at hidden 2560)
                 if (BK == 64 && mt == 1) lds_dma16_once(rw, at, vw, from);
@@ -426,6 +426,7 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 constexpr int kPfCus = 256;
 struct PfTileCost { int bm, bn, bk, per_cu; float step, lone_step, epi_in, epi_out; };
 constexpr int kPfTile32x256 = 7, kPfTile32x128 = 8, kPfTile64x256 = 9;    // (up to 64 tokens: pf_plan_short)
+constexpr int kPfTile128x160 = 10, kPfTile128x128 = 11, kPfTile128x192 = 12, kPfTile128x256 = 13;    // (65 .. 1024 tokens: pf_plan_middle)
 static const PfTileCost kPfTiles[kPfTileKinds] = {
     {64, 128, 64, 1, 0.26f, 0.f, 3.74f, 2.19f},
     {64, 128, 32, 3, 0.25f, 0.37f, 0.01f, 1.13f},
@@ -435,6 +436,7 @@ static const PfTileCost kPfTiles[kPfTileKinds] = {
     {256, 256, 32, 1, 1.10f, 0.f, 14.67f, 5.02f},
     {256, 320, 32, 1, 1.34f, 0.f, 27.44f, 6.68f},
     {32, 256, 64}, {32, 128, 64}, {64, 256, 64},
+    {128, 160, 32, 2}, {128, 128, 64, 1}, {128, 192, 32, 1}, {128, 256, 32, 1},
 };
 
 // Up to 64 tokens a product is its weights' way from memory, once.  One token tile of 32 or 64 rows (the activations
@@ -493,6 +495,13 @@ static PfPlan pf_plan(const PfParams &P, bool in, size_t part_bytes, float *cost
     return best;
 }
 
+static void pf_plan_ends(PfParams &P)
+{
+    P.row_fused = P.plan_out.splits > 1 && P.part_out == P.q;
+    const int bm = kPfTiles[P.plan_out.tile].bm;
+    P.part_out_stride = (size_t)((P.n_rows + bm - 1) / bm * bm) * P.dm.h;
+}
+
 void pf_plan_pass(PfParams &P)
 {
     float cost, cost_y;
@@ -511,9 +520,68 @@ void pf_plan_pass(PfParams &P)
         P.part_out = reinterpret_cast<float *>(P.y1);
         P.part_out_bytes += ahead;
     }
-    P.row_fused = P.plan_out.splits > 1 && P.part_out == P.q;
-    const int bm = kPfTiles[P.plan_out.tile].bm;
-    P.part_out_stride = (size_t)((P.n_rows + bm - 1) / bm * bm) * P.dm.h;
+    pf_plan_ends(P);
+}
+
+// Passes of 65 .. 1024 tokens: four more tiles of 128 tokens, where they beat the plan above.  With one or two token tiles
+// a product of few tokens is few workgroups with a whole K each, and what counts is that they come to nearly the number of
+// CUs: 160 features (two workgroups to a CU, or K in two parts) and 192 or 256 (a deeper ring); and K steps of 64 values - whole
+// lines of weights, half the barriers - where a CU has one workgroup.  Chosen by an estimate of the same form whose constants, in us, are
+// fitted to timings of whole layers (hidden 512 .. 4096, 70 .. 1024 tokens, 5500 of them, 2.4 % of a layer rms); taken where it is 2 us and
+// 2 % below that of the plan above, which made none of the fitted sizes slower.  us per layer, before -> now: hidden 2560:
+// 96 tokens 103 -> 92, 256 145 -> 123, 512 211 -> 204; hidden 4096: 96 177 -> 143, 128 171 -> 155; hidden 1536, 512 99 -> 95.
+struct PfLayerCost { float step, lone_step, epi_in, epi_out; };
+static const PfLayerCost kPfLayerCosts[kPfTileKinds] = {
+    {0.271f, 0.000f, 4.96f, 1.94f},
+    {0.237f, 0.336f, 0.98f, 0.89f},
+    {0.325f, 0.435f, 6.76f, 2.00f},
+    {0.809f, 0.000f, 9.63f, 4.32f},
+    {0.849f, 0.000f, 13.36f, 5.07f},
+    {1.007f, 0.000f, 17.27f, 6.35f},
+    {1.236f, 0.000f, 25.35f, 7.53f},
+    {},
+    {},
+    {},
+    {0.405f, 0.551f, 8.04f, 2.47f},
+    {0.376f, 0.000f, 10.05f, 3.39f},
+    {0.566f, 0.000f, 5.09f, 3.08f},
+    {0.693f, 0.000f, 6.71f, 3.74f},
+};
+static float pf_layer_cost(const PfParams &P, bool in, int kind, int sp)
+{
+    const PfTileCost &t = kPfTiles[kind];
+    const PfLayerCost &c = kPfLayerCosts[kind];
+    const int h = P.dm.h, f = P.dm.f, mt = (P.n_rows + t.bm - 1) / t.bm;
+    const int ntn = in ? (3 * h + t.bn - 1) / t.bn + (f + t.bn - 1) / t.bn : (h + t.bn - 1) / t.bn;
+    const int wgs = mt * ntn * sp, per = (wgs + kPfCus - 1) / kPfCus, rounds = (wgs + kPfCus * t.per_cu - 1) / (kPfCus * t.per_cu);
+    const float steps = (float)(in ? h : h + f) / 32.f / sp, nall = (float)(in ? 3 * h + f : h);
+    const float busy = per * steps * c.step, lone = rounds * steps * c.lone_step;
+    float cost = busy > lone ? busy : lone;
+    if (!in) cost += per * c.epi_out;
+    else if (sp == 1) cost += per * c.epi_in;
+    if (sp > 1) cost += in ? 4.32f + 8.33e-07f * sp * P.n_rows * nall : 0.08f + 9.54e-07f * sp * P.n_rows * nall;
+    return cost;
+}
+void pf_plan_middle(PfParams &P)
+{
+    if (P.n_rows <= 64 || P.n_rows > 1024) return;
+    for (int in = 1; in >= 0; --in) {
+        PfPlan &plan = in ? P.plan_in : P.plan_out;
+        const size_t room = in ? P.part_bytes : P.part_out_bytes;
+        const float was = pf_layer_cost(P, in, plan.tile, plan.splits);
+        float best = 0.98f * was - 2.f;
+        for (int k = kPfTile128x160; k <= kPfTile128x256; ++k) {
+            if (!in && (k == kPfTile128x160 || k == kPfTile128x256)) continue;     // (never the least there: not built)
+            const int mt = (P.n_rows + 127) / 128, nall = in ? 3 * P.dm.h + P.dm.f : P.dm.h;
+            for (int sp = 1; sp <= (in ? 4 : 16); ++sp) {
+                if (sp > 1 && (size_t)sp * mt * 128 * nall * sizeof(float) > room) break;
+                if ((in ? P.dm.h : P.dm.h + P.dm.f) / kPfTiles[k].bk < sp) break;
+                const float cost = pf_layer_cost(P, in, k, sp);
+                if (cost < best) { best = cost; plan.tile = k; plan.splits = sp; }
+            }
+        }
+    }
+    pf_plan_ends(P);
 }
 
 #ifdef CFPP_PROFILE
@@ -562,6 +630,10 @@ static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
     case kPfTile32x256: if (FL == kPfIn) return pf_launch<kPfIn, 32, 256, 64, 3, 1, 4>(P, pl, s); break;
     case kPfTile32x128: return pf_launch<FL, 32, 128, 64, 3, 1, 4>(P, pl, s);
     case kPfTile64x256: if (FL == kPfIn) return pf_launch<kPfIn, 64, 256, 64, 3, 1, 4>(P, pl, s); break;
+    case kPfTile128x160: if (FL == kPfIn) return pf_launch<kPfIn, 128, 160, 32, 3, 4, 1>(P, pl, s); break;
+    case kPfTile128x128: return pf_launch<FL, 128, 128, 64, 3, 2, 2>(P, pl, s);
+    case kPfTile128x192: return pf_launch<FL, 128, 192, 32, 5, 4, 2>(P, pl, s);
+    case kPfTile128x256: if (FL == kPfIn) return pf_launch<kPfIn, 128, 256, 32, 4, 4, 2>(P, pl, s); break;
     }
     return hipErrorInvalidValue;
 }

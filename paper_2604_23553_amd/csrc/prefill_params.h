@@ -49,7 +49,7 @@ CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
 }
 
 // tile (index into the table of prefill_gemm.hip) and splits of K of a product
-constexpr int kPfTileKinds = 10;
+constexpr int kPfTileKinds = 14;
 struct PfPlan { int tile, splits; };
 
 // Passes of up to this many tokens may take the narrow products (prefill_narrow.hip); the activations that feed a
@@ -110,7 +110,9 @@ inline void pf_place(PfParams &P, const PfLayout &pl, char *sc)
 bool pf_supported(const Dims &dm);
 // fills in the plans of a pass: everything else of P that does not depend on the layer is set
 void pf_plan_pass(PfParams &P);
-// that plan, and what the products' DMA would request past their operands (profiling library): see cfpp_debug_prefill_plan
+// behind it, for passes that the narrow products don't take: other tiles for 65 .. 1024 tokens
+void pf_plan_middle(PfParams &P);
+// the plan, and what the products' DMA would request past their operands (profiling library): see cfpp_debug_prefill_plan
 void pf_describe_plan(const PfParams &P, int plan[8], int past[4]);
 // the epilogues' GELU and the library's on n values (profiling library)
 hipError_t launch_debug_gelu(const float *z, float *epilogue, float *library, int n, int flags, hipStream_t s);

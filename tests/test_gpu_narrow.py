@@ -1,10 +1,13 @@
-"""GPU parity of the products for few tokens (csrc/narrow_gemm.hip) where their cut can go wrong: wavefronts with
+"""GPU parity of the kernels for few tokens (csrc/narrow_gemm.hip, prefill_narrow.hip), of the split prompt attention and of the
+tiles of middle-sized passes, where their cut can go wrong: wavefronts with
 unequal shares of K or with none, tiles of 16 rows that are partly there, one row group or eight tiles to a workgroup."""
 import numpy as np
 import pytest
+import torch                       # (ahead of the library: both take the HIP runtime that comes with it)
 
 import synth
 from tests.parity import assert_appended_rows, assert_block_close
+from tests.prefill_middle import MIDDLE
 from tests.test_gpu_stack import _batched_case
 
 pytestmark = pytest.mark.gpu
@@ -139,3 +142,15 @@ def test_prompt_attention_in_parts(orc, shape, pos0, T):
 def test_prompt_attention_in_parts_ahead_of_a_token_that_is_not_finite(shape, pos0, T, bad, kind):
     from tests.test_gpu_nonfinite import test_prompt_tokens_ahead_of_one_that_is_not_finite as check
     check(shape, pos0, T, bad, kind)
+
+
+# The tiles of passes of 65 .. 1024 tokens, over two layers, against the batched projections (as the plans of all passes are).
+@pytest.mark.parametrize("shape,T,first,second", MIDDLE)
+def test_middle_tiles_over_two_layers(shape, T, first, second):
+    import paper_2604_23553_amd as cf
+    from tests.test_gpu_prefill import test_gemm_plans_over_two_layers as check
+    cfg, rows = cf.Config.from_shape(shape, 3 + T), -(-T // 128) * 128
+    with cf.profile_build():
+        base, got = cf.cfpp_debug_prefill_plan(cfg, rows, T)[0], cf.cfpp_debug_prefill_tiles(cfg, rows, T)[0]
+    assert got == (first or base[0], second or base[1])
+    check(shape, T, *base)

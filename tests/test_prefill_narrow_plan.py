@@ -2,6 +2,7 @@
 import pytest
 
 import paper_2604_23553_amd as cf
+from tests.prefill_middle import MIDDLE
 
 
 def narrow(h, d, f, tokens, n_cu=256, rows=128):
@@ -33,3 +34,31 @@ def test_which_passes_take_them():
     assert narrow(4096, 128, 16384, 48) and narrow(4096, 128, 16384, 49) is None       # 8 tiles x 8 sets
     assert narrow(512, 64, 32768, 20) is None                           # more than 128 rows to a CU
     assert narrow(2560, 80, 10240, 20, n_cu=128) is None
+
+
+# ---- passes of 65 .. 1024 tokens: other tiles where they are better --------------------------------------------------
+def tiles(h, d, f, tokens):
+    cfg = cf.Config(h, h // d, d, 16, f, 2, 16, 1, 10000.0, 1e-5, 0)
+    rows = -(-tokens // 128) * 128
+    with cf.profile_build():
+        return cf.cfpp_debug_prefill_plan(cfg, rows, tokens), cf.cfpp_debug_prefill_tiles(cfg, rows, tokens)
+
+
+@pytest.mark.parametrize("shape,tokens,first,second", MIDDLE)
+def test_what_a_middle_size_takes(shape, tokens, first, second):
+    (base, _), (got, _) = tiles(shape.hidden, shape.head_dim, shape.ffn, tokens)
+    assert got == (first or base[0], second or base[1])
+
+
+def test_middle_sizes_take_tiles_that_the_gpu_runs_and_load_inside_their_operands():
+    run = {(k, p[2 + k][:3], p[2 + k][3] > 1) for p in MIDDLE for k in (0, 1) if p[2 + k]}
+    for h, d in ((128, 64), (512, 64), (640, 80), (1024, 128), (1280, 80), (1536, 64), (1920, 80), (2048, 64), (2560, 80), (2688, 128),
+                 (3072, 128), (3200, 80), (4096, 128)):
+        for f in (h, 4 * h, min(32768, 8 * h)):
+            for t in (*range(1, 131, 9), *range(131, 1025, 29), 1025, 2048, 4096):
+                (base, _), (got, past) = tiles(h, d, f, t)
+                assert past == ((0, 0), (0, 0)), (h, f, t, past)
+                if not 64 < t <= 1024:
+                    assert got == base
+                for k in (0, 1):
+                    assert got[k] == base[k] or (k, got[k][:3], got[k][3] > 1) in run, (h, f, t, got)
