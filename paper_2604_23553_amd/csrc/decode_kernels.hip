@@ -422,10 +422,20 @@ constexpr int kAttnBatchMax = 8, kAttnBatchThreads = 256;
 // 2 layers 168 -> 156, 182 -> 178.  A prompt group's queries share their
 // rows and don't stream: 1024, as measured above.  Pieces of a head never exceed the workspace's part_slots.
 constexpr int kAttnSpareGroups = 640, kAttnSpareShared = 1024, kAttnPieceRows = 32;
+// Up to four sequences of their own leave workgroups to spare: up to eight pieces of half as many rows.  us a block, 32 rows -> 16:
+// hidden 2560, one sequence of 1000 / 2000 / 4000 41.3 -> 39.5 / 43.4 -> 41.0 / 45.4 -> 43.7, three of 500 .. 1000 42.9 -> 41.8;
+// hidden 4096, four of 20 .. 2000 85.7 -> 83.6; but five of 37 .. 2048 45.6 -> 47.4, prompt groups 47.0 -> 47.9, and 16 pieces
+// of one sequence of 8000 49.7 -> 50.4.
+constexpr int kAttnFew = 4;
+CFPP_HD int attn_pieces(int rows, bool few)
+{
+    const int n = (rows + kAttnPieceRows - 1) / kAttnPieceRows, half = (rows + kAttnPieceRows / 2 - 1) / (kAttnPieceRows / 2);
+    return !few || n >= 8 ? n : half < 8 ? half : 8;
+}
 
 template <int D, bool STREAM>
 __global__ void __launch_bounds__(kAttnBatchThreads, 3)
-k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
+k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv)
 {
     using A = AttnShape<D>;
     constexpr int LPP = A::LPP, PPW = A::PPW, NP = A::NP, NV = A::NV, NE = (D + 63) / 64, NW = kAttnBatchThreads / 64;
@@ -433,39 +443,44 @@ k_attention_batched(StepParams P, int nb, int spare, const __half *kv)
     __shared__ float wp[NW * D], wm[NW], wl[NW];
     const Dims &dm = P.dm;
     const int H = dm.H, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // this workgroup's sequence, head and piece (rows: per head, every head of a sequence has the same number;
-    // spare * sum stays below 2^32: max_seq <= 2^20)
-    unsigned rows[kAttnBatchMax], total = 0;
+    // this workgroup's sequence, head and piece (rows: per head, every head of a sequence has the same number).  All of it
+    // stands in front of the first load, so: scalar loads, and reciprocals instead of divisions.
+    typedef const __attribute__((address_space(4))) int *Scalar;
+    const Scalar positions = (Scalar)reinterpret_cast<unsigned long long>(P.pos);
+    int rows[kAttnBatchMax], at[kAttnBatchMax], total = 0;
     bool ok = true;
 #pragma unroll
     for (int i = 0; i < kAttnBatchMax; ++i) {
-        rows[i] = 0;
-        if (i < nb) {
-            const int p = P.pos[i];
-            ok = ok && p >= 0 && p < dm.max_seq;
-            rows[i] = (unsigned)((p + 1 + PPW - 1) / PPW);
-            total += rows[i];
-        }
+        at[i] = positions[min(i, nb - 1)];
+        ok = ok && at[i] >= 0 && at[i] < dm.max_seq;
+        rows[i] = i < nb ? (at[i] + 1 + PPW - 1) / PPW : 0;
+        total += rows[i];
     }
     if (!ok) {
         if (tid == 0 && blockIdx.x == 0)
             __hip_atomic_store(&P.sync[kSyncErr], (unsigned)kErrBadPos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    int mine = -1, R = 0, pieces = 1, local = 0, base = 0;
+    const float share = (float)spare * __builtin_amdgcn_rcpf((float)total);          // (whatever it is rounded to: the shares' whole parts add up to spare at most)
+    int mine = -1, R = 0, pieces = 1, local = 0, base = 0, t_last = 0;
 #pragma unroll
     for (int i = 0; i < kAttnBatchMax; ++i) {
         if (i < nb) {
-            const int n = min(min(1 + (int)((unsigned)spare * rows[i] / total), ((int)rows[i] + kAttnPieceRows - 1) / kAttnPieceRows), P.part_slots);
-            const int at = (int)blockIdx.x - base;
-            if (at >= 0 && at < n * H) { mine = i; R = (int)rows[i]; pieces = n; local = at; }
+            const int n = min(min(1 + (int)((float)rows[i] * share), attn_pieces(rows[i], few)), P.part_slots);
+            const int in = (int)blockIdx.x - base;
+            if (in >= 0 && in < n * H) { mine = i; R = rows[i]; pieces = n; local = in; t_last = at[i]; }
             base += n * H;
         }
     }
     if (mine < 0) return;                                  // (whole workgroup)
-    const int head = local % H, piece = local / H;
-    const int b = P.b + mine * P.attn_bstep, t_last = P.pos[mine];
-    const int lo = (int)((long long)R * piece / pieces), hi = (int)((long long)R * (piece + 1) / pieces);
+    // local / H (both below 2^15: the half keeps every quotient off a whole number), and the piece's rows: R / pieces each,
+    // the first ones one more
+    const int piece = (int)(((float)local + 0.5f) * __builtin_amdgcn_rcpf((float)H)), head = local - piece * H;
+    int each = (int)((float)R * __builtin_amdgcn_rcpf((float)pieces)), rest = R - each * pieces;
+    if (rest < 0) { --each; rest += pieces; }
+    if (rest >= pieces) { ++each; rest -= pieces; }
+    const int b = P.b + mine * P.attn_bstep;
+    const int lo = piece * each + min(piece, rest), hi = lo + each + (piece < rest);
     const int sub = lane & (LPP - 1), tl = lane / LPP;
     const __half *Kh = kv + kv_offset(dm, 0, b, head, 0, 0), *Vh = kv + kv_offset(dm, 1, b, head, 0, 0);
     unsigned koff[NP];
@@ -678,14 +693,15 @@ hipError_t launch_attention_batched(const StepParams &P, int nb, const __half *k
     if (nb < 1 || nb > kAttnBatchMax) return hipErrorInvalidValue;
     const bool stream = P.attn_bstep != 0;
     const int H = P.dm.H, spare = (stream ? kAttnSpareGroups : kAttnSpareShared) / H;
+    const bool few = stream && nb <= kAttnFew;
     // no sequence has more pieces than its longest context allows (64 / LPP positions a row, as in AttnShape)
-    const int row = P.dm.d >= 128 ? 16 : 32, most = (P.dm.max_seq + row * kAttnPieceRows - 1) / (row * kAttnPieceRows);
+    const int row = P.dm.d >= 128 ? 16 : 32, most = attn_pieces((P.dm.max_seq + row - 1) / row, few);
     const dim3 grid(min(nb + spare, nb * most) * H), block(kAttnBatchThreads);
     switch (P.dm.d) {
 #define CFPP_ATTN(D) \
     case D: \
-        if (stream) hipLaunchKernelGGL((k_attention_batched<D, true>), grid, block, 0, s, P, nb, spare, kv); \
-        else hipLaunchKernelGGL((k_attention_batched<D, false>), grid, block, 0, s, P, nb, spare, kv); \
+        if (stream) hipLaunchKernelGGL((k_attention_batched<D, true>), grid, block, 0, s, P, nb, spare, few, kv); \
+        else hipLaunchKernelGGL((k_attention_batched<D, false>), grid, block, 0, s, P, nb, spare, few, kv); \
         break;
     CFPP_ATTN(64)
     CFPP_ATTN(80)
