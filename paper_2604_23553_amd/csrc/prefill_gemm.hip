@@ -107,7 +107,7 @@ k_pf_gemm(PfParams P, int splits, int gm)
     static_assert(BM % (RUA * NWV) == 0 && NWV % 2 == 0 && BN % RU == 0 && (BK == 32 || BN % (RU * NWV) == 0), "whole DMA instructions");
     constexpr int STAGE = 2 * BM * RB + BN * RB;
     constexpr int TS = 2 * kPfLo + 8, kScratch = NWV * 32 * TS * 2;   // epilogue: halves between rows of a wavefront's scratch, bytes of all
-    static_assert(kScratch + BM * 8 <= ST * STAGE, "the epilogue's memory");
+    static_assert(kScratch + BN * 8 <= ST * STAGE, "the epilogue's memory");
     extern __shared__ __align__(16) char pf_lds[];
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char *)pf_lds;
     const Dims &dm = P.dm;
@@ -215,7 +215,7 @@ k_pf_gemm(PfParams P, int splits, int gm)
                 const int a = sl % MT;
 #pragma unroll
                 for (int b = 0; b < NTL; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sl < MT ? g.ah[a] : g.al[a], g.w[b], acc[a][b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(g.w[b], sl < MT ? g.ah[a] : g.al[a], acc[a][b], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (sl == 0) {
                     // the next group's fragments, behind this group's first instructions: the wait for this
@@ -239,52 +239,63 @@ k_pf_gemm(PfParams P, int splits, int gm)
         prev = stage;
         stage = next;
     }
-    // this lane holds, per instruction tile, column lane % 32 and rows 8 (e / 4) + 4 (lane / 32) + e % 4
+    // Weights are the instruction's first operand, so that this lane holds, per instruction tile, ONE token (lane % 32) and the
+    // features 8 g + 4 (lane / 32) .. + 3, g < 4, side by side in its registers 4 g ..: a token's statistics are read once, four features
+    // go out in one store, a rotation pair is the lane's own.  us per layer, a feature and 16 tokens to a lane (2-byte stores, a
+    // statistics pair read per value) -> this: hidden 512, 4000 tokens 167 -> 143; 1536, 512 tokens 96.7 -> 89.9; 2560, 512 / 1024 /
+    // 4000 tokens 199.6 -> 194.3 / 387 -> 375 / 1379 -> 1348; 4096, 2048 tokens 1539 -> 1495.  What follows the first product of 512
+    // tokens at hidden 2560 is still some 15 of its 116 us (9.5 and 13 without the QKV and the MLP-up columns' part).
+    const int t_lane = wm * (BM / WM) + (lane & 31), f_lane = 4 * (lane >> 5);      // token of the first instruction tile; first feature of g = 0
     if (splits > 1) {
         const int nall = FL == kPfIn ? 3 * h + f : h, c0 = up ? 3 * h : 0;
-        float *part = FL == kPfIn ? P.part : P.part_out;
+        float *part = (FL == kPfIn ? P.part : P.part_out) + (size_t)z * mt * BM * nall + c0;
 #pragma unroll
         for (int b = 0; b < NTL; ++b) {
-            const int col = n0 + wn * (BN / WN) + b * 32 + (lane & 31);
-            if (col - (lane & 31) >= N) continue;          // (N: a multiple of 128)
+            const int col = n0 + wn * (BN / WN) + b * 32;
+            if (col >= N) break;                           // (uniform; N: a multiple of 128)
 #pragma unroll
             for (int a = 0; a < MT; ++a)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = m0 + wm * (BM / WM) + a * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-                    part[((size_t)z * mt * BM + row) * nall + c0 + col] = acc[a][b][e];
-                }
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<f32x4 *>(part + (size_t)(m0 + t_lane + a * 32) * nall + col + 8 * g + f_lane) =
+                        f32x4{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
         }
         return;
     }
-    // What follows the product, from the instruction's layout: a lane has one column and 16 rows of an instruction
-    // tile.  Nothing is exchanged between the wavefronts, so nobody waits for the slowest.
-    const int r_lane = wm * (BM / WM) + (lane >> 5) * 4;    // row of element 0 of the first instruction tile
-    float2 *sst = reinterpret_cast<float2 *>(pf_lds + kScratch);
-    if (FL == kPfIn) {                                     // the rows' mean and 1/sigma
+    const float inv_d = __builtin_amdgcn_rcpf((float)dm.d);            // (column / d: the half keeps every quotient off a whole number)
+    // What follows the product.  Nothing is exchanged between the wavefronts, so nobody waits for the slowest.
+    float2 st[MT];                                         // mean and 1/sigma of the lane's tokens
+    f32x4 *src = reinterpret_cast<f32x4 *>(pf_lds + kScratch);         // row constants of the tile's features, two features to a piece
+    if (FL == kPfIn) {
+#pragma unroll
+        for (int a = 0; a < MT; ++a) st[a] = P.stats[min(m0 + t_lane + a * 32, P.n_rows - 1)];      // (rows past the pass's tokens are never stored)
+        const f32x4 *rc = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float2 *>(P.w + (up ? P.lay.rc_up : P.lay.rc_qkv)) + n0);
         __syncthreads();                                   // the last step's fragments have been read: the memory is free
-        for (int r = tid; r < BM; r += NT) sst[r] = P.stats[min(m0 + r, P.n_rows - 1)];   // (rows past the pass's tokens are never stored)
+        for (int i = tid; i < BN / 2; i += NT) src[i] = rc[min(i, (N - n0) / 2 - 1)];
         __syncthreads();
     }
 #pragma unroll
     for (int b = 0; b < NTL; ++b) {
-        const int c0 = n0 + wn * (BN / WN) + b * 32, col = c0 + (lane & 31);
+        const int cw = wn * (BN / WN) + b * 32, c0 = n0 + cw;
         if (c0 >= N) break;                                // (uniform; N: a multiple of 128)
         if (FL == kPfIn && up) {
             // MLP-up: 32 tokens x 32 columns at a time through 4.5 KB of LDS that no other wavefront touches, so that
             // whole 128-byte lines (32 heads, 32 remainders) are stored
             __half *t = reinterpret_cast<__half *>(pf_lds) + wave * 32 * TS;
-            const float2 rc = reinterpret_cast<const float2 *>(P.w + P.lay.rc_up)[col];
 #pragma unroll
             for (int a = 0; a < MT; ++a) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int rl = (e >> 2) * 8 + (e & 3);
-                    const float2 st = sst[r_lane + a * 32 + rl];
-                    __half hi, lo;
-                    split_half(pf_gelu((acc[a][b][e] - st.x * rc.x) * st.y + rc.y, dm.flags), hi, lo);
-                    t[(rl + (lane >> 5) * 4) * TS + (lane & 31)] = hi;
-                    t[(rl + (lane >> 5) * 4) * TS + kPfLo + (lane & 31)] = lo;
+                for (int g = 0; g < 4; ++g) {
+                    union { __half h[4]; uint2 u; } hi, lo;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const f32x4 rc = src[(cw + 8 * g + f_lane) / 2 + j];
+                        split_half(pf_gelu((acc[a][b][4 * g + 2 * j] - st[a].x * rc[0]) * st[a].y + rc[1], dm.flags), hi.h[2 * j], lo.h[2 * j]);
+                        split_half(pf_gelu((acc[a][b][4 * g + 2 * j + 1] - st[a].x * rc[2]) * st[a].y + rc[3], dm.flags), hi.h[2 * j + 1], lo.h[2 * j + 1]);
+                    }
+                    __half *to = t + (lane & 31) * TS + 8 * g + f_lane;
+                    *reinterpret_cast<uint2 *>(to) = hi.u;
+                    *reinterpret_cast<uint2 *>(to + kPfLo) = lo.u;
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -295,67 +306,78 @@ k_pf_gemm(PfParams P, int splits, int gm)
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else if (FL == kPfIn) {
-            // QKV: the column's head, part (q, k, v) and dimension; pairs of the rotated part sit in neighbouring columns
-            const float2 rc = reinterpret_cast<const float2 *>(P.w + P.lay.rc_qkv)[col];
-            const int pd = col / dm.d, i = col - pd * dm.d, nh = pd / 3, c = pd - 3 * nh;
-            const bool rot = c < 2 && i < dm.r;
-            const int dim = rot ? (i >> 1) + (i & 1) * (dm.r >> 1) : i;
-            const bool any_rot = __any(rot);
-            const unsigned qo = (unsigned)(nh * dm.d + dim);
-            __half *kp = P.kv + kv_offset(dm, c > 0 ? c - 1 : 0, P.b, nh, dim, P.pos0);
-            const unsigned co = (unsigned)P.pos0 * (unsigned)(dm.r >> 1) + (unsigned)(rot ? i >> 1 : 0);
+            // QKV: four features are dimensions i .. i + 3 of one head's q, k or v (head sizes and i are multiples of 4); pairs
+            // of the rotated part sit side by side
 #pragma unroll
-            for (int a = 0; a < MT; ++a) {
-                const int ra = r_lane + a * 32;
-                float v[16];
+            for (int g = 0; g < 4; ++g) {
+                const int col = c0 + 8 * g + f_lane, pd = (int)(((float)col + 0.5f) * inv_d), i = col - pd * dm.d;
+                const int nh = (int)(((float)pd + 0.5f) * (1.f / 3.f)), c = pd - 3 * nh, r = dm.r, half = r >> 1;
+                const bool rot0 = c < 2 && i < r, rot1 = c < 2 && i + 2 < r;
+                const f32x4 ra = src[(cw + 8 * g + f_lane) / 2], rb = src[(cw + 8 * g + f_lane) / 2 + 1];
+                __half *kp = P.kv + kv_offset(dm, c > 0 ? c - 1 : 0, P.b, nh, 0, P.pos0);
+                const unsigned slab = (unsigned)dm.max_seq * 16u;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float2 st = sst[ra + (e >> 2) * 8 + (e & 3)];
-                    v[e] = (acc[a][b][e] - st.x * rc.x) * st.y + rc.y;
-                }
-                if (any_rot) {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const float other = dpp_mov<kDppXor1>(v[e]);     // (all lanes: the neighbouring lane holds col ^ 1)
-                        const int row = min(m0 + ra + (e >> 2) * 8 + (e & 3), P.n_rows - 1);
-                        if (rot) {
-                            const float2 cs = P.rope[co + (unsigned)row * (unsigned)(dm.r >> 1)];
-                            v[e] = i & 1 ? v[e] * cs.x + other * cs.y : v[e] * cs.x - other * cs.y;
+                for (int a = 0; a < MT; ++a) {
+                    const int row = m0 + t_lane + a * 32;
+                    if (row >= P.n_rows) continue;
+                    float v[4] = {(acc[a][b][4 * g] - st[a].x * ra[0]) * st[a].y + ra[1], (acc[a][b][4 * g + 1] - st[a].x * ra[2]) * st[a].y + ra[3],
+                                  (acc[a][b][4 * g + 2] - st[a].x * rb[0]) * st[a].y + rb[1], (acc[a][b][4 * g + 3] - st[a].x * rb[2]) * st[a].y + rb[3]};
+                    float *q = P.q + (unsigned)row * (unsigned)h + (unsigned)(nh * dm.d);
+                    __half *kv = kp + (unsigned)row * 16u;
+                    if (rot0) {                            // dimensions i / 2, i / 2 + half and, of the second pair, the next (or i + 2, i + 3)
+                        const float2 *cs = P.rope + (unsigned)(P.pos0 + row) * (unsigned)half + (unsigned)(i >> 1);
+                        const float2 s0 = cs[0];
+                        const float x0 = v[0] * s0.x - v[1] * s0.y, x1 = v[1] * s0.x + v[0] * s0.y;
+                        float x2 = v[2], x3 = v[3];
+                        int d2 = i + 2, d3 = i + 3;
+                        if (rot1) {
+                            const float2 s1 = cs[1];
+                            x2 = v[2] * s1.x - v[3] * s1.y; x3 = v[3] * s1.x + v[2] * s1.y;
+                            d2 = (i >> 1) + 1; d3 = d2 + half;
                         }
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = m0 + ra + (e >> 2) * 8 + (e & 3);
-                    if (row < P.n_rows) {
-                        if (c == 0) P.q[qo + (unsigned)row * (unsigned)h] = v[e];
-                        else kp[(size_t)row * 16] = __float2half_rn(v[e]);
+                        const int d0 = i >> 1, d1 = d0 + half;
+                        if (c == 0) {
+                            q[d0] = x0; q[d1] = x1; q[d2] = x2; q[d3] = x3;
+                        } else {
+                            kv[(unsigned)(d0 >> 4) * slab + (d0 & 15)] = __float2half_rn(x0);
+                            kv[(unsigned)(d1 >> 4) * slab + (d1 & 15)] = __float2half_rn(x1);
+                            kv[(unsigned)(d2 >> 4) * slab + (d2 & 15)] = __float2half_rn(x2);
+                            kv[(unsigned)(d3 >> 4) * slab + (d3 & 15)] = __float2half_rn(x3);
+                        }
+                    } else if (c == 0) {
+                        *reinterpret_cast<f32x4 *>(q + i) = f32x4{v[0], v[1], v[2], v[3]};
+                    } else {
+                        uint2 o;
+                        o.x = pf_pack2(v[0], v[1]); o.y = pf_pack2(v[2], v[3]);
+                        *reinterpret_cast<uint2 *>(kv + (unsigned)(i >> 4) * slab + (i & 15)) = o;
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
-            const float bde = __half2float(P.w[P.lay.b_dense + col]), bdn = __half2float(P.w[P.lay.b_down + col]);
             const bool last = P.layer == P.n_layers - 1;
 #pragma unroll
-            for (int a = 0; a < MT; ++a) {
+            for (int g = 0; g < 4; ++g) {
+                const int col = c0 + 8 * g + f_lane;
+                const uint2 de = *reinterpret_cast<const uint2 *>(P.w + P.lay.b_dense + col), dn = *reinterpret_cast<const uint2 *>(P.w + P.lay.b_down + col);
+                const float2 de0 = unpack_h2(de.x), de1 = unpack_h2(de.y), dn0 = unpack_h2(dn.x), dn1 = unpack_h2(dn.y);
+                f32x4 x[MT];
 #pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    float x[4];
+                for (int a = 0; a < MT; ++a)
+                    x[a] = *as_global(reinterpret_cast<const f32x4 *>(P.xres + (unsigned)min(m0 + t_lane + a * 32, P.n_rows - 1) * (unsigned)h + (unsigned)col));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int row = min(m0 + r_lane + a * 32 + e4 * 8 + e, P.n_rows - 1);
-                        x[e] = P.xres[(unsigned)row * (unsigned)h + (unsigned)col];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int row = m0 + r_lane + a * 32 + e4 * 8 + e;
-                        const unsigned at = (unsigned)row * (unsigned)h + (unsigned)col;
-                        const float o = x[e] + ((acc[a][b][4 * e4 + e] + bde) + bdn);
-                        if (row < P.n_rows) {
-                            if (last) P.out[at] = __float2half_rn(o);
-                            else P.xnext[at] = o;
-                        }
+                for (int a = 0; a < MT; ++a) {
+                    const int row = m0 + t_lane + a * 32;
+                    if (row >= P.n_rows) continue;
+                    const unsigned at = (unsigned)row * (unsigned)h + (unsigned)col;
+                    const f32x4 o{x[a][0] + ((acc[a][b][4 * g] + de0.x) + dn0.x), x[a][1] + ((acc[a][b][4 * g + 1] + de0.y) + dn0.y),
+                                  x[a][2] + ((acc[a][b][4 * g + 2] + de1.x) + dn1.x), x[a][3] + ((acc[a][b][4 * g + 3] + de1.y) + dn1.y)};
+                    if (last) {
+                        uint2 p;
+                        p.x = pf_pack2(o[0], o[1]); p.y = pf_pack2(o[2], o[3]);
+                        *reinterpret_cast<uint2 *>(P.out + at) = p;
+                    } else {
+                        *reinterpret_cast<f32x4 *>(P.xnext + at) = o;
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
