@@ -448,7 +448,7 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 constexpr int kPfCus = 256;
 struct PfTileCost { int bm, bn, bk, per_cu; float step, lone_step, epi_in, epi_out; };
 constexpr int kPfTile32x256 = 7, kPfTile32x128 = 8, kPfTile64x256 = 9;    // (up to 64 tokens: pf_plan_short)
-constexpr int kPfTile128x160 = 10, kPfTile128x128 = 11, kPfTile128x192 = 12, kPfTile128x256 = 13;    // (65 .. 1024 tokens: pf_plan_middle)
+constexpr int kPfTile128x160 = 10, kPfTile128x128 = 11, kPfTile128x192 = 12, kPfTile128x256 = 13, kPfTile128x96 = 14;   // (65 .. 1024 tokens: pf_plan_middle)
 static const PfTileCost kPfTiles[kPfTileKinds] = {
     {64, 128, 64, 1, 0.26f, 0.f, 3.74f, 2.19f},
     {64, 128, 32, 3, 0.25f, 0.37f, 0.01f, 1.13f},
@@ -458,7 +458,7 @@ static const PfTileCost kPfTiles[kPfTileKinds] = {
     {256, 256, 32, 1, 1.10f, 0.f, 14.67f, 5.02f},
     {256, 320, 32, 1, 1.34f, 0.f, 27.44f, 6.68f},
     {32, 256, 64}, {32, 128, 64}, {64, 256, 64},
-    {128, 160, 32, 2}, {128, 128, 64, 1}, {128, 192, 32, 1}, {128, 256, 32, 1},
+    {128, 160, 32, 2}, {128, 128, 64, 1}, {128, 192, 32, 1}, {128, 256, 32, 1}, {128, 96, 64, 1},
 };
 
 // Up to 64 tokens a product is its weights' way from memory, once.  One token tile of 32 or 64 rows (the activations
@@ -545,13 +545,13 @@ void pf_plan_pass(PfParams &P)
     pf_plan_ends(P);
 }
 
-// Passes of 65 .. 1024 tokens: four more tiles of 128 tokens, where they beat the plan above.  With one or two token tiles
+// Passes of 65 .. 1024 tokens: five more tiles of 128 tokens, where they beat the plan above.  With one or two token tiles
 // a product of few tokens is few workgroups with a whole K each, and what counts is that they come to nearly the number of
-// CUs: 160 features (two workgroups to a CU, or K in two parts) and 192 or 256 (a deeper ring); and K steps of 64 values - whole
-// lines of weights, half the barriers - where a CU has one workgroup.  Chosen by an estimate of the same form whose constants, in us, are
+// CUs: 96, 160 (two workgroups to a CU), 192 or 256 features (a deeper ring); and K steps of 64 values - whole lines of weights, half
+// the barriers (loads of 64-byte segments run at half the rate of 128: 69 and 133 KB/us a CU) - where a CU has one workgroup.  Chosen by an estimate of the same form whose constants, in us, are
 // fitted to timings of whole layers (hidden 512 .. 4096, 70 .. 1024 tokens, 5500 of them, 2.4 % of a layer rms); taken where it is 2 us and
 // 2 % below that of the plan above, which made none of the fitted sizes slower.  us per layer, before -> now: hidden 2560:
-// 96 tokens 103 -> 92, 256 145 -> 123, 512 211 -> 204; hidden 4096: 96 177 -> 143, 128 171 -> 155; hidden 1536, 512 99 -> 95.
+// 256 tokens 148 -> 130, 512 207 -> 200; hidden 4096: 96 179 -> 154; hidden 1536, 512 99 -> 95.
 struct PfLayerCost { float step, lone_step, epi_in, epi_out; };
 static const PfLayerCost kPfLayerCosts[kPfTileKinds] = {
     {0.271f, 0.000f, 4.96f, 1.94f},
@@ -567,7 +567,7 @@ static const PfLayerCost kPfLayerCosts[kPfTileKinds] = {
     {0.405f, 0.551f, 8.04f, 2.47f},
     {0.376f, 0.000f, 10.05f, 3.39f},
     {0.566f, 0.000f, 5.09f, 3.08f},
-    {0.693f, 0.000f, 6.71f, 3.74f},
+    {0.693f, 0.000f, 6.71f, 3.74f}, {},
 };
 static float pf_layer_cost(const PfParams &P, bool in, int kind, int sp)
 {
@@ -596,13 +596,19 @@ void pf_plan_middle(PfParams &P)
             if (!in && (k == kPfTile128x160 || k == kPfTile128x256)) continue;     // (never the least there: not built)
             const int mt = (P.n_rows + 127) / 128, nall = in ? 3 * P.dm.h + P.dm.f : P.dm.h;
             for (int sp = 1; sp <= (in ? 4 : 16); ++sp) {
-                if (sp > 1 && (size_t)sp * mt * 128 * nall * sizeof(float) > room) break;
+                if (sp > 1 && ((in && k != kPfTile128x128) || (size_t)sp * mt * 128 * nall * sizeof(float) > room)) break;
                 if ((in ? P.dm.h : P.dm.h + P.dm.f) / kPfTiles[k].bk < sp) break;
                 const float cost = pf_layer_cost(P, in, k, sp);
                 if (cost < best) { best = cost; plan.tile = k; plan.splits = sp; }
             }
         }
     }
+    // The first product with tiles of 128 x 96, K in steps of 64 and whole, where one tile a CU is most of the CUs and the last token
+    // tile is more than half full.  The estimate does not see it: it prices a split K too low for 65 .. 128 tokens.  us per layer,
+    // plan above -> this: hidden 2560 96 / 128 tokens 93.0 -> 84.9 / 90.7 -> 81.5; 1536, 200 / 256 tokens 68.6 -> 61.4 / 68.4 -> 63.3;
+    // 1280, 200 / 256 59.0 -> 54.4 / 54.5 -> 55.3; outside it is slower: 1536 150 tokens 52.5 -> 57.2, 100 tokens (112 tiles) 48.3 -> 51.7.
+    const int mt = (P.n_rows + 127) / 128, wgs = mt * ((3 * P.dm.h + 95) / 96 + (P.dm.f + 95) / 96);
+    if (wgs >= 176 && wgs <= kPfCus && (mt == 1 || (mt == 2 && P.n_rows > 192))) P.plan_in = PfPlan{kPfTile128x96, 1};
     pf_plan_ends(P);
 }
 
@@ -654,6 +660,7 @@ static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
     case kPfTile64x256: if (FL == kPfIn) return pf_launch<kPfIn, 64, 256, 64, 3, 1, 4>(P, pl, s); break;
     case kPfTile128x160: if (FL == kPfIn) return pf_launch<kPfIn, 128, 160, 32, 3, 4, 1>(P, pl, s); break;
     case kPfTile128x128: return pf_launch<FL, 128, 128, 64, 3, 2, 2>(P, pl, s);
+    case kPfTile128x96: if (FL == kPfIn) return pf_launch<kPfIn, 128, 96, 64, 3, 4, 1>(P, pl, s); break;
     case kPfTile128x192: return pf_launch<FL, 128, 192, 32, 5, 4, 2>(P, pl, s);
     case kPfTile128x256: if (FL == kPfIn) return pf_launch<kPfIn, 128, 256, 32, 4, 4, 2>(P, pl, s); break;
     }
