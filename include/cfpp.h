@@ -173,9 +173,10 @@ void cfpp_destroy(cfpp_ctx *ctx);
  * belong on one stream. */
 #define CFPP_OPT_MODE     1  /* CFPP_MODE_AUTO (the default): the fastest mode
                                 that supports the call - the batched path's
-                                three kernels (0) for several sequences, for a
-                                block on its own and for a stack step of hidden
-                                size < 2048, the whole-stack kernel (2) for a
+                                three kernels (0) for several sequences, three of
+                                the same cut for a block on its own and for a
+                                single sequence's stack step of hidden size
+                                < 2048, the whole-stack kernel (2) for a
                                 stack step of hidden size >= 2048, when the shape
                                 and the device allow it, else the phase kernels
                                 (0); never refuses a call for the mode's sake;
@@ -213,7 +214,13 @@ cfpp_status cfpp_get_option(const cfpp_ctx *ctx, int32_t option, int64_t *value)
  * projections run on the matrix cores; needs 512 threads, hidden and ffn
  * multiples of 256, at most 64 matrix rows per workgroup, else - and in the
  * other launch modes - the sequences run one after the other).  With several
- * sequences a bad position in any of a group skips the whole group's step. */
+ * sequences a bad position in any of a group skips the whole group's step.
+ * Range: a sequence on its own keeps every intermediate value in fp32.  What
+ * enters the matrix cores - gamma x of both LayerNorms, GELU(up) and the attention
+ * output, in a group of two or more sequences (tokens) and in
+ * cfpp_stack_prefill_gemm - is an fp16 head and an fp16 remainder: the value to
+ * 2^-22 of itself or to 2^-25, whichever is more, and NaN from 65520 on; such a
+ * sequence's (token's) output and appended rows are then NaN. */
 cfpp_status cfpp_block_decode(cfpp_ctx *ctx, const void *packed_layer, void *kv_layer,
                               const void *x, const int32_t *pos_dev, int32_t batch,
                               void *out, cfpp_stream stream);
@@ -277,8 +284,8 @@ cfpp_status cfpp_stack_prefill(cfpp_ctx *ctx, const void *const *packed_layers,
  * and MLP-down: tokens x K activations times K x rows weights, here the paper's
  * memory-bound GEMVs, Sec. 2.2, are dense contractions), one causal-attention launch
  * over the cache rows the pass has just appended, and a LayerNorm launch.  Activations enter the fp16 matrix
- * instruction as head + remainder, so the products match the fp32 path to
- * rounding.  Arguments as for cfpp_stack_prefill, plus
+ * instruction as head + remainder (range: see cfpp_block_decode), so the products
+ * match the fp32 path to rounding.  Arguments as for cfpp_stack_prefill, plus
  *   scratch      : DEVICE, 256-byte aligned, at least
  *                  cfpp_prefill_scratch_bytes(cfg, rows) bytes; the caller's,
  *                  contents undefined afterwards

@@ -215,7 +215,8 @@ struct cfpp_ctx {
     unsigned long long graph_epochs;   // tagged-word epochs one replay of the captured graph uses up
     int fused_grid, fused_threads;     // launch shape the whole-stack kernel was last found to fit
     bool fused_ok;
-    int planes;             // tokens whose GELU(up) and attention output the last step left as heads and remainders (ng_at); 0: fp32
+    int planes;             // tokens whose GELU(up) and attention output the last step left in groups of kBatMax, as heads and remainders
+                            // (ng_at) unless a group is one token; 0: fp32 throughout
 };
 
 extern "C" cfpp_status cfpp_create(const cfpp_config *c, void *workspace, size_t workspace_bytes,
@@ -414,6 +415,7 @@ static cfpp_status prepare(cfpp_ctx *ctx)
     HIP_OK(prepare_kernels(160 * 1024));
     HIP_OK(prepare_fused_kernels(160 * 1024));
     HIP_OK(prepare_narrow_kernels());
+    HIP_OK(prepare_lone_kernels());
     ctx->prepared = true;
     return CFPP_OK;
 }
@@ -481,9 +483,10 @@ static bool batched_path_shape(const cfpp_ctx *ctx, const Shape &sh)
 {
     return !(ctx->dm.flags & kFlagSequentialResidual) && bat_supported(ctx->dm, sh.grid, sh.threads);
 }
-// A single sequence takes it too where nothing asks for another mode or launch shape.  Measured, us a block, phase
-// kernels (whole-stack kernel from hidden 2048) -> narrow products, 20 .. 8000 positions: hidden 512 20.4 .. 29.9 -> 16.3 .. 20.0,
-// 1280 33.2 .. 43.4 -> 21.9 .. 30.0, 2560 42.0 .. 52.0 -> 36.2 .. 48.8, 4096 77.8 .. 95.0 -> 70.5 .. 91.8.
+// A single sequence takes the same three launches, with products of its own that keep fp32 (lone_gemm.hip), where nothing
+// asks for another mode or launch shape.  Measured, us a block, phase kernels (whole-stack kernel from hidden 2048) -> these,
+// 20 .. 8000 positions: hidden 512 20.9 .. 28.9 -> 15.1 .. 19.5, 1536 27.4 .. 38.2 -> 20.5 .. 28.3, 2560 41.6 .. 51.0 -> 34.4 .. 46.7,
+// 4096 77.2 .. 94.1 -> 69.7 .. 90.2.
 static bool batched_path(const cfpp_ctx *ctx, const Shape &sh, int batch, bool single)
 {
     return (batch > 1 || single) && batched_path_shape(ctx, sh);
@@ -513,15 +516,17 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
         B.out = static_cast<__half *>(out) + (size_t)b0 * dm.h;
         B.xres = reinterpret_cast<float *>(ctx->ws + wl.xres) + (size_t)b0 * 2 * dm.h;
         B.q = reinterpret_cast<float *>(ctx->ws + wl.q) + (size_t)b0 * dm.h;
-        B.m = reinterpret_cast<__half *>(ctx->ws + wl.m + (size_t)b0 * dm.f * 4);
-        B.o = reinterpret_cast<__half *>(ctx->ws + wl.o + (size_t)b0 * dm.h * 4);
+        B.m32 = reinterpret_cast<float *>(ctx->ws + wl.m) + (size_t)b0 * dm.f;
+        B.o32 = reinterpret_cast<float *>(ctx->ws + wl.o) + (size_t)b0 * dm.h;
+        B.m = reinterpret_cast<__half *>(B.m32);
+        B.o = reinterpret_cast<__half *>(B.o32);
         B.rope = reinterpret_cast<const float2 *>(ctx->ws + wl.rope);
         B.sync = reinterpret_cast<unsigned *>(ctx->ws + wl.sync);
-        HIP_OK(launch_bat_in(B, ctx->n_cu, s));
+        HIP_OK((B.n > 1 ? launch_bat_in : launch_lone_in)(B, ctx->n_cu, s));
         StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
         if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
         HIP_OK(launch_attention_batched(P, B.n, kv, s));
-        HIP_OK(launch_bat_out(B, ctx->n_cu, s));
+        HIP_OK((B.n > 1 ? launch_bat_out : launch_lone_out)(B, ctx->n_cu, s));
     }
     return CFPP_OK;
 }
@@ -577,10 +582,10 @@ static cfpp_status check_io(const cfpp_ctx *ctx, const void *x, const int32_t *p
 // supports the call and never refuses: the batched path (mode 0 with *narrow_out) for several
 // sequences, for a block on its own and for a step of several layers of hidden sizes below 2048; the
 // whole-stack kernel, where its shape limits and the residency check allow it, for a step of several
-// layers from hidden 2048 on (a layer, batched path against it, at 20 / 4000 positions: hidden 2048 29.8 / 36.8
-// against 28.9 / 33.1 us, 2560 36.4 / 45.0 against 32.7 / 37.0; below it hidden 1536 21.3 / 27.4 against 23.4 / 29.8,
-// 1024 17.7 / 24.1 against 22.1 / 27.5); else the phase kernels.  An explicit grid keeps a single
-// sequence with the kernels that follow it.
+// layers from hidden 2048 on (a layer, batched path against it, at 20 / 1024 / 4000 positions: hidden 2048 26.9 / 30.9 / 34.7
+// against 29.0 / 31.0 / 33.1 us, 2560 35.9 / 38.5 / 43.0 against 32.9 / 34.1 / 36.9; below it hidden 1536 19.8 / 22.7 / 25.2 against
+// 23.4 / 28.3 / 29.9, 1024 15.9 / 19.6 / 22.6 against 21.9 / 25.8 / 27.6); else the phase kernels.  An explicit grid keeps a
+// single sequence with the kernels that follow it.
 static cfpp_status resolve_mode(cfpp_ctx *ctx, const Shape &sh, const StepParams &P, int batch, bool stack,
                                 int *mode_out, bool *narrow_out)
 {
@@ -1143,7 +1148,7 @@ extern "C" cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_
     }
     if (count > n) return fail(CFPP_EINVAL, "count %zu exceeds the buffer (%zu floats)", count, n);
     HIP_OK(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
-    if ((which == 1 || which == 3) && ctx->planes > 0) {   // heads and remainders, in groups of kBatMax tokens
+    if ((which == 1 || which == 3) && ctx->planes > 1) {   // heads and remainders, in groups of kBatMax tokens
         const int width = which == 1 ? dm.f : dm.h;
         std::vector<__half> planes(2 * n);
         HIP_OK(hipMemcpy(planes.data(), ctx->ws + off, 2 * n * sizeof(__half), hipMemcpyDeviceToHost));
@@ -1151,6 +1156,7 @@ extern "C" cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_
             const int token = (int)(e / width), g0 = token / kBatMax * kBatMax, left = ctx->planes - g0, nt = left < kBatMax ? left : kBatMax;
             const __half *p = planes.data() + (size_t)g0 * width * 2;
             if (token >= ctx->planes) { dst_host[e] = 0.f; continue; }
+            if (nt == 1) { dst_host[e] = reinterpret_cast<const float *>(p)[e % width]; continue; }
             const size_t at = ng_at(token - g0, (int)(e % width), width, nt);
             const float hi = __half2float(p[at]);
             dst_host[e] = std::isinf(hi) ? hi : hi + __half2float(p[at + 8 * nt]);

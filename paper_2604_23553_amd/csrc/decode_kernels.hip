@@ -587,11 +587,12 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv)
         for (int e = 0; e < NE; ++e)
             if (lane + 64 * e < D) O[e] += wp[w * D + lane + 64 * e] * ew;
     }
-    auto deliver = [&]() {                                 // heads and remainders, as the output projection takes them
+    auto deliver = [&]() {                                 // as the output projection takes them: heads and remainders; one sequence's in fp32
         __half *out = reinterpret_cast<__half *>(P.o);
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             if (lane + 64 * e >= D) continue;
+            if (nb == 1) { P.o[head * D + lane + 64 * e] = O[e] / L; continue; }
             __half hi, lo;
             split_half(O[e] / L, hi, lo);
             const size_t at = ng_at(mine, head * D + lane + 64 * e, dm.h, nb);

@@ -1,5 +1,6 @@
-// An fp32 value as two fp16 values, head and remainder (v = hi + lo to ~2^-22): what the matrix-core paths feed
-// the fp16 instruction in turn.
+// An fp32 value as two fp16 values, head and remainder: what the matrix-core paths feed the fp16 instruction in turn.
+// v = hi + lo to 2^-22 |v| or, where the remainder is subnormal, to 2^-25; from 65520 on the head is infinite and the two are NaN
+// together.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>

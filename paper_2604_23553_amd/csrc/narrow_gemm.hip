@@ -1,4 +1,5 @@
-// Projections of a layer for few tokens (paper Sec. 2.2): the sequences of a decode step, a group of prompt tokens.  The
+// Projections of a layer for few tokens (paper Sec. 2.2): the sequences of a decode step, a group of prompt tokens; two to
+// eight of them (one: lone_gemm.hip).  The
 // weights are read once and their way from memory is what takes time, so everything here is arranged around that stream.
 //
 //   k_ng_in  : both LayerNorms, QKV rows + bias, rotary, K/V append, q; MLP-up rows + bias + GELU

@@ -1,5 +1,5 @@
-// Arguments of the narrow products (narrow_gemm.hip): a layer's projections for a few tokens - sequences of a
-// decode step, a group of prompt tokens, or a short prompt.
+// Arguments of the narrow products (narrow_gemm.hip, lone_gemm.hip): a layer's projections for a few tokens - sequences
+// of a decode step or a single one, a group of prompt tokens, or a short prompt.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -36,14 +36,20 @@ struct NarrowParams {
     float *xres;            // [n][2][h]
     float *q;               // [n][h]
     __half *m, *o;          // planes (ng_at): GELU(up), attention output
+    float *m32, *o32;       // the same in fp32, in the same memory: a single sequence's (lone_gemm.hip)
     const float2 *rope;
     unsigned *sync;
     int rows, wgs_q;        // matrix rows per workgroup, workgroups of the QKV matrix (set by the launcher)
 };
 
 bool bat_supported(const Dims &dm, int grid, int threads);
+// several sequences or tokens (narrow_gemm.hip)
 hipError_t launch_bat_in(NarrowParams P, int n_cu, hipStream_t s);
 hipError_t launch_bat_out(NarrowParams P, int n_cu, hipStream_t s);
 hipError_t prepare_narrow_kernels();
+// one (lone_gemm.hip)
+hipError_t launch_lone_in(NarrowParams P, int n_cu, hipStream_t s);
+hipError_t launch_lone_out(NarrowParams P, int n_cu, hipStream_t s);
+hipError_t prepare_lone_kernels();
 
 }  // namespace cfpp

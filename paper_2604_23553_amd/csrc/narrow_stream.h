@@ -10,7 +10,7 @@
 // eight pieces of 64 bytes instead of one KiB, hence ng_at).
 //
 // v_mfma_f32_16x16x32_f16: A = 16 rows x 32 columns of weights, from the ring; B = the same 32 columns of 8 tokens, the
-// fp16 heads of their fp32 activations in columns 0..7 and the remainders in 8..15 (y = hi + lo to ~2^-22): one
+// fp16 heads of their fp32 activations in columns 0..7 and the remainders in 8..15 (half_split.h): one
 // instruction per KiB of weights and set.  The two columns of a token and the wavefronts' parts of K are added in a fixed
 // order at the end: one bit pattern per build.
 #pragma once

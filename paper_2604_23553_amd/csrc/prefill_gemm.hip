@@ -1,6 +1,6 @@
 // Projections of the prompt-sized path (paper Sec. 2.2 applied to hundreds of tokens): C[tokens][n] =
 // A[tokens][K] . W[n][K]^T as LDS-tiled GEMMs on the matrix cores (v_mfma_f32_32x32x16_f16).
-// Activations are two fp16 planes, head and remainder (y = hi + lo to ~2^-22), each fed to the
+// Activations are two fp16 planes, head and remainder (half_split.h), each fed to the
 // instruction in turn: the product of the fp32 values to rounding, fp32 accumulation.
 //
 //   k_pf_gemm<kPfIn>  : QKV rows and MLP-up rows of a layer, one launch (their output columns side by

@@ -8,7 +8,7 @@
 //
 //   k_pf_row<>  : per token: (the previous layer's output from the parts of its product,)
 //                 mean, 1/sigma, and gamma_1 * x, gamma_2 * x as two fp16 planes each (head +
-//                 remainder: y = hi + lo to ~2^-22, so that the fp16 matrix instruction
+//                 remainder: y = hi + lo (half_split.h), so that the fp16 matrix instruction
 //                 reproduces the fp32 product to rounding)
 //   the products: prefill_gemm.hip - QKV and MLP-up in one launch, output projection and
 //                 MLP-down as one product

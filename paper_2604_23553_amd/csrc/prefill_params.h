@@ -17,7 +17,7 @@ CFPP_HD size_t pf_row_halves(int width) { return 2 * (size_t)width + 128; }
 
 // Scratch of one pass over `rows` tokens (rows a multiple of kPfTile), byte
 // offsets; the caller owns the memory.  Activations that feed a GEMM are kept
-// as two fp16 planes, head and remainder (y = hi + lo to ~2^-22), interleaved: a row is
+// as two fp16 planes, head and remainder (half_split.h), interleaved: a row is
 // groups of 64 halves, the heads of 32 consecutive values and then their remainders, so that
 // 32 values of K are one 128-byte line (see pf_at); rows sit pf_row_halves apart.
 struct PfLayout {

@@ -1,0 +1,130 @@
+"""A single sequence keeps its activations in fp32 (csrc/lone_gemm.hip): inputs whose gamma x or GELU(up) fp16 does not hold,
+inputs and cached values so small that fp16 remainders are subnormal, and inputs far from zero mean, against the oracle and
+against the phase kernels, which have held the same values in fp32 all along."""
+import numpy as np
+import pytest
+
+import synth
+from tests.parity import U32, assert_appended_rows, assert_block_close, rounding_bound, ulp16
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(h, d, f, r, layers=1, flags=0):
+    return synth.ModelShape(h, h // d, d, r, f, n_layers=layers, flags=flags, name=f"d{d}-h{h}-f{f}")
+
+
+def _inputs(shape, kind, S, seed=83):
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, seed, 0).items()}
+    K, V = synth.kv_cache(shape, seed, 0, S, S + 2)
+    x = synth.x_input(shape, seed).astype(np.float32)
+    if kind == "large x":                                  # |gamma x| to 1e5
+        x = np.clip(x * 25000.0, -60000.0, 60000.0)
+        w["ln1_g"] *= np.float16(1.6)
+        w["ln2_g"] *= np.float16(1.6)
+    elif kind == "large up":                               # GELU(up) to 1e5, its products within fp16 again
+        w["w_up"] = (w["w_up"].astype(np.float32) * (2e6 / shape.hidden ** 0.5)).astype(np.float16)
+        w["w_down"] = (w["w_down"].astype(np.float32) * (2.0 / shape.ffn ** 0.5)).astype(np.float16)
+    elif kind == "large gain":                             # a LayerNorm output beyond fp16
+        w["ln2_g"][:] = np.float16(60000.0)
+        w["w_down"] = (w["w_down"].astype(np.float32) * (2.0 / shape.ffn ** 0.5)).astype(np.float16)
+    elif kind == "small":                                  # x, GELU(up) and the attention output some 1e-5
+        x = x * 1e-5
+        V = (V.astype(np.float32) * 1e-5).astype(np.float16)
+        w["w_qkv"].reshape(shape.n_heads, 3, shape.head_dim, shape.hidden)[:, 2] *= np.float16(0.01)
+        w["w_up"] *= np.float16(0.02)
+        for n in ("ln1_b", "ln2_b", "b_qkv", "b_up"):
+            w[n][:] = 0
+    elif kind == "offset":                                 # a mean of some 100 standard deviations
+        x = x * 0.5 + 60.0
+    return w, K, V, x.astype(np.float16)
+
+
+def _run(shape, w, K, V, x, S, mode):
+    """Output, appended rows, (q, GELU(up), attention output) of the profiling build; mode None: the allocation-free call."""
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    with cf.profile_build():
+        ds = DeviceStack(shape, S + 2, 1, 1)
+        try:
+            ds.load_layer(0, w)
+            ds.load_kv(0, K, V, S)
+            ds.set_inputs(x, S)
+            if mode is None:
+                cf.cfpp_block_decode_static(ds.cfg, ds.packed[0], ds.kv[0], ds.x, ds.pos, 1, ds.out, ds.s)
+                ds.stream.synchronize()
+                taps = None
+            else:
+                ds.set_options(mode=mode)
+                ds.block_decode(0)
+                ds.check()
+                taps = {n: ds.tap(i, shape.ffn if n == "m" else shape.hidden).astype(np.float64).ravel() for n, i in (("q", 0), ("m", 1), ("attn", 3))}
+            kg, vg = ds.export_kv(0, 0, S, 1)
+            return ds.result()[0].copy(), kg[:, 0].copy(), vg[:, 0].copy(), taps
+        finally:
+            ds.close()
+
+
+SHAPES = [_shape(128, 64, 128, 16), _shape(512, 64, 2048, 16), _shape(640, 80, 2560, 20), _shape(1536, 128, 6144, 32, flags=synth.FLAG_TANH_GELU),
+          _shape(2560, 80, 10240, 20)]
+
+
+@pytest.mark.parametrize("kind", ["usual", "large x", "large up", "large gain", "small", "offset"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+def test_values_that_fp16_does_not_hold(orc, shape, kind):
+    S = 40
+    print(f"[case] single sequence {shape.name} {kind}", flush=True)
+    w, K, V, x = _inputs(shape, kind, S)
+    ref, want = orc.block_decode(shape, w, K[0].copy(), V[0].copy(), S, orc.half_to_real(x[0]), taps=True)
+    ref = np.asarray(ref, dtype=np.float64).ravel()
+    want = {n: np.asarray(want[n], dtype=np.float64).ravel() if n in ("q", "m", "attn") else want[n] for n in want}
+    assert np.abs(ref).max() < 65000.0
+    if kind == "large x":
+        assert np.abs(x[0].astype(np.float64) * w["ln1_g"].astype(np.float64)).max() > 66000.0
+    if kind == "large gain":
+        assert np.abs(x[0].astype(np.float64) * w["ln2_g"].astype(np.float64)).max() > 66000.0
+    if kind == "large up":
+        assert want["m"].max() > 66000.0
+    runs = {mode: _run(shape, w, K, V, x, S, mode) for mode in (-1, 0, None)}
+    for mode, (out, kg, vg, taps) in runs.items():
+        assert np.isfinite(out.astype(np.float32)).all() and np.isfinite(kg.astype(np.float32)).all() and np.isfinite(vg.astype(np.float32)).all(), mode
+        assert_appended_rows(kg, vg, shape, w, orc.half_to_real(x[0]), want, f"mode {mode}")
+        # the output: a rounding of a sum whose terms carry fp32 errors
+        A = np.abs(w["w_down"].astype(np.float64)) @ np.abs(want["m"]) + np.abs(w["w_dense"].astype(np.float64)) @ np.abs(want["attn"]) + np.abs(x[0].astype(np.float64)) + 1.0
+        delta = 4.0 * rounding_bound(A, shape.hidden + shape.ffn)
+        assert (np.abs(out.astype(np.float64) - ref) <= 0.5 * ulp16(np.abs(ref) + delta) + delta).all(), f"mode {mode}: block output"
+    # no value that a later kernel reads is further from 64 bits than the phase kernels': of two fp32 evaluations in different
+    # orders neither is always the closer one (half as much again), and below a rounding of the value itself none is asked for
+    for n in ("q", "m", "attn"):
+        size = np.linalg.norm(want[n])
+        e = {mode: np.linalg.norm(runs[mode][3][n] - want[n]) / size for mode in (-1, 0)}
+        print(f"[result] {n}: phase kernels {e[0]:.2e}, automatic mode {e[-1]:.2e}", flush=True)
+        assert e[-1] <= 1.5 * e[0] + 2.0 * U32, (n, e)
+
+
+# Two layers of a stack below hidden 2048: the residual between them is fp32 and has no bound.
+@pytest.mark.parametrize("shape", [_shape(512, 64, 2048, 16, 2), _shape(640, 80, 2560, 20, 2)], ids=lambda s: s.name)
+def test_a_residual_beyond_fp16_between_layers(orc, shape):
+    from paper_2604_23553_amd.harness import DeviceStack
+    S = 20
+    print(f"[case] single sequence, large residual {shape.name}", flush=True)
+    ws = [{n: a.copy() for n, a in synth.layer_weights(shape, 85, l).items()} for l in range(2)]
+    ws[0]["w_down"] = (ws[0]["w_down"].astype(np.float32) * 3e5).astype(np.float16)
+    x = synth.x_input(shape, 85)
+    kvs = [synth.kv_cache(shape, 85, l, S, S + 1) for l in range(2)]
+    Ks, Vs = [kv[0][0].copy() for kv in kvs], [kv[1][0].copy() for kv in kvs]
+    ds = DeviceStack(shape, S + 1, 1, 2)
+    try:
+        for l in range(2):
+            ds.load_layer(l, ws[l])
+            ds.load_kv(l, kvs[l][0], kvs[l][1], S)
+        ds.set_inputs(x, S)
+        ds.stack_decode()
+        ds.check()
+        rows = ds.export_kv(1, 0, S, 1)
+    finally:
+        ds.close()
+    assert np.abs(orc.block_decode(shape, ws[0], Ks[0].copy(), Vs[0].copy(), S, orc.half_to_real(x[0]))).max() > 7e4
+    orc.stack_decode(shape, ws, Ks, Vs, S, x[0])
+    for got, want in zip(rows, (Ks[1], Vs[1])):
+        assert_block_close(got[:, 0], want[:, S], "second layer's appended row")
