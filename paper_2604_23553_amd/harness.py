@@ -32,7 +32,7 @@ class DeviceStack:
         # 0xFF bytes = fp16 NaN everywhere: any read of a never-written slot shows up
         self.kv = [torch.full((B.cfpp_kv_layer_bytes(self.cfg),), 0xFF, **u8) for _ in range(self.L)]
         self.ws_bytes = B.cfpp_workspace_bytes(self.cfg)
-        self.ws = torch.empty(self.ws_bytes, **u8)
+        self.ws = torch.full((self.ws_bytes,), 0xFF, **u8)
         self.x = torch.zeros(max_batch, shape.hidden, dtype=torch.float16, device=self.dev)
         self.out = torch.zeros_like(self.x)
         self.pos = torch.zeros(max_batch, dtype=torch.int32, device=self.dev)

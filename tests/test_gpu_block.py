@@ -65,8 +65,9 @@ def check_block(orc, shape, seed, S, cap, **kw):
         assert np.array_equal(o.view(np.uint16), outs[0].view(np.uint16)), "not bit-identical run to run"
     if tap is not None:
         # (the whole-stack kernel keeps the down projection in registers and passes the
-        # attention output on as tagged words: no workspace copy of either)
-        names = ("q", "m") if kw.get("mode") == 2 else ("q", "m", "g", "attn")
+        # attention output on as tagged words: no workspace copy of either; the automatic mode's
+        # products add the down projection to the output projection in one sum)
+        names = {2: ("q", "m"), -1: ("q", "m", "attn")}.get(kw.get("mode"), ("q", "m", "g", "attn"))
         for n in names:
             e = errors(tap[n], otaps[n])
             assert e[0] < 2e-3 and e[1] < 2e-4, f"intermediate {n}: {e}"

@@ -80,7 +80,7 @@ def test_tiny_stack_direct_and_graph(orc, mode, graph):
         ds.close()
 
 
-@pytest.mark.parametrize("mode", [0, 2])
+@pytest.mark.parametrize("mode", [0, 2, -1])
 def test_bit_identical_over_replays_and_across_processes(mode):
     """Every reduction runs in a fixed order: 20 graph replays of one process give
     the same bytes (output and appended K/V rows), and so does a fresh process."""

@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 def both_ways(shape, seed, lens, cap):
-    """One block step through the context entry point (launch mode 0) and through the
-    static one, each on its own copy of the cache.  Returns (out, appended K, V) twice."""
+    """One block step through the context entry point (launch mode 0, the batched path; one sequence:
+    the automatic mode, which runs what the static call runs) and through the static one, each on its own copy of the cache.  Returns (out, appended K, V) twice."""
     import torch
     import paper_2604_23553_amd as cf
     from paper_2604_23553_amd.harness import DeviceStack
@@ -33,7 +33,7 @@ def both_ways(shape, seed, lens, cap):
                 cf.cfpp_block_decode_static(ds.cfg, ds.packed[0], ds.kv[0], ds.x, ds.pos, B, ds.out, ds.s)
                 ds.stream.synchronize()
             else:
-                ds.set_options(mode=0)
+                ds.set_options(mode=0 if B > 1 else -1)
                 ds.block_decode(0)
                 ds.check()
             out = ds.result().copy()
