@@ -603,12 +603,18 @@ void pf_plan_middle(PfParams &P)
             }
         }
     }
-    // The first product with tiles of 128 x 96, K in steps of 64 and whole, where one tile a CU is most of the CUs and the last token
-    // tile is more than half full.  The estimate does not see it: it prices a split K too low for 65 .. 128 tokens.  us per layer,
-    // plan above -> this: hidden 2560 96 / 128 tokens 93.0 -> 84.9 / 90.7 -> 81.5; 1536, 200 / 256 tokens 68.6 -> 61.4 / 68.4 -> 63.3;
-    // 1280, 200 / 256 59.0 -> 54.4 / 54.5 -> 55.3; outside it is slower: 1536 150 tokens 52.5 -> 57.2, 100 tokens (112 tiles) 48.3 -> 51.7.
-    const int mt = (P.n_rows + 127) / 128, wgs = mt * ((3 * P.dm.h + 95) / 96 + (P.dm.f + 95) / 96);
-    if (wgs >= 176 && wgs <= kPfCus && (mt == 1 || (mt == 2 && P.n_rows > 192))) P.plan_in = PfPlan{kPfTile128x96, 1};
+    // The first product with tiles of 128 x 96, K in steps of 64 and whole, one to a CU, where tiles of 64 x 128 no longer are: from
+    // there on the plan above pairs these, or splits K into more workgroups than CUs, and its estimate (of products whose weights
+    // are in the Infinity Cache in part) does not see what that costs.  us per layer, 900 MB of layers so that weights come from
+    // memory, plan above -> this, by workgroups of 64 x 128 tiles: 252 .. 255: hidden 1536, 192 tokens 55.0 -> 60.6, 2304, 96 tokens
+    // 73.4 -> 75.1, 2176 / 4352 (hidden / ffn), 176 tokens 64.7 -> 71.2; 260 .. 280: 1664 / 3328, 224 tokens 61.9 -> 60.6, 2432, 96
+    // tokens 94.3 -> 79.1, 1664, 176 tokens 68.5 -> 65.9, 1280, 256 tokens 56.7 -> 55.9, 2560, 96 tokens 104.2 -> 86.6; above: 1536, 224
+    // tokens 70.9 -> 65.0, 4096 / 8192, 96 tokens 139 -> 117.  Of 90 timed sizes above the line (hidden 1280 .. 4096) none was slower, of
+    // 108 below it 93 were.  With fewer than 1280 values of K the products are so short that either may be ahead: 1024 / 8192, 190
+    // tokens 50.8 -> 52.0, 512, 640 tokens 43.5 -> 45.3, 1024, 384 tokens 55.0 -> 53.8.
+    const int h = P.dm.h, f = P.dm.f, wgs64 = (P.n_rows + 63) / 64 * ((3 * h + f) / 128);
+    const int wgs96 = (P.n_rows + 127) / 128 * ((3 * h + 95) / 96 + (f + 95) / 96);
+    if (P.n_rows <= 256 && h >= 1280 && wgs64 > kPfCus && wgs96 <= kPfCus) P.plan_in = PfPlan{kPfTile128x96, 1};
     pf_plan_ends(P);
 }
 

@@ -4,6 +4,7 @@ tile that only such passes take, with K split and whole where a plan does (held 
 from tests.prefill_plans import H1024, H2560, H4096, _shape
 
 H1536, H1920, H3200 = _shape(1536, 64, 6144, 16), _shape(1920, 80, 7680, 20), _shape(3200, 80, 12800, 20)
+H1664 = _shape(1664, 64, 6656, 16)
 
 MIDDLE = [
     (H2560, 100, (128, 96, 64, 1), None),
@@ -12,6 +13,7 @@ MIDDLE = [
     (H1920, 100, (128, 128, 64, 2), None),
     (H1536, 512, (128, 192, 32, 1), None),
     (H1536, 205, (128, 96, 64, 1), None),
+    (H1664, 130, (128, 96, 64, 1), None),
     (H1024, 900, (128, 256, 32, 1), None),
     (H1536, 900, None, (128, 192, 32, 4)),
 ]
