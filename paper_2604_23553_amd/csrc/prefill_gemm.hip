@@ -610,11 +610,12 @@ void pf_plan_middle(PfParams &P)
     // 73.4 -> 75.1, 2176 / 4352 (hidden / ffn), 176 tokens 64.7 -> 71.2; 260 .. 280: 1664 / 3328, 224 tokens 61.9 -> 60.6, 2432, 96
     // tokens 94.3 -> 79.1, 1664, 176 tokens 68.5 -> 65.9, 1280, 256 tokens 56.7 -> 55.9, 2560, 96 tokens 104.2 -> 86.6; above: 1536, 224
     // tokens 70.9 -> 65.0, 4096 / 8192, 96 tokens 139 -> 117.  Of 90 timed sizes above the line (hidden 1280 .. 4096) none was slower, of
-    // 108 below it 93 were.  With fewer than 1280 values of K the products are so short that either may be ahead: 1024 / 8192, 190
-    // tokens 50.8 -> 52.0, 512, 640 tokens 43.5 -> 45.3, 1024, 384 tokens 55.0 -> 53.8.
+    // 108 below it 93 were.  Shorter products lose more of a pair's gain to their ends: below hidden 1280 the line lies higher (264:
+    // 1024 / 8192, 190 tokens 50.8 -> 52.0, 768 / 6144, 200 tokens 44.3 -> 45.2; 308 and 352: 896 / 7168 and 1024 / 8192, 200 tokens 52.0 -> 49.2,
+    // 57.4 -> 53.8), and with more than 256 tokens either may be ahead (512, 640 tokens 43.5 -> 45.3, 1024, 384 tokens 55.0 -> 53.8).
     const int h = P.dm.h, f = P.dm.f, wgs64 = (P.n_rows + 63) / 64 * ((3 * h + f) / 128);
     const int wgs96 = (P.n_rows + 127) / 128 * ((3 * h + 95) / 96 + (f + 95) / 96);
-    if (P.n_rows <= 256 && h >= 1280 && wgs64 > kPfCus && wgs96 <= kPfCus) P.plan_in = PfPlan{kPfTile128x96, 1};
+    if (P.n_rows <= 256 && wgs64 > (h >= 1280 ? kPfCus : kPfCus + 32) && wgs96 <= kPfCus) P.plan_in = PfPlan{kPfTile128x96, 1};
     pf_plan_ends(P);
 }
 
