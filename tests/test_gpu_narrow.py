@@ -8,6 +8,7 @@ import torch                       # (ahead of the library: both take the HIP ru
 import synth
 from tests.parity import assert_appended_rows, assert_block_close
 from tests.prefill_middle import MIDDLE
+from tests.prefill_plans import WIDE
 from tests.test_gpu_stack import _batched_case, check_appended_rows
 
 pytestmark = pytest.mark.gpu
@@ -77,11 +78,10 @@ def test_short_prompts(orc, shape, T):
 
 
 # The tiled products of few tokens, where the narrow ones do not go: an MLP of more than 128 rows to a CU.
-@pytest.mark.parametrize("T", [20, 40, 64])
-def test_short_prompts_in_tiles(orc, T):
+@pytest.mark.parametrize("shape,T", WIDE)
+def test_short_prompts_in_tiles(orc, shape, T):
     import paper_2604_23553_amd as cf
     from tests.test_gpu_prefill import _check_prompt
-    shape = _shape(512, 64, 32768, 16)
     with cf.profile_build():
         assert cf.cfpp_debug_prefill_narrow(cf.Config.from_shape(shape, 16), 128, T) is None
     _check_prompt(orc, shape, 31, 3, T, 1, 0, then_decode=False, gemm_rows=128, row_check_every=9)
@@ -158,4 +158,4 @@ def test_middle_tiles_over_two_layers(shape, T, first, second):
     with cf.profile_build():
         base, got = cf.cfpp_debug_prefill_plan(cfg, rows, T)[0], cf.cfpp_debug_prefill_tiles(cfg, rows, T)[0]
     assert got == (first or base[0], second or base[1])
-    check(shape, T, *base)
+    check(shape, T, *got)

@@ -6,7 +6,7 @@ import pytest
 
 import synth
 from tests.parity import assert_appended_rows, assert_block_close, errors
-from tests.prefill_plans import PLANS
+from tests.prefill_plans import PLANS, taken
 
 pytestmark = pytest.mark.gpu
 
@@ -205,12 +205,10 @@ def test_gemm_tiles_against_the_batched_projections(shape, pos0, T):
 @pytest.mark.parametrize("shape,T,first,second", PLANS)
 def test_gemm_plans_over_two_layers(shape, T, first, second):
     import torch
-    import paper_2604_23553_amd as cf
     import synth.device as sdev
     from paper_2604_23553_amd.harness import DeviceStack
     rows, pos0 = (T + 127) // 128 * 128, 3
-    with cf.profile_build():
-        assert cf.cfpp_debug_prefill_plan(cf.Config.from_shape(shape, pos0 + T), rows, T)[0] == (first, second)
+    assert taken(shape, T)[0] == (first, second)
     print(f"[case] gemm plan shape={shape.name} T={T}", flush=True)
     ds = DeviceStack(shape, pos0 + T, 8, 2)
     try:

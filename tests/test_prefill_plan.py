@@ -7,7 +7,9 @@ import re
 import pytest
 
 import paper_2604_23553_amd as cf
-from tests.prefill_plans import PLANS
+import synth
+from tests.prefill_middle import MIDDLE
+from tests.prefill_plans import PLANS, WIDE, kinds, taken
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(cf.__file__)), "csrc")
 TOKENS = (1, 20, 32, 33, 64, 65, 100, 128, 129, 256, 300, 384, 500, 640, 900, 1100, 1153, 1408, 1531, 2048, 2600, 2688,
@@ -32,19 +34,20 @@ def test_no_tile_loads_outside_its_operands(h, d):
 
 @pytest.mark.parametrize("shape,tokens,first,second", PLANS)
 def test_what_a_size_selects(shape, tokens, first, second):
-    got, _ = plan(shape.hidden, shape.head_dim, shape.ffn, tokens)
-    assert got == (first, second)
+    got, past = taken(shape, tokens)
+    assert got == (first, second) and past == ((0, 0), (0, 0))
 
 
-def test_the_passes_run_on_the_gpu_take_every_tile_that_plans_take():
-    def kinds(p):
-        return {(k, p[k][:3], p[k][3] > 1) for k in (0, 1)}
-    run = set().union(*(kinds(p[2:]) for p in PLANS))
-    for h, d in ((128, 64), (256, 64), (512, 64), (640, 80), (768, 64), (1024, 128), (1280, 80), (1536, 64), (1920, 80), (2048, 64),
-                 (2304, 64), (2560, 80), (2688, 64), (3072, 128), (3200, 80), (4096, 128)):
-        for t in (*range(1, 260, 3), *range(260, 4097, 19)):
-            new = kinds(plan(h, d, 4 * h, t)[0]) - run
-            assert not new, (h, t, new)
+def test_the_passes_run_on_the_gpu_take_every_tile_that_passes_take():
+    run = set().union(*(kinds(taken(p[0], p[1])[0]) for p in (*PLANS, *MIDDLE, *WIDE)))
+    for h in range(128, 4097, 128):
+        for f in sorted({h, 2 * h, 4 * h, 8 * h, h // 256 * 128, 11 * h // 512 * 128, 32768} & set(range(128, 32769, 128))):
+            shape = synth.ModelShape(h, h // 64, 64, 16, f, n_layers=2)
+            for t in (*range(1, 260, 5), *range(260, 4097, 41)):
+                for rows in (-(-t // 128) * 128, 4096):
+                    p = taken(shape, t, rows)
+                    new = kinds(p[0]) - run if p else set()
+                    assert not new, (h, f, t, new)
 
 
 def test_a_plan_is_refused_as_the_call_is():
