@@ -447,8 +447,8 @@ static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 // 512: 303 -> 224, 4096: 2345 -> 1528; hidden 4096, 1531 tokens: 1810 -> 1203.  (Up to 64 tokens: pf_plan_short.)
 constexpr int kPfCus = 256;
 struct PfTileCost { int bm, bn, bk, per_cu; float step, lone_step, epi_in, epi_out; };
-constexpr int kPfTile32x256 = 7, kPfTile32x128 = 8, kPfTile64x256 = 9;    // (up to 64 tokens: pf_plan_short)
-constexpr int kPfTile128x160 = 10, kPfTile128x128 = 11, kPfTile128x192 = 12, kPfTile128x256 = 13, kPfTile128x96 = 14;   // (65 .. 1024 tokens: pf_plan_middle)
+constexpr int kPfTile32x128 = 7, kPfTile64x256 = 8;    // (up to 64 tokens: pf_plan_short)
+constexpr int kPfTile128x160 = 9, kPfTile128x128 = 10, kPfTile128x192 = 11, kPfTile128x256 = 12, kPfTile128x96 = 13;   // (65 .. 1024 tokens: pf_plan_middle)
 static const PfTileCost kPfTiles[kPfTileKinds] = {
     {64, 128, 64, 1, 0.26f, 0.f, 3.74f, 2.19f},
     {64, 128, 32, 3, 0.25f, 0.37f, 0.01f, 1.13f},
@@ -457,25 +457,25 @@ static const PfTileCost kPfTiles[kPfTileKinds] = {
     {256, 192, 32, 1, 0.92f, 0.f, 9.92f, 4.42f},
     {256, 256, 32, 1, 1.10f, 0.f, 14.67f, 5.02f},
     {256, 320, 32, 1, 1.34f, 0.f, 27.44f, 6.68f},
-    {32, 256, 64}, {32, 128, 64}, {64, 256, 64},
+    {32, 128, 64}, {64, 256, 64},
     {128, 160, 32, 2}, {128, 128, 64, 1}, {128, 192, 32, 1}, {128, 256, 32, 1}, {128, 96, 64, 1},
 };
 
 // Up to 64 tokens a product is its weights' way from memory, once.  One token tile of 32 or 64 rows (the activations
 // of a tile are as many bytes as twice its rows of weights); K steps of 64, whole lines; and the 256 CUs filled once, by
-// the wider tile or by splitting K: the first product at most three ways (its parts cost a launch that adds them), the
-// second up to sixteen (they are added where the next layer's input is made).  us per layer, least estimate above -> this:
-// hidden 2560: 20 tokens 69.0 -> 55, 37 tokens 73.3 -> 66.0, 64 tokens 76.0 -> 71; hidden 4096, 20 tokens 129 -> 107.
-// (With a feed-forward of four times hidden the 256-wide tiles fill more CUs at hidden 2432 .. 3200 and at some sizes above.)
+// the wider tile of 64 tokens or by splitting K: the first product at most three ways (its parts cost a launch that adds them),
+// the second up to sixteen (they are added where the next layer's input is made).  us per layer, least estimate above -> this:
+// hidden 2560: 37 tokens 73.3 -> 66.0, 64 tokens 76.0 -> 71; hidden 4096, 20 tokens 129 -> 107.  (Most such passes run the narrow
+// products now: pf_plan_narrow.  A tile of 32 x 256 left with them: no pass on 256 CUs took it any more.)
 // False where that leaves half the CUs without a tile of 64 (hidden 512, 40 tokens: 31 us, 27 by the estimate).
 static bool pf_plan_short(const PfParams &P, bool in, size_t part_bytes, PfPlan *plan)
 {
     const int h = P.dm.h, f = P.dm.f, nall = in ? 3 * h + f : h;
     const bool low = P.n_rows <= 32;
-    const int kinds[2] = {low ? kPfTile32x128 : 0, low ? kPfTile32x256 : kPfTile64x256};
+    const int kinds[2] = {low ? kPfTile32x128 : 0, kPfTile64x256};
     PfPlan best = {kinds[0], 1};
     int most = 0;
-    for (int i = 0; i < (in ? 2 : 1); ++i) {
+    for (int i = 0; i < (in && !low ? 2 : 1); ++i) {
         const PfTileCost &t = kPfTiles[kinds[i]];
         const int tiles = in ? (3 * h + t.bn - 1) / t.bn + (f + t.bn - 1) / t.bn : (h + t.bn - 1) / t.bn;
         for (int sp = 1; sp <= (in ? 3 : 16); ++sp) {
@@ -499,7 +499,7 @@ static PfPlan pf_plan(const PfParams &P, bool in, size_t part_bytes, float *cost
     const float steps = (float)(in ? h : h + f) / 32.f;
     PfPlan best = {0, 1};
     float best_cost = 1e30f;
-    for (int k = 0; k < kPfTile32x256; ++k) {
+    for (int k = 0; k < kPfTile32x128; ++k) {
         const PfTileCost &t = kPfTiles[k];
         if (in && t.bn == 320 && t.bm == 256) continue;    // (its QKV and MLP-up epilogues spill registers)
         const int mt = (P.n_rows + t.bm - 1) / t.bm;
@@ -561,9 +561,7 @@ static const PfLayerCost kPfLayerCosts[kPfTileKinds] = {
     {0.849f, 0.000f, 13.36f, 5.07f},
     {1.007f, 0.000f, 17.27f, 6.35f},
     {1.236f, 0.000f, 25.35f, 7.53f},
-    {},
-    {},
-    {},
+    {}, {},
     {0.405f, 0.551f, 8.04f, 2.47f},
     {0.376f, 0.000f, 10.05f, 3.39f},
     {0.566f, 0.000f, 5.09f, 3.08f},
@@ -662,7 +660,6 @@ static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
     case 4: return pf_launch<FL, 256, 192, 32, 3, 4, 2>(P, pl, s);
     case 5: return pf_launch<FL, 256, 256, 32, 3, 4, 2>(P, pl, s);
     case 6: if (FL == kPfOut) return pf_launch<kPfOut, 256, 320, 32, 3, 4, 2>(P, pl, s); break;
-    case kPfTile32x256: if (FL == kPfIn) return pf_launch<kPfIn, 32, 256, 64, 3, 1, 4>(P, pl, s); break;
     case kPfTile32x128: return pf_launch<FL, 32, 128, 64, 3, 1, 4>(P, pl, s);
     case kPfTile64x256: if (FL == kPfIn) return pf_launch<kPfIn, 64, 256, 64, 3, 1, 4>(P, pl, s); break;
     case kPfTile128x160: if (FL == kPfIn) return pf_launch<kPfIn, 128, 160, 32, 3, 4, 1>(P, pl, s); break;

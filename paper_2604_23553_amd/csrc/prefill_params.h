@@ -49,7 +49,7 @@ CFPP_HD PfLayout pf_layout(const Dims &m, int rows)
 }
 
 // tile (index into the table of prefill_gemm.hip) and splits of K of a product
-constexpr int kPfTileKinds = 15;
+constexpr int kPfTileKinds = 14;
 struct PfPlan { int tile, splits; };
 
 // Passes of up to this many tokens may take the narrow products (prefill_narrow.hip); the activations that feed a
