@@ -190,7 +190,10 @@ void cfpp_destroy(cfpp_ctx *ctx);
                                    ffn multiples of 512, all workgroups resident,
                                    else CFPP_EUNSUPPORTED).                    */
 #define CFPP_MODE_AUTO  (-1)
-#define CFPP_OPT_GRID     2  /* workgroups; 0 = one per compute unit          */
+#define CFPP_OPT_GRID     2  /* workgroups; 0 = one per compute unit.  Batched path:
+                                most workgroups of its first product; the second
+                                has at most 16 rows to one, the attention is cut
+                                by the sequences' lengths                     */
 #define CFPP_OPT_THREADS  3  /* threads per workgroup: 256 or 512             */
 cfpp_status cfpp_set_option(cfpp_ctx *ctx, int32_t option, int64_t value);
 cfpp_status cfpp_get_option(const cfpp_ctx *ctx, int32_t option, int64_t *value);
@@ -211,9 +214,9 @@ cfpp_status cfpp_get_option(const cfpp_ctx *ctx, int32_t option, int64_t *value)
  * Asynchronous on `stream`.
  * The sequences are independent and share the weights.  Launch mode 0 (and
  * CFPP_MODE_AUTO) with batch > 1 streams the weights once per group of up to 8 sequences (the
- * projections run on the matrix cores; needs 512 threads, hidden and ffn
- * multiples of 256, at most 64 matrix rows per workgroup, else - and in the
- * other launch modes - the sequences run one after the other).  With several
+ * projections run on the matrix cores; needs 512 threads, hidden a multiple of
+ * 128 up to 4096, ffn one of hidden, a grid of (3 hidden + ffn) / 128 or more,
+ * else - and in the other launch modes - the sequences run one after the other).  With several
  * sequences a bad position in any of a group skips the whole group's step.
  * Range: a sequence on its own keeps every intermediate value in fp32.  What
  * enters the matrix cores - gamma x of both LayerNorms, GELU(up) and the attention

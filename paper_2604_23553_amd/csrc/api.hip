@@ -522,11 +522,11 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
         B.o = reinterpret_cast<__half *>(B.o32);
         B.rope = reinterpret_cast<const float2 *>(ctx->ws + wl.rope);
         B.sync = reinterpret_cast<unsigned *>(ctx->ws + wl.sync);
-        HIP_OK((B.n > 1 ? launch_bat_in : launch_lone_in)(B, ctx->n_cu, s));
+        HIP_OK((B.n > 1 ? launch_bat_in : launch_lone_in)(B, sh.grid, s));
         StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
         if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
         HIP_OK(launch_attention_batched(P, B.n, kv, s));
-        HIP_OK((B.n > 1 ? launch_bat_out : launch_lone_out)(B, ctx->n_cu, s));
+        HIP_OK((B.n > 1 ? launch_bat_out : launch_lone_out)(B, sh.grid, s));
     }
     return CFPP_OK;
 }
@@ -772,9 +772,9 @@ extern "C" cfpp_status cfpp_stack_prefill(cfpp_ctx *ctx, const void *const *pack
     if ((st = launch_shape(ctx, &sh)) != CFPP_OK) return st;
     if ((ctx->mode != 0 && ctx->mode != CFPP_MODE_AUTO) || (ctx->dm.flags & kFlagSequentialResidual))
         return fail(CFPP_EUNSUPPORTED, "prompt processing runs in launch mode 0 with the parallel residual form");
-    if (!bat_supported(ctx->dm, sh.grid, sh.threads) || sh.grid < kBatMax)
-        return fail(CFPP_EUNSUPPORTED, "prompt processing needs the batched projections: 512 threads, grid >= %d, hidden "
-                    "and ffn multiples of 128, at most 64 matrix rows per workgroup", kBatMax);
+    if (!bat_supported(ctx->dm, sh.grid, sh.threads))
+        return fail(CFPP_EUNSUPPORTED, "prompt processing needs the batched projections: 512 threads, hidden a multiple of 128 "
+                    "up to 4096, ffn one of hidden, grid >= (3 hidden + ffn) / 128 (%d given)", sh.grid);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int32_t *pos_dev = reinterpret_cast<int32_t *>(ctx->ws + ctx->wl.pf_pos);
     HIP_OK(launch_fill_positions(pos_dev, pos0, n_tokens, s));

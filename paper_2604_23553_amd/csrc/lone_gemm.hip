@@ -320,7 +320,7 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_out(NarrowParams P)
     st.p0.c0 = c0; st.p0.n = max(0, min(c1, C0) - c0);
     st.p1.w = P.w + P.lay.w_down + (size_t)r0 * f; st.p1.row_bytes = (unsigned)f * 2u;
     st.p1.c0 = max(0, c0 - C0); st.p1.n = max(0, c1 - max(c0, C0));
-    st.act = P.m32;                                          // (the workspace has the attention output behind GELU(up))
+    st.act = P.m32;                                          // (the workspace, of at most 64 sequences, has the attention output behind GELU(up))
     st.act0 = (unsigned)((const char *)P.o32 - (const char *)P.m32); st.act1 = 0u;
     st.act_bytes = st.act0 + (unsigned)h * 4u;
     st.ring = lds_address(ng_lds) + (unsigned)(wave * LoneOut::kStage);
@@ -347,10 +347,11 @@ static hipError_t lone_launch_in(const NarrowParams &P, int wgs, hipStream_t s)
     hipLaunchKernelGGL(k_lone_in<T>, dim3(wgs), dim3(kLoneThreads), lone_in_lds<T>(), s, P);
     return hipGetLastError();
 }
-hipError_t launch_lone_in(NarrowParams P, int n_cu, hipStream_t s)
+hipError_t launch_lone_in(NarrowParams P, int grid, hipStream_t s)
 {
     int wgs;
-    P.rows = ng_in_rows(P.dm, n_cu, &P.wgs_q, &wgs);
+    P.rows = ng_in_rows(P.dm, grid, &P.wgs_q, &wgs);
+    if (P.rows == 0) return hipErrorInvalidValue;
     switch ((P.rows + 15) / 16) {
     case 1: return lone_launch_in<1>(P, wgs, s);
     case 2: return lone_launch_in<2>(P, wgs, s);
@@ -361,9 +362,9 @@ hipError_t launch_lone_in(NarrowParams P, int n_cu, hipStream_t s)
     return lone_launch_in<8>(P, wgs, s);
 }
 
-hipError_t launch_lone_out(NarrowParams P, int n_cu, hipStream_t s)
+hipError_t launch_lone_out(NarrowParams P, int grid, hipStream_t s)
 {
-    P.rows = min(16, (P.dm.h + n_cu - 1) / n_cu);
+    P.rows = min(16, (P.dm.h + grid - 1) / grid);
     hipLaunchKernelGGL(k_lone_out, dim3((P.dm.h + P.rows - 1) / P.rows), dim3(kLoneThreads), lone_out_lds(), s, P);
     return hipGetLastError();
 }

@@ -191,16 +191,13 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_out(NarrowParams P)
 }
 
 // ---------------------------------------------------------------------------
-// Shapes and launch options that run the batched path.  (The bounds on rows per workgroup and on LDS are those of the
-// grid that the option names; the kernels here choose their own.)
+// Shapes and launch options that run the batched path: a wavefront's part of gamma (x) is 512 columns at most, a workgroup of the
+// first product has up to kNgTileMax tiles of rows.  (An MLP that is no multiple of hidden keeps to the phase kernels.)
 bool bat_supported(const Dims &dm, int grid, int threads)
 {
-    if (threads != 512 || grid < 1 || dm.h % 128 != 0 || dm.f % dm.h != 0 || dm.h > 4096) return false;
-    auto rows = [&](int n) { return (n + grid - 1) / grid; };
-    auto rc = [](int n) { return (n + 3) & ~3; };
-    const int rq = (rows(3 * dm.h) + 1) & ~1, ru = rows(dm.f), rh = rows(dm.h);
-    const size_t act = (size_t)32 * (dm.h + 32), in = act + (132 + (size_t)64 * (rc(rq) + rc(ru))) * 4, out = act + (size_t)256 * rc(rh);
-    return (ru > rq ? ru : rq) <= 64 && (in > out ? in : out) <= 160 * 1024 && (unsigned long long)packed_layout(dm.h, dm.f).total * 2 < (1ull << 32);
+    int wgs_q, wgs;
+    return threads == kNgThreads && grid >= 1 && dm.h % 128 == 0 && dm.f % dm.h == 0 && dm.h <= 4096 &&
+           ng_in_rows(dm, grid, &wgs_q, &wgs) > 0;
 }
 
 template <int T>
@@ -211,10 +208,11 @@ static hipError_t ng_launch_in(const NarrowParams &P, int wgs, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_bat_in(NarrowParams P, int n_cu, hipStream_t s)
+hipError_t launch_bat_in(NarrowParams P, int grid, hipStream_t s)
 {
     int wgs;
-    P.rows = ng_in_rows(P.dm, n_cu, &P.wgs_q, &wgs);
+    P.rows = ng_in_rows(P.dm, grid, &P.wgs_q, &wgs);
+    if (P.rows == 0) return hipErrorInvalidValue;
     const int t = (P.rows + 15) / 16;
     if (t <= 1) return ng_launch_in<1>(P, wgs, s);
     if (t <= 2) return ng_launch_in<2>(P, wgs, s);
@@ -223,9 +221,9 @@ hipError_t launch_bat_in(NarrowParams P, int n_cu, hipStream_t s)
     return ng_launch_in<8>(P, wgs, s);
 }
 
-hipError_t launch_bat_out(NarrowParams P, int n_cu, hipStream_t s)
+hipError_t launch_bat_out(NarrowParams P, int grid, hipStream_t s)
 {
-    P.rows = min(16, (P.dm.h + n_cu - 1) / n_cu);
+    P.rows = min(16, (P.dm.h + grid - 1) / grid);
     hipLaunchKernelGGL(k_ng_out, dim3((P.dm.h + P.rows - 1) / P.rows), dim3(kNgThreads), ng_out_lds(), s, P);
     return hipGetLastError();
 }

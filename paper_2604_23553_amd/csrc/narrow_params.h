@@ -44,12 +44,13 @@ struct NarrowParams {
 
 bool bat_supported(const Dims &dm, int grid, int threads);
 // several sequences or tokens (narrow_gemm.hip)
-hipError_t launch_bat_in(NarrowParams P, int n_cu, hipStream_t s);
-hipError_t launch_bat_out(NarrowParams P, int n_cu, hipStream_t s);
+// grid: most workgroups of the first product; the second has rows of at most 16 to one and may have twice as many
+hipError_t launch_bat_in(NarrowParams P, int grid, hipStream_t s);
+hipError_t launch_bat_out(NarrowParams P, int grid, hipStream_t s);
 hipError_t prepare_narrow_kernels();
 // one (lone_gemm.hip)
-hipError_t launch_lone_in(NarrowParams P, int n_cu, hipStream_t s);
-hipError_t launch_lone_out(NarrowParams P, int n_cu, hipStream_t s);
+hipError_t launch_lone_in(NarrowParams P, int grid, hipStream_t s);
+hipError_t launch_lone_out(NarrowParams P, int grid, hipStream_t s);
 hipError_t prepare_lone_kernels();
 
 }  // namespace cfpp

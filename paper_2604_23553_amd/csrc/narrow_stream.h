@@ -265,16 +265,15 @@ __device__ __forceinline__ float2 ng_total2(const float *red, int stride, int ro
     return s;
 }
 
-// Rows of a workgroup such that the workgroups of both matrices of the first product come to at most one (or, where that
-// would be more than kNgTileMax tiles of 16, a few) per CU; even: a rotary pair stays in one workgroup.
-inline int ng_in_rows(const Dims &dm, int n_cu, int *wgs_q, int *wgs)
+// Rows of a workgroup such that the workgroups of both matrices of the first product come to at most `grid`; even: a rotary
+// pair stays in one workgroup.  0 where that would be more than kNgTileMax tiles of 16.
+inline int ng_in_rows(const Dims &dm, int grid, int *wgs_q, int *wgs)
 {
-    for (int per = 1;; ++per) {
-        for (int rows = 2; rows <= 16 * kNgTileMax; rows += 2) {
-            const int q = (3 * dm.h + rows - 1) / rows, u = (dm.f + rows - 1) / rows;
-            if (q + u <= per * n_cu) { *wgs_q = q; *wgs = q + u; return rows; }
-        }
+    for (int rows = 2; rows <= 16 * kNgTileMax; rows += 2) {
+        const int q = (3 * dm.h + rows - 1) / rows, u = (dm.f + rows - 1) / rows;
+        if (q + u <= grid) { *wgs_q = q; *wgs = q + u; return rows; }
     }
+    return 0;
 }
 
 }  // namespace cfpp

@@ -259,7 +259,7 @@ bool pf_plan_narrow(PfParams &P, int n_cu)
     PfNarrow &N = P.nrw;
     if (P.n_rows > kPfNarrowMax) return false;
     N.rows_in = ng_in_rows(P.dm, n_cu, &N.wgs_q, &N.wgs_in);
-    if (N.wgs_in > n_cu || pn_tiles_of(N.rows_in) * pn_sets_of(P.n_rows) > kPnMostSums) return false;
+    if (N.rows_in == 0 || pn_tiles_of(N.rows_in) * pn_sets_of(P.n_rows) > kPnMostSums) return false;
     int splits = 0;
     pn_plan_out(P, n_cu, &N.rows_out, &splits);
     const size_t bytes = P.part_bytes + (size_t)((char *)P.part - (char *)P.q), stride = (size_t)P.n_rows * P.dm.h;

@@ -159,3 +159,30 @@ def test_middle_tiles_over_two_layers(shape, T, first, second):
         base, got = cf.cfpp_debug_prefill_plan(cfg, rows, T)[0], cf.cfpp_debug_prefill_tiles(cfg, rows, T)[0]
     assert got == (first or base[0], second or base[1])
     check(shape, T, *got)
+
+
+# The launch option names the workgroups of the first product: eight tiles of rows to each of the fewest, two rows to each of
+# the most.  One workgroup fewer and there is no such cut: a prompt is refused, sequences run one after the other.
+@pytest.mark.parametrize("grid", [34, 35, 100, 1024])
+def test_explicit_grids(orc, grid):
+    from paper_2604_23553_amd import CfppError
+    from tests.test_gpu_stack import build_stack, oracle_stack
+    shape, lens = _shape(640, 80, 2560, 20), np.array([5, 6, 7], dtype=np.int32)
+    print(f"[case] batched path, grid {grid}", flush=True)
+    ds, ws, kvs = build_stack(shape, 61, lens, 12, batch=3)
+    try:
+        ds.set_options(mode=0, grid=grid)
+        x = synth.x_input(shape, 61, 3)
+        ds.set_inputs(x, lens)
+        ds.stack_decode()
+        ds.check()
+        for b in range(3):
+            assert_block_close(ds.result()[b], oracle_stack(orc, shape, ws, kvs, lens[b], x[b], b)[0], f"sequence {b}")
+        if grid < 35:
+            with pytest.raises(CfppError) as e:
+                ds.prefill(x, 0)
+            assert e.value.status == -2
+        else:
+            assert_block_close(ds.prefill(x[:1], 5), oracle_stack(orc, shape, ws, kvs, 5, x[0])[0], "prompt")
+    finally:
+        ds.close()
