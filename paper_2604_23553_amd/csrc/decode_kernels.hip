@@ -433,7 +433,7 @@ CFPP_HD int attn_pieces(int rows, bool few)
     return !few || n >= 8 ? n : half < 8 ? half : 8;
 }
 
-template <int D, bool STREAM>
+template <int D, bool STREAM, bool ONE>
 __global__ void __launch_bounds__(kAttnBatchThreads, 3)
 k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv)
 {
@@ -592,7 +592,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv)
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             if (lane + 64 * e >= D) continue;
-            if (nb == 1) { P.o[head * D + lane + 64 * e] = O[e] / L; continue; }
+            if (ONE) { P.o[head * D + lane + 64 * e] = O[e] / L; continue; }
             __half hi, lo;
             split_half(O[e] / L, hi, lo);
             const size_t at = ng_at(mine, head * D + lane + 64 * e, dm.h, nb);
@@ -701,8 +701,10 @@ hipError_t launch_attention_batched(const StepParams &P, int nb, const __half *k
     switch (P.dm.d) {
 #define CFPP_ATTN(D) \
     case D: \
-        if (stream) hipLaunchKernelGGL((k_attention_batched<D, true>), grid, block, 0, s, P, nb, spare, few, kv); \
-        else hipLaunchKernelGGL((k_attention_batched<D, false>), grid, block, 0, s, P, nb, spare, few, kv); \
+        if (stream && nb == 1) hipLaunchKernelGGL((k_attention_batched<D, true, true>), grid, block, 0, s, P, nb, spare, few, kv); \
+        else if (stream) hipLaunchKernelGGL((k_attention_batched<D, true, false>), grid, block, 0, s, P, nb, spare, few, kv); \
+        else if (nb == 1) hipLaunchKernelGGL((k_attention_batched<D, false, true>), grid, block, 0, s, P, nb, spare, few, kv); \
+        else hipLaunchKernelGGL((k_attention_batched<D, false, false>), grid, block, 0, s, P, nb, spare, few, kv); \
         break;
     CFPP_ATTN(64)
     CFPP_ATTN(80)
