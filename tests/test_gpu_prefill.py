@@ -160,6 +160,9 @@ def test_gemm_prompt_wide_attention_head_dim_128(orc):
     (synth.ModelShape(2048, 32, 64, 16, 2048, name="d64-h2048"), 31, 801),
     (synth.ModelShape(2048, 32, 64, 16, 2048, name="d64-h2048"), 0, 2050),
     (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 1000, 33),
+    # a rotated part that ends between the two pairs of a lane's four features (not a multiple of four dimensions)
+    (synth.ModelShape(512, 8, 64, 18, 2048, name="neox-h512-r18"), 5, 150),
+    (synth.ModelShape(640, 8, 80, 22, 2560, name="d80-h640-r22"), 2, 1100),
     # a group of 8 whose heads are 16 pieces each in the batched attention
     (synth.ModelShape(1024, 8, 128, 32, 4096, name="d128-h1024"), 8000, 8),
 ])

@@ -65,7 +65,7 @@ def _run(shape, w, K, V, x, S, mode):
             ds.close()
 
 
-SHAPES = [_shape(128, 64, 128, 16), _shape(512, 64, 2048, 16), _shape(640, 80, 2560, 20), _shape(1536, 128, 6144, 32, flags=synth.FLAG_TANH_GELU),
+SHAPES = [_shape(128, 64, 128, 18), _shape(512, 64, 2048, 16), _shape(640, 80, 2560, 20), _shape(1536, 128, 6144, 32, flags=synth.FLAG_TANH_GELU),
           _shape(2560, 80, 10240, 20)]
 
 
