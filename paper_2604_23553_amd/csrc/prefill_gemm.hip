@@ -550,8 +550,11 @@ void pf_plan_pass(PfParams &P)
 // CUs: 96, 160 (two workgroups to a CU), 192 or 256 features (a deeper ring); and K steps of 64 values - whole lines of weights, half
 // the barriers (loads of 64-byte segments run at half the rate of 128: 69 and 133 KB/us a CU) - where a CU has one workgroup.  Chosen by an estimate of the same form whose constants, in us, are
 // fitted to timings of whole layers (hidden 512 .. 4096, 70 .. 1024 tokens, 5500 of them, 2.4 % of a layer rms); taken where it is 2 us and
-// 2 % below that of the plan above, which made none of the fitted sizes slower.  us per layer, before -> now: hidden 2560:
-// 256 tokens 148 -> 130, 512 207 -> 200; hidden 4096: 96 179 -> 154; hidden 1536, 512 99 -> 95.
+// 2 % below that of the plan above.  us per layer, before -> now: hidden 2560: 256 tokens 148 -> 130, 512 207 -> 200; hidden 4096: 96
+// 179 -> 154; hidden 1536, 512 99 -> 95.  The timings were of three layers, whose weights stay in the Infinity Cache below hidden 1800 or
+// so, and there the estimate prices a split of the first product too low: with 900 MB of layers a whole one that is cut in two
+// loses 4.5 .. 12 % of a layer at every size of 15 (1792, 128 tokens 54.5 -> 60.6; 2304, 100 tokens 71.2 -> 76.5).  So K is
+// split only where the plan above splits it; of the 188 other changes timed that way none is slower (0 .. 19 % of a layer faster).
 struct PfLayerCost { float step, lone_step, epi_in, epi_out; };
 static const PfLayerCost kPfLayerCosts[kPfTileKinds] = {
     {0.271f, 0.000f, 4.96f, 1.94f},
@@ -588,13 +591,14 @@ void pf_plan_middle(PfParams &P)
     for (int in = 1; in >= 0; --in) {
         PfPlan &plan = in ? P.plan_in : P.plan_out;
         const size_t room = in ? P.part_bytes : P.part_out_bytes;
+        const bool whole = plan.splits == 1;
         const float was = pf_layer_cost(P, in, plan.tile, plan.splits);
         float best = 0.98f * was - 2.f;
         for (int k = kPfTile128x160; k <= kPfTile128x256; ++k) {
             if (!in && (k == kPfTile128x160 || k == kPfTile128x256)) continue;     // (never the least there: not built)
             const int mt = (P.n_rows + 127) / 128, nall = in ? 3 * P.dm.h + P.dm.f : P.dm.h;
             for (int sp = 1; sp <= (in ? 4 : 16); ++sp) {
-                if (sp > 1 && ((in && k != kPfTile128x128) || (size_t)sp * mt * 128 * nall * sizeof(float) > room)) break;
+                if (sp > 1 && ((in && (k != kPfTile128x128 || whole)) || (size_t)sp * mt * 128 * nall * sizeof(float) > room)) break;
                 if ((in ? P.dm.h : P.dm.h + P.dm.f) / kPfTiles[k].bk < sp) break;
                 const float cost = pf_layer_cost(P, in, k, sp);
                 if (cost < best) { best = cost; plan.tile = k; plan.splits = sp; }

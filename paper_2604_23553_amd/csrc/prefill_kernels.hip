@@ -312,7 +312,7 @@ __device__ __forceinline__ void pf_attn_finish(const PfParams &P, const __half *
 
 // SPLIT: workgroup z of a head's block takes the z-th part of the block's tiles of keys and leaves its queries' sums,
 // maxima and weights in memory, where k_pf_attn_join adds them.  For few queries behind a long context: a workgroup takes a
-// tile of keys in about 1.4 us, and 37 queries of 32 heads are 64 workgroups.
+// tile of keys in about 1.3 us, and 37 queries of 32 heads are 64 workgroups.
 template <int D, int QW, bool SPLIT>
 __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P, PfAttnParts A)
 {
