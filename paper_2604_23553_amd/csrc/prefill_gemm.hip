@@ -248,17 +248,27 @@ k_pf_gemm(PfParams P, int splits, int gm)
     const int t_lane = wm * (BM / WM) + (lane & 31), f_lane = 4 * (lane >> 5);      // token of the first instruction tile; first feature of g = 0
     if (splits > 1) {
         const int nall = FL == kPfIn ? 3 * h + f : h, c0 = up ? 3 * h : 0;
-        float *part = (FL == kPfIn ? P.part : P.part_out) + (size_t)z * mt * BM * nall + c0;
+        // 32 tokens x 32 columns at a time through LDS that no other wavefront touches, so that whole 128-byte lines are stored:
+        // 16 bytes of a token from each lane, four lines' quarters to a store, cost 0.5 .. 1 us a launch
+        float *part = (FL == kPfIn ? P.part : P.part_out) + ((size_t)z * mt * BM + m0 + wm * (BM / WM)) * nall + c0;
+        float *t = reinterpret_cast<float *>(pf_lds) + wave * 32 * (TS / 2);
+        __syncthreads();                                   // the last step's fragments have been read: the memory is free
 #pragma unroll
         for (int b = 0; b < NTL; ++b) {
             const int col = n0 + wn * (BN / WN) + b * 32;
             if (col >= N) break;                           // (uniform; N: a multiple of 128)
 #pragma unroll
-            for (int a = 0; a < MT; ++a)
+            for (int a = 0; a < MT; ++a) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<f32x4 *>(part + (size_t)(m0 + t_lane + a * 32) * nall + col + 8 * g + f_lane) =
+                    *reinterpret_cast<f32x4 *>(t + (lane & 31) * (TS / 2) + 8 * g + f_lane) =
                         f32x4{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 8 * i + (lane >> 3), c = 4 * (lane & 7);
+                    *reinterpret_cast<f32x4 *>(part + (size_t)(a * 32 + r) * nall + col + c) = *reinterpret_cast<const f32x4 *>(t + r * (TS / 2) + c);
+                }
+            }
         }
         return;
     }
