@@ -8,7 +8,7 @@
 // How the weights are streamed: narrow_stream.h.
 // Kernel times, 8 sequences, the kernels before (weights through registers, four rows to a load, activations of a
 // workgroup in LDS) -> these: hidden 2560: k_ng_in 28.7 -> 17.5 us, k_ng_out 23.5 -> 15.2 (5 sequences) and 24.7 -> 17.3 (8);
-// hidden 4096: 49.1 -> 37.9, 43.6 -> 32.1.  What is left of k_ng_out beyond its weights (13 us at 2560) is the activations:
+// hidden 4096: 49.1 -> 37.5, 43.6 -> 31.3.  What is left of k_ng_out beyond its weights (13 us at 2560) is the activations:
 // every workgroup reads all of them from the L2, 8 tokens 410 KB beside 256 KB of weights.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
