@@ -416,6 +416,7 @@ static cfpp_status prepare(cfpp_ctx *ctx)
     HIP_OK(prepare_fused_kernels(160 * 1024));
     HIP_OK(prepare_narrow_kernels());
     HIP_OK(prepare_lone_kernels());
+    HIP_OK(prepare_attention_kernels());
     ctx->prepared = true;
     return CFPP_OK;
 }
@@ -520,13 +521,16 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
         B.o32 = reinterpret_cast<float *>(ctx->ws + wl.o) + (size_t)b0 * dm.h;
         B.m = reinterpret_cast<__half *>(B.m32);
         B.o = reinterpret_cast<__half *>(B.o32);
+        B.part = reinterpret_cast<float *>(ctx->ws + wl.part) + (size_t)b0 * dm.H * wl.part_slots * (dm.d + 2);
+        B.part_slots = wl.part_slots;
+        B.downs = down_parts_of(dm.h, dm.f, B.n == 1);
         B.rope = reinterpret_cast<const float2 *>(ctx->ws + wl.rope);
         B.sync = reinterpret_cast<unsigned *>(ctx->ws + wl.sync);
         HIP_OK((B.n > 1 ? launch_bat_in : launch_lone_in)(B, sh.grid, s));
         StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
         if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
-        HIP_OK(launch_attention_batched(P, B.n, kv, s));
-        HIP_OK((B.n > 1 ? launch_bat_out : launch_lone_out)(B, sh.grid, s));
+        HIP_OK(launch_attention_batched(P, B.n, w, kv, s));
+        HIP_OK((B.n > 1 ? launch_bat_dense : launch_lone_dense)(B, sh.grid, s));
     }
     return CFPP_OK;
 }

@@ -2,7 +2,7 @@
 // fp32 activations.
 //
 //   k_lone_in  : both LayerNorms, QKV rows + bias, rotary, K/V append, q; MLP-up rows + bias + GELU
-//   k_lone_out : output projection and MLP-down as one product over the concatenated K, + biases + residual
+//   k_lone_dense : output projection, + MLP-down's parts, which the attention launch leaves (narrow_attention.hip), + biases + residual
 //
 // One token would fill two columns of a matrix instruction, and its heads and remainders in fp16 have fp16's range: a finite
 // input whose gamma x or GELU(up) passes 65504 came out as NaN, and an element below 2^-3 lost bits.  A row of weights
@@ -13,147 +13,12 @@
 // 4096 74.6 -> 73.9; a layer of a stack: 512 16.4 -> 15.6, 1536 24.4 -> 22.7.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
-#include "narrow_stream.h"
+#include "lone_stream.h"
 #include "prefill_device.h"
 
 namespace cfpp {
 
 constexpr int kLoneWaves = 8, kLoneThreads = 64 * kLoneWaves;
-
-// The stream of one wavefront: chunks of 64 columns of T pairs of 8 rows, CH chunks to a stage, through an LDS ring of its own.  A
-// load brings 8 rows x 128 bytes, and a lane reads back the 16 bytes that it asked for.  ACT: every fourth chunk is
-// preceded by a load of the four chunks' activations (256 fp32 values); else they are in LDS, at y.  Every load has its
-// place in the ring and is requested again, for the next stage, as soon as what it brought has been read: NI - 2 loads (behind
-// activations NI - 1) are always in flight behind those that are waited for, by count.  Loads without a purpose
-// (rows past the last, chunks past the end) read one line over and over.  A wavefront with no more chunks than a stage
-// requests just these and waits for all of them at once.
-template <int T, int CH, bool ACT>
-struct LoneStream {
-    static constexpr int PER = 2 * T, NI = CH * PER + (ACT ? CH / 4 : 0), kStage = NI * 1024;
-    static_assert(NI <= 62, "the memory counter's range");
-    static_assert(!ACT || CH % 4 == 0, "");
-    NgPiece p0, p1;
-    const void *act;        // ACT: what the resource of the activations starts at
-    unsigned act_bytes, act0, act1;        // its size; where the activations of each matrix's first column lie in it
-    unsigned ring;          // LDS address of this wavefront's ring
-    const char *mem;        // the same as a pointer
-    const float *y;         // !ACT: this wavefront's activations
-    int lane, octets, tail; // whole 8-row groups, rows beyond them
-    float acc[2 * T];       // this lane's columns of row lane / 8 of each group
-
-    static constexpr unsigned place_w(int ch, int o) { return (unsigned)((ACT ? ch / 4 + 1 : 0) + ch * PER + o) * 1024u; }
-    static constexpr unsigned place_a(int quad) { return (unsigned)(quad * (1 + 4 * PER)) * 1024u; }
-
-    __device__ __forceinline__ void issue_a(int i, int quad) const
-    {
-        const int k = i + (lane >> 4), c = k < p0.n ? p0.c0 + k : p1.c0 + k - p0.n;
-        const unsigned v = (k < p0.n ? act0 : act1) + (unsigned)c * 256u + (unsigned)(lane & 15) * 16u;
-        lds_dma16(dma_rsrc(act, act_bytes), ring + place_a(quad), k < p0.n + p1.n ? v : 0u, 0u);
-    }
-    __device__ __forceinline__ void issue_w(int i, int ch, int t) const
-    {
-        const bool second = i >= p0.n, live = i < p0.n + p1.n;
-        const int c = second ? p1.c0 + i - p0.n : p0.c0 + i;
-        const unsigned row_bytes = second ? p1.row_bytes : p0.row_bytes;
-        const i32x4 rs = dma_rsrc(second ? p1.w : p0.w, row_bytes * (unsigned)(8 * octets + tail));
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int o = 2 * t + k;                       // row group; its last rows may not be there
-            const unsigned r = o < octets ? (unsigned)(lane >> 3) : (unsigned)min(lane >> 3, tail - 1);
-            const bool real = live && (o < octets || (o == octets && tail > 0));
-            lds_dma16_once(rs, ring + place_w(ch, o), real ? r * row_bytes + (unsigned)(lane & 7) * 16u : 0u,
-                           real ? (unsigned)(8 * o) * row_bytes + (unsigned)c * 128u : 0u);
-        }
-    }
-    __device__ __forceinline__ void begin(int rows, int tid)
-    {
-        lane = tid & 63;
-        octets = rows >> 3; tail = rows & 7;
-#pragma unroll
-        for (int o = 0; o < 2 * T; ++o) acc[o] = 0.f;
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            if (ch >= p0.n + p1.n) break;                  // (uniform)
-            if (ACT && ch % 4 == 0) issue_a(ch, ch / 4);
-#pragma unroll
-            for (int t = 0; t < T; ++t) issue_w(ch, ch, t);
-        }
-    }
-    // what was requested ahead of begin() is there (!ACT: begin() requested whole chunks, CH or as many as there are)
-    template <int N = CH>
-    __device__ __forceinline__ void wait_ahead() const
-    {
-        if (p0.n + p1.n >= N) ng_wait<N * PER>();
-        else if constexpr (N > 0) wait_ahead<N - 1>();
-    }
-    enum { kSteady, kLast, kOnly };
-    template <int KIND>
-    __device__ __forceinline__ void stage(int i)
-    {
-        constexpr bool LAST = KIND != kSteady;
-        float4 a[ACT ? 8 : 2];
-        if (KIND == kOnly) ng_wait<0>();
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            const bool live = CH == 1 || i + ch < p0.n + p1.n;             // (uniform)
-            if (KIND == kOnly && !live) break;
-            if (ACT && ch % 4 == 0) {
-                if (KIND == kLast) ng_wait_for<NI>(NI - ch * PER - ch / 4 - 1);
-                else if (KIND == kSteady) ng_wait<NI - 1>();
-                const float4 *at = reinterpret_cast<const float4 *>(mem + place_a(ch / 4) + (lane & 7) * 32);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) { a[2 * k] = at[16 * k]; a[2 * k + 1] = at[16 * k + 1]; }
-                ng_lds_read();                             // the place in the ring is free
-                if (!LAST) issue_a(i + CH + ch, ch / 4);
-            } else if (!ACT && live) {
-                const float4 *at = reinterpret_cast<const float4 *>(y + (i + ch) * kNgChunk + (lane & 7) * 8);
-                a[0] = at[0]; a[1] = at[1];
-            }
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                if (KIND == kLast) ng_wait_for<NI>(NI - ch * PER - (ACT ? ch / 4 + 1 : 0) - 2 * (t + 1));
-                else if (KIND == kSteady) ng_wait<NI - 2>();
-                const u32x4 w0 = *reinterpret_cast<const u32x4 *>(mem + place_w(ch, 2 * t) + lane * 16);
-                const u32x4 w1 = *reinterpret_cast<const u32x4 *>(mem + place_w(ch, 2 * t + 1) + lane * 16);
-                ng_lds_read();
-                if (!LAST) issue_w(i + CH + ch, ch, t);
-                if (live) {                                // (a chunk's eight first, then its sum: shorter chains of roundings)
-                    const int k = ACT ? 2 * (ch % 4) : 0;
-                    acc[2 * t] += dot8(w0, a[k], a[k + 1], 0.f);
-                    acc[2 * t + 1] += dot8(w1, a[k], a[k + 1], 0.f);
-                }
-            }
-        }
-    }
-    __device__ __forceinline__ void run()
-    {
-        const int n = p0.n + p1.n;
-        if (n == 0) return;
-        if (n <= CH) { stage<kOnly>(0); return; }
-        int i = 0;
-        for (; i + CH < n; i += CH) stage<kSteady>(i);
-        stage<kLast>(i);
-    }
-    // the sums of the wavefront's columns, row by row
-    __device__ __forceinline__ void leave(float *red, int wave) const
-    {
-#pragma unroll
-        for (int o = 0; o < 2 * T; ++o) {
-            float v = acc[o];
-            v += dpp_mov<kDppXor1>(v);
-            v += dpp_mov<kDppXor2>(v);
-            v += dpp_mov<kDppHalfMirror>(v);
-            if ((lane & 7) == 0) red[wave * 16 * T + 8 * o + (lane >> 3)] = v;
-        }
-    }
-    static __device__ __forceinline__ float total(const float *red, int row)
-    {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < kLoneWaves; ++w) s += red[w * 16 * T + row];
-        return s;
-    }
-};
 
 // the position, if it is inside the cache (uniform over the grid)
 __device__ __forceinline__ bool lone_position_ok(const NarrowParams &P, int *pos)
@@ -281,11 +146,11 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     __syncthreads();
     if (!ok) return;
     if (up) {
-        if (tid < rn) P.m32[r0 + tid] = pf_gelu(Stream::total(red, tid) + __half2float(k0), dm.flags);
+        if (tid < rn) P.m32[r0 + tid] = pf_gelu(Stream::template total<kLoneWaves>(red, tid) + __half2float(k0), dm.flags);
         return;
     }
     if (2 * tid >= rn) return;
-    float v0 = Stream::total(red, 2 * tid) + __half2float(k0), v1 = Stream::total(red, 2 * tid + 1) + __half2float(k1);
+    float v0 = Stream::template total<kLoneWaves>(red, 2 * tid) + __half2float(k0), v1 = Stream::template total<kLoneWaves>(red, 2 * tid + 1) + __half2float(k1);
     int d0 = i, d1 = i + 1;
     if (rot) {
         const float lo = v0 * cs.x - v1 * cs.y, hi = v1 * cs.x + v0 * cs.y;
@@ -301,30 +166,29 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     }
 }
 
-// Output projection and MLP-down as one product over the concatenated K ([attention | GELU(up)] . [W_dense | W_down]^T),
-// + biases + residual.  A workgroup has at most 16 rows; a wavefront an eighth of the K values, with their activations.
-// Four chunks to a stage, 8 KiB of weights a wavefront in flight: with eight a block takes 1.1 us more at hidden 2560, 0.9 at 4096.
-using LoneOut = LoneStream<1, 4, true>;
-constexpr int lone_out_lds() { return kLoneWaves * LoneOut::kStage; }
-__global__ void __launch_bounds__(kLoneThreads, 2) k_lone_out(NarrowParams P)
+// Output projection, + MLP-down's parts (narrow_attention.hip) + biases + residual.  A workgroup has at most 16 rows; a wavefront
+// an eighth of the K values, with their activations.
+using LoneDense = LoneStream<1, 4, true>;
+constexpr int lone_dense_lds() { return kLoneWaves * LoneDense::kStage; }
+__global__ void __launch_bounds__(kLoneThreads, 2) k_lone_dense(NarrowParams P)
 {
     extern __shared__ __align__(16) char ng_lds[];
     const Dims &dm = P.dm;
-    const int h = dm.h, f = dm.f, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = dm.h, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r0 = (int)blockIdx.x * P.rows, rn = min(P.rows, h - r0), row = min(tid, rn - 1);
     const __half de = P.w[P.lay.b_dense + r0 + row], dn = P.w[P.lay.b_down + r0 + row];
     const float x = P.layer == 0 ? __half2float(P.x_in[r0 + row]) : P.xres[(size_t)((P.layer - 1) & 1) * h + r0 + row];
-    const int C0 = h / kNgChunk, C = (h + f) / kNgChunk, c0 = C * wave / kLoneWaves, c1 = C * (wave + 1) / kLoneWaves;
-    LoneOut st;
+    float down[kDownParts];
+    down_parts(P, 0, r0 + row, down);
+    const int C = h / kNgChunk, c0 = C * wave / kLoneWaves;
+    LoneDense st;
     st.p0.w = P.w + P.lay.w_dense + (size_t)r0 * h; st.p0.row_bytes = (unsigned)h * 2u;
-    st.p0.c0 = c0; st.p0.n = max(0, min(c1, C0) - c0);
-    st.p1.w = P.w + P.lay.w_down + (size_t)r0 * f; st.p1.row_bytes = (unsigned)f * 2u;
-    st.p1.c0 = max(0, c0 - C0); st.p1.n = max(0, c1 - max(c0, C0));
-    st.act = P.m32;                                          // (the workspace, of at most 64 sequences, has the attention output behind GELU(up))
-    st.act0 = (unsigned)((const char *)P.o32 - (const char *)P.m32); st.act1 = 0u;
-    st.act_bytes = st.act0 + (unsigned)h * 4u;
-    st.ring = lds_address(ng_lds) + (unsigned)(wave * LoneOut::kStage);
-    st.mem = ng_lds + wave * LoneOut::kStage;
+    st.p0.c0 = c0; st.p0.n = C * (wave + 1) / kLoneWaves - c0;
+    st.p1 = st.p0; st.p1.n = 0;
+    st.act = P.o32; st.act0 = st.act1 = 0u;
+    st.act_bytes = (unsigned)h * 4u;
+    st.ring = lds_address(ng_lds) + (unsigned)(wave * LoneDense::kStage);
+    st.mem = ng_lds + wave * LoneDense::kStage;
     st.y = nullptr;
     st.begin(rn, tid);
     int pos;
@@ -335,7 +199,7 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_out(NarrowParams P)
     st.leave(red, wave);
     __syncthreads();
     if (!ok || tid >= rn) return;
-    const float res = x + ((LoneOut::total(red, row) + __half2float(de)) + __half2float(dn));
+    const float res = x + (((LoneDense::total<kLoneWaves>(red, row) + down_sum(P, down)) + __half2float(de)) + __half2float(dn));
     if (P.layer == P.n_layers - 1) P.out[r0 + row] = __float2half_rn(res);
     else P.xres[(size_t)(P.layer & 1) * h + r0 + row] = res;
 }
@@ -362,10 +226,10 @@ hipError_t launch_lone_in(NarrowParams P, int grid, hipStream_t s)
     return lone_launch_in<8>(P, wgs, s);
 }
 
-hipError_t launch_lone_out(NarrowParams P, int grid, hipStream_t s)
+hipError_t launch_lone_dense(NarrowParams P, int grid, hipStream_t s)
 {
     P.rows = min(16, (P.dm.h + grid - 1) / grid);
-    hipLaunchKernelGGL(k_lone_out, dim3((P.dm.h + P.rows - 1) / P.rows), dim3(kLoneThreads), lone_out_lds(), s, P);
+    hipLaunchKernelGGL(k_lone_dense, dim3((P.dm.h + P.rows - 1) / P.rows), dim3(kLoneThreads), lone_dense_lds(), s, P);
     return hipGetLastError();
 }
 
@@ -380,7 +244,7 @@ hipError_t prepare_lone_kernels()
     hipError_t e;
     if ((e = lone_prepare<1>()) != hipSuccess || (e = lone_prepare<2>()) != hipSuccess || (e = lone_prepare<3>()) != hipSuccess ||
         (e = lone_prepare<5>()) != hipSuccess || (e = lone_prepare<7>()) != hipSuccess || (e = lone_prepare<8>()) != hipSuccess) return e;
-    return hipFuncSetAttribute((const void *)k_lone_out, hipFuncAttributeMaxDynamicSharedMemorySize, lone_out_lds());
+    return hipFuncSetAttribute((const void *)k_lone_dense, hipFuncAttributeMaxDynamicSharedMemorySize, lone_dense_lds());
 }
 
 }  // namespace cfpp

@@ -3,12 +3,12 @@
 // weights are read once and their way from memory is what takes time, so everything here is arranged around that stream.
 //
 //   k_ng_in  : both LayerNorms, QKV rows + bias, rotary, K/V append, q; MLP-up rows + bias + GELU
-//   k_ng_out : output projection and MLP-down as one product over the concatenated K, + biases + residual
+//   k_ng_dense : output projection, + MLP-down's parts, which the attention launch leaves (narrow_attention.hip), + biases + residual
 //
 // How the weights are streamed: narrow_stream.h.
 // Kernel times, 8 sequences, the kernels before (weights through registers, four rows to a load, activations of a
-// workgroup in LDS) -> these: hidden 2560: k_ng_in 28.7 -> 17.5 us, k_ng_out 23.5 -> 15.2 (5 sequences) and 24.7 -> 17.3 (8);
-// hidden 4096: 49.1 -> 37.5, 43.6 -> 31.3.  What is left of k_ng_out beyond its weights (13 us at 2560) is the activations:
+// workgroup in LDS) -> these: hidden 2560: k_ng_in 28.7 -> 17.5 us, k_ng_dense 23.5 -> 15.2 (5 sequences) and 24.7 -> 17.3 (8);
+// hidden 4096: 49.1 -> 37.5, 43.6 -> 31.3.  What is left of k_ng_dense beyond its weights (13 us at 2560) is the activations:
 // every workgroup reads all of them from the L2, 8 tokens 410 KB beside 256 KB of weights.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -148,30 +148,30 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_in(NarrowParams P)
     }
 }
 
-// Output projection and MLP-down as one product over the concatenated K ([attention | GELU(up)] . [W_dense | W_down]^T),
-// + biases + residual.  A workgroup has at most 16 rows; a wavefront an eighth of the K values.
-constexpr int kNgOutChunks = 3;
-constexpr int ng_out_lds() { return kNgWaves * NgStream<1, 1, kNgPlanes, kNgOutChunks>::kStage; }
-__global__ void __launch_bounds__(kNgThreads, 2) k_ng_out(NarrowParams P)
+// Output projection, + MLP-down's parts (narrow_attention.hip) + biases + residual.  A workgroup has at most 16 rows; a
+// wavefront an eighth of the K values.
+constexpr int kNgDenseChunks = 3;
+constexpr int ng_dense_lds() { return kNgWaves * NgStream<1, 1, kNgPlanes, kNgDenseChunks>::kStage; }
+__global__ void __launch_bounds__(kNgThreads, 2) k_ng_dense(NarrowParams P)
 {
-    using Stream = NgStream<1, 1, kNgPlanes, kNgOutChunks>;
+    using Stream = NgStream<1, 1, kNgPlanes, kNgDenseChunks>;
     extern __shared__ __align__(16) char ng_lds[];
     const Dims &dm = P.dm;
-    const int h = dm.h, f = dm.f, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = dm.h, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r0 = (int)blockIdx.x * P.rows, rn = min(P.rows, h - r0);
     const int b = tid & (kNgSet - 1), row = min(tid >> 3, rn - 1);
     const __half de = P.w[P.lay.b_dense + r0 + row], dn = P.w[P.lay.b_down + r0 + row];
     const int xb = min(b, P.n - 1);                        // the layer input, fp16 or fp32 (converted when the weights are through)
     const __half x16 = P.x_in[(size_t)xb * h + r0 + row];
     const float x32 = P.xres[((size_t)xb * 2 + ((P.layer - 1) & 1)) * h + r0 + row];
-    const int C0 = h / kNgChunk, C = (h + f) / kNgChunk, c0 = C * wave / kNgWaves, c1 = C * (wave + 1) / kNgWaves;
+    float down[kDownParts];
+    down_parts(P, xb, r0 + row, down);
+    const int C = h / kNgChunk, c0 = C * wave / kNgWaves;
     Stream st;
     st.p0.w = P.w + P.lay.w_dense + (size_t)r0 * h; st.p0.row_bytes = (unsigned)h * 2u;
     st.p0.b = P.o; st.p0.b_bytes = (unsigned)P.nt * (unsigned)h * 4u;
-    st.p0.c0 = c0; st.p0.n = max(0, min(c1, C0) - c0);
-    st.p1.w = P.w + P.lay.w_down + (size_t)r0 * f; st.p1.row_bytes = (unsigned)f * 2u;
-    st.p1.b = P.m; st.p1.b_bytes = (unsigned)P.nt * (unsigned)f * 4u;
-    st.p1.c0 = max(0, c0 - C0); st.p1.n = max(0, c1 - max(c0, C0));
+    st.p0.c0 = c0; st.p0.n = C * (wave + 1) / kNgWaves - c0;
+    st.p1 = st.p0; st.p1.n = 0;
     st.ring = lds_address(ng_lds) + (unsigned)(wave * Stream::kStage);
     st.mem = ng_lds + wave * Stream::kStage;
     st.gamma = nullptr;
@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(kNgThreads, 2) k_ng_out(NarrowParams P)
     __syncthreads();
     if (!ok || b >= P.n || (tid >> 3) >= rn) return;
     const float x = P.layer == 0 ? __half2float(x16) : x32;
-    const float res = x + ((ng_total<kNgWaves>(red, Stream::kSetFloats, row, b) + __half2float(de)) + __half2float(dn));
+    const float res = x + (((ng_total<kNgWaves>(red, Stream::kSetFloats, row, b) + down_sum(P, down)) + __half2float(de)) + __half2float(dn));
     if (P.layer == P.n_layers - 1) P.out[(size_t)b * h + r0 + row] = __float2half_rn(res);
     else P.xres[((size_t)b * 2 + (P.layer & 1)) * h + r0 + row] = res;
 }
@@ -221,10 +221,10 @@ hipError_t launch_bat_in(NarrowParams P, int grid, hipStream_t s)
     return ng_launch_in<8>(P, wgs, s);
 }
 
-hipError_t launch_bat_out(NarrowParams P, int grid, hipStream_t s)
+hipError_t launch_bat_dense(NarrowParams P, int grid, hipStream_t s)
 {
     P.rows = min(16, (P.dm.h + grid - 1) / grid);
-    hipLaunchKernelGGL(k_ng_out, dim3((P.dm.h + P.rows - 1) / P.rows), dim3(kNgThreads), ng_out_lds(), s, P);
+    hipLaunchKernelGGL(k_ng_dense, dim3((P.dm.h + P.rows - 1) / P.rows), dim3(kNgThreads), ng_dense_lds(), s, P);
     return hipGetLastError();
 }
 
@@ -241,7 +241,7 @@ hipError_t prepare_narrow_kernels()
     hipError_t e;
     if ((e = ng_prepare<1>()) != hipSuccess || (e = ng_prepare<2>()) != hipSuccess || (e = ng_prepare<3>()) != hipSuccess ||
         (e = ng_prepare<5>()) != hipSuccess || (e = ng_prepare<8>()) != hipSuccess) return e;
-    return hipFuncSetAttribute((const void *)k_ng_out, hipFuncAttributeMaxDynamicSharedMemorySize, ng_out_lds());
+    return hipFuncSetAttribute((const void *)k_ng_dense, hipFuncAttributeMaxDynamicSharedMemorySize, ng_dense_lds());
 }
 
 }  // namespace cfpp

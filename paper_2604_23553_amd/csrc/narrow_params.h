@@ -39,18 +39,32 @@ struct NarrowParams {
     float *m32, *o32;       // the same in fp32, in the same memory: a single sequence's (lone_gemm.hip)
     const float2 *rope;
     unsigned *sync;
+    float *part;            // the attention's partials (StepParams::part), behind which MLP-down's parts are (down_at)
+    int part_slots, downs;  // slots of a head; parts of MLP-down
     int rows, wgs_q;        // matrix rows per workgroup, workgroups of the QKV matrix (set by the launcher)
 };
 
+// MLP-down runs beside the attention (narrow_attention.hip), its K cut into up to kDownParts parts, and leaves their sums where
+// the partials of the attention end: the last kDownParts slots of every head, which the attention does not use.  Part z of row
+// j for token i of the launch:
+constexpr int kDownParts = 8;
+CFPP_HD size_t down_at(int i, int j, int z, int H, int d, int part_slots)
+{
+    const int head = j / d;
+    return (((size_t)i * H + head) * part_slots + (part_slots - kDownParts + z)) * (d + 2) + (j - head * d);
+}
+constexpr int kDownRowsOne = 16, kDownRows = 32;       // rows of a workgroup: one sequence, several
+int down_parts_of(int h, int f, bool one);
+
 bool bat_supported(const Dims &dm, int grid, int threads);
 // several sequences or tokens (narrow_gemm.hip)
-// grid: most workgroups of the first product; the second has rows of at most 16 to one and may have twice as many
+// grid: most workgroups of the first product; the output projection has rows of at most 16 to one and may have twice as many
 hipError_t launch_bat_in(NarrowParams P, int grid, hipStream_t s);
-hipError_t launch_bat_out(NarrowParams P, int grid, hipStream_t s);
+hipError_t launch_bat_dense(NarrowParams P, int grid, hipStream_t s);
 hipError_t prepare_narrow_kernels();
 // one (lone_gemm.hip)
 hipError_t launch_lone_in(NarrowParams P, int grid, hipStream_t s);
-hipError_t launch_lone_out(NarrowParams P, int grid, hipStream_t s);
+hipError_t launch_lone_dense(NarrowParams P, int grid, hipStream_t s);
 hipError_t prepare_lone_kernels();
 
 }  // namespace cfpp

@@ -265,6 +265,21 @@ __device__ __forceinline__ float2 ng_total2(const float *red, int stride, int ro
     return s;
 }
 
+// MLP-down's parts of a row of a token, requested together (past the last: the last again), and their sum in order
+__device__ __forceinline__ void down_parts(const NarrowParams &P, int token, int row, float (&v)[kDownParts])
+{
+    const float *at = P.part + down_at(token, row, 0, P.dm.H, P.dm.d, P.part_slots);
+#pragma unroll
+    for (int z = 0; z < kDownParts; ++z) v[z] = at[min(z, P.downs - 1) * (P.dm.d + 2)];
+}
+__device__ __forceinline__ float down_sum(const NarrowParams &P, const float (&v)[kDownParts])
+{
+    float s = v[0];
+#pragma unroll
+    for (int z = 1; z < kDownParts; ++z) s += z < P.downs ? v[z] : 0.f;
+    return s;
+}
+
 // Rows of a workgroup such that the workgroups of both matrices of the first product come to at most `grid`; even: a rotary
 // pair stays in one workgroup.  0 where that would be more than kNgTileMax tiles of 16.
 inline int ng_in_rows(const Dims &dm, int grid, int *wgs_q, int *wgs)

@@ -28,6 +28,33 @@ def test_shares_of_rows_and_columns(orc, shape, B):
     _batched_case(orc, shape, B, shape.n_layers, synth.seq_lens(5, B, 0, 40))
 
 
+# MLP-down beside the attention: K in one, two, three, five, seven and eight parts, one workgroup to a CU and two, parts and wavefronts
+# with unequal shares of chunks; and 64 heads of so long a context that their pieces stop where the parts begin.
+@pytest.mark.parametrize("shape,lens", [
+    (_shape(512, 64, 512, 16), [9, 3]), (_shape(640, 80, 3200, 20), [40, 0, 7]), (_shape(1408, 128, 7040, 32), [33, 5]),
+    (_shape(1152, 64, 9216, 16), [12, 30]), (_shape(3072, 128, 12288, 32, 1), [4, 90]), (_shape(4096, 64, 4096, 16, 1), [11300]),
+    (_shape(4096, 64, 4096, 16, 1), [11300, 0]), (_shape(1920, 80, 7680, 20), [21]), (_shape(640, 80, 1920, 20), [21]),
+])
+def test_mlp_down_beside_the_attention(orc, shape, lens):
+    from paper_2604_23553_amd.harness import DeviceStack
+    if len(lens) > 1:
+        return _batched_case(orc, shape, len(lens), shape.n_layers, np.array(lens, dtype=np.int32))
+    print(f"[case] one sequence {shape.name} S={lens[0]}", flush=True)
+    S, w = lens[0], synth.layer_weights(shape, 13, 0)
+    K, V = synth.kv_cache(shape, 13, 0, S, S + 1)
+    x = synth.x_input(shape, 13)
+    ds = DeviceStack(shape, S + 1, 1, 1)
+    try:
+        ds.load_layer(0, w)
+        ds.load_kv(0, K, V, S)
+        ds.set_inputs(x, S)
+        ds.block_decode(0)
+        ds.check()
+        assert_block_close(ds.result()[0], orc.block_decode_f16(shape, w, K[0].copy(), V[0].copy(), S, x[0]), shape.name)
+    finally:
+        ds.close()
+
+
 # The statistics come from 16 columns at a time: inputs far from zero mean and with single large values lose nothing
 # (the appended rows are held to the bound of fp32 sums, in which the mean's size enters).
 @pytest.mark.parametrize("shape", [_shape(640, 80, 2560, 20, 1), _shape(1024, 128, 4096, 32, 1)])
