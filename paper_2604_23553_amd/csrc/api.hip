@@ -495,12 +495,12 @@ static bool batched_path(const cfpp_ctx *ctx, const Shape &sh, int batch, bool s
 
 // kv_seq < 0: row i of x / pos / out is sequence i with its own cache (a decode step of
 // `batch` sequences).  kv_seq >= 0: the rows are consecutive positions of sequence kv_seq
-// (a group of prompt tokens): they use the workspace rows 0.. but all append to, and attend
+// (a group of prompt tokens), the first of them `first`: they use the workspace rows 0.. but all append to, and attend
 // over, that one cache - the rows of the group are in the cache before its attention runs,
 // so a token sees the tokens before it.
 static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, const __half *w, __half *kv, int l,
                                         int n_layers, const void *x, const int32_t *pos_dev, int batch, void *out,
-                                        hipStream_t s, int kv_seq = -1)
+                                        hipStream_t s, int kv_seq = -1, int first = 0)
 {
     const Dims &dm = ctx->dm;
     const WorkspaceLayout &wl = ctx->wl;
@@ -529,7 +529,8 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
         HIP_OK((B.n > 1 ? launch_bat_in : launch_lone_in)(B, sh.grid, s));
         StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
         if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
-        HIP_OK(launch_attention_batched(P, B.n, w, kv, s));
+        if (kv_seq >= 0 && group_attention_takes(dm, B.n, first + b0)) HIP_OK(launch_attention_group(P, B.n, first + b0, w, kv, s));
+        else HIP_OK(launch_attention_batched(P, B.n, w, kv, s));
         HIP_OK((B.n > 1 ? launch_bat_dense : launch_lone_dense)(B, sh.grid, s));
     }
     return CFPP_OK;
@@ -792,7 +793,7 @@ extern "C" cfpp_status cfpp_stack_prefill(cfpp_ctx *ctx, const void *const *pack
         for (int l = 0; l < L; ++l)
             if ((st = launch_batched_layer(ctx, sh, static_cast<const __half *>(packed_layers[l]),
                                            static_cast<__half *>(kv_layers[l]), l, L, xg, pos_dev + t0, nb, og, s,
-                                           b)) != CFPP_OK)
+                                           b, pos0 + t0)) != CFPP_OK)
                 return st;
     }
     ctx->planes = (n_tokens - 1) % group + 1;

@@ -44,7 +44,7 @@ struct NarrowParams {
     int rows, wgs_q;        // matrix rows per workgroup, workgroups of the QKV matrix (set by the launcher)
 };
 
-// MLP-down runs beside the attention (narrow_attention.hip), its K cut into up to kDownParts parts, and leaves their sums where
+// MLP-down runs beside the attention (mlp_down.h), its K cut into up to kDownParts parts, and leaves their sums where
 // the partials of the attention end: the last kDownParts slots of every head, which the attention does not use.  Part z of row
 // j for token i of the launch:
 constexpr int kDownParts = 8;
@@ -54,8 +54,17 @@ CFPP_HD size_t down_at(int i, int j, int z, int H, int d, int part_slots)
     return (((size_t)i * H + head) * part_slots + (part_slots - kDownParts + z)) * (d + 2) + (j - head * d);
 }
 constexpr int kDownRowsOne = 16, kDownRows = 32;       // rows of a workgroup: one sequence, several
-int down_parts_of(int h, int f, bool one);
-
+// At most 1024 columns to a part.  For several sequences one workgroup to a CU, or two where that is more than 256 KiB of weights
+// to one (a wavefront has 8 KiB of them in flight): us per layer with one / two: hidden 2560 41.7 / 41.9, 2048 32.1 / 32.1, 3072 58.1 / 56.1,
+// 4096 77.8 / 73.7; but 288 workgroups take 2 - 3 % more of a layer than 240 (hidden 1536 33.5 / 34.6), 320 6 %.  One
+// sequence has no planes to read beside its weights: parts as small as they come (hidden 2560, in three / eight: 35.4 / 34.2).
+inline int down_parts_of(int h, int f, bool one)
+{
+    const int most = min(kDownParts, max(1, f / 1024));
+    if (one) return most;
+    const int per_cu = (size_t)h * f * 2 > (size_t)256 * 256 * 1024 ? 2 : 1;
+    return min(most, max(1, per_cu * 256 * kDownRows / h));
+}
 bool bat_supported(const Dims &dm, int grid, int threads);
 // several sequences or tokens (narrow_gemm.hip)
 // grid: most workgroups of the first product; the output projection has rows of at most 16 to one and may have twice as many

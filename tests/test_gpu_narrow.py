@@ -55,6 +55,112 @@ def test_mlp_down_beside_the_attention(orc, shape, lens):
         ds.close()
 
 
+# A group of prompt tokens behind a longer context attends together: the first such position and the one ahead of it, lengths on both
+# sides of a row of 32 positions, groups of 2 to 8 tokens (the last one of a prompt smaller; one alone takes the other kernel), pieces that
+# share rows unevenly, fewer than eight, another sequence's cache, at the three head sizes; eight heads of 128, which keep to the other kernel.
+@pytest.mark.parametrize("shape,pos0,T,max_batch,b", [
+    (_shape(512, 64, 2048, 16), 890, 13, 8, 1), (_shape(512, 64, 2048, 16), 896, 10, 8, 0), (_shape(512, 64, 2048, 16, 1), 6000, 7, 8, 0),
+    (_shape(1280, 80, 2560, 20), 927, 8, 8, 0), (_shape(1280, 80, 2560, 20), 928, 5, 5, 4), (_shape(1280, 80, 2560, 20), 929, 15, 6, 0),
+    (_shape(2560, 80, 2560, 20, 1), 2060, 8, 8, 0), (_shape(2560, 80, 2560, 20, 1), 1023, 3, 3, 0),
+    (_shape(2048, 128, 2048, 32), 1025, 9, 8, 3), (_shape(4096, 128, 4096, 32, 1), 1300, 4, 4, 0), (_shape(1024, 128, 4096, 32, 1), 2049, 6, 8, 0),
+    (_shape(4096, 64, 4096, 16, 1), 1500, 8, 8, 0), (_shape(4096, 64, 4096, 16, 1), 900, 2, 2, 1),
+])
+def test_group_attention(orc, shape, pos0, T, max_batch, b):
+    from tests.test_gpu_prefill import _check_prompt
+    _check_prompt(orc, shape, 41, pos0, T, max_batch, b, then_decode=False, row_check_every=5)
+
+
+# Its error against 64 bits: the queries and the cache rows that the kernel read (taps, exported cache), attention in numpy's doubles.
+# What bounds it: the tap's head and remainder, 2^-25 of an output of about 1 / sqrt(positions) (1e-6 of it at 1000 positions), a few 2^-24 of
+# the weights (exponential, head and remainder) and of the sums; and the scores' own rounding, 2^-24 of the sum of a score's terms' sizes or
+# so, which the weights take up as it stands.  Also where the queries are large or small as a whole.
+@pytest.mark.parametrize("gain", [1.0, 300.0, 1e-4])
+@pytest.mark.parametrize("shape,pos0", [(_shape(512, 64, 2048, 16, 1), 1001), (_shape(1280, 80, 2560, 20, 1), 930), (_shape(2048, 128, 2048, 32, 1), 2100)])
+def test_group_attention_against_64_bits(shape, pos0, gain):
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    T, h, H, d = 8, shape.hidden, shape.n_heads, shape.head_dim
+    print(f"[case] group attention error {shape.name} pos0={pos0} gain={gain}", flush=True)
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, 43, 0).items()}
+    rows = np.arange(3 * h).reshape(H, 3, d)[:, 0].ravel()                 # the queries' rows
+    w["w_qkv"][rows] = (w["w_qkv"][rows].astype(np.float32) * gain).astype(np.float16)
+    w["b_qkv"][rows] = (w["b_qkv"][rows].astype(np.float32) * gain).astype(np.float16)
+    with cf.profile_build():
+        ds = DeviceStack(shape, pos0 + T, T, 1)
+        try:
+            ds.load_layer(0, w)
+            K, V = synth.kv_cache(shape, 43, 0, pos0, pos0 + T, T)
+            if gain > 1.0:
+                K = (K.astype(np.float32) / gain).astype(np.float16)
+            ds.load_kv(0, K, V, pos0)
+            ds.prefill(synth.x_input(shape, 43, T), pos0)
+            ds.check()
+            q = ds.tap(0, T * h).reshape(T, H, d).astype(np.float64)
+            o = ds.tap(3, T * h).reshape(T, H, d).astype(np.float64)
+            k, v = (a.astype(np.float64) for a in ds.export_kv(0, 0, 0, pos0 + T))
+        finally:
+            ds.close()
+    for t in range(T):
+        s = np.einsum("hd,hpd->hp", q[t], k[:, :pos0 + t + 1]) / np.sqrt(d)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        want = np.einsum("hp,hpd->hd", p / p.sum(axis=1, keepdims=True), v[:, :pos0 + t + 1])
+        terms = np.einsum("hd,hpd->hp", np.abs(q[t]), np.abs(k[:, :pos0 + t + 1])) / np.sqrt(d)
+        err = np.abs(o[t] - want)
+        size = np.einsum("hp,hpd->hd", p / p.sum(axis=1, keepdims=True), np.abs(v[:, :pos0 + t + 1]))
+        bound = 2.0 ** -25 + 2.0 ** -22 * np.abs(want) + 2.0 ** -24 * size * (4 + terms.max(axis=1, keepdims=True))
+        print(f"  token {t}: relative 2-norm {np.linalg.norm(err) / np.linalg.norm(want):.2e}, most of the bound {(err / bound).max():.2f}")
+        assert (err <= bound).all(), f"token {t}"
+
+
+# A token of the group that is not finite reaches no earlier one; a cached V element that is infinite makes that dimension of every
+# token's output infinite and no other.
+@pytest.mark.parametrize("shape,pos0,bad", [
+    (_shape(512, 64, 2048, 16), 37, 3), (_shape(512, 64, 2048, 16), 911, 3), (_shape(1280, 80, 2560, 20), 1200, 7), (_shape(2048, 128, 2048, 32), 1024, 5),
+])
+def test_group_with_a_token_that_is_not_finite(shape, pos0, bad):
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] group ahead of a NaN {shape.name} bad={bad}", flush=True)
+    T, X = 8, synth.x_input(shape, 47, 8)
+    outs = []
+    for nan in (False, True):
+        ds = DeviceStack(shape, pos0 + T, T, shape.n_layers)
+        try:
+            for l in range(shape.n_layers):
+                ds.load_layer(l, synth.layer_weights(shape, 47, l))
+                ds.load_kv(l, *synth.kv_cache(shape, 47, l, pos0, pos0 + T, T), pos0)
+            if nan:
+                X[bad] = np.nan
+            outs.append(ds.prefill(X, pos0).copy())
+        finally:
+            ds.close()
+    assert np.array_equal(outs[0][:bad].view(np.uint16), outs[1][:bad].view(np.uint16))
+    assert not np.isfinite(outs[1][bad:].astype(np.float32)).all(axis=1).any()
+
+
+@pytest.mark.parametrize("shape,pos0", [
+    (_shape(512, 64, 2048, 16, 1), 300), (_shape(512, 64, 2048, 16, 1), 901), (_shape(1280, 80, 2560, 20, 1), 1333), (_shape(2048, 128, 2048, 32, 1), 1040),
+])
+def test_group_behind_an_infinite_v_element(shape, pos0):
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    T, h = 8, shape.hidden
+    print(f"[case] group behind an infinite V {shape.name}", flush=True)
+    K, V = synth.kv_cache(shape, 49, 0, pos0, pos0 + T, T)
+    V[0, 1, pos0 // 2, 3] = np.inf
+    with cf.profile_build():
+        ds = DeviceStack(shape, pos0 + T, T, 1)
+        try:
+            ds.load_layer(0, synth.layer_weights(shape, 49, 0))
+            ds.load_kv(0, K, V, pos0)
+            ds.prefill(synth.x_input(shape, 49, T), pos0)
+            o = ds.tap(3, T * h).reshape(T, h)
+        finally:
+            ds.close()
+    at = shape.head_dim + 3
+    assert (o[:, at] == np.inf).all()
+    assert np.isfinite(np.delete(o, at, axis=1)).all()
+
+
 # The statistics come from 16 columns at a time: inputs far from zero mean and with single large values lose nothing
 # (the appended rows are held to the bound of fp32 sums, in which the mean's size enters).
 @pytest.mark.parametrize("shape", [_shape(640, 80, 2560, 20, 1), _shape(1024, 128, 4096, 32, 1)])
