@@ -35,9 +35,8 @@ __device__ __forceinline__ bool lone_position_ok(const NarrowParams &P, int *pos
 // A chunk to a stage, or as many as keep 8 KiB of a wavefront's weights in flight.
 template <int T>
 constexpr int lone_chunks() { return T == 1 ? 4 : T == 2 ? 2 : 1; }
-constexpr int kLoneX = 2048, kLoneVec = 1024;              // bytes of a wavefront's x (then y), gamma, beta
 template <int T>
-constexpr int lone_in_lds() { return kLoneWaves * (LoneStream<T, lone_chunks<T>(), false>::kStage + kLoneX + 2 * kLoneVec); }
+constexpr int lone_in_lds() { return kLoneWaves * (LoneStream<T, lone_chunks<T>(), false>::kStage + kLoneNorm); }
 
 // LayerNorms, QKV rows and MLP-up rows.  Workgroups 0 .. wgs_q - 1 have P.rows rows each of the QKV matrix (even: a rotary
 // pair stays in one), the others of the MLP-up matrix.  A wavefront has the x, gamma and beta of its own columns; mean and
@@ -50,7 +49,7 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     static_assert(lone_in_lds<T>() <= 160 * 1024, "");
     extern __shared__ __align__(16) char ng_lds[];
     const Dims &dm = P.dm;
-    const int h = dm.h, f = dm.f, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = dm.h, f = dm.f, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool up = (int)blockIdx.x >= P.wgs_q;
     const int r0 = ((int)blockIdx.x - (up ? P.wgs_q : 0)) * P.rows, rn = min(P.rows, (up ? f : 3 * h) - r0);
     // the epilogue's row (MLP-up) or row pair (QKV) of this thread, and its biases: requested ahead of the weights
@@ -58,7 +57,7 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     const __half *bias = P.w + (up ? P.lay.b_up : P.lay.b_qkv) + r0;
     const __half k0 = bias[e0], k1 = bias[up ? e0 : e0 + 1];
     const int C = h / kNgChunk, c0 = C * wave / kLoneWaves, cn = C * (wave + 1) / kLoneWaves - c0;    // (hidden <= 4096: cn <= 8)
-    char *vec = ng_lds + kLoneWaves * Stream::kStage, *mine = vec + wave * (kLoneX + 2 * kLoneVec);
+    char *vec = ng_lds + kLoneWaves * Stream::kStage;
     Stream st;
     st.p0.w = P.w + (up ? P.lay.w_up : P.lay.w_qkv) + (size_t)r0 * h;
     st.p0.row_bytes = (unsigned)h * 2u;
@@ -66,21 +65,10 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     st.p1 = st.p0; st.p1.n = 0;
     st.ring = lds_address(ng_lds) + (unsigned)(wave * Stream::kStage);
     st.mem = ng_lds + wave * Stream::kStage;
-    st.y = reinterpret_cast<const float *>(mine);
-    if (cn > 0) {
-        const unsigned at = lds_address(mine), last = (unsigned)cn * 8u - 1u, p16 = min((unsigned)lane, last) * 16u;
-        if (P.layer == 0) {                                // (the second load has no purpose: the number of loads is fixed)
-            const i32x4 rs = dma_rsrc(P.x_in + c0 * kNgChunk, (unsigned)cn * 128u);
-            lds_dma16(rs, at, p16, 0u);
-            lds_dma16(rs, at + 1024u, p16, 0u);
-        } else {
-            const i32x4 rs = dma_rsrc(P.xres + (size_t)((P.layer - 1) & 1) * h + c0 * kNgChunk, (unsigned)cn * 256u);
-            lds_dma16(rs, at, min((unsigned)lane, 2u * last + 1u) * 16u, 0u);
-            lds_dma16(rs, at + 1024u, min((unsigned)lane + 64u, 2u * last + 1u) * 16u, 0u);
-        }
-        lds_dma16(dma_rsrc(P.w + (up ? P.lay.ln2_g : P.lay.ln1_g) + c0 * kNgChunk, (unsigned)cn * 128u), at + kLoneX, p16, 0u);
-        lds_dma16(dma_rsrc(P.w + (up ? P.lay.ln2_b : P.lay.ln1_b) + c0 * kNgChunk, (unsigned)cn * 128u), at + kLoneX + kLoneVec, p16, 0u);
-    }
+    st.y = reinterpret_cast<const float *>(vec + wave * kLoneNorm);
+    LoneNorm<kLoneWaves> norm;
+    norm.request(vec, c0, cn, P.layer == 0 ? (const void *)P.x_in : (const void *)(P.xres + (size_t)((P.layer - 1) & 1) * h), P.layer == 0,
+                 P.w + (up ? P.lay.ln2_g : P.lay.ln1_g), P.w + (up ? P.lay.ln2_b : P.lay.ln1_b), tid);
     st.begin(rn, tid);
     int pos;
     const bool ok = lone_position_ok(P, &pos);
@@ -88,56 +76,7 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     const int pk = r0 + e0, pd = pk / dm.d, i = pk - pd * dm.d, nh = pd / 3, c = pd - 3 * nh;
     const bool rot = !up && c < 2 && i < dm.r;
     st.wait_ahead();                                       // x, gamma and beta are there
-    float x[8];
-    u32x4 g, b;
-    {
-        const bool real = lane < 8 * cn;                   // this lane's 8 columns
-        const char *at = mine + (P.layer == 0 ? lane * 16 : lane * 32);
-        const u32x4 xa = *reinterpret_cast<const u32x4 *>(at), xb = *reinterpret_cast<const u32x4 *>(P.layer == 0 ? at : at + 16);
-        g = *reinterpret_cast<const u32x4 *>(mine + kLoneX + lane * 16);
-        b = *reinterpret_cast<const u32x4 *>(mine + kLoneX + kLoneVec + lane * 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float2 v = unpack_h2(xa[e]);
-            const float lo = P.layer == 0 ? v.x : __uint_as_float(e < 2 ? xa[2 * e] : xb[2 * e - 4]);
-            const float hi = P.layer == 0 ? v.y : __uint_as_float(e < 2 ? xa[2 * e + 1] : xb[2 * e - 3]);
-            x[2 * e] = real ? lo : 0.f;
-            x[2 * e + 1] = real ? hi : 0.f;
-        }
-    }
-    auto stat = [&](int w) { return reinterpret_cast<float *>(vec + w * (kLoneX + 2 * kLoneVec) + kLoneX); };
-    auto joined = [&](float v, int slot) {                 // sum over the workgroup, in order
-        v = wave_sum(v);
-        if (lane == 0) stat(wave)[slot] = v;
-        __syncthreads();
-        float t = 0.f;
-#pragma unroll
-        for (int w = 0; w < kLoneWaves; ++w) t += stat(w)[slot];
-        return t;
-    };
-    float s = 0.f, q = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s += x[e];
-    const float mean = joined(s, 0) / (float)h;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        x[e] -= mean;
-        q += lane < 8 * cn ? x[e] * x[e] : 0.f;
-    }
-    const float inv = 1.0f / sqrtf(joined(q, 1) / (float)h + dm.ln_eps);
-    {
-        float4 y[2];
-        float *v = reinterpret_cast<float *>(y);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float2 gg = unpack_h2(g[e]), bb = unpack_h2(b[e]);
-            v[2 * e] = x[2 * e] * inv * gg.x + bb.x;
-            v[2 * e + 1] = x[2 * e + 1] * inv * gg.y + bb.y;
-        }
-        float4 *to = reinterpret_cast<float4 *>(mine + lane * 32);
-        to[0] = y[0]; to[1] = y[1];
-        ng_lds_read();                                     // (only this wavefront reads them)
-    }
+    norm.finish(h, dm.ln_eps);
     const float2 cs = P.rope[rot ? (size_t)pos * (dm.r >> 1) + (i >> 1) : 0];
     st.run();
     __syncthreads();                                       // the rings have been read

@@ -142,4 +142,87 @@ struct LoneStream {
     }
 };
 
+// LayerNorm of one token, dealt like the stream: a wavefront has the x, gamma and beta of its own columns, at most 512; mean and
+// squared deviations are joined over the W wavefronts in order, one behind the other (two passes over registers).
+constexpr int kLoneX = 2048, kLoneVec = 1024;              // bytes of a wavefront's x (then its normalised columns), gamma, beta
+constexpr int kLoneNorm = kLoneX + 2 * kLoneVec;
+template <int W>
+struct LoneNorm {
+    char *vec, *mine;       // LDS: of all wavefronts, of this one
+    int cn, lane, wave;
+    bool half;              // x is fp16
+    // four loads (where the wavefront has columns); columns: chunks [c0, c0 + cn) of 64
+    __device__ __forceinline__ void request(char *lds, int c0, int cn_, const void *x, bool x_half, const __half *gamma, const __half *beta, int tid)
+    {
+        vec = lds; cn = cn_; half = x_half;
+        lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        mine = vec + wave * kLoneNorm;
+        if (cn <= 0) return;
+        const unsigned at = lds_address(mine), last = (unsigned)cn * 8u - 1u, p16 = min((unsigned)lane, last) * 16u;
+        if (half) {                                        // (the second load has no purpose: the number of loads is fixed)
+            const i32x4 rs = dma_rsrc(static_cast<const __half *>(x) + c0 * kNgChunk, (unsigned)cn * 128u);
+            lds_dma16(rs, at, p16, 0u);
+            lds_dma16(rs, at + 1024u, p16, 0u);
+        } else {
+            const i32x4 rs = dma_rsrc(static_cast<const float *>(x) + c0 * kNgChunk, (unsigned)cn * 256u);
+            lds_dma16(rs, at, min((unsigned)lane, 2u * last + 1u) * 16u, 0u);
+            lds_dma16(rs, at + 1024u, min((unsigned)lane + 64u, 2u * last + 1u) * 16u, 0u);
+        }
+        lds_dma16(dma_rsrc(gamma + c0 * kNgChunk, (unsigned)cn * 128u), at + kLoneX, p16, 0u);
+        lds_dma16(dma_rsrc(beta + c0 * kNgChunk, (unsigned)cn * 128u), at + kLoneX + kLoneVec, p16, 0u);
+    }
+    // what request() asked for is there: the normalised columns in the place of x.  Two workgroup barriers.
+    __device__ __forceinline__ void finish(int h, float eps)
+    {
+        float x[8];
+        u32x4 g, b;
+        {
+            const bool real = lane < 8 * cn;               // this lane's 8 columns
+            const char *at = mine + (half ? lane * 16 : lane * 32);
+            const u32x4 xa = *reinterpret_cast<const u32x4 *>(at), xb = *reinterpret_cast<const u32x4 *>(half ? at : at + 16);
+            g = *reinterpret_cast<const u32x4 *>(mine + kLoneX + lane * 16);
+            b = *reinterpret_cast<const u32x4 *>(mine + kLoneX + kLoneVec + lane * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float2 v = unpack_h2(xa[e]);
+                const float lo = half ? v.x : __uint_as_float(e < 2 ? xa[2 * e] : xb[2 * e - 4]);
+                const float hi = half ? v.y : __uint_as_float(e < 2 ? xa[2 * e + 1] : xb[2 * e - 3]);
+                x[2 * e] = real ? lo : 0.f;
+                x[2 * e + 1] = real ? hi : 0.f;
+            }
+        }
+        auto stat = [&](int w) { return reinterpret_cast<float *>(vec + w * kLoneNorm + kLoneX); };
+        auto joined = [&](float v, int slot) {             // sum over the workgroup, in order
+            v = wave_sum(v);
+            if (lane == 0) stat(wave)[slot] = v;
+            __syncthreads();
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) t += stat(w)[slot];
+            return t;
+        };
+        float s = 0.f, q = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += x[e];
+        const float mean = joined(s, 0) / (float)h;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            x[e] -= mean;
+            q += lane < 8 * cn ? x[e] * x[e] : 0.f;
+        }
+        const float inv = 1.0f / sqrtf(joined(q, 1) / (float)h + eps);
+        float4 y[2];
+        float *v = reinterpret_cast<float *>(y);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float2 gg = unpack_h2(g[e]), bb = unpack_h2(b[e]);
+            v[2 * e] = x[2 * e] * inv * gg.x + bb.x;
+            v[2 * e + 1] = x[2 * e + 1] * inv * gg.y + bb.y;
+        }
+        float4 *to = reinterpret_cast<float4 *>(mine + lane * 32);
+        to[0] = y[0]; to[1] = y[1];
+        ng_lds_read();                                     // (only this wavefront reads them)
+    }
+};
+
 }  // namespace cfpp

@@ -247,3 +247,38 @@ def test_lm_head_with_fewer_rows_than_workgroups_and_ties(orc, vocab):
             assert int(ds.tokens[2].item()) == 2
     finally:
         ds.close()
+
+
+# The LM head through LDS rings: wavefronts with unequal shares of the columns or with none, groups of 16 rows that are partly
+# there, one row to a workgroup; and the shapes and launches that keep to the other kernel (columns that are no whole chunks, more than
+# 4096, 256 threads).  Twice in a row: the count of workgroups that have delivered starts at zero again.
+@pytest.mark.parametrize("heads,d,vocab,threads", [
+    (2, 64, 300, 512), (8, 80, 4100, 512), (16, 80, 5000, 512), (22, 64, 777, 512), (32, 128, 600, 512), (1, 80, 500, 512), (36, 128, 300, 512), (8, 64, 900, 256),
+])
+def test_lm_head_shares_of_rows_and_columns(orc, heads, d, vocab, threads):
+    import torch
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    h = heads * d
+    print(f"[case] LM head hidden={h} vocab={vocab} threads={threads}", flush=True)
+    shape = synth.ModelShape(h, heads, d, 16, 512, n_layers=1, name=f"lm-h{h}")
+    head, hidden = synth.lm_head(shape, 15, vocab=vocab), synth.x_input(shape, 15)
+    ds = DeviceStack(shape, 8, 1, 1)
+    try:
+        ds.set_options(threads=threads)
+        ds.load_lm(head, synth.embedding(shape, 15, vocab=vocab))
+        ds.out[:1].copy_(torch.from_numpy(hidden))
+        want = orc.lm_head_logits(shape, head, orc.half_to_real(hidden[0]))
+        bits = None
+        for step in range(2):
+            ds.set_tokens([0, 0], 1)
+            cf.cfpp_lm_next(ds.ctx, ds.lm, ds.out, ds.tokens, ds.pos, ds.logits, ds.s)
+            ds.check()
+            lg = ds.logits.cpu().numpy()
+            # fp32 sums of h products of |y| <= 5 and |w| <= 0.1 or so: h 2^-24 of their sizes' sum is far above what fixed trees lose
+            assert np.abs(lg.astype(np.float64) - want).max() <= 1e-4 * max(1.0, h / 1024)
+            assert int(ds.tokens[2].item()) == int(np.argmax(lg)) and int(ds.pos[0].item()) == 2
+            assert bits is None or np.array_equal(bits, lg.view(np.uint32))
+            bits = lg.view(np.uint32).copy()
+    finally:
+        ds.close()
