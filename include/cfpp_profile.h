@@ -57,6 +57,13 @@ cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_
 cfpp_status cfpp_debug_prefill_tiles(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                      int32_t plan[8], int32_t past[4]);
 
+/* What the first product of a pass of more than 512 tokens runs as, behind the two above (the second product is theirs).
+ * plan[0..1]: tokens and output features of its tile, plan[2]: MLP-up rows that the launch takes (all of them: there
+ * is no other), plan[3..4]: the tile of the launch that takes the others, or 0.  past[0..1]: by how many rows the tiles'
+ * loads reach past the weights in the first launch, in the second. */
+cfpp_status cfpp_debug_prefill_long(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
+                                    int32_t plan[5], int32_t past[2]);
+
 /* The narrow products of a pass of n_tokens tokens on a device of n_cu CUs (host arithmetic, no
  * GPU): plan[0] 1 if the pass takes them; plan[1], plan[2] rows and tiles of a workgroup of the
  * first product, plan[3], plan[4] of the second, plan[5] the parts of the second one's K,

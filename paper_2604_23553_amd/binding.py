@@ -287,6 +287,13 @@ def cfpp_debug_prefill_tiles(cfg: Config, rows: int, n_tokens: int):
     return (tuple(plan[:4]), tuple(plan[4:])), (tuple(past[:2]), tuple(past[2:]))
 
 
+def cfpp_debug_prefill_long(cfg: Config, rows: int, n_tokens: int):
+    """Profiling library: (tile, MLP-up rows of the first launch, tile of the second or None) and the reach past the weights."""
+    plan, past = (C.c_int32 * 5)(), (C.c_int32 * 2)()
+    _check(lib().cfpp_debug_prefill_long(C.byref(cfg), C.c_int32(rows), C.c_int32(n_tokens), plan, past), "cfpp_debug_prefill_long")
+    return ((plan[0], plan[1]), plan[2], (plan[3], plan[4]) if plan[3] else None), tuple(past)
+
+
 def cfpp_debug_prefill_narrow(cfg: Config, rows: int, n_tokens: int, n_cu: int = 256):
     """None, or (rows, tiles of the first product, rows, tiles, parts of the second, sets of tokens)."""
     plan = (C.c_int32 * 7)()

@@ -849,7 +849,7 @@ extern "C" cfpp_status cfpp_stack_prefill_gemm(cfpp_ctx *ctx, const void *const 
         pf_place(P, pl, sc);
         P.rope = reinterpret_cast<const float2 *>(ctx->ws + ctx->wl.rope);
         pf_plan_pass(P);
-        if (!pf_plan_narrow(P, ctx->n_cu)) pf_plan_middle(P);
+        if (!pf_plan_narrow(P, ctx->n_cu)) { pf_plan_middle(P); pf_plan_long(P); }
         float *xa = reinterpret_cast<float *>(sc + pl.xres), *xb2 = reinterpret_cast<float *>(sc + pl.xnext);
         for (int l = 0; l < L; ++l) {
             P.layer = l;
@@ -1204,6 +1204,25 @@ extern "C" cfpp_status cfpp_debug_prefill_tiles(const cfpp_config *c, int32_t ro
     pf_plan_pass(P);
     pf_plan_middle(P);
     pf_describe_plan(P, plan, past);
+    return CFPP_OK;
+}
+
+extern "C" cfpp_status cfpp_debug_prefill_long(const cfpp_config *c, int32_t rows, int32_t n_tokens, int32_t plan[5],
+                                               int32_t past[2])
+{
+    int32_t base[8], reach[4];
+    cfpp_status st = cfpp_debug_prefill_plan(c, rows, n_tokens, base, reach);      // (refuses what it refuses)
+    if (st != CFPP_OK) return st;
+    if (!plan || !past) return fail(CFPP_EINVAL, "NULL argument");
+    PfParams P;
+    std::memset(&P, 0, sizeof P);
+    P.dm = dims_of(*c); P.lay = packed_layout(P.dm.h, P.dm.f);
+    P.n_rows = n_tokens; P.rows = rows; P.n_layers = c->n_layers;
+    pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));
+    pf_plan_pass(P);
+    pf_plan_middle(P);
+    pf_plan_long(P);
+    pf_describe_long(P, plan, past);
     return CFPP_OK;
 }
 

@@ -114,8 +114,8 @@ k_pf_gemm(PfParams P, int splits, int gm)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int h = dm.h, f = dm.f;
-    const int ntn0 = FL == kPfIn ? (3 * h + BN - 1) / BN : (h + BN - 1) / BN;
-    const int ntn = FL == kPfIn ? ntn0 + (f + BN - 1) / BN : ntn0;
+    const int ntn0 = FL == kPfIn ? (P.qkv ? (3 * h + BN - 1) / BN : 0) : (h + BN - 1) / BN;
+    const int ntn = FL == kPfIn ? ntn0 + (P.up1 - P.up0 + BN - 1) / BN : ntn0;
     const int mt = (P.n_rows + BM - 1) / BM, tiles = ntn * mt, total = tiles * splits;
     const int per_xcd = (total + 7) >> 3;
     const int v = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
@@ -126,7 +126,7 @@ k_pf_gemm(PfParams P, int splits, int gm)
     const int grp = tile / (gm * ntn), in_grp = tile - grp * gm * ntn, gh = min(gm, mt - grp * gm);
     const int m0 = (grp * gm + in_grp % gh) * BM, tn = in_grp / gh;
     const bool up = FL == kPfIn && tn >= ntn0;
-    const int n0 = (up ? tn - ntn0 : tn) * BN, N = FL == kPfIn ? (up ? f : 3 * h) : h;
+    const int n0 = up ? P.up0 + (tn - ntn0) * BN : tn * BN, N = FL == kPfIn ? (up ? P.up1 : 3 * h) : h;
     const int n_steps = (FL == kPfIn ? h : h + f) / BK, j_dense = h / BK;
     const int js = (int)((long long)n_steps * z / splits), je = (int)((long long)n_steps * (z + 1) / splits);
 
@@ -426,7 +426,7 @@ template <int FL, int BM, int BN, int BK, int ST, int WM, int WN>
 static hipError_t pf_launch(const PfParams &P, const PfPlan &pl, hipStream_t s)
 {
     const int h = P.dm.h, f = P.dm.f, splits = pl.splits;
-    const int ntn = FL == kPfIn ? (3 * h + BN - 1) / BN + (f + BN - 1) / BN : (h + BN - 1) / BN;
+    const int ntn = FL == kPfIn ? (P.qkv ? (3 * h + BN - 1) / BN : 0) + (P.up1 - P.up0 + BN - 1) / BN : (h + BN - 1) / BN;
     const int mt = (P.n_rows + BM - 1) / BM, nall = FL == kPfIn ? 3 * h + f : h;
     // the parts of a split product, [splits][mt * BM][all columns] floats, must fit what the scratch holds for them
     if (splits > 1 && (size_t)splits * mt * BM * nall * sizeof(float) > (FL == kPfIn ? P.part_bytes : P.part_out_bytes))
@@ -511,7 +511,7 @@ static PfPlan pf_plan(const PfParams &P, bool in, size_t part_bytes, float *cost
     float best_cost = 1e30f;
     for (int k = 0; k < kPfTile32x128; ++k) {
         const PfTileCost &t = kPfTiles[k];
-        if (in && t.bn == 320 && t.bm == 256) continue;    // (its QKV and MLP-up epilogues spill registers)
+        if (in && t.bn == 320 && t.bm == 256) continue;    // (left to pf_plan_long)
         const int mt = (P.n_rows + t.bm - 1) / t.bm;
         const int ntn = in ? (3 * h + t.bn - 1) / t.bn + (f + t.bn - 1) / t.bn : (h + t.bn - 1) / t.bn;
         for (int sp = 1; sp <= 16; ++sp) {
@@ -529,6 +529,7 @@ static PfPlan pf_plan(const PfParams &P, bool in, size_t part_bytes, float *cost
 
 static void pf_plan_ends(PfParams &P)
 {
+    P.up_cut = P.dm.f;
     P.row_fused = P.plan_out.splits > 1 && P.part_out == P.q;
     const int bm = kPfTiles[P.plan_out.tile].bm;
     P.part_out_stride = (size_t)((P.n_rows + bm - 1) / bm * bm) * P.dm.h;
@@ -631,6 +632,58 @@ void pf_plan_middle(PfParams &P)
     pf_plan_ends(P);
 }
 
+// The first product of a long pass: what a CU does is whole tiles, and 2.1 or 4.4 rounds of large ones take as long as 3 or 5.  So it may
+// run as two launches: a whole number of rounds of large tiles (QKV and most of MLP-up), and the rest of MLP-up in smaller ones
+// that fill one round more; and 256 x 320 tiles are among the large ones (with a feature and 16 tokens to a lane their epilogues spilled
+// registers; now they don't).  Chosen by an estimate of
+//     rounds x (K / 32 x step + epilogue) + kPfCutLaunch for a second launch
+// whose constants, in us, are fitted to timings of whole layers with every one of these tiles (hidden 1280 .. 4096, 600 .. 4096 tokens, 352 of
+// them, 1.1 % rms; the tile it picks is 0.1 % from the fastest in the mean, 1.9 % at worst).  It prices the last, partly filled round of a launch
+// too high (fewer CUs, more power and bandwidth to each) and the gap between two launches too low: 12 us for the second one, and 2.5 %
+// and 2 us, put the line where 130 random sizes had it (with 4 us 1536, 3198 tokens 481 -> 494).  us per layer, plan above -> this: whole: hidden
+// 2560, 1000 tokens 377 -> 357, 3120 1153 -> 1121; 1536, 3482 541 -> 516; 3072, 1690 824 -> 774; 4096, 3362 2731 -> 2613; in two: 2560, 2880 tokens
+// 1020 -> 983, 4096 1383 -> 1361; 2048, 3573 888 -> 832; 4096, 1531 behind 700 1192 -> 1185, 1670 1380 -> 1313.  Of the 130 sizes none lost more
+// than the runs of one side differ (1 %).
+struct PfLongCost { float step, epi; };
+constexpr float kPfCutLaunch = 12.f;
+static const PfLongCost kPfLongCosts[kPfTileKinds] = {
+    {}, {}, {}, {0.786f, 8.5f}, {0.891f, 7.6f}, {1.089f, 10.5f}, {1.291f, 14.9f}, {}, {}, {0.399f, 3.3f}, {0.375f, 6.9f}, {0.530f, 5.5f}, {0.652f, 6.1f}, {},
+};
+void pf_plan_long(PfParams &P)
+{
+    if (P.plan_in.splits != 1 || P.n_rows <= 512 || kPfLongCosts[P.plan_in.tile].step == 0.f) return;
+    const int h = P.dm.h, f = P.dm.f;
+    auto columns = [](int n, int bn) { return (n + bn - 1) / bn; };
+    // `wide`: columns of tiles
+    auto cost = [&](int kind, int wide) {
+        const PfTileCost &t = kPfTiles[kind];
+        const int wgs = (P.n_rows + t.bm - 1) / t.bm * wide, rest = wgs % (kPfCus * t.per_cu);
+        float rounds = (float)(wgs / (kPfCus * t.per_cu) * t.per_cu);
+        if (rest > 0) rounds += t.per_cu == 1 ? 1.f : rest <= kPfCus ? 1.36f : 2.f;        // (128 x 160, two to a CU: one alone is faster, by 1.36)
+        return rounds * ((float)h / 32.f * kPfLongCosts[kind].step + kPfLongCosts[kind].epi);
+    };
+    const int bn0 = kPfTiles[P.plan_in.tile].bn;
+    float best = cost(P.plan_in.tile, columns(3 * h, bn0) + columns(f, bn0)) * 0.975f - 2.f;
+    for (int k = 0; k < kPfTileKinds; ++k) {
+        if (kPfLongCosts[k].step == 0.f) continue;
+        const PfTileCost &t = kPfTiles[k];
+        const int mt = (P.n_rows + t.bm - 1) / t.bm, nq = columns(3 * h, t.bn);
+        const float whole = cost(k, nq + columns(f, t.bn));
+        if (whole < best) { best = whole; P.plan_in.tile = k; P.up_cut = f; }
+        if (t.per_cu > 1) continue;
+        for (int r = 1; r * kPfCus < mt * (nq + columns(f, t.bn)); ++r) {
+            const int cut = (r * kPfCus / mt - nq) * t.bn / kPfTile * kPfTile;
+            if (cut <= 0 || cut >= f) continue;
+            const float first = cost(k, nq + columns(cut, t.bn)) + kPfCutLaunch;
+            for (int j = 0; j < kPfTileKinds; ++j) {
+                if (kPfLongCosts[j].step == 0.f || j == kPfTile128x128) continue;
+                const float both = first + cost(j, columns(f - cut, kPfTiles[j].bn));
+                if (both < best) { best = both; P.plan_in.tile = k; P.up_cut = cut; P.up_tile = j; }
+            }
+        }
+    }
+}
+
 #ifdef CFPP_PROFILE
 __global__ void __launch_bounds__(256) k_debug_gelu(const float *z, float *epilogue, float *library, int n, int flags)
 {
@@ -643,6 +696,22 @@ hipError_t launch_debug_gelu(const float *z, float *epilogue, float *library, in
 {
     hipLaunchKernelGGL(k_debug_gelu, dim3((n + 255) / 256), dim3(256), 0, s, z, epilogue, library, n, flags);
     return hipGetLastError();
+}
+
+void pf_describe_long(const PfParams &P, int plan[5], int past[2])
+{
+    const int h = P.dm.h, f = P.dm.f;
+    const PfTileCost &a = kPfTiles[P.plan_in.tile], &b = kPfTiles[P.up_tile];
+    auto reach = [](int from, int to, const PfTileCost &t) {           // of a matrix's rows [from, to)
+        const int ru = 1024 / (2 * t.bk);
+        int w = 0;
+        for (int u = from; u < from + (to - from + t.bn - 1) / t.bn * t.bn; u += ru) w = max(w, pf_dma_row(u, to, ru) + ru - to);
+        return w;
+    };
+    plan[0] = a.bm; plan[1] = a.bn; plan[2] = P.up_cut;
+    plan[3] = P.up_cut < f ? b.bm : 0; plan[4] = P.up_cut < f ? b.bn : 0;
+    past[0] = max(reach(0, 3 * h, a), reach(0, P.up_cut, a));
+    past[1] = P.up_cut < f ? reach(P.up_cut, f, b) : 0;
 }
 
 void pf_describe_plan(const PfParams &P, int plan[8], int past[4])
@@ -673,7 +742,7 @@ static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
     case 3: return pf_launch<FL, 128, 320, 32, 4, 4, 2>(P, pl, s);
     case 4: return pf_launch<FL, 256, 192, 32, 3, 4, 2>(P, pl, s);
     case 5: return pf_launch<FL, 256, 256, 32, 3, 4, 2>(P, pl, s);
-    case 6: if (FL == kPfOut) return pf_launch<kPfOut, 256, 320, 32, 3, 4, 2>(P, pl, s); break;
+    case 6: return pf_launch<FL, 256, 320, 32, 3, 4, 2>(P, pl, s);
     case kPfTile32x128: return pf_launch<FL, 32, 128, 64, 3, 1, 4>(P, pl, s);
     case kPfTile64x256: if (FL == kPfIn) return pf_launch<kPfIn, 64, 256, 64, 3, 1, 4>(P, pl, s); break;
     case kPfTile128x160: if (FL == kPfIn) return pf_launch<kPfIn, 128, 160, 32, 3, 4, 1>(P, pl, s); break;
@@ -685,7 +754,15 @@ static hipError_t pf_gemm(const PfParams &P, const PfPlan &pl, hipStream_t s)
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s) { return pf_gemm<kPfIn>(P, P.plan_in, s); }
+hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s)
+{
+    PfParams Q = P;
+    Q.qkv = true; Q.up0 = 0; Q.up1 = P.up_cut;
+    const hipError_t e = pf_gemm<kPfIn>(Q, P.plan_in, s);
+    if (e != hipSuccess || P.up_cut == P.dm.f) return e;
+    Q.qkv = false; Q.up0 = P.up_cut; Q.up1 = P.dm.f;
+    return pf_gemm<kPfIn>(Q, PfPlan{P.up_tile, 1}, s);
+}
 hipError_t launch_pf_gemm_out(const PfParams &P, hipStream_t s) { return pf_gemm<kPfOut>(P, P.plan_out, s); }
 
 }  // namespace cfpp

@@ -89,6 +89,11 @@ struct PfParams {
     float *part_out;        // parts of the second one, part_out_bytes
     size_t part_bytes, part_out_bytes, part_out_stride;     // (stride: floats between the second product's parts)
     PfPlan plan_in, plan_out;
+    // the first product in two launches (pf_plan_long): MLP-up rows [up_cut, f) with the tile up_tile (up_cut = f: one launch); what a
+    // launch takes: the QKV matrix or not, MLP-up rows [up0, up1)
+    int up_cut, up_tile;
+    int up0, up1;
+    bool qkv;
     PfNarrow nrw;
     bool row_fused;         // the kernel that adds the second product's parts prepares the next layer's input too
     const float2 *rope;
@@ -112,8 +117,11 @@ bool pf_supported(const Dims &dm);
 void pf_plan_pass(PfParams &P);
 // behind it, for passes that the narrow products don't take: other tiles for 65 .. 1024 tokens
 void pf_plan_middle(PfParams &P);
+// behind that, for more than 512 tokens: other tiles for the first product, or two launches
+void pf_plan_long(PfParams &P);
 // the plan, and what the products' DMA would request past their operands (profiling library): see cfpp_debug_prefill_plan
 void pf_describe_plan(const PfParams &P, int plan[8], int past[4]);
+void pf_describe_long(const PfParams &P, int plan[5], int past[2]);
 // the epilogues' GELU and the library's on n values (profiling library)
 hipError_t launch_debug_gelu(const float *z, float *epilogue, float *library, int n, int flags, hipStream_t s);
 // one block for the tokens of a pass: LayerNorm inputs, QKV and up, attention, dense and down

@@ -7,6 +7,7 @@ import torch                       # (ahead of the library: both take the HIP ru
 
 import synth
 from tests.parity import MAX_ABS, assert_appended_rows, assert_block_close, ulp16
+from tests.prefill_long import LONG, first_product
 from tests.prefill_middle import MIDDLE
 from tests.prefill_plans import WIDE
 from tests.test_gpu_stack import _batched_case, check_appended_rows
@@ -294,6 +295,16 @@ def test_middle_tiles_over_two_layers(shape, T, first, second):
         base, got = cf.cfpp_debug_prefill_plan(cfg, rows, T)[0], cf.cfpp_debug_prefill_tiles(cfg, rows, T)[0]
     assert got == (first or base[0], second or base[1])
     check(shape, T, *got)
+
+
+# Long passes: the first product with 256 x 320 tiles and as two launches, over two layers (as above).
+@pytest.mark.parametrize("shape,T,tile,second", LONG)
+def test_long_passes_over_two_layers(shape, T, tile, second):
+    from tests.prefill_plans import taken
+    from tests.test_gpu_prefill import test_gemm_plans_over_two_layers as check
+    got, _ = first_product(shape, T)
+    assert (got[0], got[2]) == (tile, second)
+    check(shape, T, *taken(shape, T)[0])
 
 
 # The launch option names the workgroups of the first product: eight tiles of rows to each of the fewest, two rows to each of
