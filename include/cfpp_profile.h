@@ -66,8 +66,8 @@ cfpp_status cfpp_debug_prefill_long(const cfpp_config *cfg, int32_t rows, int32_
 
 /* The narrow products of a pass of n_tokens tokens on a device of n_cu CUs (host arithmetic, no
  * GPU): plan[0] 1 if the pass takes them; plan[1], plan[2] rows and tiles of a workgroup of the
- * first product, plan[3], plan[4] of the second, plan[5] the parts of the second one's K,
- * plan[6] the sets of tokens. */
+ * first product, plan[3], plan[4] of the second (of the output projection alone where MLP-down
+ * runs beside the attention), plan[5] the parts of its K, plan[6] the sets of tokens. */
 cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *cfg, int32_t rows, int32_t n_tokens, int32_t n_cu, int32_t plan[7]);
 
 /* Where cfpp_stack_prefill_gemm keeps a layer's intermediates in the caller's scratch, byte

@@ -16,9 +16,9 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcfpp.so")
 LIB_PROFILE = os.path.join(PKG, "libcfpp_profile.so")
 SOURCES = ["api.hip", "decode_kernels.hip", "fused_kernel.hip", "lm_kernels.hip", "narrow_gemm.hip", "lone_gemm.hip", "narrow_attention.hip", "group_attention.hip", "prefill_narrow.hip",
-           "prep_kernels.hip", "prefill_kernels.hip", "prefill_gemm.hip"]
+           "prep_kernels.hip", "prefill_kernels.hip", "prefill_beside.hip", "prefill_gemm.hip"]
 HEADERS = ["layout.h", "device_utils.h", "decode_params.h", "attention_common.h", "decode_blocks.h",
-           "attention_blocks.h", "lm_params.h", "narrow_params.h", "narrow_stream.h", "lone_stream.h", "mlp_down.h", "lds_dma.h", "prefill_params.h", "prefill_device.h", "half_split.h"]
+           "attention_blocks.h", "lm_params.h", "narrow_params.h", "narrow_stream.h", "lone_stream.h", "mlp_down.h", "lds_dma.h", "prefill_params.h", "prefill_device.h", "prefill_attention.h", "half_split.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -143,9 +143,9 @@ __global__ void __launch_bounds__((64 * pn_waves<T, S>()), (pn_waves<T, S>() > 4
     extern __shared__ __align__(16) char pn_lds[];
     const Dims &dm = P.dm;
     const int h = dm.h, f = dm.f, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int splits = P.plan_out.splits, g = (int)blockIdx.x / splits, z = (int)blockIdx.x - g * splits;
+    const int downs = P.nrw.downs, splits = P.plan_out.splits - downs, g = (int)blockIdx.x / splits, z = (int)blockIdx.x - g * splits;
     const int r0 = g * P.nrw.rows_out, rn = min(P.nrw.rows_out, h - r0);
-    const int C0 = h / kNgChunk, C = (h + f) / kNgChunk, z0 = C * z / splits, zn = C * (z + 1) / splits - z0;
+    const int C0 = h / kNgChunk, C = downs > 0 ? C0 : (h + f) / kNgChunk, z0 = C * z / splits, zn = C * (z + 1) / splits - z0;
     const int c0 = z0 + zn * wave / W, c1 = z0 + zn * (wave + 1) / W;
     Stream st;
     st.p0.w = P.w + P.lay.w_dense + (size_t)r0 * h; st.p0.row_bytes = (unsigned)h * 2u;
@@ -159,7 +159,7 @@ __global__ void __launch_bounds__((64 * pn_waves<T, S>()), (pn_waves<T, S>() > 4
     st.gamma = nullptr;
     st.begin(rn, P.n_rows, kNgSet, 0u, tid);
     st.run();
-    float *red = reinterpret_cast<float *>(pn_lds), *part = P.part_out + (size_t)z * P.part_out_stride + r0;
+    float *red = reinterpret_cast<float *>(pn_lds), *part = P.part_out + (size_t)(downs + z) * P.part_out_stride + r0;
     __syncthreads();                                       // the rings have been read
     st.template leave<S>(red, wave, 0);
     __syncthreads();
@@ -192,7 +192,7 @@ static hipError_t pn_launch(const PfParams &P, bool in, hipStream_t s)
     } else {
         const int groups = (P.dm.h + P.nrw.rows_out - 1) / P.nrw.rows_out;
         if ((size_t)P.plan_out.splits * P.part_out_stride * sizeof(float) > P.part_out_bytes) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_pf_narrow_out<T, S>), dim3(groups * P.plan_out.splits), dim3(64 * pn_waves<T, S>()), lds, s, P);
+        hipLaunchKernelGGL((k_pf_narrow_out<T, S>), dim3(groups * (P.plan_out.splits - P.nrw.downs)), dim3(64 * pn_waves<T, S>()), lds, s, P);
     }
     return hipGetLastError();
     }
@@ -231,9 +231,9 @@ hipError_t launch_pf_narrow_out(const PfParams &P, hipStream_t s) { return pn_ti
 
 // Rows and parts of K of the second product: the least estimate, in us, of a workgroup's weights at 27 KB/us, the
 // activations it reads from the L2 at 90 KB/us (64 tokens' of 2560 columns: 7 us) and the parts' way to memory and back.
-static void pn_plan_out(const PfParams &P, int n_cu, int *rows, int *splits)
+static void pn_plan_out(const PfParams &P, int n_cu, bool dense, int *rows, int *splits)
 {
-    const int h = P.dm.h, C = (h + P.dm.f) / kNgChunk, tokens = (P.n_rows + 7) / 8 * 8;
+    const int h = P.dm.h, C = (dense ? h : h + P.dm.f) / kNgChunk, tokens = (P.n_rows + 7) / 8 * 8;
     float best = 1e30f;
     for (int sp = 1; sp <= 16 && sp <= C; ++sp) {
         for (int per = 1; per <= 2; ++per) {
@@ -261,13 +261,25 @@ bool pf_plan_narrow(PfParams &P, int n_cu)
     N.rows_in = ng_in_rows(P.dm, n_cu, &N.wgs_q, &N.wgs_in);
     if (N.rows_in == 0 || pn_tiles_of(N.rows_in) * pn_sets_of(P.n_rows) > kPnMostSums) return false;
     int splits = 0;
-    pn_plan_out(P, n_cu, &N.rows_out, &splits);
-    const size_t bytes = P.part_bytes + (size_t)((char *)P.part - (char *)P.q), stride = (size_t)P.n_rows * P.dm.h;
-    if (splits == 0 || splits * stride * sizeof(float) > bytes) return false;
-    P.part_out = reinterpret_cast<float *>(P.q);
+    N.downs = pf_down_parts(P.dm, P.n_rows, P.pos0);
+    pn_plan_out(P, n_cu, N.downs > 0, &N.rows_out, &splits);
+    const size_t stride = (size_t)P.n_rows * P.dm.h, bytes = ((size_t)(splits + N.downs) * stride * sizeof(float) + 255) / 256 * 256;
+    if (splits == 0) return false;
+    if (N.downs > 0) {
+        // the parts lie at the end of the scratch: the attention beside MLP-down reads its queries, and may leave parts of its own
+        // ahead of them
+        const size_t room = P.part_bytes / 256 * 256;
+        if (bytes > room) return false;
+        P.part_bytes = room - bytes;
+        P.part_out = P.part + P.part_bytes / sizeof(float);
+        P.part_out_bytes = bytes;
+    } else {
+        P.part_out = reinterpret_cast<float *>(P.q);
+        P.part_out_bytes = P.part_bytes + (size_t)((char *)P.part - (char *)P.q);
+        if (bytes > P.part_out_bytes) return false;
+    }
     P.part_out_stride = stride;
-    P.part_out_bytes = bytes;
-    P.plan_out.splits = splits;
+    P.plan_out.splits = splits + N.downs;
     P.row_fused = true;
     N.on = true;
     return true;
@@ -278,7 +290,7 @@ void pf_describe_narrow(const PfParams &P, int plan[7])
 {
     plan[0] = 1;
     plan[1] = P.nrw.rows_in; plan[2] = pn_tiles_of(P.nrw.rows_in);
-    plan[3] = P.nrw.rows_out; plan[4] = pn_tiles_of(P.nrw.rows_out); plan[5] = P.plan_out.splits;
+    plan[3] = P.nrw.rows_out; plan[4] = pn_tiles_of(P.nrw.rows_out); plan[5] = P.plan_out.splits - P.nrw.downs;
     plan[6] = pn_sets_of(P.n_rows);
 }
 #endif

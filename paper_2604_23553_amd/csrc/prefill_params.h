@@ -58,7 +58,9 @@ constexpr int kPfNarrowMax = 64;
 struct PfNarrow {
     bool on;
     int rows_in, wgs_q, wgs_in;     // first product: rows of a workgroup, workgroups of the QKV matrix and in all
-    int rows_out;                   // second product: rows of a workgroup (parts of K: plan_out.splits)
+    // second product: MLP-down beside the attention in `downs` parts of K, the output projection behind it in plan_out.splits - downs,
+    // with rows_out rows to a workgroup; downs 0: both behind the attention, as one product over the concatenated K
+    int downs, rows_out;
 };
 
 // the parts of a split attention (k_pf_attn): unnormalised sums [parts][tokens][h], maximum and weight [parts][tokens][H]
@@ -66,6 +68,7 @@ struct PfAttnParts {
     float *o;
     float2 *ml;
     int parts;
+    int blocks, first_down; // blocks of queries; the first workgroup that has MLP-down (prefill_beside.hip)
 };
 
 struct PfParams {
@@ -131,6 +134,10 @@ hipError_t launch_pf_gemm_in(const PfParams &P, hipStream_t s);
 hipError_t launch_pf_gemm_out(const PfParams &P, hipStream_t s);
 // The narrow products (prefill_narrow.hip).  pf_plan_narrow: behind pf_plan_pass; true, and P for them, if the pass takes them.
 bool pf_plan_narrow(PfParams &P, int n_cu);
+// (prefill_beside.hip) the attention with MLP-down in the same launch; parts of K that it takes for so many tokens, 0: it does not
+constexpr int kPfDownParts = 8;
+hipError_t launch_pf_attention_beside(const PfParams &P, const PfAttnParts &A, hipStream_t s);
+int pf_down_parts(const Dims &dm, int tokens, int pos0);
 void pf_describe_narrow(const PfParams &P, int plan[7]);   // (profiling library: cfpp_debug_prefill_narrow)
 hipError_t launch_pf_narrow_in(const PfParams &P, hipStream_t s);
 hipError_t launch_pf_narrow_out(const PfParams &P, hipStream_t s);

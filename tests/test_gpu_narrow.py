@@ -213,6 +213,18 @@ def test_short_prompts(orc, shape, T):
     _check_prompt(orc, shape, 29, 5, T, 2, 1, then_decode=False, gemm_rows=128, row_check_every=7)
 
 
+# MLP-down beside the attention of a short prompt: 1 .. 6 sets of tokens, the last one partly there, K in one to eight parts, wavefronts without
+# chunks, one and two workgroups to a CU, behind a context that the attention cuts into parts of its own, at the three head sizes.
+@pytest.mark.parametrize("shape,pos0,T", [
+    (_shape(128, 64, 128, 16), 3, 5), (_shape(512, 64, 2048, 16), 0, 16), (_shape(512, 64, 2048, 16), 7, 23), (_shape(640, 80, 1920, 20), 40, 31),
+    (_shape(1280, 80, 2560, 20), 1, 40), (_shape(1280, 80, 5120, 20), 5, 48), (_shape(1024, 128, 4096, 32), 9, 33), (_shape(1152, 64, 9216, 0), 2, 3),
+    (_shape(4096, 128, 8192, 32, 1), 4, 12), (_shape(512, 64, 2048, 16, 1), 1500, 44), (_shape(640, 80, 2560, 20, 1), 1300, 8), (_shape(1024, 128, 4096, 32, 1), 900, 19),
+])
+def test_short_prompts_with_mlp_down_beside_the_attention(orc, shape, pos0, T):
+    from tests.test_gpu_prefill import _check_prompt
+    _check_prompt(orc, shape, 53, pos0, T, 2, 1, then_decode=False, gemm_rows=128, row_check_every=13)
+
+
 # The tiled products of few tokens, where the narrow ones do not go: an MLP of more than 128 rows to a CU.
 @pytest.mark.parametrize("shape,T", WIDE)
 def test_short_prompts_in_tiles(orc, shape, T):
