@@ -288,6 +288,44 @@ def test_prompt_attention_in_parts(orc, shape, pos0, T):
     _check_prompt(orc, shape, 37, pos0, T, 1, 0, then_decode=False, gemm_rows=128, row_check_every=11)
 
 
+# The weights of a query are relative to a score that follows its maximum only when that is 2^8 times it: scores that rise along the
+# context in steps below and far above that, fall again, and start with keys that weigh nothing against the later ones; 32, 64 and 128 queries
+# to a workgroup, keys whole and in parts, wavefronts that share the keys.  Against the batched path, which keeps the maximum.
+@pytest.mark.parametrize("shape,pos0,T", [
+    (_shape(512, 64, 2048, 0, 1), 700, 40), (_shape(640, 80, 2560, 0, 1), 900, 100), (_shape(2560, 80, 2560, 0, 1), 650, 800), (_shape(1024, 128, 4096, 0, 1), 500, 70),
+    (_shape(2048, 64, 2048, 0, 1), 300, 2050),
+])
+def test_prompt_attention_with_scores_that_rise(shape, pos0, T):
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] rising scores {shape.name} pos0={pos0} T={T}", flush=True)
+    H, d, h, cap = shape.n_heads, shape.head_dim, shape.hidden, pos0 + T
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, 59, 0).items()}
+    rng = np.random.default_rng(59)
+    u = rng.choice([-1.0, 1.0], (H, d))
+    rows = np.arange(3 * h).reshape(H, 3, d)
+    w["w_qkv"][rows[:, 0].ravel()] *= np.float16(0.05)                     # every query: nearly u
+    w["b_qkv"][rows[:, 0].ravel()] = u.ravel().astype(np.float16)
+    K, V = synth.kv_cache(shape, 59, 0, pos0, cap, 8)
+    level = np.array([0.0, 2.0, 4.5, 9.0, 11.0, 25.0, 18.0, 26.0])[np.minimum(np.arange(pos0) * 8 // pos0, 7)]         # scores, in units of e
+    K[0, :, :pos0] = (u[:, None] * (level / np.sqrt(d))[None, :, None] + 0.3 * K[0, :, :pos0].astype(np.float32)).astype(np.float16)
+    X = synth.x_input(shape, 61, batch=T)
+    outs = []
+    for gemm in (False, True):
+        ds = DeviceStack(shape, cap, 8, 1)
+        try:
+            ds.load_layer(0, w)
+            ds.load_kv(0, K, V, pos0)
+            outs.append((ds.prefill_gemm(X, pos0, rows=-(-T // 128) * 128) if gemm else ds.prefill(X, pos0)).astype(np.float64))
+            ds.check()
+        finally:
+            ds.close()
+    want, got = outs
+    rms = np.sqrt((want ** 2).mean(axis=1, keepdims=True))
+    step = np.ldexp(1.0, np.frexp(np.maximum(np.abs(got), np.abs(want)).clip(2.0 ** -14))[1] - 11)
+    assert np.isfinite(got).all() and (np.abs(got - want) <= 1.001 * step + 2e-3 * rms + 2e-5).all()       # (as test_gpu_prefill.py's)
+    assert np.linalg.norm(got - want) <= 2.5e-4 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("kind", ["overflow", "nan"])
 @pytest.mark.parametrize("shape,pos0,T,bad", [
     (_shape(512, 64, 2048, 16), 1200, 64, 31), (_shape(640, 80, 2560, 20), 1210, 37, 36), (_shape(1024, 128, 4096, 32), 640, 100, 63),
