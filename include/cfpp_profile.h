@@ -53,7 +53,8 @@ cfpp_status cfpp_debug_read(cfpp_ctx *ctx, int32_t which, float *dst_host, size_
 cfpp_status cfpp_debug_prefill_plan(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                     int32_t plan[8], int32_t past[4]);
 
-/* The same with the tiles that a pass of 65 .. 1024 tokens takes in the end. */
+/* The same with the tiles that a pass of 65 .. 1024 tokens takes; the first product of more than 512 tokens:
+ * cfpp_debug_prefill_long. */
 cfpp_status cfpp_debug_prefill_tiles(const cfpp_config *cfg, int32_t rows, int32_t n_tokens,
                                      int32_t plan[8], int32_t past[4]);
 

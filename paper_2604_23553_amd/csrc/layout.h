@@ -108,7 +108,8 @@ struct WorkspaceLayout {
     size_t m;         // float[max_batch][f]: GELU(up)
     size_t g;         // float[max_batch][h]: down projection + bias
     size_t o;         // float[max_batch][h]: attention output
-    size_t part;      // float[max_batch*H][part_slots][d+2]: split-KV partials (acc[d], max, sum)
+    size_t part;      // float[max_batch*H][part_slots][d+2]: split-KV partials (acc[d], max, sum); batched path: a head's last slots
+                      // hold MLP-down's parts (down_at)
     size_t lm_best;   // float[kMaxGrid][2]: (logit, row) of every workgroup of the LM-head kernel
     size_t pf_pos;    // int32[max_seq]: positions of a prompt's tokens (prompt processing)
     size_t trace;     // uint64[kTraceWaves][kTraceLen][2]: (tag, 100 MHz clock) pairs (profiling library only, else empty)

@@ -30,7 +30,7 @@ namespace cfpp {
 // 232.0 / 230.4 (234 .. 236 before).  Elsewhere 640 was held against the kernels of before only, us per whole step: 8 heads, 4 layers,
 // 2 sequences of 6000 .. 8000 183 -> 157, 8 of 2000 190 -> 169; 24 heads, 4 layers 245 -> 232, 266 -> 257; 32 heads of 80,
 // 2 layers 168 -> 156, 182 -> 178.  A prompt group's queries share their
-// rows and don't stream: 1024, as measured above.  Pieces of a head never exceed the workspace's part_slots.
+// rows and don't stream: 1024, as measured above.  A head's pieces leave the last kDownParts of its part_slots to MLP-down.
 constexpr int kAttnSpareGroups = 640, kAttnSpareShared = 1024, kAttnPieceRows = 32;
 // Up to four sequences of their own leave workgroups to spare: up to eight pieces of half as many rows.  us a block, 32 rows -> 16:
 // hidden 2560, one sequence of 1000 / 2000 / 4000 41.3 -> 39.5 / 43.4 -> 41.0 / 45.4 -> 43.7, three of 500 .. 1000 42.9 -> 41.8;

@@ -1,6 +1,5 @@
 // Projections of a layer for few tokens (paper Sec. 2.2): the sequences of a decode step, a group of prompt tokens; two to
-// eight of them (one: lone_gemm.hip).  The
-// weights are read once and their way from memory is what takes time, so everything here is arranged around that stream.
+// eight of them (one: lone_gemm.hip).  The weights are read once and their way from memory is what takes time, so everything here is arranged around that stream.
 //
 //   k_ng_in  : both LayerNorms, QKV rows + bias, rotary, K/V append, q; MLP-up rows + bias + GELU
 //   k_ng_dense : output projection, + MLP-down's parts, which the attention launch leaves (narrow_attention.hip), + biases + residual

@@ -1,5 +1,5 @@
 // The stream of a product for few tokens: weights from memory through LDS rings into matrix instructions (narrow_gemm.hip,
-// prefill_narrow.hip).
+// prefill_narrow.hip; MLP-down of both: mlp_down.h, prefill_beside.hip).
 //
 // A workgroup (up to 8 wavefronts, one workgroup to a CU) owns a contiguous range of rows of one matrix and its wavefronts
 // split K: a wavefront streams its columns of all rows, 64 columns (a chunk: whole 128-byte lines) at a time, through an LDS

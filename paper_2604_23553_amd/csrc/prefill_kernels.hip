@@ -12,9 +12,10 @@
 //                 reproduces the fp32 product to rounding)
 //   the products: prefill_gemm.hip - QKV and MLP-up in one launch, output projection and
 //                 MLP-down as one product
-//   k_pf_attn<> : causal attention of a block of 32, 64 or 128 queries of one head over the
+//   k_pf_attn<> : (prefill_attention.h) causal attention of a block of 32, 64 or 128 queries of one head over the
 //                 cache, keys in LDS tiles, both products on the matrix cores
-//                 (v_mfma_f32_32x32x16_f16), online softmax in fp32
+//                 (v_mfma_f32_32x32x16_f16), online softmax in fp32; of a short prompt with MLP-down in the same
+//                 launch (prefill_beside.hip)
 //
 // Every sum has a fixed order: one bit pattern per build and pass size.
 #include <hip/hip_runtime.h>
