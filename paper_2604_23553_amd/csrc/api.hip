@@ -487,7 +487,7 @@ static bool batched_path_shape(const cfpp_ctx *ctx, const Shape &sh)
 // A single sequence takes the same three launches, with products of its own that keep fp32 (lone_gemm.hip), where nothing
 // asks for another mode or launch shape.  Measured, us a block, phase kernels (whole-stack kernel from hidden 2048) -> these,
 // 20 .. 8000 positions: hidden 512 20.9 .. 28.9 -> 15.1 .. 19.5, 1536 27.4 .. 38.2 -> 20.5 .. 28.3, 2560 41.6 .. 51.0 -> 34.4 .. 46.7,
-// 4096 77.2 .. 94.1 -> 69.7 .. 90.2.
+// 4096 77.2 .. 94.1 -> 69.7 .. 90.2; with MLP-down beside the attention less again: 2560, 1024 positions 37.2 -> 34.1, 4096, 1777 76.6 -> 70.9.
 static bool batched_path(const cfpp_ctx *ctx, const Shape &sh, int batch, bool single)
 {
     return (batch > 1 || single) && batched_path_shape(ctx, sh);
@@ -588,7 +588,8 @@ static cfpp_status check_io(const cfpp_ctx *ctx, const void *x, const int32_t *p
 // sequences, for a block on its own and for a step of several layers of hidden sizes below 2048; the
 // whole-stack kernel, where its shape limits and the residency check allow it, for a step of several
 // layers from hidden 2048 on (a layer, batched path against it, at 20 / 1024 / 4000 positions: hidden 2048 26.9 / 30.9 / 34.7
-// against 29.0 / 31.0 / 33.1 us, 2560 35.9 / 38.5 / 43.0 against 32.9 / 34.1 / 36.9; below it hidden 1536 19.8 / 22.7 / 25.2 against
+// against 29.0 / 31.0 / 33.1 us, 2560 35.9 / 38.5 / 43.0 against 32.9 / 34.1 / 36.9; since MLP-down runs beside the attention 2048 25.6 / 30.0 / 33.5
+// against 28.1 / 30.5 / 32.6, 2560 33.6 / 36.1 / 41.0 against 32.3 / 33.6 / 36.6, and the line stays: from hidden 2048 on a stack is one launch; below it hidden 1536 19.8 / 22.7 / 25.2 against
 // 23.4 / 28.3 / 29.9, 1024 15.9 / 19.6 / 22.6 against 21.9 / 25.8 / 27.6); else the phase kernels.  An explicit grid keeps a
 // single sequence with the kernels that follow it.
 static cfpp_status resolve_mode(cfpp_ctx *ctx, const Shape &sh, const StepParams &P, int batch, bool stack,

@@ -6,9 +6,9 @@
 //
 // How the weights are streamed: narrow_stream.h.
 // Kernel times, 8 sequences, the kernels before (weights through registers, four rows to a load, activations of a
-// workgroup in LDS) -> these: hidden 2560: k_ng_in 28.7 -> 17.5 us, k_ng_dense 23.5 -> 15.2 (5 sequences) and 24.7 -> 17.3 (8);
-// hidden 4096: 49.1 -> 37.5, 43.6 -> 31.3.  What is left of k_ng_dense beyond its weights (13 us at 2560) is the activations:
-// every workgroup reads all of them from the L2, 8 tokens 410 KB beside 256 KB of weights.
+// workgroup in LDS) -> these: hidden 2560: k_ng_in 28.7 -> 17.5 us; output projection and MLP-down in one
+// kernel 23.5 -> 15.2 (5 sequences) and 24.7 -> 17.3 (8), without MLP-down, which the attention launch has now, k_ng_dense is 6.3 and 6.8;
+// hidden 4096: 49.1 -> 37.5, 43.6 -> 31.3 and 8.8.  k_ng_dense is a launch, a trip for the weights and one for the sums: 13 MB at hidden 2560.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include "narrow_stream.h"
