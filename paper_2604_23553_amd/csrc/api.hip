@@ -523,14 +523,13 @@ static cfpp_status launch_batched_layer(const cfpp_ctx *ctx, const Shape &sh, co
         B.o = reinterpret_cast<__half *>(B.o32);
         B.part = reinterpret_cast<float *>(ctx->ws + wl.part) + (size_t)b0 * dm.H * wl.part_slots * (dm.d + 2);
         B.part_slots = wl.part_slots;
-        B.downs = down_parts_of(dm.h, dm.f, B.n == 1);
         B.rope = reinterpret_cast<const float2 *>(ctx->ws + wl.rope);
         B.sync = reinterpret_cast<unsigned *>(ctx->ws + wl.sync);
         HIP_OK((B.n > 1 ? launch_bat_in : launch_lone_in)(B, sh.grid, s));
         StepParams P = make_params(ctx, sh, b0, x, pos_dev, out, n_layers);
         if (kv_seq >= 0) { P.b = kv_seq; P.attn_bstep = 0; }
-        if (kv_seq >= 0 && group_attention_takes(dm, B.n, first + b0)) HIP_OK(launch_attention_group(P, B.n, first + b0, w, kv, s));
-        else HIP_OK(launch_attention_batched(P, B.n, w, kv, s));
+        if (kv_seq >= 0 && group_attention_takes(dm, B.n, first + b0)) HIP_OK(launch_attention_group(P, B.n, first + b0, w, kv, &B.downs, s));
+        else HIP_OK(launch_attention_batched(P, B.n, first + b0, w, kv, &B.downs, s));
         HIP_OK((B.n > 1 ? launch_bat_dense : launch_lone_dense)(B, sh.grid, s));
     }
     return CFPP_OK;

@@ -51,11 +51,12 @@ hipError_t launch_phases(const StepParams &P, const __half *w, __half *kv, int l
 hipError_t launch_block_persistent(const StepParams &P, const __half *w, __half *kv, int layer,
                                    int grid, int threads, hipStream_t s);
 // implemented in narrow_attention.hip: the attention of nb sequences (P: the first one's parameters) in one launch, heads cut into
-// pieces by cache length, and MLP-down beside it (w: the packed layer)
-hipError_t launch_attention_batched(const StepParams &P, int nb, const __half *w, const __half *kv, hipStream_t s);
+// pieces by cache length, and MLP-down beside it (w: the packed layer), in *downs parts.  first: the first position of a prompt
+// group (P.attn_bstep 0), else unused
+hipError_t launch_attention_batched(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s);
 // implemented in group_attention.hip: that of 2 .. 8 prompt tokens, positions first .. (only where it takes them)
 bool group_attention_takes(const Dims &dm, int nb, int first);
-hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, hipStream_t s);
+hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s);
 hipError_t prepare_attention_kernels();
 // stores the per-layer pointer table in device memory (the whole-stack kernels read it there)
 hipError_t launch_store_layer_ptrs(const LayerPtrs &ptrs, LayerPtrs *dst, int n, hipStream_t s);

@@ -26,12 +26,13 @@ typedef _Float16 ga_f16x4 __attribute__((ext_vector_type(4)));
 constexpr int kGaWaves = kAttnBatchThreads / 64, kGaRow = 32;          // positions of a row, a wavefront's step
 constexpr int kGaStride = kGaRow + 4;                                  // halves between V's dimensions in LDS
 
-// Pieces of the positions ahead of the group: at least a row to each wavefront, as many as fill the CUs, and at most eight: with the
-// group's own rows their sums are one round of loads (12 or 16 pieces, two rounds: hidden 1280 behind 2500 positions 26.1 -> 27.9 / 28.4 us a layer).
+// Pieces of the positions ahead of the group: at least a row to each wavefront, as many as fill the CUs once, and at most eight: with the
+// group's own rows their sums are one round of loads (12 or 16 pieces, two rounds: hidden 1280 behind 2500 positions 26.1 -> 27.9 / 28.4 us a layer).  The group's own rows are a piece too: with 8 and that one 32
+// heads are 288 workgroups, with 7 256: 8 tokens behind 1000 of hidden 2560 41.7 -> 41.2, of 4096 behind 3000 87.9 -> 84.2; with 5 or 6 0.5 .. 3.5 % more.
 constexpr int kGaPieces = 8;
 CFPP_HD int ga_pieces(int first, int H)
 {
-    const int rows = (first + kGaRow - 1) / kGaRow, want = (rows + kGaWaves - 1) / kGaWaves, fill = 256 / H;
+    const int rows = (first + kGaRow - 1) / kGaRow, want = (rows + kGaWaves - 1) / kGaWaves, fill = 256 / H - 1;
     const int n = want < fill ? want : fill < 1 ? 1 : fill;
     return n < kGaPieces ? n : kGaPieces;
 }
@@ -380,7 +381,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
     if (tid == 0) __hip_atomic_store(&P.seg_cnt[head], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, hipStream_t s)
+hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s)
 {
     if (nb < 2 || nb > kBatMax || first < 0 || first + nb > P.dm.max_seq || P.part_slots < kGaPieces + 1 + kDownParts) return hipErrorInvalidValue;
     GaParams G;
@@ -388,8 +389,9 @@ hipError_t launch_attention_group(const StepParams &P, int nb, int first, const 
     G.pieces = ga_pieces(first, P.dm.H);
     DownPlan down;
     down.w = w;
-    down.parts = down_parts_of(P.dm.h, P.dm.f, false);
     down.first = P.dm.H * (G.pieces + 1);
+    down.parts = down_parts_beside(P.dm.h, P.dm.f, false, down.first, first);
+    *downs = down.parts;
     const dim3 grid(down.first + P.dm.h / kDownRows * down.parts), block(kAttnBatchThreads);
     switch (P.dm.d) {
     case 64: hipLaunchKernelGGL(k_attention_group<64>, grid, block, down_lds<false>(), s, P, G, down); break;

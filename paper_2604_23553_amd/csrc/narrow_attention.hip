@@ -10,7 +10,7 @@ namespace cfpp {
 // sequence; sequence i follows at the workspace's usual strides.  A workgroup (4 wavefronts,
 // several to a CU) takes one piece of ONE head of one sequence: every head of sequence i is cut
 // into 1 + spare * rows_i / rows_all pieces, worked out by every workgroup from the positions in
-// device memory (the grid is the most that can come out; what is over leaves at once).  So a
+// device memory (the grid is the most that can come out; what is over leaves at once); of a prompt group, into `spare`.  So a
 // short sequence is as many workgroups as it has heads, and none does several heads one after
 // the other: dealing 256 workgroups of 512 threads to the sequences by length left the heads of
 // a short one to one or two of them, a staging, merge and hand-over (about 1.2 us) per head.
@@ -29,13 +29,18 @@ namespace cfpp {
 // 218.2 / 222.7 / 223.7 us (218.2 with the 256 workgroups of before); of 1024 .. 8192 positions 640 / 1024 / 2048: 231.8 /
 // 232.0 / 230.4 (234 .. 236 before).  Elsewhere 640 was held against the kernels of before only, us per whole step: 8 heads, 4 layers,
 // 2 sequences of 6000 .. 8000 183 -> 157, 8 of 2000 190 -> 169; 24 heads, 4 layers 245 -> 232, 266 -> 257; 32 heads of 80,
-// 2 layers 168 -> 156, 182 -> 178.  A prompt group's queries share their
-// rows and don't stream: 1024, as measured above.  A head's pieces leave the last kDownParts of its part_slots to MLP-down.
-constexpr int kAttnSpareGroups = 640, kAttnSpareShared = 1024, kAttnPieceRows = 32;
-// Up to four sequences of their own leave workgroups to spare: up to eight pieces of half as many rows.  us a block, 32 rows -> 16:
+// 2 layers 168 -> 156, 182 -> 178.
+// A prompt group's queries share their rows and don't stream: every head of a query is cut into as many pieces as come to 256 workgroups, one at
+// least, and the host, which knows the group's positions, makes the grid no larger.  Before, 1024 spare ones and a grid for the longest context, in which
+// hundreds of workgroups left at once ahead of MLP-down's.  us a layer, before -> this, room for 4100 positions: 8 tokens of hidden 1536
+// behind 20 / 400 24.0 / 25.0 -> 21.1 / 22.5, 2560 39.2 / 39.5 -> 36.3 / 38.1, 4096 behind 880 86.5 -> 77.3; 8 heads of 128, behind 2500
+// 27.1 -> 24.7; 512 or 1024 workgroups of pieces: 0 .. 10 % more where a head has two or more.
+// A head's pieces leave the last kDownParts of its part_slots to MLP-down.
+constexpr int kAttnSpareGroups = 640, kAttnSharedGroups = 256, kAttnPieceRows = 32;
+// Up to four sequences, or tokens of a group, leave workgroups to spare: up to eight pieces of half as many rows.  us a block, 32 rows -> 16:
 // hidden 2560, one sequence of 1000 / 2000 / 4000 41.3 -> 39.5 / 43.4 -> 41.0 / 45.4 -> 43.7, three of 500 .. 1000 42.9 -> 41.8;
-// hidden 4096, four of 20 .. 2000 85.7 -> 83.6; but five of 37 .. 2048 45.6 -> 47.4, prompt groups 47.0 -> 47.9, and 16 pieces
-// of one sequence of 8000 49.7 -> 50.4.
+// hidden 4096, four of 20 .. 2000 85.7 -> 83.6; but five of 37 .. 2048 45.6 -> 47.4, prompt groups of 8 47.0 -> 47.9, and 16 pieces
+// of one sequence of 8000 49.7 -> 50.4.  Groups of 2 tokens, which are as few: hidden 2560 behind 880 39.2 -> 36.9, 3072 51.4 -> 50.0.
 constexpr int kAttnFew = 4;
 CFPP_HD int attn_pieces(int rows, bool few)
 {
@@ -81,7 +86,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
 #pragma unroll
     for (int i = 0; i < kAttnBatchMax; ++i) {
         if (i < nb) {
-            const int n = min(min(1 + (int)((float)rows[i] * share), attn_pieces(rows[i], few)), P.part_slots - kDownParts);
+            const int n = min(min(STREAM ? 1 + (int)((float)rows[i] * share) : spare, attn_pieces(rows[i], few)), P.part_slots - kDownParts);
             const int in = (int)blockIdx.x - base;
             if (in >= 0 && in < n * H) { mine = i; R = rows[i]; pieces = n; local = in; t_last = at[i]; }
             base += n * H;
@@ -259,18 +264,19 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
     if (lane == 0) __hip_atomic_store(&P.seg_cnt[hd], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-hipError_t launch_attention_batched(const StepParams &P, int nb, const __half *w, const __half *kv, hipStream_t s)
+hipError_t launch_attention_batched(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s)
 {
-    if (nb < 1 || nb > kAttnBatchMax) return hipErrorInvalidValue;
     const bool stream = P.attn_bstep != 0;
-    const int H = P.dm.H, spare = (stream ? kAttnSpareGroups : kAttnSpareShared) / H;
-    const bool few = stream && nb <= kAttnFew;
-    // no sequence has more pieces than its longest context allows (64 / LPP positions a row, as in AttnShape)
-    const int row = P.dm.d >= 128 ? 16 : 32, most = attn_pieces((P.dm.max_seq + row - 1) / row, few);
+    if (nb < 1 || nb > kAttnBatchMax || (!stream && (first < 0 || first + nb > P.dm.max_seq))) return hipErrorInvalidValue;
+    const int H = P.dm.H, spare = stream ? kAttnSpareGroups / H : max(1, kAttnSharedGroups / (H * nb));
+    const bool few = nb <= kAttnFew;
+    // no sequence has more pieces than its longest context allows (64 / LPP positions a row, as in AttnShape); a group's is known
+    const int row = P.dm.d >= 128 ? 16 : 32, most = attn_pieces(((stream ? P.dm.max_seq : first + nb) + row - 1) / row, few);
     DownPlan down;
     down.w = w;
-    down.parts = down_parts_of(P.dm.h, P.dm.f, nb == 1);
-    down.first = min(nb + spare, nb * most) * H;
+    down.first = (stream ? min(nb + spare, nb * most) : nb * min(spare, most)) * H;
+    down.parts = stream ? down_parts_of(P.dm.h, P.dm.f, nb == 1) : down_parts_beside(P.dm.h, P.dm.f, nb == 1, down.first, first);
+    *downs = down.parts;
     const dim3 grid(down.first + P.dm.h / (nb == 1 ? kDownRowsOne : kDownRows) * down.parts), block(kAttnBatchThreads);
     if (P.part_slots <= kDownParts) return hipErrorInvalidValue;
     switch (P.dm.d) {

@@ -65,6 +65,17 @@ inline int down_parts_of(int h, int f, bool one)
     const int per_cu = (size_t)h * f * 2 > (size_t)256 * 256 * 1024 ? 2 : 1;
     return min(most, max(1, per_cu * 256 * kDownRows / h));
 }
+// Beside the `attn` workgroups of a prompt group's attention, positions `first` .., whose number the host knows: up to half as many
+// workgroups more than CUs take longer than one to each, so as many parts as leave it at that, if these are half as many at least.  us a
+// layer, parts as above -> this: 8 tokens of hidden 1280 (328 workgroups -> 248) behind 20 / 400 positions 19.6 / 21.5 -> 19.1 / 20.3; 2 tokens of
+// 1536 (336 -> 240) 20.1 / 21.8 -> 19.0 / 20.1; 2 of 2560 (304 -> 224) behind 400 36.3 -> 35.1, but behind 20 34.2 -> 34.9: two parts
+// are few where the attention is next to nothing.
+inline int down_parts_beside(int h, int f, bool one, int attn, int first)
+{
+    const int parts = down_parts_of(h, f, one), groups = h / kDownRows, room = (256 - attn) / groups;
+    const bool between = attn + groups * parts > 256 && attn + groups * parts < 384;
+    return !one && between && 2 * room >= parts && (room > 2 || first >= 128) ? room : parts;
+}
 bool bat_supported(const Dims &dm, int grid, int threads);
 // several sequences or tokens (narrow_gemm.hip)
 // grid: most workgroups of the first product; the output projection has rows of at most 16 to one and may have twice as many

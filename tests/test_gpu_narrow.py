@@ -71,6 +71,19 @@ def test_group_attention(orc, shape, pos0, T, max_batch, b):
     _check_prompt(orc, shape, 41, pos0, T, max_batch, b, then_decode=False, row_check_every=5)
 
 
+# Ahead of that every query attends for itself, in a grid made for the group's positions: one piece a head and the first position with
+# two, of 16 rows (up to 4 tokens) and of 32; heads of 128, whose rows are 16 positions; as many pieces as workgroups allow; one token; and fewer
+# parts of MLP-down beside it (hidden 1280 and 1536) or not, on both sides of position 128 (hidden 2560).
+@pytest.mark.parametrize("shape,pos0,T,max_batch,b", [
+    (_shape(1280, 80, 5120, 20), 0, 11, 8, 0), (_shape(1280, 80, 5120, 20, 1), 880, 8, 8, 0), (_shape(1536, 64, 6144, 16, 1), 510, 4, 2, 1),
+    (_shape(2560, 80, 10240, 20, 1), 126, 4, 2, 0), (_shape(1024, 128, 4096, 32, 1), 2040, 9, 8, 0), (_shape(1024, 128, 1024, 32, 1), 505, 10, 8, 2),
+    (_shape(4096, 128, 4096, 32, 1), 255, 3, 2, 0), (_shape(640, 80, 640, 20, 1), 3000, 1, 8, 0), (_shape(512, 64, 512, 16, 1), 511, 3, 3, 0),
+])
+def test_group_with_a_grid_for_its_positions(orc, shape, pos0, T, max_batch, b):
+    from tests.test_gpu_prefill import _check_prompt
+    _check_prompt(orc, shape, 47, pos0, T, max_batch, b, then_decode=False, row_check_every=5)
+
+
 # Its error against 64 bits: the queries and the cache rows that the kernel read (taps, exported cache), attention in numpy's doubles.
 # What bounds it: the tap's head and remainder, 2^-25 of an output of about 1 / sqrt(positions) (1e-6 of it at 1000 positions), a few 2^-24 of
 # the weights (exponential, head and remainder) and of the sums; and the scores' own rounding, 2^-24 of the sum of a score's terms' sizes or
