@@ -14,17 +14,18 @@ namespace cfpp {
 //         registers 8 m .. 8 m + 7 are, as they stand, a lane's 8 K values of the next product
 //         if V's operand takes the same keys in the same order;
 //   O^T += V^T P^T (dimensions x queries): the running sums are rescaled lane by lane, and only
-//         when some query's maximum has moved by more than 2^8; V sits in LDS transposed ([dimension][key]).
+//         when some query's maximum has moved by more than 2^4 (kPfFollow); V sits in LDS transposed ([dimension][key]).
 // q (scaled by log2 e / sqrt(D)) and P are fp32 values and enter as fp16 head + remainder (two
 // instructions each), K and V are the cache's fp16; sums and softmax in fp32.  Keys behind a
 // query are masked in the tiles that the diagonal crosses only.  With QW < 4 the wavefronts of
 // the same queries keep a maximum and sums of their own and are added in wavefront order at the end.
-// What bounds it: vector instructions (about 6 per score: exponential, sum, maximum, the two halves of P) beside 22 matrix
-// instructions per 32 x 32 scores at D = 80, in equal parts.  Of the vector instructions: the scores' sums start at minus the
-// maximum, so that nothing is subtracted behind them (and a large score's sum ends near zero, where its rounding is small); two halves of P
-// come from one conversion and a remainder from one v_fma_mix: 8.3 -> 6.2 a score.  us of layers, before -> now: hidden 512, 4000 tokens 163.5 -> 156.1;
-// 1536, 3000 behind 900 498 -> 487; 2560, 4096 tokens 1358 -> 1344, 300 behind 3000 204.7 -> 201.9; 1024, 600 behind 3000 112.6 -> 110.6.  Error against 64
-// bits (2-norm of the outputs, queries and keys doubled): d 64 2.99e-7 -> 2.75e-7, 80 7.5e-7 -> 5.7e-7, 128 8.3e-7 -> 6.7e-7.
+// What bounds it: vector instructions (about 7 per score: difference, exponential, sum, maximum, the two halves of P) beside 22 matrix
+// instructions per 32 x 32 scores at D = 80, in equal parts.  Two halves of P come from one conversion and a remainder from one v_fma_mix;
+// with a reference that follows a query's maximum only when it has to, 8.3 -> 7.2 vector instructions a score.
+// The scores' sums start at zero and the reference is subtracted behind them.  Starting them at minus the reference would save the subtraction,
+// but where a query's scores then rise by J its sums carry roundings of the size of J: error of the outputs against 64 bits after a
+// rise of 30 / 500 / 2000 in base 2, D = 64: 4.7e-7 / 7.5e-6 / 2.7e-5, as it is 5.3e-8 / 4.1e-8 / 4.1e-8 (80 and 128 alike), and at no size measured
+// was it more than 1 % faster.
 typedef _Float16 pf_f16x2 __attribute__((ext_vector_type(2)));
 typedef float pf_f32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 pf_f16x4 __attribute__((ext_vector_type(4)));
@@ -283,10 +284,12 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P, PfAttnParts A)
             ql[ks][j] = (_Float16)(v - (float)qh[ks][j]);
         }
     }
-    float m_run = -INFINITY, l_run = 0.f;                  // what the query's weights are relative to; l_run: of this lane's keys
-    pf_f32x16 O[NB], base;                                 // base: minus m_run, where the scores' sums start
-#pragma unroll
-    for (int e = 0; e < 16; ++e) base[e] = 0.f;
+    // what the query's weights are relative to: its maximum or up to kPfFollow less (in base 2: the difference of two scores keeps its bits, and
+    // the weights stay below 2^4); l_run: of this lane's keys.  us of layers with 1 / 4 / 8: hidden 512, 4000 tokens 1252 / 1246 / 1254,
+    // 2560, 300 behind 3000 1615 / 1600 / 1596; with 8 the error after rises of 5 .. 8 is up to 11 % more in its largest, with 4 as with 0.
+    constexpr float kPfFollow = 4.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    pf_f32x16 O[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -307,7 +310,7 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P, PfAttnParts A)
 #pragma unroll
             for (int s = 0; s < SUB; ++s) kf[s] = *reinterpret_cast<const pf_f16x8 *>(&sK[(kw0 + 32 * s + col) * KS + 16 * ks + 8 * hf]);
 #pragma unroll
-            for (int s = 0; s < SUB; ++s) st[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s], qh[ks], ks ? st[s] : base, 0, 0, 0);
+            for (int s = 0; s < SUB; ++s) st[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s], qh[ks], ks ? st[s] : pf_f32x16{}, 0, 0, 0);
 #pragma unroll
             for (int s = 0; s < SUB; ++s) st[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s], ql[ks], st[s], 0, 0, 0);
         }
@@ -324,31 +327,25 @@ __global__ void __launch_bounds__(256, 2) k_pf_attn(PfParams P, PfAttnParts A)
 #pragma unroll
             for (int e = 0; e < 16; ++e) mloc = fmaxf(mloc, st[s][e]);
         mloc = fmaxf(mloc, pf_other_half(mloc));
-        // the query's first keys, or a score far above what its weights are relative to (up to 2^8 they are as exact as below 1)
-        const bool moves = mloc > (m_run == -INFINITY ? -INFINITY : 8.f);
+        // the query's first keys, or a score above what its weights are relative to by more than kPfFollow
+        const bool moves = mloc > (m_run == -INFINITY ? -INFINITY : m_run + kPfFollow);
         if (__any(moves)) {                                // (uniform)
-            const float from = -base[0], to = from + mloc;
-            const float by = moves ? to - from : 0.f, corr = !moves ? 1.f : m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(-by);
-            if (moves) m_run = to;
+            const float corr = !moves ? 1.f : m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mloc);
+            if (moves) m_run = mloc;
             l_run *= corr;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) O[nb][e] *= corr;
-#pragma unroll
-            for (int s = 0; s < SUB; ++s)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) st[s][e] -= by;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) base[e] = m_run == -INFINITY ? 0.f : -m_run;      // (a query none of whose keys this wavefront has seen)
         }
+        const float mref = m_run == -INFINITY ? 0.f : m_run;           // (a query none of whose keys this wavefront has seen)
 #pragma unroll
         for (int s = 0; s < SUB; ++s) {
             pf_f16x8 ph[2], pl[2];
             float sum = 0.f;
 #pragma unroll
             for (int e = 0; e < 16; e += 2) {
-                const pf_f32x2 p{__builtin_amdgcn_exp2f(st[s][e]), __builtin_amdgcn_exp2f(st[s][e + 1])};
+                const pf_f32x2 p{__builtin_amdgcn_exp2f(st[s][e] - mref), __builtin_amdgcn_exp2f(st[s][e + 1] - mref)};
                 sum += p[0];
                 sum += p[1];
                 const pf_f16x2 h = __builtin_convertvector(p, pf_f16x2);

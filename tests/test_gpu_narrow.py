@@ -301,7 +301,7 @@ def test_prompt_attention_in_parts(orc, shape, pos0, T):
     _check_prompt(orc, shape, 37, pos0, T, 1, 0, then_decode=False, gemm_rows=128, row_check_every=11)
 
 
-# The weights of a query are relative to a score that follows its maximum only when that is 2^8 times it: scores that rise along the
+# The weights of a query are relative to a score that follows its maximum only when that is 2^4 times it: scores that rise along the
 # context in steps below and far above that, fall again, and start with keys that weigh nothing against the later ones; 32, 64 and 128 queries
 # to a workgroup, keys whole and in parts, wavefronts that share the keys.  Against the batched path, which keeps the maximum.
 @pytest.mark.parametrize("shape,pos0,T", [
@@ -337,6 +337,66 @@ def test_prompt_attention_with_scores_that_rise(shape, pos0, T):
     step = np.ldexp(1.0, np.frexp(np.maximum(np.abs(got), np.abs(want)).clip(2.0 ** -14))[1] - 11)
     assert np.isfinite(got).all() and (np.abs(got - want) <= 1.001 * step + 2e-3 * rms + 2e-5).all()       # (as test_gpu_prefill.py's)
     assert np.linalg.norm(got - want) <= 2.5e-4 * np.linalg.norm(want)
+
+
+# What such a rise leaves in the weights, against 64 bits: sixteen keys in one tile are `rise` (base 2) above all others, nearly 0, so that the
+# outputs are these keys' and carry their scores' errors as they stand.  Queries and rows are their biases (no rotary, zero weights): known to the
+# last bit.  Bound: the output's head and remainder, 2^-22 of it and 2^-25; of a key's weight, 2^-22 for its own head and remainder, the exponential and the
+# sum, and its score's error, 2^-22 of the sum of its terms' sizes (the query's head and remainder, and the roundings of so small a sum).  A rounding of
+# the size of the rise is 2^-24 of it, 7 times that at 30.
+@pytest.mark.parametrize("rise", [6, 30, 500])
+@pytest.mark.parametrize("shape,pos0,T", [
+    (_shape(512, 64, 512, 0, 1), 900, 40), (_shape(640, 80, 640, 0, 1), 700, 100), (_shape(1024, 128, 1024, 0, 1), 500, 30), (_shape(2560, 80, 2560, 0, 1), 512, 800),
+    (_shape(2048, 64, 2048, 0, 1), 512, 2050), (_shape(2048, 128, 2048, 0, 1), 512, 200),
+])
+def test_prompt_attention_after_a_rise_against_64_bits(shape, pos0, T, rise):
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    print(f"[case] error after a rise of {rise} {shape.name} pos0={pos0} T={T}", flush=True)
+    H, d, h, cap, rows = shape.n_heads, shape.head_dim, shape.hidden, pos0 + T, -(-T // 128) * 128
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, 59, 0).items()}
+    rng, at = np.random.default_rng(59), np.arange(3 * h).reshape(H, 3, d)
+    u = rng.choice([-1.0, 1.0], (H, d)).astype(np.float16)
+    low = (-u.astype(np.float32) * rise * np.log(2.0) / np.sqrt(d)).astype(np.float16)             # a key `rise` below 0
+    for i, bias in ((0, u), (1, low)):
+        w["w_qkv"][at[:, i].ravel()] = 0
+        w["b_qkv"][at[:, i].ravel()] = bias.ravel()
+    K, V = synth.kv_cache(shape, 59, 0, pos0, cap, 1)
+    K[0, :, :pos0] = (low[:, None] + 0.3 * K[0, :, :pos0].astype(np.float32)).astype(np.float16)
+    K[0, :, 300:316] = (0.3 * rng.standard_normal((H, 16, d))).astype(np.float16)
+    with cf.profile_build():
+        cfg = cf.Config.from_shape(shape, cap)
+        narrow = cf.cfpp_debug_prefill_narrow(cfg, rows, T) is not None
+        offsets, halves = cf.cfpp_debug_prefill_scratch(cfg, rows)
+        ds = DeviceStack(shape, cap, 1, 1)
+        try:
+            ds.load_layer(0, w)
+            ds.load_kv(0, K, V, pos0)
+            x = torch.from_numpy(synth.x_input(shape, 61, batch=T)).to(ds.dev)
+            out, nbytes = torch.zeros_like(x), cf.cfpp_prefill_scratch_bytes(ds.cfg, rows)
+            scratch = torch.empty(nbytes, dtype=torch.uint8, device=ds.dev)
+            torch.cuda.synchronize()
+            cf.cfpp_stack_prefill_gemm(ds.ctx, ds.packed, ds.kv, x, pos0, T, 0, out, scratch, nbytes, rows, ds.s)
+            ds.check()
+            k, v = (a.astype(np.float64) for a in ds.export_kv(0, 0, 0, cap))
+            planes = scratch[offsets[3]:].view(torch.float16)[:rows * halves[0]].cpu().numpy().astype(np.float64)
+        finally:
+            ds.close()
+    if narrow:      # sets of 8 tokens, 32 columns at a time: four times 8 columns of heads [token][8], then of remainders
+        o = planes[:-(-T // 8) * h * 16].reshape(-1, h // 32, 4, 2, 8, 8).sum(axis=3).transpose(0, 3, 1, 2, 4).reshape(-1, H, d)[:T]
+    else:           # rows of 32 heads, then their 32 remainders
+        o = planes.reshape(rows, -1)[:T, :2 * h].reshape(T, h // 32, 2, 32).sum(axis=2).reshape(T, H, d)
+    q, worst = u.astype(np.float64), 0.0
+    for n in range(0, H, max(1, H // 4)):
+        s, terms = k[n] @ q[n] / np.sqrt(d), np.abs(k[n]) @ np.abs(q[n]) / np.sqrt(d)
+        e = np.exp(s - s.max())
+        for t in list(range(0, T, max(1, T // 40))) + [T - 1]:
+            p = e[:pos0 + t + 1] / e[:pos0 + t + 1].sum()
+            want = p @ v[n, :pos0 + t + 1]
+            bound = 2.0 ** -25 + 2.0 ** -22 * np.abs(want) + 2.0 ** -22 * ((p * (1 + terms[:pos0 + t + 1])) @ np.abs(v[n, :pos0 + t + 1]))
+            worst = max(worst, (np.abs(o[t, n] - want) / bound).max())
+    print(f"  most of the bound {worst:.2f}")
+    assert worst <= 1.0
 
 
 @pytest.mark.parametrize("kind", ["overflow", "nan"])
