@@ -1,14 +1,20 @@
 // Attention of a group of prompt tokens (2 .. 8 consecutive positions of one sequence, batched path) behind a longer context, and MLP-down in the same launch.
 //
 // The queries of a head read the same cached rows, so a workgroup takes them together: a piece of the positions ahead of the
-// group, of one head, on the matrix cores (v_mfma_f32_16x16x32_f16).  Heads of the 8 queries are columns 0 .. 7 of an operand and
-// their remainders columns 8 .. 15 (half_split.h), as in narrow_stream.h:
-//   S = K Q^T   (16 positions x 16 columns): a lane holds column lane % 16 and positions 4 (lane / 16) .. + 3; head and remainder are
-//               eight lanes apart.  A query is divided by a power of two above its largest element first, and its scores multiplied
-//               by it: the split loses nothing, whatever the size.
+// group, of one head, on the matrix cores (v_mfma_f32_16x16x32_f16).  A query's element or a weight goes in as two fp16 values, its head and
+// 2^11 times what the head leaves: columns 0 .. 7 of an operand are the heads of the 8 queries, columns 8 .. 15 the others, and so are the sums:
+//   S = K Q^T   (16 positions x 16 columns): a lane holds column lane % 16 and positions 4 (lane / 16) .. + 3; the two columns of a query are
+//               eight lanes apart.  A query is scaled by a power of two first, its largest element to 2^14 .. 2^15, and its scores back.
 //   O^T += V^T P^T (16 dimensions x 16 columns): a lane's 8 K values are the positions of its own scores in two tiles of 16, so that P
-//               needs no exchange; its head goes in on the lanes of columns 0 .. 7, its remainder on the others.  V goes through LDS of
-//               the wavefront's own, transposed, two positions to a word.
+//               needs no exchange.  Weights go in 2^14 times.  V goes through LDS of the wavefront's own, transposed, two positions to a word.
+// So an element or weight keeps 2^-23 of itself down to 2^-26 of the largest, and below that 2^-50 of the largest (the two as they are, half_split.h: 2^-25).
+// Error of the outputs against 64 bits (2-norm; 8 tokens behind 1001 positions; head size 64 / 80 / 128), every query for itself in fp32 -> head
+// and remainder as they are -> this:
+//   queries four times as large as usual 7.5e-8 / 2.1e-7 / 2.6e-7 -> 6.8e-8 / 1.9e-7 / 3.2e-7 -> 6.5e-8 / 1.8e-7 / 2.6e-7;
+//   light keys behind one of 2^16 times their weight, whose V is zero 1.4e-6 -> 7.5e-6 -> 1.4e-6 at all three;
+//   a query's element of 3000 that meets zeros in K 2.2e-8 / 2.3e-8 / 2.4e-8 -> 3.1e-6 / 3.6e-6 / 4.2e-6 -> 2.2e-8 / 2.3e-8 / 2.5e-8.
+// us of layers, head and remainder as they are -> this, 8 tokens: 32 of hidden 2560 behind 1000 1315 -> 1321, 10 of 4096 behind 3000 841 -> 837, 16 of 512
+// behind 2500 291.2 -> 290.9.
 // Every query sees every one of these positions.  The group's own rows, where the causal mask lies, are a workgroup more to a
 // head, in fp32: no masked weight is ever multiplied by a V row.  An output that is not finite (a cached V row may be infinite, and the
 // remainder of its weight zero) is worked out once more in fp32.
@@ -43,6 +49,16 @@ CFPP_HD int ga_pieces(int first, int H)
 // 4096 behind 1000 73.6 -> 76.8 / 86.1 -> 81.4, 4000 100 -> 85.8 / 118 -> 90.1.  Eight heads of 128 dimensions are too few workgroups with too
 // much to read (1024 behind 1500 22.8 -> 24.3, 4000 28.9 -> 27.7 but for three tokens 23.6 -> 25.4): left with the other kernel, as are eight of 80.
 bool group_attention_takes(const Dims &dm, int nb, int first) { return nb >= 2 && first >= 28 * kGaRow && (dm.H >= 16 || dm.d == 64); }
+
+constexpr float kGaWeight = 16384.f;   // a weight's factor
+// Both columns of a query, eight lanes apart, work its values out alike.  One of them feeds the head of v (below 2^15 in size), the other what it
+// leaves: (float)head * -b + v * a is v itself, or 2^11 (v - head), exactly.  Their sums join to the same value in both.
+struct GaSide {
+    float a, b, own, other;
+    __device__ __forceinline__ explicit GaSide(bool heads) : a(heads ? 1.f : 2048.f), b(heads ? 0.f : -2048.f), own(heads ? 1.f : 1.f / 2048.f), other(heads ? 1.f / 2048.f : 1.f) {}
+    __device__ __forceinline__ _Float16 part(float v) const { return (_Float16)fmaf((float)(_Float16)v, b, v * a); }
+    __device__ __forceinline__ float joined(float sum) const { return fmaf(sum, own, dpp_mov<kDppRor8>(sum) * other); }
+};
 
 struct GaParams {
     int nb, first, pieces;  // tokens; the first one's position; pieces of the positions ahead of it
@@ -224,7 +240,8 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
         const int col = lane & 15, kg = lane >> 4;
         GaRow<D> r;                                        // (one row ahead: pieces are cut so that a wavefront has few)
         r.request(Kh, Vh, slab, lo + wave, last, lane);
-        // Q^T: dimensions 32 s + 8 kg .. + 7 of query col % 8, heads or remainders
+        const GaSide side(col < 8);
+        // Q^T: dimensions 32 s + 8 kg .. + 7 of query col % 8
         ga_f16x8 Q[KS];
         float qscale;
         {
@@ -242,16 +259,12 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
                 }
             }
             most = ga_max4(most);
-            const int ex = most > 0.f && most < INFINITY ? __builtin_amdgcn_frexp_expf(most) : 0;
+            const int ex = (most > 0.f && most < INFINITY ? __builtin_amdgcn_frexp_expf(most) : 0) - 15;
             qscale = __builtin_amdgcn_ldexpf(scale, ex);
 #pragma unroll
             for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float v = split_value(__builtin_amdgcn_ldexpf(x[s][e], -ex));
-                    const _Float16 hd = (_Float16)v;
-                    Q[s][e] = col < 8 ? hd : (_Float16)(v - (float)hd);
-                }
+                for (int e = 0; e < 8; ++e) Q[s][e] = side.part(split_value(__builtin_amdgcn_ldexpf(x[s][e], -ex)));
         }
         f32x4 O[NT];
 #pragma unroll
@@ -264,13 +277,15 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
             f32x4 S[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                S[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                f32x4 half[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};          // (128 dimensions in two sums: smaller roundings)
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     u32x4 k = r.k[t][s];
                     if (D % 32 != 0 && s == KS - 1 && 32 * s + 8 * kg >= D) k = u32x4{0u, 0u, 0u, 0u};
-                    S[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ga_f16x8, k), Q[s], S[t], 0, 0, 0);
+                    half[KS > 3 ? s / 2 : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ga_f16x8, k), Q[s], half[KS > 3 ? s / 2 : 0], 0, 0, 0);
                 }
+                if (KS > 3) __builtin_amdgcn_sched_barrier(0);             // (a tile at a time: registers)
+                S[t] = KS > 3 ? half[0] + half[1] : half[0];
             }
             r.request(Kh, Vh, slab, row + W, last, lane);
             float most = -INFINITY;
@@ -278,7 +293,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float s = (S[t][j] + dpp_mov<kDppRor8>(S[t][j])) * qscale;
+                    const float s = side.joined(S[t][j]) * qscale;
                     S[t][j] = row * kGaRow + 16 * t + 4 * kg + j <= last ? s : -INFINITY;
                     most = fmaxf(most, S[t][j]);
                 }
@@ -291,8 +306,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
                 for (int j = 0; j < 4; ++j) {
                     const float v = split_value(S[t][j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(S[t][j] - mn));
                     sum += v;
-                    const _Float16 hd = (_Float16)v;
-                    p[4 * t + j] = col < 8 ? hd : (_Float16)(v - (float)hd);
+                    p[4 * t + j] = side.part(v * kGaWeight);
                 }
             l_run = l_run * corr + sum;
             m_run = mn;
@@ -314,7 +328,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                O[t][j] += dpp_mov<kDppRor8>(O[t][j]);
+                O[t][j] = side.joined(O[t][j]) * (1.f / kGaWeight);
                 finite = finite && fabsf(O[t][j]) < INFINITY;
             }
         const unsigned long long again = __ballot(!finite);            // (bit l: query l % 8)

@@ -126,6 +126,60 @@ def test_group_attention_against_64_bits(shape, pos0, gain):
         assert (err <= bound).all(), f"token {t}"
 
 
+# Weights far below the largest and query elements far below theirs keep the precision of fp32.  "light": one key has 2^16 times the weight of
+# every other, and its V is zero, so that the outputs are the light ones'.  "uneven": a query's first element is 3000 where every
+# other is about 1, and meets zeros in K.  Bound: the tap's head and remainder, 2^-25 and 2^-22 of the output; of a key's weight, 2^-22 (its two halves, the
+# exponential, the sums) and its score's error, 2^-23 of the sum of its terms' sizes, plus 2^-24 of its distance from the largest score, whose
+# difference is rounded.  Two fp16 values that keep 2^-25 of the largest only are off by 12 to 30 of it.
+@pytest.mark.parametrize("kind", ["light", "uneven"])
+@pytest.mark.parametrize("shape,pos0", [(_shape(512, 64, 512, 0, 1), 1001), (_shape(1280, 80, 1280, 0, 1), 1700), (_shape(2048, 128, 2048, 0, 1), 1001)])
+def test_group_attention_of_light_keys_and_uneven_queries(shape, pos0, kind):
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    T, h, H, d = 8, shape.hidden, shape.n_heads, shape.head_dim
+    print(f"[case] group attention {kind} {shape.name} pos0={pos0}", flush=True)
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, 67, 0).items()}
+    rng, at = np.random.default_rng(67), np.arange(3 * h).reshape(H, 3, d)
+    K, V = synth.kv_cache(shape, 67, 0, pos0, pos0 + T, T)
+    if kind == "light":
+        u = rng.choice([-1.0, 1.0], (H, d))
+        w["w_qkv"][at[:, 0].ravel()] *= np.float16(0.05)                   # every query: nearly u
+        w["b_qkv"][at[:, 0].ravel()] = u.ravel().astype(np.float16)
+        K[0, :, :pos0] *= np.float16(0.3)
+        V[0, :, :pos0] *= np.float16(100.0)
+        K[0, :, pos0 // 2] = (u * 16 * np.log(2.0) / np.sqrt(d)).astype(np.float16)
+        V[0, :, pos0 // 2] = 0
+    else:
+        w["b_qkv"][at[:, 0, 0]] = np.float16(3000.0)
+        w["w_qkv"][at[:, 1, 0]] = 0
+        w["b_qkv"][at[:, 1, 0]] = 0
+        K[0, :, :, 0] = 0
+    with cf.profile_build():
+        ds = DeviceStack(shape, pos0 + T, T, 1)
+        try:
+            ds.load_layer(0, w)
+            ds.load_kv(0, K, V, pos0)
+            ds.prefill(synth.x_input(shape, 67, T), pos0)
+            ds.check()
+            q = ds.tap(0, T * h).reshape(T, H, d).astype(np.float64)
+            o = ds.tap(3, T * h).reshape(T, H, d).astype(np.float64)
+            k, v = (a.astype(np.float64) for a in ds.export_kv(0, 0, 0, pos0 + T))
+        finally:
+            ds.close()
+    worst = 0.0
+    for t in range(T):
+        n = pos0 + t + 1
+        s = np.einsum("hd,hpd->hp", q[t], k[:, :n]) / np.sqrt(d)
+        far = s.max(axis=1, keepdims=True) - s
+        p = np.exp(-far) / np.exp(-far).sum(axis=1, keepdims=True)
+        want = np.einsum("hp,hpd->hd", p, v[:, :n])
+        terms = np.einsum("hd,hpd->hp", np.abs(q[t]), np.abs(k[:, :n])) / np.sqrt(d)
+        bound = 2.0 ** -25 + 2.0 ** -22 * np.abs(want) + np.einsum("hp,hpd->hd", p * (2.0 ** -22 + 2.0 ** -23 * terms + 2.0 ** -24 * far), np.abs(v[:, :n]))
+        worst = max(worst, (np.abs(o[t] - want) / bound).max())
+    print(f"  most of the bound {worst:.2f}")
+    assert worst <= 1.0
+
+
 # A token of the group that is not finite reaches no earlier one; a cached V element that is infinite makes that dimension of every
 # token's output infinite and no other.
 @pytest.mark.parametrize("shape,pos0,bad", [
