@@ -150,7 +150,8 @@ __device__ __forceinline__ void ga_alone(const float *q, const __half *Kh, const
 #pragma unroll
             for (int e = 0; e < NE; ++e) s = lane + 64 * e < D ? fmaf(qs[e], __half2float(Kh[at[e] + (unsigned)t * 16u]), s) : s;
             s = wave_sum(s);
-            const float mn = fmaxf(m, s), corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(s - mn);
+            const float mn = fmaxf(m, s), corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+            const float p = s == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - mn);
             m = mn;
             l = l * corr + p;
 #pragma unroll
@@ -209,7 +210,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
             float m = fmaxf(s, dpp_mov<kDppXor1>(s));
             m = fmaxf(m, dpp_mov<kDppXor2>(m));
             m = fmaxf(m, dpp_mov<kDppHalfMirror>(m));
-            const float p = sj <= si ? __builtin_amdgcn_exp2f(s - m) : 0.f;
+            const float p = s == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - m);      // (not only masked ones: an infinite K element)
             float l = p + dpp_mov<kDppXor1>(p);
             l += dpp_mov<kDppXor2>(l);
             l += dpp_mov<kDppHalfMirror>(l);
@@ -384,7 +385,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, 3) k_attention_group(StepPa
         for (int j = 0; j < CB; ++j) {
             if (j <= pieces) {
                 const float mn = fmaxf(M, mj[j]);
-                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = __builtin_amdgcn_exp2f(mj[j] - mn);
+                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = mj[j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mj[j] - mn);
                 L = L * c0 + lj[j] * c1;
                 s = s * c0 + oj[j] * c1;
                 M = mn;

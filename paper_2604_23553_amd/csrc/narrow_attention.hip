@@ -155,7 +155,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
         const float sc = valid ? sp : -INFINITY;
         const float mn = fmaxf(m_run, sc);
         const float corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
-        const float p = valid ? __builtin_amdgcn_exp2f(sc - mn) : 0.f;
+        const float p = sc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc - mn);       // (a valid one too: an infinite K element)
         l_run = l_run * corr + p;
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
@@ -196,7 +196,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
     if (wave != 0) return;
     float M = wm[0], L = 0.f, O[NE];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, wm[w]);      // (the piece has rows: finite)
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, wm[w]);
 #pragma unroll
     for (int e = 0; e < NE; ++e) O[e] = 0.f;
 #pragma unroll
@@ -252,7 +252,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
         for (int j = 0; j < CB; ++j) {
             if (j0 + j < pieces) {
                 const float mn = fmaxf(M, mj[j]);
-                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = __builtin_amdgcn_exp2f(mj[j] - mn);
+                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = mj[j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mj[j] - mn);
                 L = L * c0 + lj[j] * c1;
 #pragma unroll
                 for (int e = 0; e < NE; ++e) O[e] = O[e] * c0 + oj[j][e] * c1;

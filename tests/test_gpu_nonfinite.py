@@ -88,3 +88,81 @@ def test_batched_step_with_a_v_element_that_overflows(shape, lens):
     assert o[0, at] == np.inf
     o[0, at] = 0.0
     assert np.isfinite(o).all()
+
+
+def _check_minus_infinity(shape, taps, k, v, lens, what):
+    """The attention outputs of one head against 64 bits where some scores are minus infinity: those keys weigh nothing."""
+    q, o = taps
+    d = shape.head_dim
+    for t, n in enumerate(lens):
+        with np.errstate(invalid="ignore"):
+            s = np.where(np.isinf(k[t][:n]).any(axis=1), -np.inf, k[t][:n] @ q[t] / np.sqrt(d))
+        p = np.exp(s - s.max())
+        want = (p / p.sum()) @ v[t][:n]
+        assert np.isfinite(o[t]).all(), f"{what}: query {t} is not finite"
+        assert np.abs(o[t] - want).max() <= 2e-5 * np.abs(v[t][:n]).max(), f"{what}: query {t}"
+
+
+# A K element that is infinite and meets a query's element of the other sign: that key weighs nothing, wherever it lies - the
+# only key that a lane has, a token's own, the first of a group, cached ahead of a group that attends together or of one that does not.
+@pytest.mark.parametrize("d,H,lens,bad", [(64, 8, [0, 3, 70], 0), (80, 8, [5], 2), (128, 8, [40, 7], 7), (64, 8, [2000], 1999)])
+def test_step_behind_a_key_of_minus_infinity(d, H, lens, bad):
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    shape = synth.ModelShape(H * d, H, d, 0, H * d, n_layers=1, name=f"d{d}")
+    print(f"[case] minus infinity, step {shape.name} {lens}", flush=True)
+    B, cap, h = len(lens), max(lens) + 1, H * d
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, 75, 0).items()}
+    w["w_qkv"][3 * HEAD * d + DIM] = 0
+    w["b_qkv"][3 * HEAD * d + DIM] = -1.0                                  # the query's element
+    K, V = synth.kv_cache(shape, 75, 0, np.array(lens), cap, B)
+    for b, n in enumerate(lens):
+        if bad < n:
+            K[b, HEAD, bad, DIM] = np.inf
+    with cf.profile_build():
+        ds = DeviceStack(shape, cap, B, 1)
+        try:
+            ds.load_layer(0, w)
+            ds.load_kv(0, K, V, np.array(lens))
+            ds.set_inputs(synth.x_input(shape, 75, B), np.array(lens, dtype=np.int32))
+            ds.block_decode(0)
+            ds.check()
+            q, o = (ds.tap(i, B * h).reshape(B, H, d)[:, HEAD].astype(np.float64) for i in (0, 3))
+            kv = [ds.export_kv(0, b, 0, lens[b] + 1) for b in range(B)]
+        finally:
+            ds.close()
+    k, v = ([a[i][HEAD].astype(np.float64) for a in kv] for i in (0, 1))
+    _check_minus_infinity(shape, (q, o), k, v, [n + 1 for n in lens], shape.name)
+
+
+@pytest.mark.parametrize("d,H,pos0,token,cached", [(64, 8, 930, 0, None), (80, 16, 1000, 3, None), (128, 16, 900, 0, 37), (64, 8, 930, None, 929), (64, 8, 300, 0, 299), (80, 16, 40, 2, 33)])
+def test_group_with_a_key_of_minus_infinity(d, H, pos0, token, cached):
+    import paper_2604_23553_amd as cf
+    from paper_2604_23553_amd.harness import DeviceStack
+    T, h = 8, H * d
+    shape = synth.ModelShape(h, H, d, 0, h, n_layers=1, name=f"d{d}")
+    print(f"[case] minus infinity, group {shape.name} pos0={pos0} token={token}", flush=True)
+    x = synth.x_input(shape, 77, T)
+    w = {n: a.copy() for n, a in synth.layer_weights(shape, 77, 0).items()}
+    w["w_qkv"][3 * HEAD * d + DIM] = 0
+    w["b_qkv"][3 * HEAD * d + DIM] = -1.0
+    if token is not None:       # the K row of (HEAD, DIM) along LayerNorm1 of that token: 120000 for it, which fp16 does not hold
+        row = _overflowing(shape, 77, 0, x[token])["w_qkv"][(3 * HEAD + 2) * d + DIM]
+        w["w_qkv"][(3 * HEAD + 1) * d + DIM] = row
+    K, V = synth.kv_cache(shape, 77, 0, pos0, pos0 + T, T)
+    if cached is not None:
+        K[0, HEAD, cached, DIM] = np.inf
+    with cf.profile_build():
+        ds = DeviceStack(shape, pos0 + T, T, 1)
+        try:
+            ds.load_layer(0, w)
+            ds.load_kv(0, K, V, pos0)
+            ds.prefill(x, pos0)
+            ds.check()
+            q, o = (ds.tap(i, T * h).reshape(T, H, d)[:, HEAD].astype(np.float64) for i in (0, 3))
+            k, v = (a[HEAD].astype(np.float64) for a in ds.export_kv(0, 0, 0, pos0 + T))
+        finally:
+            ds.close()
+    if token is not None:
+        assert k[pos0 + token, DIM] == np.inf
+    _check_minus_infinity(shape, (q, o), [k] * T, [v] * T, [pos0 + t + 1 for t in range(T)], shape.name)
