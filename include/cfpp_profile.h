@@ -71,6 +71,13 @@ cfpp_status cfpp_debug_prefill_long(const cfpp_config *cfg, int32_t rows, int32_
  * runs beside the attention), plan[5] the parts of its K, plan[6] the sets of tokens. */
 cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *cfg, int32_t rows, int32_t n_tokens, int32_t n_cu, int32_t plan[7]);
 
+/* The same for tokens from position pos0 on, in a scratch whose last part, for the parts of products and of the attention, has part_bytes
+ * bytes (0: what it has).  plan[0] as above; plan[1] parts of MLP-down beside the attention, 0: behind it; plan[2] parts of the
+ * second product's K (as plan[5] above); plan[3] parts of the attention's keys; plan[4] workgroups of MLP-down.  Where the pass does not take
+ * the narrow products, plan[1] is 1 if what was planned before is as it was. */
+cfpp_status cfpp_debug_prefill_beside(const cfpp_config *cfg, int32_t rows, int32_t n_tokens, int32_t pos0, int32_t n_cu,
+                                      size_t part_bytes, int32_t plan[5]);
+
 /* Where cfpp_stack_prefill_gemm keeps a layer's intermediates in the caller's scratch, byte
  * offsets: at[0], at[1] gamma_1 x and gamma_2 x, at[3] the attention output, at[4] GELU(up),
  * each as rows of groups of 32 fp16 heads and then their 32 fp16 remainders (value = head +

@@ -302,6 +302,15 @@ def cfpp_debug_prefill_narrow(cfg: Config, rows: int, n_tokens: int, n_cu: int =
     return tuple(plan[1:]) if plan[0] else None
 
 
+def cfpp_debug_prefill_beside(cfg: Config, rows: int, n_tokens: int, pos0: int = 0, part_bytes: int = 0, n_cu: int = 256):
+    """(parts of MLP-down beside the attention, parts of the second product, parts of the attention, workgroups of MLP-down), or whether
+    the plan before is as it was where the narrow products are not taken."""
+    plan = (C.c_int32 * 5)()
+    _check(lib().cfpp_debug_prefill_beside(C.byref(cfg), C.c_int32(rows), C.c_int32(n_tokens), C.c_int32(pos0), C.c_int32(n_cu),
+                                           C.c_size_t(part_bytes), plan), "cfpp_debug_prefill_beside")
+    return tuple(plan[1:]) if plan[0] else bool(plan[1])
+
+
 def cfpp_debug_prefill_scratch(cfg: Config, rows: int):
     """((offsets of gamma_1 x, gamma_2 x, q, attention output, GELU(up)), (halves per row of hidden, of ffn))."""
     at, halves = (C.c_size_t * 5)(), (C.c_int32 * 2)()

@@ -1245,6 +1245,30 @@ extern "C" cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *c, int32_t r
     return CFPP_OK;
 }
 
+extern "C" cfpp_status cfpp_debug_prefill_beside(const cfpp_config *c, int32_t rows, int32_t n_tokens, int32_t pos0, int32_t n_cu,
+                                                 size_t part_bytes, int32_t plan[5])
+{
+    int32_t narrow[7];
+    cfpp_status st = cfpp_debug_prefill_narrow(c, rows, n_tokens, n_cu, narrow);   // (refuses what it refuses)
+    if (st != CFPP_OK) return st;
+    if (!plan || pos0 < 0 || (part_bytes & 255)) return fail(CFPP_EINVAL, "plan is NULL, or pos0 %d, part_bytes %zu", pos0, part_bytes);
+    PfParams P;
+    std::memset(&P, 0, sizeof P);
+    P.dm = dims_of(*c); P.lay = packed_layout(P.dm.h, P.dm.f);
+    P.n_rows = n_tokens; P.rows = rows; P.n_layers = c->n_layers; P.pos0 = pos0;
+    pf_place(P, pf_layout(P.dm, rows), reinterpret_cast<char *>(4096));
+    if (part_bytes > 0) {
+        P.part_out_bytes += part_bytes - P.part_bytes;
+        P.part_bytes = part_bytes;
+    }
+    pf_plan_pass(P);
+    const PfParams before = P;
+    std::memset(plan, 0, 5 * sizeof plan[0]);
+    if (pf_plan_narrow(P, n_cu)) pf_describe_beside(P, plan);
+    else plan[1] = std::memcmp(&before, &P, sizeof P) == 0;
+    return CFPP_OK;
+}
+
 extern "C" cfpp_status cfpp_debug_prefill_scratch(const cfpp_config *c, int32_t rows, size_t at[5], int32_t halves[2])
 {
     cfpp_status st = cfpp_validate_config(c);

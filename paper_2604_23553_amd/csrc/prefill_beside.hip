@@ -41,6 +41,8 @@ hipError_t launch_pf_attention_beside(const PfParams &P, const PfAttnParts &A, h
     return hipErrorInvalidValue;
 }
 
+int pf_down_rows(int tokens) { return 16 * ((tokens + 7) / 8 <= 5 ? pf_down_tiles<5>() : pf_down_tiles<6>()); }
+
 // Parts of K: 640 columns to one or more, and one workgroup to a CU, or two where that is more than 256 KiB of weights to one (hidden 1280, 21 tokens
 // in five / eight parts: 25.5 / 24.5 us a layer; 2560, 8 tokens in six / twelve 39.4 / 39.9).  Not taken, 0, where the sets' activations are too much
 // beside the weights: every workgroup reads those of its part from the L2, and a ring that holds them holds fewer weights.  us a layer, both
@@ -53,7 +55,7 @@ int pf_down_parts(const Dims &dm, int tokens, int pos0)
     const int sets = (tokens + 7) / 8;
     if (sets > 6 || (sets > 2 && sets * dm.h > 7680)) return 0;
     if (sets == 5 && (dm.h < 768 || (dm.d == 80 && pos0 >= 1000))) return 0;
-    const int rows = 16 * (sets <= 5 ? pf_down_tiles<5>() : pf_down_tiles<6>()), per_cu = (size_t)dm.h * dm.f * 2 > (size_t)256 * 256 * 1024 ? 2 : 1;
+    const int rows = pf_down_rows(tokens), per_cu = (size_t)dm.h * dm.f * 2 > (size_t)256 * 256 * 1024 ? 2 : 1;
     return min(min(kPfDownParts, max(1, dm.f / 640)), max(1, per_cu * 256 * rows / dm.h));
 }
 

@@ -207,6 +207,20 @@ bool pf_supported(const Dims &dm)
 // hidden 4096, 37 tokens 120 -> 109 / 160 -> 114; hidden 512, 37 tokens 29.4 -> 28.0 / 44.8 -> 26.7.  With more (16 parts, or
 // two workgroups to a CU) the parts' traffic and the join cost what the shorter walks save.
 constexpr int kPfAttnPartsMax = 8;
+static int pf_attn_blocks(const Dims &dm, int tokens)                  // blocks of 32 queries to a workgroup
+{
+    const int n = dm.H * ((tokens + 31) / 32);
+    return n >= (dm.d == 128 ? 1536 : 2048) ? 4 : dm.d == 128 || n >= 768 ? 2 : 1;
+}
+int pf_attn_parts(const PfParams &P)
+{
+    const int qw = pf_attn_blocks(P.dm, P.n_rows);
+    if (qw != (P.dm.d == 128 ? 2 : 1)) return 1;           // (with more queries to a workgroup there are more workgroups than CUs)
+    const int tk = 128 / qw, wgs = P.dm.H * ((P.n_rows + 32 * qw - 1) / (32 * qw)), tiles = (P.pos0 + P.n_rows + tk - 1) / tk;
+    const size_t row = (size_t)P.n_rows * (P.dm.h * sizeof(float) + P.dm.H * sizeof(float2));
+    const int parts = min(min(tiles / 2, (256 + wgs - 1) / wgs), min(kPfAttnPartsMax, (int)(P.part_bytes / row)));
+    return parts >= 2 && tiles - (tiles + parts - 1) / parts >= 5 ? parts : 1;
+}
 template <int D, int QW, bool SPLIT>
 static hipError_t pf_attention_launch(const PfParams &P, const PfAttnParts &A, hipStream_t s)
 {
@@ -221,16 +235,11 @@ static hipError_t pf_attention_launch(const PfParams &P, const PfAttnParts &A, h
 template <int D, int QW>
 static hipError_t pf_attention_of(const PfParams &P, hipStream_t s)
 {
-    constexpr int TK = 128 / QW * (QW == 4 ? 2 : 1);
-    const int blocks = (P.n_rows + 32 * QW - 1) / (32 * QW), wgs = P.dm.H * blocks, tiles = (P.pos0 + P.n_rows + TK - 1) / TK;
+    const int blocks = (P.n_rows + 32 * QW - 1) / (32 * QW), wgs = P.dm.H * blocks;
     PfAttnParts A{P.part, nullptr, 1, blocks, 0};
     if constexpr (QW == (D == 128 ? 2 : 1)) {              // (with more queries to a workgroup there are more workgroups than CUs)
-        const size_t row = (size_t)P.n_rows * (P.dm.h * sizeof(float) + P.dm.H * sizeof(float2));
-        const int parts = min(min(tiles / 2, (256 + wgs - 1) / wgs), min(kPfAttnPartsMax, (int)(P.part_bytes / row)));
-        if (parts >= 2 && tiles - (tiles + parts - 1) / parts >= 5) {
-            A.parts = parts;
-            A.ml = reinterpret_cast<float2 *>(P.part + (size_t)parts * P.n_rows * P.dm.h);
-        }
+        A.parts = pf_attn_parts(P);
+        if (A.parts > 1) A.ml = reinterpret_cast<float2 *>(P.part + (size_t)A.parts * P.n_rows * P.dm.h);
         A.first_down = wgs * A.parts;
         const bool down = P.nrw.on && P.nrw.downs > 0;
         if (down || A.parts > 1) {
@@ -245,8 +254,7 @@ static hipError_t pf_attention_of(const PfParams &P, hipStream_t s)
 template <int D>
 static hipError_t pf_attention(const PfParams &P, hipStream_t s)
 {
-    const int n = P.dm.H * ((P.n_rows + 31) / 32);
-    const int qw = n >= (D == 128 ? 1536 : 2048) ? 4 : D == 128 || n >= 768 ? 2 : 1;
+    const int qw = pf_attn_blocks(P.dm, P.n_rows);
     if (qw == 4) return pf_attention_of<D, 4>(P, s);
     if (qw == 2) return pf_attention_of<D, 2>(P, s);
     if constexpr (D != 128) return pf_attention_of<D, 1>(P, s);

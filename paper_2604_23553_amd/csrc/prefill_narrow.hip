@@ -254,35 +254,35 @@ static void pn_plan_out(const PfParams &P, int n_cu, bool dense, int *rows, int 
 // 8 / 64 34.3 -> 25.5 / 47.5 -> 40.5; hidden 2560, 8 / 40 / 64 53.5 -> 41.9 / 67.9 -> 56.1 / 72.4 -> 68.7; hidden 4096, 8 / 48
 // 109.4 -> 82.8 / 123.6 -> 109.5.  (The tiled ones are left where an MLP is much wider than four times hidden, where the
 // device shows fewer CUs, and 49 .. 64 tokens from hidden 2944 on.)
+// P is touched only where they are taken.
 bool pf_plan_narrow(PfParams &P, int n_cu)
 {
-    PfNarrow &N = P.nrw;
+    PfNarrow N = P.nrw;
     if (P.n_rows > kPfNarrowMax) return false;
     N.rows_in = ng_in_rows(P.dm, n_cu, &N.wgs_q, &N.wgs_in);
     if (N.rows_in == 0 || pn_tiles_of(N.rows_in) * pn_sets_of(P.n_rows) > kPnMostSums) return false;
-    int splits = 0;
-    N.downs = pf_down_parts(P.dm, P.n_rows, P.pos0);
-    pn_plan_out(P, n_cu, N.downs > 0, &N.rows_out, &splits);
-    const size_t stride = (size_t)P.n_rows * P.dm.h, bytes = ((size_t)(splits + N.downs) * stride * sizeof(float) + 255) / 256 * 256;
-    if (splits == 0) return false;
-    if (N.downs > 0) {
-        // the parts lie at the end of the scratch: the attention beside MLP-down reads its queries, and may leave parts of its own
-        // ahead of them
-        const size_t room = P.part_bytes / 256 * 256;
-        if (bytes > room) return false;
-        P.part_bytes = room - bytes;
-        P.part_out = P.part + P.part_bytes / sizeof(float);
-        P.part_out_bytes = bytes;
-    } else {
-        P.part_out = reinterpret_cast<float *>(P.q);
-        P.part_out_bytes = P.part_bytes + (size_t)((char *)P.part - (char *)P.q);
-        if (bytes > P.part_out_bytes) return false;
+    const size_t stride = (size_t)P.n_rows * P.dm.h;
+    for (N.downs = pf_down_parts(P.dm, P.n_rows, P.pos0);; N.downs = 0) {
+        int splits = 0;
+        pn_plan_out(P, n_cu, N.downs > 0, &N.rows_out, &splits);
+        // The parts lie from the queries on or, beside an attention that reads these, at the end of the scratch, where the attention may
+        // leave parts of its own ahead of them.
+        const size_t need = (size_t)(splits + N.downs) * stride * sizeof(float), bytes = (need + 255) / 256 * 256, end = P.part_bytes / 256 * 256;
+        const size_t room = N.downs > 0 ? end : P.part_bytes + (size_t)((char *)P.part - (char *)P.q);
+        if (splits == 0 || (N.downs > 0 ? bytes : need) > room) {
+            if (N.downs > 0) continue;                     // (then behind the attention, if there is room for that)
+            return false;
+        }
+        if (N.downs > 0) P.part_bytes = end - bytes;
+        P.part_out = N.downs > 0 ? P.part + P.part_bytes / sizeof(float) : reinterpret_cast<float *>(P.q);
+        P.part_out_bytes = N.downs > 0 ? bytes : room;
+        P.part_out_stride = stride;
+        P.plan_out.splits = splits + N.downs;
+        P.row_fused = true;
+        N.on = true;
+        P.nrw = N;
+        return true;
     }
-    P.part_out_stride = stride;
-    P.plan_out.splits = splits + N.downs;
-    P.row_fused = true;
-    N.on = true;
-    return true;
 }
 
 #ifdef CFPP_PROFILE
@@ -292,6 +292,13 @@ void pf_describe_narrow(const PfParams &P, int plan[7])
     plan[1] = P.nrw.rows_in; plan[2] = pn_tiles_of(P.nrw.rows_in);
     plan[3] = P.nrw.rows_out; plan[4] = pn_tiles_of(P.nrw.rows_out); plan[5] = P.plan_out.splits - P.nrw.downs;
     plan[6] = pn_sets_of(P.n_rows);
+}
+void pf_describe_beside(const PfParams &P, int plan[5])
+{
+    plan[0] = 1;
+    plan[1] = P.nrw.downs; plan[2] = P.plan_out.splits - P.nrw.downs;
+    plan[3] = pf_attn_parts(P);
+    plan[4] = P.nrw.downs * ((P.dm.h + pf_down_rows(P.n_rows) - 1) / pf_down_rows(P.n_rows));
 }
 #endif
 
