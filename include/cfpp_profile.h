@@ -78,6 +78,11 @@ cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *cfg, int32_t rows, int3
 cfpp_status cfpp_debug_prefill_beside(const cfpp_config *cfg, int32_t rows, int32_t n_tokens, int32_t pos0, int32_t n_cu,
                                       size_t part_bytes, int32_t plan[5]);
 
+/* The attention of the batched path (host arithmetic, no GPU) with n sequences' step (first < 0; 1 for one sequence) or
+ * n tokens of a prompt's group from position first on: plan[0] 1 if the group attends together; plan[1] pieces of a head, at most; plan[2]
+ * workgroups ahead of MLP-down's; plan[3] parts of MLP-down, plan[4] its workgroups. */
+cfpp_status cfpp_debug_attention_plan(const cfpp_config *cfg, int32_t n, int32_t first, int32_t plan[5]);
+
 /* Where cfpp_stack_prefill_gemm keeps a layer's intermediates in the caller's scratch, byte
  * offsets: at[0], at[1] gamma_1 x and gamma_2 x, at[3] the attention output, at[4] GELU(up),
  * each as rows of groups of 32 fp16 heads and then their 32 fp16 remainders (value = head +

@@ -311,6 +311,13 @@ def cfpp_debug_prefill_beside(cfg: Config, rows: int, n_tokens: int, pos0: int =
     return tuple(plan[1:]) if plan[0] else bool(plan[1])
 
 
+def cfpp_debug_attention_plan(cfg: Config, n: int, first: int = -1):
+    """(together, pieces of a head, workgroups ahead of MLP-down, parts of MLP-down, its workgroups) of a step (first < 0) or a group."""
+    plan = (C.c_int32 * 5)()
+    _check(lib().cfpp_debug_attention_plan(C.byref(cfg), C.c_int32(n), C.c_int32(first), plan), "cfpp_debug_attention_plan")
+    return (bool(plan[0]), *plan[1:])
+
+
 def cfpp_debug_prefill_scratch(cfg: Config, rows: int):
     """((offsets of gamma_1 x, gamma_2 x, q, attention output, GELU(up)), (halves per row of hidden, of ffn))."""
     at, halves = (C.c_size_t * 5)(), (C.c_int32 * 2)()

@@ -1245,6 +1245,19 @@ extern "C" cfpp_status cfpp_debug_prefill_narrow(const cfpp_config *c, int32_t r
     return CFPP_OK;
 }
 
+extern "C" cfpp_status cfpp_debug_attention_plan(const cfpp_config *c, int32_t n, int32_t first, int32_t plan[5])
+{
+    cfpp_status st = cfpp_validate_config(c);
+    if (st != CFPP_OK) return st;
+    if (!plan || n < 1 || n > kBatMax || (first >= 0 && first + n > c->max_seq)) return fail(CFPP_EINVAL, "plan is NULL, or n %d, first %d", n, first);
+    const Dims dm = dims_of(*c);
+    plan[0] = first >= 0 && group_attention_takes(dm, n, first);
+    const AttnPlan A = plan[0] ? plan_attention_group(dm, n, first) : plan_attention_batched(dm, n, first);
+    plan[1] = A.pieces; plan[2] = A.attn; plan[3] = A.downs;
+    plan[4] = A.downs * (dm.h / (n == 1 ? kDownRowsOne : kDownRows));
+    return CFPP_OK;
+}
+
 extern "C" cfpp_status cfpp_debug_prefill_beside(const cfpp_config *c, int32_t rows, int32_t n_tokens, int32_t pos0, int32_t n_cu,
                                                  size_t part_bytes, int32_t plan[5])
 {

@@ -58,6 +58,11 @@ hipError_t launch_attention_batched(const StepParams &P, int nb, int first, cons
 bool group_attention_takes(const Dims &dm, int nb, int first);
 hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s);
 hipError_t prepare_attention_kernels();
+// What such a launch is: pieces of a head (at most; a step's are cut by its positions on the device), workgroups ahead of
+// MLP-down's, and MLP-down's parts.  Of a prompt group as above from `first` on, or of a step (first < 0).
+struct AttnPlan { int pieces, attn, downs; };
+AttnPlan plan_attention_batched(const Dims &dm, int nb, int first);
+AttnPlan plan_attention_group(const Dims &dm, int nb, int first);
 // stores the per-layer pointer table in device memory (the whole-stack kernels read it there)
 hipError_t launch_store_layer_ptrs(const LayerPtrs &ptrs, LayerPtrs *dst, int n, hipStream_t s);
 // most co-resident workgroups per compute unit for the persistent kernels

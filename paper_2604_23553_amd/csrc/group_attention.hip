@@ -398,16 +398,26 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
     if (tid == 0) __hip_atomic_store(&P.seg_cnt[head], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+AttnPlan plan_attention_group(const Dims &dm, int, int first)
+{
+    AttnPlan A;
+    A.pieces = ga_pieces(first, dm.H);
+    A.attn = dm.H * (A.pieces + 1);
+    A.downs = down_parts_beside(dm.h, dm.f, false, A.attn, first);
+    return A;
+}
+
 hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s)
 {
     if (nb < 2 || nb > kBatMax || first < 0 || first + nb > P.dm.max_seq || P.part_slots < kGaPieces + 1 + kDownParts) return hipErrorInvalidValue;
+    const AttnPlan plan = plan_attention_group(P.dm, nb, first);
     GaParams G;
     G.nb = nb; G.first = first; G.kv = kv;
-    G.pieces = ga_pieces(first, P.dm.H);
+    G.pieces = plan.pieces;
     DownPlan down;
     down.w = w;
-    down.first = P.dm.H * (G.pieces + 1);
-    down.parts = down_parts_beside(P.dm.h, P.dm.f, false, down.first, first);
+    down.first = plan.attn;
+    down.parts = plan.downs;
     *downs = down.parts;
     const dim3 grid(down.first + P.dm.h / kDownRows * down.parts), block(kAttnBatchThreads);
     switch (P.dm.d) {

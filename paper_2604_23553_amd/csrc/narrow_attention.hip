@@ -264,18 +264,30 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
     if (lane == 0) __hip_atomic_store(&P.seg_cnt[hd], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+AttnPlan plan_attention_batched(const Dims &dm, int nb, int first)
+{
+    const bool stream = first < 0;
+    const int H = dm.H, spare = stream ? kAttnSpareGroups / H : max(1, kAttnSharedGroups / (H * nb));
+    // no sequence has more pieces than its longest context allows (64 / LPP positions a row, as in AttnShape); a group's is known
+    const int row = dm.d >= 128 ? 16 : 32, most = attn_pieces(((stream ? dm.max_seq : first + nb) + row - 1) / row, nb <= kAttnFew);
+    AttnPlan A;
+    A.pieces = stream ? 1 + spare : spare;
+    A.attn = (stream ? min(nb + spare, nb * most) : nb * min(spare, most)) * H;
+    A.downs = stream ? down_parts_of(dm.h, dm.f, nb == 1) : down_parts_beside(dm.h, dm.f, nb == 1, A.attn, first);
+    return A;
+}
+
 hipError_t launch_attention_batched(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s)
 {
     const bool stream = P.attn_bstep != 0;
     if (nb < 1 || nb > kAttnBatchMax || (!stream && (first < 0 || first + nb > P.dm.max_seq))) return hipErrorInvalidValue;
-    const int H = P.dm.H, spare = stream ? kAttnSpareGroups / H : max(1, kAttnSharedGroups / (H * nb));
+    const AttnPlan plan = plan_attention_batched(P.dm, nb, stream ? -1 : first);
+    const int spare = plan.pieces - (stream ? 1 : 0);
     const bool few = nb <= kAttnFew;
-    // no sequence has more pieces than its longest context allows (64 / LPP positions a row, as in AttnShape); a group's is known
-    const int row = P.dm.d >= 128 ? 16 : 32, most = attn_pieces(((stream ? P.dm.max_seq : first + nb) + row - 1) / row, few);
     DownPlan down;
     down.w = w;
-    down.first = (stream ? min(nb + spare, nb * most) : nb * min(spare, most)) * H;
-    down.parts = stream ? down_parts_of(P.dm.h, P.dm.f, nb == 1) : down_parts_beside(P.dm.h, P.dm.f, nb == 1, down.first, first);
+    down.first = plan.attn;
+    down.parts = plan.downs;
     *downs = down.parts;
     const dim3 grid(down.first + P.dm.h / (nb == 1 ? kDownRowsOne : kDownRows) * down.parts), block(kAttnBatchThreads);
     if (P.part_slots <= kDownParts) return hipErrorInvalidValue;

@@ -6,6 +6,7 @@ import pytest
 import torch                       # (ahead of the library: both take the HIP runtime that comes with it)
 
 import synth
+from tests.beside_plans import ALONE, GROUPS, SHORT, STEPS, groups, short, step
 from tests.parity import MAX_ABS, assert_appended_rows, assert_block_close, ulp16
 from tests.prefill_long import LONG, first_product
 from tests.prefill_middle import MIDDLE
@@ -29,15 +30,12 @@ def test_shares_of_rows_and_columns(orc, shape, B):
     _batched_case(orc, shape, B, shape.n_layers, synth.seq_lens(5, B, 0, 40))
 
 
-# MLP-down beside the attention: K in one, two, three, five, seven and eight parts, one workgroup to a CU and two, parts and wavefronts
+# MLP-down beside the attention: K in one to five, seven and eight parts (six there are none), one workgroup to a CU and two, parts and wavefronts
 # with unequal shares of chunks; and 64 heads of so long a context that their pieces stop where the parts begin.
-@pytest.mark.parametrize("shape,lens", [
-    (_shape(512, 64, 512, 16), [9, 3]), (_shape(640, 80, 3200, 20), [40, 0, 7]), (_shape(1408, 128, 7040, 32), [33, 5]),
-    (_shape(1152, 64, 9216, 16), [12, 30]), (_shape(3072, 128, 12288, 32, 1), [4, 90]), (_shape(4096, 64, 4096, 16, 1), [11300]),
-    (_shape(4096, 64, 4096, 16, 1), [11300, 0]), (_shape(1920, 80, 7680, 20), [21]), (_shape(640, 80, 1920, 20), [21]),
-])
-def test_mlp_down_beside_the_attention(orc, shape, lens):
+@pytest.mark.parametrize("shape,lens,downs,workgroups", STEPS)
+def test_mlp_down_beside_the_attention(orc, shape, lens, downs, workgroups):
     from paper_2604_23553_amd.harness import DeviceStack
+    assert step(shape, lens)[3:] == (downs, workgroups)
     if len(lens) > 1:
         return _batched_case(orc, shape, len(lens), shape.n_layers, np.array(lens, dtype=np.int32))
     print(f"[case] one sequence {shape.name} S={lens[0]}", flush=True)
@@ -59,28 +57,20 @@ def test_mlp_down_beside_the_attention(orc, shape, lens):
 # A group of prompt tokens behind a longer context attends together: the first such position and the one ahead of it, lengths on both
 # sides of a row of 32 positions, groups of 2 to 8 tokens (the last one of a prompt smaller; one alone takes the other kernel), pieces that
 # share rows unevenly, fewer than eight, another sequence's cache, at the three head sizes; eight heads of 128, which keep to the other kernel.
-@pytest.mark.parametrize("shape,pos0,T,max_batch,b", [
-    (_shape(512, 64, 2048, 16), 890, 13, 8, 1), (_shape(512, 64, 2048, 16), 896, 10, 8, 0), (_shape(512, 64, 2048, 16, 1), 6000, 7, 8, 0),
-    (_shape(1280, 80, 2560, 20), 927, 8, 8, 0), (_shape(1280, 80, 2560, 20), 928, 5, 5, 4), (_shape(1280, 80, 2560, 20), 929, 15, 6, 0),
-    (_shape(2560, 80, 2560, 20, 1), 2060, 8, 8, 0), (_shape(2560, 80, 2560, 20, 1), 1023, 3, 3, 0),
-    (_shape(2048, 128, 2048, 32), 1025, 9, 8, 3), (_shape(4096, 128, 4096, 32, 1), 1300, 4, 4, 0), (_shape(1024, 128, 4096, 32, 1), 2049, 6, 8, 0),
-    (_shape(4096, 64, 4096, 16, 1), 1500, 8, 8, 0), (_shape(4096, 64, 4096, 16, 1), 900, 2, 2, 1),
-])
-def test_group_attention(orc, shape, pos0, T, max_batch, b):
+@pytest.mark.parametrize("shape,pos0,T,max_batch,b,plans", GROUPS)
+def test_group_attention(orc, shape, pos0, T, max_batch, b, plans):
     from tests.test_gpu_prefill import _check_prompt
+    assert [(g[0], g[1], g[3]) for g in groups(shape, pos0, T, max_batch)] == plans
     _check_prompt(orc, shape, 41, pos0, T, max_batch, b, then_decode=False, row_check_every=5)
 
 
 # Ahead of that every query attends for itself, in a grid made for the group's positions: one piece a head and the first position with
 # two, of 16 rows (up to 4 tokens) and of 32; heads of 128, whose rows are 16 positions; as many pieces as workgroups allow; one token; and fewer
 # parts of MLP-down beside it (hidden 1280 and 1536) or not, on both sides of position 128 (hidden 2560).
-@pytest.mark.parametrize("shape,pos0,T,max_batch,b", [
-    (_shape(1280, 80, 5120, 20), 0, 11, 8, 0), (_shape(1280, 80, 5120, 20, 1), 880, 8, 8, 0), (_shape(1536, 64, 6144, 16, 1), 510, 4, 2, 1),
-    (_shape(2560, 80, 10240, 20, 1), 126, 4, 2, 0), (_shape(1024, 128, 4096, 32, 1), 2040, 9, 8, 0), (_shape(1024, 128, 1024, 32, 1), 505, 10, 8, 2),
-    (_shape(4096, 128, 4096, 32, 1), 255, 3, 2, 0), (_shape(640, 80, 640, 20, 1), 3000, 1, 8, 0), (_shape(512, 64, 512, 16, 1), 511, 3, 3, 0),
-])
-def test_group_with_a_grid_for_its_positions(orc, shape, pos0, T, max_batch, b):
+@pytest.mark.parametrize("shape,pos0,T,max_batch,b,plans", ALONE)
+def test_group_with_a_grid_for_its_positions(orc, shape, pos0, T, max_batch, b, plans):
     from tests.test_gpu_prefill import _check_prompt
+    assert [(g[0], g[1], g[3]) for g in groups(shape, pos0, T, max_batch)] == plans
     _check_prompt(orc, shape, 47, pos0, T, max_batch, b, then_decode=False, row_check_every=5)
 
 
@@ -282,13 +272,11 @@ def test_short_prompts(orc, shape, T):
 
 # MLP-down beside the attention of a short prompt: 1 .. 6 sets of tokens, the last one partly there, K in one to eight parts, wavefronts without
 # chunks, one and two workgroups to a CU, behind a context that the attention cuts into parts of its own, at the three head sizes.
-@pytest.mark.parametrize("shape,pos0,T", [
-    (_shape(128, 64, 128, 16), 3, 5), (_shape(512, 64, 2048, 16), 0, 16), (_shape(512, 64, 2048, 16), 7, 23), (_shape(640, 80, 1920, 20), 40, 31),
-    (_shape(1280, 80, 2560, 20), 1, 40), (_shape(1280, 80, 5120, 20), 5, 48), (_shape(1024, 128, 4096, 32), 9, 33), (_shape(1152, 64, 9216, 0), 2, 3),
-    (_shape(4096, 128, 8192, 32, 1), 4, 12), (_shape(512, 64, 2048, 16, 1), 1500, 44), (_shape(640, 80, 2560, 20, 1), 1300, 8), (_shape(1024, 128, 4096, 32, 1), 900, 19),
-])
-def test_short_prompts_with_mlp_down_beside_the_attention(orc, shape, pos0, T):
+@pytest.mark.parametrize("shape,pos0,T,downs,workgroups,attention", SHORT)
+def test_short_prompts_with_mlp_down_beside_the_attention(orc, shape, pos0, T, downs, workgroups, attention):
     from tests.test_gpu_prefill import _check_prompt
+    got = short(shape, pos0, T)
+    assert (got[0], got[3], got[2]) == (downs, workgroups, attention)
     _check_prompt(orc, shape, 53, pos0, T, 2, 1, then_decode=False, gemm_rows=128, row_check_every=13)
 
 
