@@ -43,12 +43,25 @@ CFPP_HD int ga_pieces(int first, int H)
     return n < kGaPieces ? n : kGaPieces;
 }
 // Where it is taken.  Below some 900 positions the pieces' way to memory and back (4 - 5 us, whatever their size) is more than the
-// other kernel's reading of every row once a query: us a layer, one query to a workgroup -> this, groups of 3 / 8 tokens: hidden 2560 behind
-// 500 36.6 -> 36.5 / 39.5 -> 39.8, behind 1000 39.1 -> 37.6 / 41.3 -> 41.2, 2500 44.8 -> 39.8 / 55.7 -> 43.9; 512 behind 500 15.2 -> 15.4 / 16.6 -> 16.8,
-// 1000 17.0 -> 15.8 / 18.3 -> 17.4; 1280 behind 750 22.5 -> 22.3 (5) / 23.2 -> 23.8, 1000 22.9 -> 21.2 / 24.3 -> 24.2, 4000 26.0 -> 25.4 / 31.9 -> 28.5;
-// 4096 behind 1000 73.6 -> 76.8 / 86.1 -> 81.4, 4000 100 -> 85.8 / 118 -> 90.1.  Eight heads of 128 dimensions are too few workgroups with too
-// much to read (1024 behind 1500 22.8 -> 24.3, 4000 28.9 -> 27.7 but for three tokens 23.6 -> 25.4): left with the other kernel, as are eight of 80.
-bool group_attention_takes(const Dims &dm, int nb, int first) { return nb >= 2 && first >= 28 * kGaRow && (dm.H >= 16 || dm.d == 64); }
+// other kernel's reading of every row once a query.  16 .. 21 heads are 144 .. 189 workgroups, which leave that many of the 256 CUs without, and the
+// other kernel nearly fills them: there heads x tokens x positions have to come to 160000.  us a layer, one query to a workgroup -> this, positions
+// behind which 2 / 3 / 5 / 8 tokens attend:
+//   8 heads of 64, hidden 512: 850 16.6 / 16.6 / 16.9 / 17.2 -> 15.7 / 15.8 / 16.8 / 17.2, 1000 16.5 / 16.6 / 17.2 / 17.5 -> 15.8 / 15.9 / 17.0 / 17.4, 4000 17.7 / 17.9 / 19.1 / 20.0 -> 17.7 / 17.8 / 18.8 / 19.1;
+//   16 of 64, 1024: 1000 18.3 / 18.4 / 18.8 / 19.2 -> 18.6 / 18.8 / 19.9 / 20.2, 2000 18.8 / 18.8 / 20.5 / 21.5 -> 19.3 / 19.5 / 20.6 / 20.8, 4000 21.6 / 22.0 / 23.6 / 26.2 -> 22.2 / 22.3 / 23.4 / 23.7;
+//   16 of 80, 1280: 1000 21.6 / 21.6 / 22.3 / 22.7 -> 21.3 / 21.4 / 22.6 / 24.1, 1500 21.9 / 22.7 / 23.9 / 24.4 -> 22.1 / 22.3 / 23.5 / 24.9, 3000 23.6 / 24.0 / 25.4 / 27.8 -> 23.6 / 23.8 / 25.1 / 26.7;
+//   20 of 128, 2560: 1000 36.6 / 37.0 / 40.2 / 44.5 -> 38.4 / 39.0 / 40.3 / 42.5, 2000 39.0 / 40.7 / 45.6 / 52.6 -> 39.9 / 41.0 / 42.5 / 44.9, 3500 42.6 / 45.5 / 52.6 / 66.3 -> 43.4 / 44.6 / 46.3 / 48.8;
+//   24 of 64, 1536: 850 21.8 / 23.3 / 23.8 / 24.3 -> 22.5 / 22.6 / 23.7 / 24.3, 1000 22.0 / 23.5 / 24.3 / 24.7 -> 22.7 / 22.9 / 24.0 / 24.6, 4000 26.7 / 28.6 / 30.9 / 37.4 -> 27.0 / 27.2 / 28.7 / 29.6;
+//   32 of 80, 2560: 850 37.0 / 37.0 / 39.2 / 40.4 -> 36.4 / 36.7 / 37.8 / 39.9, 1000 37.5 / 37.4 / 39.6 / 40.8 -> 36.4 / 36.8 / 38.1 / 40.2, 4000 43.0 / 48.1 / 55.0 / 55.6 -> 42.9 / 43.2 / 44.7 / 46.9;
+//   32 of 128, 4096: 850 72.0 / 72.0 / 74.7 / 77.1 -> 71.7 / 72.3 / 73.9 / 77.0, 1000 72.2 / 72.4 / 75.8 / 77.9 -> 72.8 / 73.2 / 74.7 / 77.6, 4000 80.2 / 87.5 / 103.3 / 104.9 -> 81.1 / 81.9 / 83.5 / 86.4.
+// Over 19 shapes, two to eight tokens and positions from 1000 to 4000 (16 .. 21 heads, 118 of them): the slower one by 0.5 % in the mean, 1.0 % with the
+// line at 896 positions alone; what it takes loses 2 % at most (before 7 %), what it leaves 3 % but for 18 heads of 64 (up to 12 % with 4 tokens behind 2000).  From
+// 22 heads on: 3 % for 2 tokens behind 1000 at 24 heads, 5 % for 5 at 24 heads of 80, else below 2 %.  Eight heads of 128 dimensions are too few
+// workgroups with too much to read (hidden 1024 behind 1000 / 4000: 3 tokens 7.5 / 9.4 % more, 8 8.4 / 0.9 % more): left with the other kernel, as are
+// eight of 80 (2 tokens behind 1000 6 % less, but 8 3 % more behind 1200).
+bool group_attention_takes(const Dims &dm, int nb, int first)
+{
+    return nb >= 2 && first >= 28 * kGaRow && (dm.H < 16 ? dm.d == 64 : dm.H >= 22 || dm.H * nb * first >= 160000);
+}
 
 constexpr float kGaWeight = 16384.f;   // a weight's factor
 // Both columns of a query, eight lanes apart, work its values out alike.  One of them feeds the head of v (below 2^15 in size), the other what it

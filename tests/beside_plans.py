@@ -22,14 +22,16 @@ GROUPS = [
     (_shape(512, 64, 2048, 16), 890, 13, 8, 1, [(False, 4, 2), (True, 8, 2)]), (_shape(512, 64, 2048, 16), 896, 10, 8, 0, [(True, 7, 2), (True, 8, 2)]),
     (_shape(512, 64, 2048, 16), 895, 9, 8, 0, [(False, 4, 2), (False, 32, 2)]), (_shape(512, 64, 2048, 16), 888, 16, 8, 0, [(False, 4, 2), (True, 7, 2)]),
     (_shape(512, 64, 2048, 16, 1), 6000, 7, 8, 0, [(True, 8, 2)]),
-    (_shape(1280, 80, 2560, 20), 927, 8, 8, 0, [(True, 8, 2)]), (_shape(1280, 80, 2560, 20), 928, 5, 5, 4, [(True, 8, 2)]),
-    (_shape(1280, 80, 2560, 20), 929, 15, 6, 0, [(True, 8, 2)] * 3),
+    (_shape(1280, 80, 2560, 20), 927, 8, 8, 0, [(False, 2, 2)]), (_shape(1280, 80, 2560, 20), 928, 5, 5, 4, [(False, 3, 2)]),
+    (_shape(1280, 80, 2560, 20), 929, 15, 6, 0, [(False, 2, 2)] * 2 + [(False, 5, 2)]), (_shape(1280, 80, 2560, 20), 1249, 16, 8, 0, [(False, 2, 2), (True, 8, 2)]),
+    (_shape(1280, 80, 2560, 20), 1250, 8, 8, 0, [(True, 8, 2)]), (_shape(1280, 80, 5120, 20, 1), 2000, 5, 5, 4, [(True, 8, 5)]), (_shape(1280, 64, 1280, 16, 1), 1700, 15, 6, 0, [(True, 8, 1), (True, 8, 1), (False, 4, 1)]),
     (_shape(2560, 80, 2560, 20, 1), 2060, 8, 8, 0, [(True, 7, 2)]), (_shape(2560, 80, 2560, 20, 1), 1023, 3, 3, 0, [(True, 7, 2)]),
-    (_shape(2048, 128, 2048, 32), 1025, 9, 8, 3, [(True, 8, 1), (False, 16, 2)]), (_shape(4096, 128, 4096, 32, 1), 1300, 4, 4, 0, [(True, 7, 2)]),
+    (_shape(2048, 128, 2048, 32), 1025, 9, 8, 3, [(False, 2, 2), (False, 16, 2)]), (_shape(2048, 128, 2048, 32), 1281, 9, 8, 3, [(True, 8, 1), (False, 16, 2)]),
+    (_shape(4096, 128, 4096, 32, 1), 1300, 4, 4, 0, [(True, 7, 2)]),
     (_shape(1024, 128, 4096, 32, 1), 2049, 6, 8, 0, [(False, 5, 4)]),
     (_shape(4096, 64, 4096, 16, 1), 1500, 8, 8, 0, [(True, 3, 2)]), (_shape(4096, 64, 4096, 16, 1), 900, 2, 2, 1, [(True, 3, 2)]),
 ]
-# ... ahead of that line: in a grid for the positions they have.
+# ... where every query attends for itself: in a grid for the positions they have.
 ALONE = [
     (_shape(1280, 80, 5120, 20), 0, 11, 8, 0, [(False, 2, 3), (False, 5, 5)]), (_shape(1280, 80, 5120, 20, 1), 880, 8, 8, 0, [(False, 2, 3)]), (_shape(1536, 64, 6144, 16, 1), 510, 4, 2, 1, [(False, 5, 4), (False, 5, 3)]),
     (_shape(2560, 80, 10240, 20, 1), 126, 4, 2, 0, [(False, 4, 3), (False, 4, 2)]), (_shape(1024, 128, 4096, 32, 1), 2040, 9, 8, 0, [(False, 4, 4), (False, 32, 4)]), (_shape(1024, 128, 1024, 32, 1), 505, 10, 8, 2, [(False, 4, 1), (False, 16, 1)]),

@@ -62,3 +62,7 @@ def test_parts_stay_inside_their_limits():
 def test_every_branch_has_its_shapes():
     assert groups(_shape(640, 80, 640, 20), 896, 8, 8)[0][0] is False and groups(_shape(512, 64, 512, 0), 896, 2, 8)[0][0] is True
     assert groups(_shape(512, 64, 512, 0), 4000, 1, 8)[0][0] is False                  # one token
+    for h, d, line in ((1024, 64, 10000), (1280, 64, 8000), (1280, 80, 10000), (2560, 128, 8000), (1408, 64, 0), (2816, 128, 0), (1920, 80, 0), (4096, 64, 0)):
+        for n in (2, 3, 5, 8):
+            at = max(896, -(-line // n))               # the first position at which a group of n attends together
+            assert [g[0] for p in (at - 1, at) for g in groups(_shape(h, d, h, 0), p, n, 8)] == [False, True], (h, d, n)

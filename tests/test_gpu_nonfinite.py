@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import synth
+from tests.beside_plans import groups
 
 pytestmark = pytest.mark.gpu
 
@@ -135,12 +136,13 @@ def test_step_behind_a_key_of_minus_infinity(d, H, lens, bad):
     _check_minus_infinity(shape, (q, o), k, v, [n + 1 for n in lens], shape.name)
 
 
-@pytest.mark.parametrize("d,H,pos0,token,cached", [(64, 8, 930, 0, None), (80, 16, 1000, 3, None), (128, 16, 900, 0, 37), (64, 8, 930, None, 929), (64, 8, 300, 0, 299), (80, 16, 40, 2, 33)])
+@pytest.mark.parametrize("d,H,pos0,token,cached", [(64, 8, 930, 0, None), (80, 16, 1300, 3, None), (128, 16, 1260, 0, 37), (64, 8, 930, None, 929), (64, 8, 300, 0, 299), (80, 16, 40, 2, 33)])
 def test_group_with_a_key_of_minus_infinity(d, H, pos0, token, cached):
     import paper_2604_23553_amd as cf
     from paper_2604_23553_amd.harness import DeviceStack
     T, h = 8, H * d
     shape = synth.ModelShape(h, H, d, 0, h, n_layers=1, name=f"d{d}")
+    assert groups(shape, pos0, T, T)[0][0] == (pos0 > 800)
     print(f"[case] minus infinity, group {shape.name} pos0={pos0} token={token}", flush=True)
     x = synth.x_input(shape, 77, T)
     w = {n: a.copy() for n, a in synth.layer_weights(shape, 77, 0).items()}
