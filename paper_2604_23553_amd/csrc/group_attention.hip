@@ -148,7 +148,7 @@ __device__ __forceinline__ void ga_alone(const float *q, const __half *Kh, const
 {
     constexpr int NE = (D + 63) / 64;
     const float scale = 1.44269504088896340736f / sqrtf((float)D);
-    float qs[NE], o[NE], m = -INFINITY, l = 0.f;
+    float qs[NE], o[NE], m = kAttnLowest, l = 0.f;
     unsigned at[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
@@ -163,8 +163,7 @@ __device__ __forceinline__ void ga_alone(const float *q, const __half *Kh, const
 #pragma unroll
             for (int e = 0; e < NE; ++e) s = lane + 64 * e < D ? fmaf(qs[e], __half2float(Kh[at[e] + (unsigned)t * 16u]), s) : s;
             s = wave_sum(s);
-            const float mn = fmaxf(m, s), corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
-            const float p = s == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - mn);
+            const float mn = fmaxf(m, s), corr = __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(s - mn);
             m = mn;
             l = l * corr + p;
 #pragma unroll
@@ -222,10 +221,10 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
                 s += dot8(load16(kr + (unsigned)(c >> 1) * slab + (c & 1) * 8u), *reinterpret_cast<const float4 *>(qr + 8 * c),
                           *reinterpret_cast<const float4 *>(qr + 8 * c + 4), 0.f);
             s = sj <= si ? s * scale : -INFINITY;
-            float m = fmaxf(s, dpp_mov<kDppXor1>(s));
+            float m = fmaxf(fmaxf(s, kAttnLowest), dpp_mov<kDppXor1>(s));
             m = fmaxf(m, dpp_mov<kDppXor2>(m));
             m = fmaxf(m, dpp_mov<kDppHalfMirror>(m));
-            const float p = s == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - m);      // (not only masked ones: an infinite K element)
+            const float p = __builtin_amdgcn_exp2f(s - m);
             float l = p + dpp_mov<kDppXor1>(p);
             l += dpp_mov<kDppXor2>(l);
             l += dpp_mov<kDppHalfMirror>(l);
@@ -285,7 +284,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
         f32x4 O[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) O[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float m_run = -INFINITY, l_run = 0.f;              // l_run: of this lane's positions
+        float m_run = kAttnLowest, l_run = 0.f;            // l_run: of this lane's positions
         __half *vt = reinterpret_cast<__half *>(ga_mem) + wave * D * kGaStride;
         for (int row = lo + wave; row < hi; row += W) {
             r.store(vt, row, last, lane);
@@ -313,14 +312,14 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
                     S[t][j] = row * kGaRow + 16 * t + 4 * kg + j <= last ? s : -INFINITY;
                     most = fmaxf(most, S[t][j]);
                 }
-            const float mn = fmaxf(m_run, ga_max4(most)), corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
+            const float mn = fmaxf(m_run, ga_max4(most)), corr = __builtin_amdgcn_exp2f(m_run - mn);
             ga_f16x8 p;
             float sum = 0.f;
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float v = split_value(S[t][j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(S[t][j] - mn));
+                    const float v = split_value(__builtin_amdgcn_exp2f(S[t][j] - mn));
                     sum += v;
                     p[4 * t + j] = side.part(v * kGaWeight);
                 }
@@ -368,7 +367,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
             for (int w = 1; w < W; ++w) M = fmaxf(M, wm[w * Q8 + i]);
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                const float mw = wm[w * Q8 + i], ew = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+                const float ew = __builtin_amdgcn_exp2f(wm[w * Q8 + i] - M);
                 L += wl[w * Q8 + i] * ew;
                 s += wp[(w * Q8 + i) * D + dim] * ew;
             }
@@ -386,7 +385,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
     for (int e = tid; e < nb * D; e += kAttnBatchThreads) {
         const int i = e / D, dim = e - i * D;
         const float *first = part + i * part_step;
-        float M = -INFINITY, L = 0.f, s = 0.f;
+        float M = kAttnLowest, L = 0.f, s = 0.f;
         constexpr int CB = kGaPieces + 1;                  // all of them in flight together
         float mj[CB], lj[CB], oj[CB];
 #pragma unroll
@@ -400,7 +399,7 @@ __global__ void __launch_bounds__(kAttnBatchThreads, D == 80 ? 4 : 3) k_attentio
         for (int j = 0; j < CB; ++j) {
             if (j <= pieces) {
                 const float mn = fmaxf(M, mj[j]);
-                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = mj[j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mj[j] - mn);
+                const float c0 = __builtin_amdgcn_exp2f(M - mn), c1 = __builtin_amdgcn_exp2f(mj[j] - mn);
                 L = L * c0 + lj[j] * c1;
                 s = s * c0 + oj[j] * c1;
                 M = mn;

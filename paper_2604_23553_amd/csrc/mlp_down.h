@@ -7,6 +7,9 @@
 namespace cfpp {
 
 constexpr int kAttnBatchMax = 8, kAttnBatchThreads = 256;
+// What a maximum of scores starts at.  Not minus infinity: the weight of a score of minus infinity (masked, or of an infinite K element) is then
+// zero as it comes, with or without others beside it, and so is what no key has been added to.
+constexpr float kAttnLowest = -3.402823466e38f;
 
 // MLP-down beside the attention, in workgroups of the same launch behind the attention's: it depends on GELU(up) alone, and an attention
 // that is short of bytes, or waits for its merges, leaves the way from memory to these weights.  Workgroup `id` has the rows of

@@ -132,7 +132,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
     issue(k1, v1, lo + wave + NW);
     if (tid < D) qs[tid] = q_r * (1.44269504088896340736f / sqrtf((float)D));
     __syncthreads();
-    float acc[NV], m_run = -INFINITY, l_run = 0.f;
+    float acc[NV], m_run = kAttnLowest, l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) acc[i] = 0.f;
     auto process = [&](const u32x4 (&kk)[NP], u32x4 (&vv)[NP], int row) {
@@ -154,8 +154,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
         if constexpr (LPP == 4) sp += lane_xor<2>(sp);
         const float sc = valid ? sp : -INFINITY;
         const float mn = fmaxf(m_run, sc);
-        const float corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
-        const float p = sc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc - mn);       // (a valid one too: an infinite K element)
+        const float corr = __builtin_amdgcn_exp2f(m_run - mn), p = __builtin_amdgcn_exp2f(sc - mn);
         l_run = l_run * corr + p;
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
@@ -174,10 +173,10 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
         if (r + NW < hi) process(k1, v1, r + NW);          // (uniform)
         issue(k1, v1, r + 3 * NW);
     }
-    // lanes -> wavefront (a wavefront without rows leaves (0, -inf, 0)) -> workgroup
+    // lanes -> wavefront (a wavefront without rows leaves (0, kAttnLowest, 0)) -> workgroup
     {
         const float mw = wave_max(m_run);
-        const float fl = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mw);
+        const float fl = __builtin_amdgcn_exp2f(m_run - mw);
         const float lw = wave_sum(sub == 0 ? l_run * fl : 0.f);
 #pragma unroll
         for (int i = 0; i < NV; ++i) acc[i] *= fl;
@@ -201,7 +200,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
     for (int e = 0; e < NE; ++e) O[e] = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float ew = wm[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(wm[w] - M);
+        const float ew = __builtin_amdgcn_exp2f(wm[w] - M);
         L += wl[w] * ew;
 #pragma unroll
         for (int e = 0; e < NE; ++e)
@@ -235,7 +234,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
     if (lane == 0) old = __hip_atomic_fetch_add(&P.seg_cnt[hd], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__builtin_amdgcn_readfirstlane((int)old) != pieces - 1) return;
     constexpr int CB = 8;                                  // pieces whose loads are in flight together
-    M = -INFINITY; L = 0.f;
+    M = kAttnLowest; L = 0.f;
 #pragma unroll
     for (int e = 0; e < NE; ++e) O[e] = 0.f;
     for (int j0 = 0; j0 < pieces; j0 += CB) {
@@ -252,7 +251,7 @@ k_attention_batched(StepParams P, int nb, int spare, bool few, const __half *kv,
         for (int j = 0; j < CB; ++j) {
             if (j0 + j < pieces) {
                 const float mn = fmaxf(M, mj[j]);
-                const float c0 = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn), c1 = mj[j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mj[j] - mn);
+                const float c0 = __builtin_amdgcn_exp2f(M - mn), c1 = __builtin_amdgcn_exp2f(mj[j] - mn);
                 L = L * c0 + lj[j] * c1;
 #pragma unroll
                 for (int e = 0; e < NE; ++e) O[e] = O[e] * c0 + oj[j][e] * c1;
