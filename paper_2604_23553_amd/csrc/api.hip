@@ -416,7 +416,6 @@ static cfpp_status prepare(cfpp_ctx *ctx)
     HIP_OK(prepare_fused_kernels(160 * 1024));
     HIP_OK(prepare_narrow_kernels());
     HIP_OK(prepare_lone_kernels());
-    HIP_OK(prepare_attention_kernels());
     ctx->prepared = true;
     return CFPP_OK;
 }

@@ -57,7 +57,6 @@ hipError_t launch_attention_batched(const StepParams &P, int nb, int first, cons
 // implemented in group_attention.hip: that of 2 .. 8 prompt tokens, positions first .. (only where it takes them)
 bool group_attention_takes(const Dims &dm, int nb, int first);
 hipError_t launch_attention_group(const StepParams &P, int nb, int first, const __half *w, const __half *kv, int *downs, hipStream_t s);
-hipError_t prepare_attention_kernels();
 // What such a launch is: pieces of a head (at most; a step's are cut by its positions on the device), workgroups ahead of
 // MLP-down's, and MLP-down's parts.  Of a prompt group as above from `first` on, or of a step (first < 0).
 struct AttnPlan { int pieces, attn, downs; };

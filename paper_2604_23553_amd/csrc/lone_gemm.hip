@@ -62,7 +62,6 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_in(NarrowParams P)
     st.p0.w = P.w + (up ? P.lay.w_up : P.lay.w_qkv) + (size_t)r0 * h;
     st.p0.row_bytes = (unsigned)h * 2u;
     st.p0.c0 = c0; st.p0.n = cn;
-    st.p1 = st.p0; st.p1.n = 0;
     st.ring = lds_address(ng_lds) + (unsigned)(wave * Stream::kStage);
     st.mem = ng_lds + wave * Stream::kStage;
     st.y = reinterpret_cast<const float *>(vec + wave * kLoneNorm);
@@ -123,8 +122,7 @@ __global__ void __launch_bounds__(kLoneThreads, 2) k_lone_dense(NarrowParams P)
     LoneDense st;
     st.p0.w = P.w + P.lay.w_dense + (size_t)r0 * h; st.p0.row_bytes = (unsigned)h * 2u;
     st.p0.c0 = c0; st.p0.n = C * (wave + 1) / kLoneWaves - c0;
-    st.p1 = st.p0; st.p1.n = 0;
-    st.act = P.o32; st.act0 = st.act1 = 0u;
+    st.act = P.o32;
     st.act_bytes = (unsigned)h * 4u;
     st.ring = lds_address(ng_lds) + (unsigned)(wave * LoneDense::kStage);
     st.mem = ng_lds + wave * LoneDense::kStage;

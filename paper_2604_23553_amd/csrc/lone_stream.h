@@ -17,9 +17,9 @@ struct LoneStream {
     static constexpr int PER = 2 * T, NI = CH * PER + (ACT ? CH / 4 : 0), kStage = NI * 1024;
     static_assert(NI <= 62, "the memory counter's range");
     static_assert(!ACT || CH % 4 == 0, "");
-    NgPiece p0, p1;
-    const void *act;        // ACT: what the resource of the activations starts at
-    unsigned act_bytes, act0, act1;        // its size; where the activations of each matrix's first column lie in it
+    NgPiece p0;
+    const void *act;        // ACT: the activations, from the matrix's first column on
+    unsigned act_bytes;     // their size
     unsigned ring;          // LDS address of this wavefront's ring
     const char *mem;        // the same as a pointer
     const float *y;         // !ACT: this wavefront's activations
@@ -31,16 +31,16 @@ struct LoneStream {
 
     __device__ __forceinline__ void issue_a(int i, int quad) const
     {
-        const int k = i + (lane >> 4), c = k < p0.n ? p0.c0 + k : p1.c0 + k - p0.n;
-        const unsigned v = (k < p0.n ? act0 : act1) + (unsigned)c * 256u + (unsigned)(lane & 15) * 16u;
-        lds_dma16(dma_rsrc(act, act_bytes), ring + place_a(quad), k < p0.n + p1.n ? v : 0u, 0u);
+        const int k = i + (lane >> 4);
+        const unsigned v = (unsigned)(p0.c0 + k) * 256u + (unsigned)(lane & 15) * 16u;
+        lds_dma16(dma_rsrc(act, act_bytes), ring + place_a(quad), k < p0.n ? v : 0u, 0u);
     }
     __device__ __forceinline__ void issue_w(int i, int ch, int t) const
     {
-        const bool second = i >= p0.n, live = i < p0.n + p1.n;
-        const int c = second ? p1.c0 + i - p0.n : p0.c0 + i;
-        const unsigned row_bytes = second ? p1.row_bytes : p0.row_bytes;
-        const i32x4 rs = dma_rsrc(second ? p1.w : p0.w, row_bytes * (unsigned)(8 * octets + tail));
+        const bool live = i < p0.n;
+        const int c = p0.c0 + i;
+        const unsigned row_bytes = p0.row_bytes;
+        const i32x4 rs = dma_rsrc(p0.w, row_bytes * (unsigned)(8 * octets + tail));
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int o = 2 * t + k;                       // row group; its last rows may not be there
@@ -58,7 +58,7 @@ struct LoneStream {
         for (int o = 0; o < 2 * T; ++o) acc[o] = 0.f;
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) {
-            if (ch >= p0.n + p1.n) break;                  // (uniform)
+            if (ch >= p0.n) break;                         // (uniform)
             if (ACT && ch % 4 == 0) issue_a(ch, ch / 4);
 #pragma unroll
             for (int t = 0; t < T; ++t) issue_w(ch, ch, t);
@@ -68,7 +68,7 @@ struct LoneStream {
     template <int N = CH>
     __device__ __forceinline__ void wait_ahead() const
     {
-        if (p0.n + p1.n >= N) ng_wait<N * PER>();
+        if (p0.n >= N) ng_wait<N * PER>();
         else if constexpr (N > 0) wait_ahead<N - 1>();
     }
     enum { kSteady, kLast, kOnly };
@@ -80,7 +80,7 @@ struct LoneStream {
         if (KIND == kOnly) ng_wait<0>();
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) {
-            const bool live = CH == 1 || i + ch < p0.n + p1.n;             // (uniform)
+            const bool live = CH == 1 || i + ch < p0.n;    // (uniform)
             if (KIND == kOnly && !live) break;
             if (ACT && ch % 4 == 0) {
                 if (KIND == kLast) ng_wait_for<NI>(NI - ch * PER - ch / 4 - 1);
@@ -112,7 +112,7 @@ struct LoneStream {
     }
     __device__ __forceinline__ void run()
     {
-        const int n = p0.n + p1.n;
+        const int n = p0.n;
         if (n == 0) return;
         if (n <= CH) { stage<kOnly>(0); return; }
         int i = 0;

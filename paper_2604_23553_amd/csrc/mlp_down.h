@@ -40,12 +40,11 @@ __device__ __forceinline__ void mlp_down(const StepParams &P, const DownPlan &pl
     Stream st;
     st.p0.w = plan.w + P.lay.w_down + (size_t)r0 * f; st.p0.row_bytes = (unsigned)f * 2u;
     st.p0.c0 = c0; st.p0.n = z0 + zn * (wave + 1) / W - c0;
-    st.p1 = st.p0; st.p1.n = 0;
     st.ring = lds_address(lds) + (unsigned)(wave * Stream::kStage);
     st.mem = lds + wave * Stream::kStage;
     float *red = reinterpret_cast<float *>(lds), *part = P.part;
     if constexpr (ONE) {
-        st.act = P.m; st.act0 = st.act1 = 0u; st.act_bytes = (unsigned)f * 4u;
+        st.act = P.m; st.act_bytes = (unsigned)f * 4u;
         st.y = nullptr;
         st.begin(ROWS, tid);
         st.run();
@@ -55,7 +54,7 @@ __device__ __forceinline__ void mlp_down(const StepParams &P, const DownPlan &pl
         if (tid < ROWS) part[down_at(0, r0 + tid, z, P.dm.H, P.dm.d, P.part_slots)] = Stream::template total<W>(red, tid);
     } else {
         st.p0.b = P.m; st.p0.b_bytes = (unsigned)nb * (unsigned)f * 4u;
-        st.p1.b = st.p0.b; st.p1.b_bytes = st.p0.b_bytes;
+        st.p1 = st.p0; st.p1.n = 0;
         st.gamma = nullptr;
         st.begin(ROWS, nb, nb, 0u, tid);
         st.run();

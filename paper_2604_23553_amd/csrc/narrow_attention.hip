@@ -289,6 +289,7 @@ hipError_t launch_attention_batched(const StepParams &P, int nb, int first, cons
     down.parts = plan.downs;
     *downs = down.parts;
     const dim3 grid(down.first + P.dm.h / (nb == 1 ? kDownRowsOne : kDownRows) * down.parts), block(kAttnBatchThreads);
+    static_assert(down_lds<true>() <= 64 * 1024 && down_lds<false>() <= 64 * 1024, "the default limit");
     if (P.part_slots <= kDownParts) return hipErrorInvalidValue;
     switch (P.dm.d) {
 #define CFPP_ATTN(D) \
@@ -305,21 +306,6 @@ hipError_t launch_attention_batched(const StepParams &P, int nb, int first, cons
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
-}
-
-// allow more than the default 64 KiB of dynamic LDS
-hipError_t prepare_attention_kernels()
-{
-    hipError_t e;
-#define CFPP_ATTN(D, S, O) \
-    if ((e = hipFuncSetAttribute((const void *)k_attention_batched<D, S, O>, hipFuncAttributeMaxDynamicSharedMemorySize, down_lds<O>())) != hipSuccess) return e;
-#define CFPP_ATTN_ALL(D) CFPP_ATTN(D, true, true) CFPP_ATTN(D, true, false) CFPP_ATTN(D, false, true) CFPP_ATTN(D, false, false)
-    CFPP_ATTN_ALL(64)
-    CFPP_ATTN_ALL(80)
-    CFPP_ATTN_ALL(128)
-#undef CFPP_ATTN_ALL
-#undef CFPP_ATTN
-    return hipSuccess;
 }
 
 }  // namespace cfpp
