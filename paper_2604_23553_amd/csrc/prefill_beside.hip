@@ -48,13 +48,17 @@ int pf_down_rows(int tokens) { return 16 * ((tokens + 7) / 8 <= 5 ? pf_down_tile
 // beside the weights: every workgroup reads those of its part from the L2, and a ring that holds them holds fewer weights.  us a layer, both
 // products behind the attention -> this: hidden 512, 8 / 30 tokens 17.1 -> 15.9 / 19.1 -> 18.8; 1024, 13 / 37 / 44 22.1 -> 20.1 / 26.7 -> 24.2 / 27.9 -> 25.2;
 // 1280, 8 / 37 23.3 -> 21.1 / 30.0 -> 28.3; 1536, 8 / 30 25.1 -> 23.8 / 30.7 -> 29.9, but 44 34.2 -> 34.3; 2560, 8 / 13 / 21 41.3 -> 39.4 / 43.7 -> 42.8 / 46.5
-// -> 46.5, but 37 / 44 53.9 -> 54.2 / 59.3 -> 63.1; 4096, 8 / 13 81.3 -> 76.2 / 83.8 -> 81.8, but 30 97.5 -> 99.1.  Behind 2000 positions the same
-// (1024, 37 tokens 36.8 -> 33.9) but for five sets of head size 80 (1280 37.8 -> 38.7); and five sets of hidden 512 are 24 workgroups (19.7 -> 19.9).
-int pf_down_parts(const Dims &dm, int tokens, int pos0)
+// -> 46.5, but 37 / 44 53.9 -> 54.2 / 59.3 -> 63.1; 4096, 8 / 13 81.3 -> 76.2 / 83.8 -> 81.8, but 30 97.5 -> 99.1.  Five sets of small hidden sizes are
+// 12 or 24 workgroups of 64 rows: 36 tokens from an empty cache / behind 1000 / 2000 positions, hidden 384 18.7 -> 19.5 / 24.5 -> 23.8 / 24.0 -> 24.1, 512 19.7 -> 20.0 /
+// 25.4 -> 24.0 / 24.6 -> 24.1; from 640 on they gain: 640 (80) 22.9 -> 21.6 / 30.8 -> 29.3 / 30.2 -> 28.7, 640 (64) 22.0 -> 21.5 / 27.9 -> 26.1 / 27.7 -> 26.9, 768
+// 22.9 -> 22.5 / 28.9 -> 26.8 / 28.6 -> 27.6, 1024 (128) 26.8 -> 24.2 / 35.1 -> 32.1 / 36.1 -> 33.4, 1280 (80) 30.0 -> 28.3 / 38.0 -> 37.6 / 37.7 -> 38.5, 1536
+// 32.3 -> 31.7 / 38.3 -> 38.2 / 40.1 -> 38.9, but 1024 (64) 24.9 -> 24.1 / 30.7 -> 28.2 / 30.6 -> 31.1.  (Where the context lies does not enter: the same
+// tokens are added in the same order wherever they stand.)
+int pf_down_parts(const Dims &dm, int tokens)
 {
     const int sets = (tokens + 7) / 8;
     if (sets > 6 || (sets > 2 && sets * dm.h > 7680)) return 0;
-    if (sets == 5 && (dm.h < 768 || (dm.d == 80 && pos0 >= 1000))) return 0;
+    if (sets == 5 && dm.h < 640) return 0;
     const int rows = pf_down_rows(tokens), per_cu = (size_t)dm.h * dm.f * 2 > (size_t)256 * 256 * 1024 ? 2 : 1;
     return min(min(kPfDownParts, max(1, dm.f / 640)), max(1, per_cu * 256 * rows / dm.h));
 }

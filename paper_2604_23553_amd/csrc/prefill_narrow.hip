@@ -262,7 +262,7 @@ bool pf_plan_narrow(PfParams &P, int n_cu)
     N.rows_in = ng_in_rows(P.dm, n_cu, &N.wgs_q, &N.wgs_in);
     if (N.rows_in == 0 || pn_tiles_of(N.rows_in) * pn_sets_of(P.n_rows) > kPnMostSums) return false;
     const size_t stride = (size_t)P.n_rows * P.dm.h;
-    for (N.downs = pf_down_parts(P.dm, P.n_rows, P.pos0);; N.downs = 0) {
+    for (N.downs = pf_down_parts(P.dm, P.n_rows);; N.downs = 0) {
         int splits = 0;
         pn_plan_out(P, n_cu, N.downs > 0, &N.rows_out, &splits);
         // The parts lie from the queries on or, beside an attention that reads these, at the end of the scratch, where the attention may

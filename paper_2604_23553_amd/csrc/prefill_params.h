@@ -137,7 +137,7 @@ bool pf_plan_narrow(PfParams &P, int n_cu);
 // (prefill_beside.hip) the attention with MLP-down in the same launch; parts of K that it takes for so many tokens, 0: it does not
 constexpr int kPfDownParts = 8;
 hipError_t launch_pf_attention_beside(const PfParams &P, const PfAttnParts &A, hipStream_t s);
-int pf_down_parts(const Dims &dm, int tokens, int pos0);
+int pf_down_parts(const Dims &dm, int tokens);
 int pf_down_rows(int tokens);          // rows of a workgroup of MLP-down there
 int pf_attn_parts(const PfParams &P);  // parts of the attention's keys (prefill_kernels.hip)
 void pf_describe_narrow(const PfParams &P, int plan[7]);   // (profiling library: cfpp_debug_prefill_narrow)

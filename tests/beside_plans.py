@@ -44,6 +44,7 @@ SHORT = [
     (_shape(1280, 80, 2560, 20), 1, 40, 4, 80, 1), (_shape(1280, 80, 5120, 20), 5, 48, 6, 240, 1), (_shape(1024, 128, 4096, 32), 9, 33, 6, 96, 1), (_shape(1152, 64, 9216, 0), 2, 3, 8, 144, 1),
     (_shape(4096, 128, 8192, 32, 1), 4, 12, 4, 256, 1), (_shape(512, 64, 2048, 16, 1), 1500, 44, 3, 48, 6), (_shape(640, 80, 2560, 20, 1), 1300, 8, 4, 40, 5), (_shape(1024, 128, 4096, 32, 1), 900, 19, 6, 96, 7),
     (_shape(640, 80, 1280, 20), 6, 14, 2, 20, 1), (_shape(640, 64, 3200, 16), 2, 26, 5, 50, 1), (_shape(640, 128, 4480, 32), 3, 8, 7, 70, 1), (_shape(3072, 128, 12288, 32, 1), 4, 11, 8, 384, 1),
+    (_shape(512, 64, 2048, 16), 5, 38, 0, 0, 1), (_shape(640, 80, 2560, 20, 1), 1300, 37, 4, 40, 5), (_shape(640, 64, 2560, 16), 9, 34, 4, 40, 1), (_shape(1280, 80, 5120, 20, 1), 2000, 33, 8, 160, 8),
     (_shape(4096, 64, 16384, 16, 1), 2000, 16, 8, 512, 4),
 ]
 

@@ -33,7 +33,7 @@ def test_the_cases_take_every_branch():
     fewer = [g for c in GROUPS + ALONE for i, g in enumerate(groups(*c[:4])) if min(c[3], 8, c[2] - i * min(c[3], 8)) > 1
              and g[3] < step(c[0], [1] * min(c[3], 8, c[2] - i * min(c[3], 8)))[3]]
     assert fewer and any(g[0] for g in fewer) and any(not g[0] for g in fewer)                              # (fewer parts than a step's)
-    assert {c[3] for c in SHORT} >= {1, 2, 3, 4, 5, 6, 7, 8} and any(c[4] > 256 for c in SHORT)
+    assert {c[3] for c in SHORT} == set(range(9)) and any(c[4] > 256 for c in SHORT)
     assert {-(-c[2] // 8) for c in SHORT} == {1, 2, 3, 4, 5, 6} and any(c[5] == 1 for c in SHORT)
     assert {c[0].head_dim for c in SHORT if c[5] > 1} == {64, 80, 128}
 
