@@ -32,7 +32,7 @@ typedef _Float16 ga_f16x4 __attribute__((ext_vector_type(4)));
 constexpr int kGaWaves = kAttnBatchThreads / 64, kGaRow = 32;          // positions of a row, a wavefront's step
 constexpr int kGaStride = kGaRow + 4;                                  // halves between V's dimensions in LDS
 
-// Pieces of the positions ahead of the group: at least a row to each wavefront, as many as fill the CUs once, and at most eight: with the
+// Pieces of the positions ahead of the group: about a row to each wavefront or more (a piece of three leaves one without), as many as fill the CUs once, and at most eight: with the
 // group's own rows their sums are one round of loads (12 or 16 pieces, two rounds: hidden 1280 behind 2500 positions 26.1 -> 27.9 / 28.4 us a layer).  The group's own rows are a piece too: with 8 and that one 32
 // heads are 288 workgroups, with 7 256: 8 tokens behind 1000 of hidden 2560 41.7 -> 41.2, of 4096 behind 3000 87.9 -> 84.2; with 5 or 6 0.5 .. 3.5 % more.
 constexpr int kGaPieces = 8;

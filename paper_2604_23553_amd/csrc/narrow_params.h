@@ -66,10 +66,12 @@ inline int down_parts_of(int h, int f, bool one)
     return min(most, max(1, per_cu * 256 * kDownRows / h));
 }
 // Beside the `attn` workgroups of a prompt group's attention, positions `first` .., whose number the host knows: up to half as many
-// workgroups more than CUs take longer than one to each, so as many parts as leave it at that, if these are half as many at least.  us a
-// layer, parts as above -> this: 8 tokens of hidden 1280 (328 workgroups -> 248) behind 20 / 400 positions 19.6 / 21.5 -> 19.1 / 20.3; 2 tokens of
-// 1536 (336 -> 240) 20.1 / 21.8 -> 19.0 / 20.1; 2 of 2560 (304 -> 224) behind 400 36.3 -> 35.1, but behind 20 34.2 -> 34.9: two parts
-// are few where the attention is next to nothing.
+// workgroups more than CUs take longer than one to each, so as many parts as leave it at that, if these are half as many at least (16 heads of 80
+// behind 1500, 144 + 200, stay in between: two parts for five).  us a layer, parts as above -> this: 8 tokens of hidden 1280 (328 workgroups -> 248) behind
+// 20 / 400 positions 19.7 -> 19.3 / 21.6 -> 20.3; 2 tokens of 1536 (336 -> 240) 20.3 -> 19.1 / 21.9 -> 20.2.  Two parts are few where the attention is next
+// to nothing, so they wait for position 128; behind 20 / 127 / 200 / 400: 2 tokens of 2560 (80) 34.3 -> 34.9 / 35.1 -> 35.0 / 35.4 -> 35.0 / 36.4 -> 35.1, of 2560
+// (128) 34.6 -> 34.9 / 35.5 -> 35.0 / 36.3 -> 35.1 / 36.2 -> 35.4, 5 of 2048 (128) 28.1 -> 29.6 / 29.2 -> 29.5 / 29.8 -> 29.6 / 31.4 -> 29.6, 3 of 2048 (64) 27.5 -> 28.6 /
+// 28.0 -> 28.7 / 28.0 -> 28.7 / 29.1 -> 28.7, 5 of 1920 26.1 -> 28.0 / 26.9 -> 28.0 / 27.1 -> 28.0 / 28.5 -> 28.1: where they cross lies between 60 and 350.
 inline int down_parts_beside(int h, int f, bool one, int attn, int first)
 {
     const int parts = down_parts_of(h, f, one), groups = h / kDownRows, room = (256 - attn) / groups;
