@@ -16,8 +16,8 @@
 // us of layers, head and remainder as they are -> this, 8 tokens: 32 of hidden 2560 behind 1000 1315 -> 1321, 10 of 4096 behind 3000 841 -> 837, 16 of 512
 // behind 2500 291.2 -> 290.9.
 // Every query sees every one of these positions.  The group's own rows, where the causal mask lies, are a workgroup more to a
-// head, in fp32: no masked weight is ever multiplied by a V row.  An output that is not finite (a cached V row may be infinite, and the
-// remainder of its weight zero) is worked out once more in fp32.
+// head, in fp32: no masked weight is ever multiplied by a V row.  An output that is not finite (a cached K or V element may be infinite, and
+// what a head leaves zero) is worked out once more in fp32.
 // Maxima and sums of the wavefronts and pieces are joined in order, as in narrow_attention.hip.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>

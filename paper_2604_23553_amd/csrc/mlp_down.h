@@ -18,7 +18,7 @@ constexpr float kAttnLowest = -3.402823466e38f;
 // products in the launch behind the attention -> this: hidden 2560: five sequences of 37 .. 2048 positions 46.9 -> 44.2, eight
 // of 100 .. 300 44.5 -> 39.6, eight prompt tokens behind 1000 46.3 -> 41.7, one block of 1024 positions 37.2 -> 34.1; hidden 4096:
 // two of 500 .. 700 78.1 -> 73.7, a block of 1777 positions 76.6 -> 70.9; hidden 1024: eight prompt tokens 21.8 -> 19.7; 1280: two of up
-// to 600 23.5 -> 21.5; 512: one sequence 15.8 -> 15.2.
+// to 600 23.5 -> 21.5; 512: one sequence, a layer of a stack 15.8 -> 15.2 (a block on its own 14.4, as before).
 // Behind the attention's workgroups: ahead of them the block of 1024 positions takes 37.1 us, five sequences the same,
 // eight prompt tokens of hidden 4096 5 % more.
 struct DownPlan {

@@ -56,7 +56,8 @@ def test_mlp_down_beside_the_attention(orc, shape, lens, downs, workgroups):
 
 # A group of prompt tokens behind a longer context attends together: the first such position and the one ahead of it, lengths on both
 # sides of a row of 32 positions, groups of 2 to 8 tokens (the last one of a prompt smaller; one alone takes the other kernel), pieces that
-# share rows unevenly, fewer than eight, another sequence's cache, at the three head sizes; eight heads of 128, which keep to the other kernel.
+# share rows unevenly, fewer than eight, another sequence's cache, at the three head sizes; 16 to 21 heads on both sides of their own line; eight heads of
+# 128, which keep to the other kernel.
 @pytest.mark.parametrize("shape,pos0,T,max_batch,b,plans", GROUPS)
 def test_group_attention(orc, shape, pos0, T, max_batch, b, plans):
     from tests.test_gpu_prefill import _check_prompt
