@@ -25,7 +25,9 @@ namespace cfpp {
 // The scores' sums start at zero and the reference is subtracted behind them.  Starting them at minus the reference would save the subtraction,
 // but where a query's scores then rise by J its sums carry roundings of the size of J: error of the outputs against 64 bits after a
 // rise of 30 / 500 / 2000 in base 2, D = 64: 4.7e-7 / 7.5e-6 / 2.7e-5, as it is 5.3e-8 / 4.1e-8 / 4.1e-8 (80 and 128 alike), and at no size measured
-// was it more than 1 % faster.
+// was it more than 1 % faster.  Where nothing rises a large score's last sums then end near zero, and its roundings are a quarter smaller (queries and keys
+// six times as large, D = 64 / 80 / 128: 4.7e-7 / 1.2e-6 / 1.8e-6, as it is 6.6e-7 / 1.5e-6 / 2.3e-6).  Adding all remainders ahead of the heads does that too, at any
+// rise (4.8e-7 / 1.1e-6 / 1.6e-6), for 0.3 - 0.7 % of a layer at 1500 tokens and more; not taken.
 typedef _Float16 pf_f16x2 __attribute__((ext_vector_type(2)));
 typedef float pf_f32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 pf_f16x4 __attribute__((ext_vector_type(4)));
